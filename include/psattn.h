@@ -215,7 +215,7 @@ int psattn_pack_ffd(int32_t n_samples, const int32_t* prefix_len, const int32_t*
  * never computed (Section 3.1).  dt selects the element type of Q, K, V, O
  * (float, or bfloat16 with float accumulation); LSE is always float.
  * head_dim: 64 or 128 for either type.  The matrix-core kernels serve PSATTN_BF16 with
- * head_dim 128, scale > 0 and the default tile grids; every other valid request runs on
+ * scale > 0 and the default tile grids; every other valid request runs on
  * plain one-thread-per-row kernels that are orders of magnitude slower (they exist for the
  * fp32 correctness configuration).  psattn_uses_mfma tells which one a call would take.
  */

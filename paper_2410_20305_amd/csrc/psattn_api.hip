@@ -202,7 +202,7 @@ int check_common(const psattn_meta* meta, int32_t dt, int32_t Hq, int32_t Hkv, i
 // The MFMA kernels fold the scale into a base-2 exponent and take row maxima before
 // scaling, which needs scale > 0; anything else runs on the generic kernels.
 bool mfma_fwd_ok(const psattn_meta* m, int32_t dt, int32_t d, float scale) {
-    return dt == PSATTN_BF16 && d == 128 && scale > 0.f && m->fwd.tile_q == kFwdTileQ &&
+    return dt == PSATTN_BF16 && (d == 128 || d == 64) && scale > 0.f && m->fwd.tile_q == kFwdTileQ &&
            m->fwd.tile_k == kFwdTileK;
 }
 bool mfma_bwd_ok(const psattn_meta* m, int32_t dt, int32_t d, float scale) {
@@ -268,7 +268,7 @@ int bwd_checked(const psattn_meta* meta, int32_t dt, int32_t n_q_heads, int32_t 
     a.lse2 = a.delta + align_up(sizeof(float) * static_cast<size_t>(meta->T) * n_q_heads, 256) / sizeof(float);
     int err = 0;
     const bool mfma = mfma_bwd_ok(meta, dt, head_dim, scale);
-    if (rope_table && !mfma) return PSATTN_EUNSUPPORTED;  // rotary embedding lives in the matrix-core kernels only
+    if (rope_table && !(mfma && head_dim == 128)) return PSATTN_EUNSUPPORTED;  // rotary embedding lives in these matrix-core kernels only
     if (!mfma) {  // the MFMA dQ kernel computes delta itself and leaves it in the scratch
         PassTimer t(1, hip_stream);
         err = launch_delta(dt, a, hip_stream);
@@ -283,8 +283,9 @@ int bwd_checked(const psattn_meta* meta, int32_t dt, int32_t n_q_heads, int32_t 
     if (err) return PSATTN_EHIP;
     {
         PassTimer t(3, hip_stream);
-        err = mfma ? launch_mfma_dkdv(a, hip_stream) : launch_generic_dkdv(dt, a, hip_stream);
-        g_last_kernel[3] = mfma ? "psattn_dkdv_bf16_mfma" : "generic_dkdv";
+        err = !mfma ? launch_generic_dkdv(dt, a, hip_stream)
+                    : head_dim == 64 ? launch_mfma_dkdv64(a, hip_stream) : launch_mfma_dkdv(a, hip_stream);
+        g_last_kernel[3] = !mfma ? "generic_dkdv" : head_dim == 64 ? "psattn_dkdv64_bf16_mfma" : "psattn_dkdv_bf16_mfma";
     }
     return err == 0 ? PSATTN_OK : PSATTN_EHIP;
 }
@@ -302,7 +303,7 @@ int fwd_checked(const psattn_meta* meta, int32_t dt, int32_t n_q_heads, int32_t 
     a.Q = Q; a.K = K; a.V = V; a.Oout = O; a.LSEout = LSE;
     a.rope = rope_table; a.Qr = Qr;
     const bool mfma = mfma_fwd_ok(meta, dt, head_dim, scale);
-    if (rope_table && !mfma) return PSATTN_EUNSUPPORTED;  // rotary embedding lives in the matrix-core kernels only
+    if (rope_table && !(mfma && head_dim == 128)) return PSATTN_EUNSUPPORTED;  // rotary embedding lives in these matrix-core kernels only
     int err;
     {
         PassTimer t(0, hip_stream);

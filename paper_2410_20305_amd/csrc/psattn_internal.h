@@ -131,5 +131,6 @@ int launch_delta(int dt, const AttnArgs& a, void* stream);
 int launch_mfma_fwd(const AttnArgs& a, void* stream);
 int launch_mfma_dq(const AttnArgs& a, void* stream);
 int launch_mfma_dkdv(const AttnArgs& a, void* stream);
+int launch_mfma_dkdv64(const AttnArgs& a, void* stream);
 
 }  // namespace psattn

@@ -6,9 +6,12 @@ namespace {
 using namespace mma;
 
 // ------------------------------------------------------------------ dQ (q-major)
-__global__ __launch_bounds__(256, 2) void psattn_dq_bf16_mfma(AttnArgs a) {
-    __shared__ __attribute__((aligned(16))) char sKb[2][64 * kRowBytes];  // double buffered
-    __shared__ __attribute__((aligned(16))) char sVb[2][64 * kRowBytes];
+// D = head_dim.  D = 128: 64 KB of LDS and under 256 registers, two workgroups per CU.  D = 64: half of both.
+template <int D>
+__global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_dq_bf16_mfma(AttnArgs a) {
+    constexpr int kRB = kRowBytesOf<D>, kSteps = D / 16, kBlocks = D / 32;  // MFMA steps of a score, 32-wide blocks of a dQ row
+    __shared__ __attribute__((aligned(16))) char sKb[2][64 * kRB];  // double buffered
+    __shared__ __attribute__((aligned(16))) char sVb[2][64 * kRB];
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, c32 = l & 31, g = l >> 5;
     const int T = a.meta.T, Hq = a.Hq, Hkv = a.Hkv, G = Hq / Hkv;
     const DeviceCsr& csr = a.meta.fwd;
@@ -20,13 +23,13 @@ __global__ __launch_bounds__(256, 2) void psattn_dq_bf16_mfma(AttnArgs a) {
     Tok4 tk = {kPadStart, 0, 0, 0};
     if (valid) tk = a.meta.tok[q_row];
 
-    const uint16_t* K = static_cast<const uint16_t*>(a.K) + kvh * 128;
-    const uint16_t* V = static_cast<const uint16_t*>(a.V) + kvh * 128;
-    const size_t qoff = (static_cast<size_t>(q_row) * Hq + h) * 128;
+    const uint16_t* K = static_cast<const uint16_t*>(a.K) + kvh * D;
+    const uint16_t* V = static_cast<const uint16_t*>(a.V) + kvh * D;
+    const size_t qoff = (static_cast<size_t>(q_row) * Hq + h) * D;
 
-    Frag8 qf[8], gf[8];
+    Frag8 qf[kSteps], gf[kSteps];
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {
+    for (int t = 0; t < kSteps; ++t) {
         qf[t].u = valid ? *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(a.Q) + qoff + 16 * t + 8 * g)
                         : make_uint4(0, 0, 0, 0);
         gf[t].u = valid ? *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(a.dO) + qoff + 16 * t + 8 * g)
@@ -41,7 +44,7 @@ __global__ __launch_bounds__(256, 2) void psattn_dq_bf16_mfma(AttnArgs a) {
     float dl = 0.f;
     if (valid) {
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
+        for (int t = 0; t < kSteps; ++t) {
             const uint4 ov = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(a.O) + qoff + 16 * t + 8 * g);
             const uint32_t ow[4] = {ov.x, ov.y, ov.z, ov.w};
             const uint32_t gw[4] = {gf[t].u.x, gf[t].u.y, gf[t].u.z, gf[t].u.w};
@@ -59,17 +62,17 @@ __global__ __launch_bounds__(256, 2) void psattn_dq_bf16_mfma(AttnArgs a) {
     }
     const float c = a.scale * kLog2e;
 
-    f32x16 dq[4];
+    f32x16 dq[kBlocks];
 #pragma unroll
-    for (int db = 0; db < 4; ++db)
+    for (int db = 0; db < kBlocks; ++db)
 #pragma unroll
         for (int i = 0; i < 16; ++i) dq[db][i] = 0.f;
 
     // K / V tiles are copied global -> LDS asynchronously, one tile ahead, into the
     // buffer the previous tile has just vacated; one barrier per tile.
-    const uint32_t row_bytes = static_cast<uint32_t>(Hkv) * 256u;
-    const DmaLane dml = dma_lane(row_bytes, w, l);
-    PairCopy pc;
+    const uint32_t row_bytes = static_cast<uint32_t>(Hkv) * kRB;
+    const DmaLaneOf<D> dml = dma_lane<D>(row_bytes, w, l);
+    PairCopyOf<D> pc;
     auto copy_setup = [&](int ent) {
         const int k0 = (ent >> 2) * 64;
         pair_copy_setup(pc, reinterpret_cast<const char*>(K) + static_cast<size_t>(k0) * row_bytes,
@@ -82,19 +85,20 @@ __global__ __launch_bounds__(256, 2) void psattn_dq_bf16_mfma(AttnArgs a) {
     if (n_ent > 0) {
         ent = rl.first_entry;
         copy_setup(ent);
-        static_for<0, 8>([&](auto P) { pair_copy_piece<decltype(P)::value>(pc, sKb[0], sVb[0], w); });
+        static_for<0, 2 * kBlocks>([&](auto P) { pair_copy_piece<decltype(P)::value>(pc, sKb[0], sVb[0], w); });
     }
-    const LaneOffsets lo = lane_offsets(l);
+    const LaneOffsets lo = lane_offsets<D>(l);
     constexpr int kAhead = 2, kRing = 4;  // measured: 1 and 3 are both slower
-    // One tile = 48 MFMA slots, per block kb of 32 keys:
-    //   slots 24 kb +  0-15  S^T = K Q^T and dP^T = V dO^T (alternating)
+    // One tile = 2 kB MFMA slots, per block kb of 32 keys:
+    //   slots kB kb + 0 .. kS - 1   S^T = K Q^T and dP^T = V dO^T (alternating)
     //   (dS arithmetic of the block)
-    //   slots 24 kb + 16-23  dQ^T += K^T dS^T
+    //   slots kB kb + kS .. kB - 1  dQ^T += K^T dS^T
     // The LDS operand of slot m is requested kAhead slots earlier into a register ring,
     // across the arithmetic too.  Two workgroups share a CU: the other wave of the SIMD
     // fills the gaps.  The buffer index is a compile-time constant (the loop below is
     // unrolled by two), so every LDS address is a lane constant plus an immediate offset.
     // Only PARTIAL tiles (full == false) run the mask arithmetic.
+    constexpr int kS = 2 * kSteps, kB = kS + 2 * kBlocks;
     auto tile = [&](auto BUF, int k0, bool full) {
         constexpr int buf = decltype(BUF)::value;
         // PARTIAL tile: this lane's allowed elements as a bit mask (the query reads keys
@@ -103,14 +107,14 @@ __global__ __launch_bounds__(256, 2) void psattn_dq_bf16_mfma(AttnArgs a) {
         // workgroup's wave.
         uint32_t bits = 0xffffffffu;
         // skip32[kb]: none of the wave's 32 queries reads any of the 32 keys of block kb (PARTIAL tiles
-        // only): the block's 24 MFMAs and its arithmetic are left out
+        // only): the block's kB MFMAs and its arithmetic are left out
         bool skip32[2] = {false, false};
         if (!full) {
             bits = elem_range_bits(tk.s - k0, q_row + 1 - k0, g) & ~elem_range_bits(tk.hole_lo - k0, tk.hole_hi - k0, g);
             skip32[0] = __builtin_amdgcn_ballot_w64((bits & 0xffffu) != 0) == 0;
             skip32[1] = __builtin_amdgcn_ballot_w64((bits >> 16) != 0) == 0;
             if (skip32[0]) {  // the next tile's copy rides on the first block's slots: issue it here instead
-                static_for<0, 8>([&](auto P) { pair_copy_piece<decltype(P)::value>(pc, sKb[buf ^ 1], sVb[buf ^ 1], w); });
+                static_for<0, 2 * kBlocks>([&](auto P) { pair_copy_piece<decltype(P)::value>(pc, sKb[buf ^ 1], sVb[buf ^ 1], w); });
                 if (skip32[1]) return;
             }
         }
@@ -119,14 +123,14 @@ __global__ __launch_bounds__(256, 2) void psattn_dq_bf16_mfma(AttnArgs a) {
         Frag8 ring[kRing];
         auto request = [&](auto M) {
             constexpr int m = decltype(M)::value;
-            if constexpr (m < 48) {
-                constexpr int kb = m / 24, j = m % 24;
-                if constexpr (j < 16) {
+            if constexpr (m < 2 * kB) {
+                constexpr int kb = m / kB, j = m % kB;
+                if constexpr (j < kS) {
                     constexpr int t = j >> 1;
-                    ring[m % kRing].v = ld_rows<t>(((j & 1) ? sV : sK) + kb * 32 * kRowBytes, lo.nat);
+                    ring[m % kRing].v = ld_rows<t>(((j & 1) ? sV : sK) + kb * 32 * kRB, lo.nat);
                 } else {
-                    constexpr int half = (j >> 2) & 1, db = j & 3;
-                    ring[m % kRing].v = ld_cols<db, half>(sK + 32 * kb * kRowBytes, lo.tr1, lo.tr2);
+                    constexpr int half = (j - kS) / kBlocks, db = (j - kS) % kBlocks;
+                    ring[m % kRing].v = ld_cols<db, half, D>(sK + 32 * kb * kRB, lo.tr1, lo.tr2);
                 }
             }
         };
@@ -134,14 +138,14 @@ __global__ __launch_bounds__(256, 2) void psattn_dq_bf16_mfma(AttnArgs a) {
             constexpr int kb = decltype(KB)::value;
             if (skip32[kb]) return;
             // the first operands of a block are requested by the block before it, unless there is none
-            if (kb == 0 || skip32[0]) static_for<0, kAhead>([&](auto M) { request(std::integral_constant<int, 24 * kb + decltype(M)::value>{}); });
+            if (kb == 0 || skip32[0]) static_for<0, kAhead>([&](auto M) { request(std::integral_constant<int, kB * kb + decltype(M)::value>{}); });
             f32x16 s, dp;
 #pragma unroll
             for (int i = 0; i < 16; ++i) { s[i] = 0.f; dp[i] = 0.f; }
-            static_for<0, 16>([&](auto J) {
-                constexpr int j = decltype(J)::value, m = 24 * kb + j, t = j >> 1;
+            static_for<0, kS>([&](auto J) {
+                constexpr int j = decltype(J)::value, m = kB * kb + j, t = j >> 1;
                 request(std::integral_constant<int, m + kAhead>{});
-                if constexpr (m < 16 && (m & 1) == 0) pair_copy_piece<m / 2>(pc, sKb[buf ^ 1], sVb[buf ^ 1], w);  // every other slot: see PairCopy
+                if constexpr (m < kS && (m & 1) == 0) pair_copy_piece<m / 2>(pc, sKb[buf ^ 1], sVb[buf ^ 1], w);  // every other slot: see PairCopy
                 if constexpr (j & 1) dp = mfma(ring[m % kRing].v, gf[t].v, dp);
                 else s = mfma(ring[m % kRing].v, qf[t].v, s);
                 __builtin_amdgcn_sched_barrier(0);
@@ -163,8 +167,8 @@ __global__ __launch_bounds__(256, 2) void psattn_dq_bf16_mfma(AttnArgs a) {
             dsb[0] = pack8(s, 0);
             dsb[1] = pack8(s, 1);
             __builtin_amdgcn_sched_barrier(0);
-            static_for<16, 24>([&](auto J) {
-                constexpr int j = decltype(J)::value, m = 24 * kb + j, half = (j >> 2) & 1, db = j & 3;
+            static_for<kS, kB>([&](auto J) {
+                constexpr int j = decltype(J)::value, m = kB * kb + j, half = (j - kS) / kBlocks, db = (j - kS) % kBlocks;
                 request(std::integral_constant<int, m + kAhead>{});
                 dq[db] = mfma(ring[m % kRing].v, dsb[half], dq[db]);
                 __builtin_amdgcn_sched_barrier(0);
@@ -198,7 +202,7 @@ __global__ __launch_bounds__(256, 2) void psattn_dq_bf16_mfma(AttnArgs a) {
     if (it < n_ent) step(std::integral_constant<int, 0>{});
     // no copy may still be writing to LDS when the workgroup ends
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if (a.rope) {
+    if constexpr (D == 128) if (a.rope) {
         // Q arrived rotated: what was accumulated is the gradient w.r.t. the rotated query; turning
         // it back by the same angles gives the gradient w.r.t. the unrotated one.  Accumulator
         // element i of block db is head dim 32 db + 8 (i / 4) + 4 g + i % 4; its partner sits in
@@ -224,7 +228,7 @@ __global__ __launch_bounds__(256, 2) void psattn_dq_bf16_mfma(AttnArgs a) {
         uint16_t* row = static_cast<uint16_t*>(a.dQ) + qoff;
         const float sc = a.scale;
 #pragma unroll
-        for (int db = 0; db < 4; ++db)
+        for (int db = 0; db < kBlocks; ++db)
 #pragma unroll
             for (int i4 = 0; i4 < 4; ++i4)
                 store4(row + 32 * db + 8 * i4 + 4 * g, dq[db][4 * i4] * sc, dq[db][4 * i4 + 1] * sc,
@@ -237,7 +241,9 @@ __global__ __launch_bounds__(256, 2) void psattn_dq_bf16_mfma(AttnArgs a) {
 int launch_mfma_dq(const AttnArgs& a, void* stream) {
     const unsigned grid = static_cast<unsigned>(a.meta.fwd.n_rows) * a.Hq;
     if (grid == 0) return 0;
-    psattn_dq_bf16_mfma<<<grid, 256, 0, static_cast<hipStream_t>(stream)>>>(a);
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    if (a.d == 128) psattn_dq_bf16_mfma<128><<<grid, 256, 0, s>>>(a);
+    else psattn_dq_bf16_mfma<64><<<grid, 256, 0, s>>>(a);
     return static_cast<int>(hipGetLastError());
 }
 

@@ -1,4 +1,4 @@
-// bf16 flash-attention kernels for gfx950 (MI355X), head_dim 128.
+// bf16 flash-attention kernels for gfx950 (MI355X), head_dim 128 and 64.
 //
 // What is computed is ordinary softmax attention on the pairs allowed by the
 // prefix-sharing mask (paper Algorithm 1 / Algorithm 3); tiles of the block mask
@@ -12,7 +12,7 @@
 //    next MFMA as a B operand straight from the accumulator registers (the
 //    accumulator's row order is absorbed into the order in which the other
 //    operand's rows are fetched).
-//  * K/V (or Q/dO) tiles are staged in LDS, 256-byte rows, with the 16-byte chunk
+//  * K/V (or Q/dO) tiles are staged in LDS, rows of 2 d bytes, with the 16-byte chunk
 //    index XOR-swizzled by the row so that both row-wise 128-bit reads and the
 //    transposing 64-bit reads (ds_read_b64_tr_b16) are bank-conflict free without
 //    padding.  Tiles are copied global -> LDS asynchronously, one tile ahead, into
@@ -41,7 +41,11 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
-constexpr int kRowBytes = 256;  // 128 bf16
+
+// LDS tile rows are the head dimension: 256 bytes (d = 128) or 128 bytes (d = 64).
+template <int D>
+constexpr int kRowBytesOf = 2 * D;
+constexpr int kRowBytes = kRowBytesOf<128>;
 
 // compile-time loop: f(std::integral_constant<int, I>) for I in [B, E)
 template <int B, int E, typename F>
@@ -59,32 +63,19 @@ union Frag8 {
     uint4 u;
 };
 
+// XOR on the 16-byte chunk index of row `row`.  Sixteen consecutive rows at one logical chunk cover all 64 banks
+// (row-wise 128-bit reads), and so do four consecutive rows at four neighbouring chunks (transposing reads).  A
+// 128-byte row is half the width of the banks: the row's lowest bit selects the half, the next three make the XOR.
+template <int D>
+__device__ inline int row_swizzle(int row) {
+    if constexpr (D == 128) return ((row & 3) << 2) | ((row >> 2) & 3);
+    else return ((row & 2) << 1) | ((row >> 2) & 3);
+}
+
 // byte offset of 16-byte chunk `chunk` of row `row` in a swizzled tile
+template <int D>
 __device__ inline int tile_off(int row, int chunk) {
-    const int sw = ((row & 3) << 2) | ((row >> 2) & 3);
-    return row * kRowBytes + ((chunk ^ sw) << 4);
-}
-
-// MFMA A operand, rows taken as they are stored: 8 consecutive bf16 of one row.
-__device__ inline bf16x8 lds_rows(const char* tile, int row, int chunk) {
-    return *reinterpret_cast<const bf16x8*>(tile + tile_off(row, chunk));
-}
-
-// MFMA A operand of the transposed tile: lane (l % 32) is column col0 + l % 32 of
-// the stored tile, its 8 values are stored rows r0 + {0..3} and r0 + 8 + {0..3}
-// where r0 = row0 + 4 * (l / 32).  This is the row order in which a 32x32
-// accumulator hands its values to the next MFMA.
-__device__ inline bf16x8 lds_cols(const char* tile, int row0, int col0, int l) {
-    const int i16 = l & 15;
-    const int row = row0 + 4 * (l >> 5) + (i16 >> 2);
-    const int col = col0 + 16 * ((l >> 4) & 1) + 4 * (i16 & 3);
-    const int sub = (col & 7) * 2;
-    Frag8 f;
-    f.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
-        (lds_bf16x4*)(tile + tile_off(row, col >> 3) + sub));
-    f.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
-        (lds_bf16x4*)(tile + tile_off(row + 8, col >> 3) + sub));
-    return f.v;
+    return row * kRowBytesOf<D> + ((chunk ^ row_swizzle<D>(row)) << 4);
 }
 
 // Per-lane LDS byte offsets of the two operand fetch patterns, relative to the first
@@ -95,18 +86,22 @@ __device__ inline bf16x8 lds_cols(const char* tile, int row0, int col0, int l) {
 //   transposed, block db:    tr1 ^ (db << 6)    rows 4 (l / 32) + (l % 16) / 4, first four
 //                            tr2 ^ (db << 6)    the same, eight rows further down
 // A tile base that is a multiple of 256 bytes may be added to the lane constant first.
+// MFMA operands: row-wise, a lane holds 8 consecutive bf16 of one row; transposed, lane l holds column
+// col0 + l % 32, stored rows r0 + {0..3} and r0 + 8 + {0..3} with r0 = row0 + 4 * (l / 32), which is the
+// row order in which a 32x32 accumulator hands its values to the next MFMA.
 struct LaneOffsets {
     int nat, tr1, tr2;
 };
 
+template <int D = 128>
 __device__ inline LaneOffsets lane_offsets(int l) {
     LaneOffsets o;
     const int c32 = l & 31, g = l >> 5, i16 = l & 15;
-    o.nat = tile_off(c32, g);
+    o.nat = tile_off<D>(c32, g);
     const int row = 4 * g + (i16 >> 2);
     const int col = 16 * ((l >> 4) & 1) + 4 * (i16 & 3);
-    o.tr1 = tile_off(row, col >> 3) + (col & 7) * 2;
-    o.tr2 = tile_off(row + 8, col >> 3) + (col & 7) * 2;
+    o.tr1 = tile_off<D>(row, col >> 3) + (col & 7) * 2;
+    o.tr2 = tile_off<D>(row + 8, col >> 3) + (col & 7) * 2;
     return o;
 }
 
@@ -117,11 +112,11 @@ __device__ __forceinline__ bf16x8 ld_rows(const char* blk, int nat) {
 }
 
 // transposed MFMA operand: head-dim block DB, stored rows 16 HALF + {0..15} of the block
-template <int DB, int HALF>
+template <int DB, int HALF, int D = 128>
 __device__ __forceinline__ bf16x8 ld_cols(const char* blk, int tr1, int tr2) {
     Frag8 f;
-    f.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(blk + (tr1 ^ (DB << 6)) + 16 * HALF * kRowBytes));
-    f.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(blk + (tr2 ^ (DB << 6)) + 16 * HALF * kRowBytes));
+    f.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(blk + (tr1 ^ (DB << 6)) + 16 * HALF * kRowBytesOf<D>));
+    f.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(blk + (tr2 ^ (DB << 6)) + 16 * HALF * kRowBytesOf<D>));
     return f.v;
 }
 
@@ -199,24 +194,27 @@ __device__ __forceinline__ void dma_wait_barrier() {
     asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
-// Copy of a 64-row tile (256-byte rows, rows `row_bytes` apart in global memory) into a
-// swizzled LDS tile.  A wave instruction fills four tile rows, so the swizzle is applied
-// on the global side: lane l fetches the logical chunk that belongs at physical chunk
-// l % 16 of row r4 + l / 16.  Each of the four waves of a workgroup copies 16 rows in 4
+// Copy of a 64-row tile (rows `row_bytes` apart in global memory) into a swizzled LDS tile.
+// A wave instruction fills 1024 bytes, four tile rows (d = 128) or eight (d = 64), so the
+// swizzle is applied on the global side: lane l fetches the logical chunk that belongs at its
+// physical chunk.  Each of the four waves of a workgroup copies 16 rows in D / 32
 // instructions; DmaLane holds the lane's byte offsets for them, so that a copy costs no
 // vector ALU work: the address is a scalar tile base plus that 32-bit lane offset.
-struct DmaLane {
-    uint32_t off[4];
+template <int D>
+struct DmaLaneOf {
+    uint32_t off[D / 32];
 };
+using DmaLane = DmaLaneOf<128>;
 
 // `w` (wave index in the workgroup) must be wave-uniform; rows past `last_row` re-read it
-__device__ __forceinline__ DmaLane dma_lane(uint32_t row_bytes, int w, int l, int last_row = 63) {
-    DmaLane d;
+template <int D = 128>
+__device__ __forceinline__ DmaLaneOf<D> dma_lane(uint32_t row_bytes, int w, int l, int last_row = 63) {
+    DmaLaneOf<D> d;
+    constexpr int kChunks = D / 8, kRows = 64 / kChunks;  // 16-byte chunks of a row, rows per instruction
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int row = 16 * w + 4 * i + (l >> 4);
-        const int sw = ((row & 3) << 2) | ((row >> 2) & 3);
-        d.off[i] = static_cast<uint32_t>(min(row, last_row)) * row_bytes + (((l & 15) ^ sw) << 4);
+    for (int i = 0; i < D / 32; ++i) {
+        const int row = 16 * w + kRows * i + l / kChunks;
+        d.off[i] = static_cast<uint32_t>(min(row, last_row)) * row_bytes + (((l % kChunks) ^ row_swizzle<D>(row)) << 4);
     }
     return d;
 }
@@ -225,48 +223,37 @@ __device__ __forceinline__ void dma16(const void* base, uint32_t lane_off, uint3
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(lane_off), "s"(base) : "memory");
 }
 
-// `base`: first row of the tile (wave-uniform); `tile`: LDS tile; `full`: the lane offsets
-// of an unclipped tile; a tile whose last valid row is < 63 takes the clamped offsets.
-__device__ __forceinline__ void dma_tile64(const char* base, uint32_t row_bytes, int last_row, const DmaLane& full, const char* tile, int w, int l) {
-    const uint32_t lds = lds_addr(tile) + 16 * w * kRowBytes;
-    if (last_row >= 63) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) dma16(base, full.off[i], lds + 4 * i * kRowBytes);
-    } else {
-        asm volatile("; clipped tile" : "+s"(last_row));  // keeps the clamped offsets' arithmetic in this branch
-        const DmaLane c = dma_lane(row_bytes, w, l, last_row);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) dma16(base, c.off[i], lds + 4 * i * kRowBytes);
-    }
-}
-
 // Copy of a pair of tiles (K and V of one key block, or Q and dO of one query block) as
 // eight separate instructions per lane, so that a kernel can spread them over its MFMA
 // slots: issued back to back they hold the wave for about a thousand cycles (the CU's
 // address unit takes one such instruction per ~16 cycles and the waves of a workgroup issue
 // theirs at the same moment).  One piece every other slot keeps the unit's queue short.
-// Pieces 0-3 belong to the first tile, 4-7 to the second.
-struct PairCopy {
+// The first D / 32 pieces belong to the first tile, the rest to the second.
+template <int D = 128>
+struct PairCopyOf {
     const char* a;  // first row of the first tile (wave-uniform)
     const char* b;  // first row of the second tile
-    DmaLane lane;
+    DmaLaneOf<D> lane;
 };
+using PairCopy = PairCopyOf<128>;
 
-__device__ __forceinline__ void pair_copy_setup(PairCopy& c, const char* a, const char* b, uint32_t row_bytes, int last_row,
-                                                const DmaLane& full, int w, int l) {
+template <int D>
+__device__ __forceinline__ void pair_copy_setup(PairCopyOf<D>& c, const char* a, const char* b, uint32_t row_bytes, int last_row,
+                                                const DmaLaneOf<D>& full, int w, int l) {
     c.a = a;
     c.b = b;
     c.lane = full;
     if (last_row < 63) {
         asm volatile("; clipped tile" : "+s"(last_row));  // keeps the clamped offsets' arithmetic in this branch
-        c.lane = dma_lane(row_bytes, w, l, last_row);
+        c.lane = dma_lane<D>(row_bytes, w, l, last_row);
     }
 }
 
-template <int P>
-__device__ __forceinline__ void pair_copy_piece(const PairCopy& c, const char* tile_a, const char* tile_b, int w) {
-    if constexpr (P < 4) dma16(c.a, c.lane.off[P], lds_addr(tile_a) + (16 * w + 4 * P) * kRowBytes);
-    else dma16(c.b, c.lane.off[P - 4], lds_addr(tile_b) + (16 * w + 4 * (P - 4)) * kRowBytes);
+template <int P, int D>
+__device__ __forceinline__ void pair_copy_piece(const PairCopyOf<D>& c, const char* tile_a, const char* tile_b, int w) {
+    constexpr int n = D / 32;
+    if constexpr (P < n) dma16(c.a, c.lane.off[P], lds_addr(tile_a) + 16 * w * kRowBytesOf<D> + 1024 * P);
+    else dma16(c.b, c.lane.off[P - n], lds_addr(tile_b) + 16 * w * kRowBytesOf<D> + 1024 * (P - n));
 }
 
 // Reader of a tile list walked in one direction: position k = 0, 1, ... maps to

@@ -10,9 +10,12 @@ __device__ __forceinline__ float fmax3(float a, float b, float c) { return __bui
 
 // ------------------------------------------------------------------ forward
 // grid: one workgroup per (q-tile of 128 queries, q-head); 4 waves x 32 queries.
-__global__ __launch_bounds__(256, 2) void psattn_fwd_bf16_mfma(AttnArgs a) {
-    __shared__ __attribute__((aligned(16))) char sKb[2][64 * kRowBytes];  // double buffered
-    __shared__ __attribute__((aligned(16))) char sVb[2][64 * kRowBytes];
+// D = head_dim.  D = 128: 64 KB of LDS and under 256 registers, two workgroups per CU.  D = 64: half of both.
+template <int D>
+__global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(AttnArgs a) {
+    constexpr int kRB = kRowBytesOf<D>, kSteps = D / 16, kBlocks = D / 32;  // MFMA steps of a score, 32-wide blocks of an output row
+    __shared__ __attribute__((aligned(16))) char sKb[2][64 * kRB];  // double buffered
+    __shared__ __attribute__((aligned(16))) char sVb[2][64 * kRB];
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, c32 = l & 31, g = l >> 5;
     const int T = a.meta.T, Hq = a.Hq, Hkv = a.Hkv, G = Hq / Hkv;
     const DeviceCsr& csr = a.meta.fwd;
@@ -26,17 +29,16 @@ __global__ __launch_bounds__(256, 2) void psattn_fwd_bf16_mfma(AttnArgs a) {
     if (valid) tk = a.meta.tok[q_row];
 
     const uint16_t* Q = static_cast<const uint16_t*>(a.Q);
-    const uint16_t* K = static_cast<const uint16_t*>(a.K) + kvh * 128;
-    const uint16_t* V = static_cast<const uint16_t*>(a.V) + kvh * 128;
-    const size_t kv_stride = static_cast<size_t>(Hkv) * 128;
+    const uint16_t* K = static_cast<const uint16_t*>(a.K) + kvh * D;
+    const uint16_t* V = static_cast<const uint16_t*>(a.V) + kvh * D;
 
-    Frag8 qf[8];
+    Frag8 qf[kSteps];
 #pragma unroll
-    for (int t = 0; t < 8; ++t)
-        qf[t].u = valid ? *reinterpret_cast<const uint4*>(Q + (static_cast<size_t>(q_row) * Hq + h) * 128 + 16 * t + 8 * g)
+    for (int t = 0; t < kSteps; ++t)
+        qf[t].u = valid ? *reinterpret_cast<const uint4*>(Q + (static_cast<size_t>(q_row) * Hq + h) * D + 16 * t + 8 * g)
                         : make_uint4(0, 0, 0, 0);
 
-    if (a.rope) {
+    if constexpr (D == 128) if (a.rope) {
         // rotary embedding of this lane's query in registers; the rotated row is also saved for
         // the backward, which streams Q tiles straight into LDS and cannot rotate them on the way
         const float* row = a.rope + static_cast<size_t>(rope_position(tk, q_row)) * 128;
@@ -48,23 +50,23 @@ __global__ __launch_bounds__(256, 2) void psattn_fwd_bf16_mfma(AttnArgs a) {
             for (int t = 0; t < 8; ++t) *reinterpret_cast<uint4*>(qr + 16 * t + 8 * g) = qf[t].u;
         }
     }
-    f32x16 o[4];
+    f32x16 o[kBlocks];
 #pragma unroll
-    for (int db = 0; db < 4; ++db)
+    for (int db = 0; db < kBlocks; ++db)
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[db][i] = 0.f;
     float m = -INFINITY, lsum = 0.f;
     const float c = a.scale * kLog2e;
-    const LaneOffsets lo = lane_offsets(l);
+    const LaneOffsets lo = lane_offsets<D>(l);
     constexpr int kAhead = 2, kRing = 4;  // measured: 1 and 3 are both slower
 
     // K / V tiles are copied global -> LDS asynchronously, one tile ahead, into the
     // buffer the previous tile has just vacated; one barrier per tile.
-    const uint32_t row_bytes = static_cast<uint32_t>(Hkv) * 256u;
+    const uint32_t row_bytes = static_cast<uint32_t>(Hkv) * kRB;
     const char* Kb = reinterpret_cast<const char*>(K);
     const char* Vb = reinterpret_cast<const char*>(V);
-    const DmaLane dl = dma_lane(row_bytes, w, l);
-    PairCopy pc;
+    const DmaLaneOf<D> dl = dma_lane<D>(row_bytes, w, l);
+    PairCopyOf<D> pc;
     auto copy_setup = [&](int ent) {
         const int k0 = (ent >> 2) * 64;
         pair_copy_setup(pc, Kb + static_cast<size_t>(k0) * row_bytes, Vb + static_cast<size_t>(k0) * row_bytes, row_bytes,
@@ -77,7 +79,7 @@ __global__ __launch_bounds__(256, 2) void psattn_fwd_bf16_mfma(AttnArgs a) {
     if (n_ent > 0) {
         ent = rl.first_entry;
         copy_setup(ent);
-        static_for<0, 8>([&](auto P) { pair_copy_piece<decltype(P)::value>(pc, sKb[0], sVb[0], w); });
+        static_for<0, 2 * kBlocks>([&](auto P) { pair_copy_piece<decltype(P)::value>(pc, sKb[0], sVb[0], w); });
     }
     // One tile.  The buffer index is a compile-time constant (the loop below is unrolled
     // by two), so every LDS address is a lane constant plus an immediate offset.
@@ -104,24 +106,25 @@ __global__ __launch_bounds__(256, 2) void psattn_fwd_bf16_mfma(AttnArgs a) {
         if (!full) {
             bits = elem_range_bits(tk.s - k0, q_row + 1 - k0, g) & ~elem_range_bits(tk.hole_lo - k0, tk.hole_hi - k0, g);
             if (__builtin_amdgcn_ballot_w64(bits != 0) == 0) {
-                static_for<0, 8>([&](auto P) { pair_copy_piece<decltype(P)::value>(pc, sKb[buf ^ 1], sVb[buf ^ 1], w); });
+                static_for<0, 2 * kBlocks>([&](auto P) { pair_copy_piece<decltype(P)::value>(pc, sKb[buf ^ 1], sVb[buf ^ 1], w); });
                 return;
             }
         }
         const char* sK = sKb[buf];
         const char* sV = sVb[buf];
-        // 32 MFMA slots per tile: 0-15 S^T = K Q^T (rows = keys, column = this lane's
-        // query), 16-31 O^T += V^T P^T.  The LDS operand of slot m is requested kAhead
+        // 2 kS MFMA slots per tile: 0 .. kS - 1 S^T = K Q^T (rows = keys, column = this lane's
+        // query), kS .. 2 kS - 1 O^T += V^T P^T.  The LDS operand of slot m is requested kAhead
         // slots earlier into a register ring.
+        constexpr int kS = 2 * kSteps;
         Frag8 ring[kRing];
         auto request = [&](auto M) {
             constexpr int m = decltype(M)::value;
-            if constexpr (m < 16) {
+            if constexpr (m < kS) {
                 constexpr int t = m >> 1, kb = m & 1;
-                ring[m % kRing].v = ld_rows<t>(sK + kb * 32 * kRowBytes, lo.nat);
-            } else if constexpr (m < 32) {
-                constexpr int j = m - 16, kb = j >> 3, half = (j >> 2) & 1, db = j & 3;
-                ring[m % kRing].v = ld_cols<db, half>(sV + 32 * kb * kRowBytes, lo.tr1, lo.tr2);
+                ring[m % kRing].v = ld_rows<t>(sK + kb * 32 * kRB, lo.nat);
+            } else if constexpr (m < 2 * kS) {
+                constexpr int j = m - kS, kb = j / (2 * kBlocks), half = (j / kBlocks) & 1, db = j % kBlocks;
+                ring[m % kRing].v = ld_cols<db, half, D>(sV + 32 * kb * kRB, lo.tr1, lo.tr2);
             }
         };
         f32x16 s[2];
@@ -130,7 +133,7 @@ __global__ __launch_bounds__(256, 2) void psattn_fwd_bf16_mfma(AttnArgs a) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) s[kb][i] = 0.f;
         static_for<0, kAhead>([&](auto M) { request(M); });
-        static_for<0, 16>([&](auto M) {
+        static_for<0, kS>([&](auto M) {
             constexpr int m = decltype(M)::value, t = m >> 1, kb = m & 1;
             request(std::integral_constant<int, m + kAhead>{});
             if constexpr ((m & 1) == 0) pair_copy_piece<m / 2>(pc, sKb[buf ^ 1], sVb[buf ^ 1], w);  // every other slot: see PairCopy
@@ -173,7 +176,7 @@ __global__ __launch_bounds__(256, 2) void psattn_fwd_bf16_mfma(AttnArgs a) {
             const float alpha = __builtin_amdgcn_exp2f(m - m_to);  // m = -inf: 0 (nothing accumulated yet)
             lsum *= alpha;
 #pragma unroll
-            for (int db = 0; db < 4; ++db)
+            for (int db = 0; db < kBlocks; ++db)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) o[db][i] *= alpha;
             m = m_new;
@@ -194,8 +197,8 @@ __global__ __launch_bounds__(256, 2) void psattn_fwd_bf16_mfma(AttnArgs a) {
         const float psum = (ps[0] + ps[1]) + (ps[2] + ps[3]);
         lsum += psum;
         __builtin_amdgcn_sched_barrier(0);
-        static_for<16, 32>([&](auto M) {
-            constexpr int m_ = decltype(M)::value, j = m_ - 16, kb = j >> 3, half = (j >> 2) & 1, db = j & 3;
+        static_for<kS, 2 * kS>([&](auto M) {
+            constexpr int m_ = decltype(M)::value, j = m_ - kS, kb = j / (2 * kBlocks), half = (j / kBlocks) & 1, db = j % kBlocks;
             request(std::integral_constant<int, m_ + kAhead>{});
             o[db] = mfma(ring[m_ % kRing].v, pb[kb][half], o[db]);
             __builtin_amdgcn_sched_barrier(0);
@@ -214,9 +217,9 @@ __global__ __launch_bounds__(256, 2) void psattn_fwd_bf16_mfma(AttnArgs a) {
     const float l_tot = lsum + other_half(lsum);
     const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
     if (valid) {
-        uint16_t* orow = static_cast<uint16_t*>(a.Oout) + (static_cast<size_t>(q_row) * Hq + h) * 128;
+        uint16_t* orow = static_cast<uint16_t*>(a.Oout) + (static_cast<size_t>(q_row) * Hq + h) * D;
 #pragma unroll
-        for (int db = 0; db < 4; ++db)
+        for (int db = 0; db < kBlocks; ++db)
 #pragma unroll
             for (int i4 = 0; i4 < 4; ++i4)
                 store4(orow + 32 * db + 8 * i4 + 4 * g, o[db][4 * i4] * inv, o[db][4 * i4 + 1] * inv,
@@ -231,7 +234,9 @@ __global__ __launch_bounds__(256, 2) void psattn_fwd_bf16_mfma(AttnArgs a) {
 int launch_mfma_fwd(const AttnArgs& a, void* stream) {
     const unsigned grid = static_cast<unsigned>(a.meta.fwd.n_rows) * a.Hq;
     if (grid == 0) return 0;
-    psattn_fwd_bf16_mfma<<<grid, 256, 0, static_cast<hipStream_t>(stream)>>>(a);
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    if (a.d == 128) psattn_fwd_bf16_mfma<128><<<grid, 256, 0, s>>>(a);
+    else psattn_fwd_bf16_mfma<64><<<grid, 256, 0, s>>>(a);
     return static_cast<int>(hipGetLastError());
 }
 

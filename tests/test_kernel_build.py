@@ -100,3 +100,14 @@ def test_compiler_keeps_m0_and_the_copy_counter_free(tmp_path, src):
             m = re.match(r"(global_load|buffer_load|flat_load|scratch_load)\w*", code)
             if m:
                 assert m.group(0) == "global_load_dword", code
+
+
+def test_dkdv64_two_waves_per_simd_without_spills(tmp_path):
+    """The head_dim 64 dK/dV kernel is left to the compiler: two waves per SIMD, nothing spilled, M0 untouched."""
+    text = _asm(tmp_path, "psattn_mfma_dkdv64.hip")
+    meta = _kernel_meta(text, "psattn_dkdv64_bf16_mfma")
+    assert int(meta["vgpr_count"]) <= 256 and int(meta["agpr_count"]) == 0
+    assert int(meta["vgpr_spill_count"]) == 0 and int(meta["sgpr_spill_count"]) == 0
+    assert int(meta["private_segment_fixed_size"]) == 0
+    for code in _outside_asm(text):
+        assert not re.search(r"\bm0\b", code), code

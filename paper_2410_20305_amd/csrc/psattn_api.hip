@@ -269,16 +269,10 @@ int bwd_checked(const psattn_meta* meta, int32_t dt, int32_t n_q_heads, int32_t 
     int err = 0;
     const bool mfma = mfma_bwd_ok(meta, dt, head_dim, scale);
     if (rope_table && !(mfma && head_dim == 128)) return PSATTN_EUNSUPPORTED;  // rotary embedding lives in these matrix-core kernels only
-    if (!mfma) {  // the MFMA dQ kernel computes delta itself and leaves it in the scratch
-        PassTimer t(1, hip_stream);
-        err = launch_delta(dt, a, hip_stream);
-        g_last_kernel[1] = "delta_kernel";
-    }
-    if (err) return PSATTN_EHIP;
-    {
+    {  // the dQ kernels compute delta themselves and leave it in the scratch for the dK/dV pass
         PassTimer t(2, hip_stream);
         err = mfma ? launch_mfma_dq(a, hip_stream) : launch_generic_dq(dt, a, hip_stream);
-        g_last_kernel[2] = mfma ? "psattn_dq_bf16_mfma" : "generic_dq";
+        g_last_kernel[1] = g_last_kernel[2] = mfma ? "psattn_dq_bf16_mfma" : "generic_dq";
     }
     if (err) return PSATTN_EHIP;
     {
@@ -427,7 +421,7 @@ const char* psattn_kernel_name(int32_t dt, int32_t pass) {
     const bool bf = dt == PSATTN_BF16;
     switch (pass) {
         case 0: return bf ? "psattn_fwd_bf16_mfma" : "generic_fwd";
-        case 1: return "delta_kernel";
+        case 1:
         case 2: return bf ? "psattn_dq_bf16_mfma" : "generic_dq";
         default: return bf ? "psattn_dkdv_bf16_mfma" : "generic_dkdv";
     }

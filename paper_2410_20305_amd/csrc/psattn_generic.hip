@@ -1,12 +1,27 @@
-// Plain-FMA kernels for any tile grid, float or bfloat16 storage, head_dim 64 or
-// 128.  They serve the fp32 configuration (where the 1e-5 tolerance rules out
-// bf16 matrix cores) and every shape the MFMA kernels are not built for.  One
-// thread owns one query row (forward, dQ) or one key row (dK/dV); scores are
-// never stored.  All accumulation is fp32 with expf/logf.
+// fp32 matrix-core kernels for any tile grid, any scale, float or bfloat16 storage, head_dim 64 or 128.  They serve
+// the fp32 configuration (where the 1e-5 tolerance rules out bf16 products) and every shape the bf16 kernels are not
+// built for.  All products are v_mfma_f32_16x16x4_f32 (fp32 operands, fp32 accumulation), exponentials are expf / logf;
+// scores are never stored.
 //
-// The tile lists come from the block mask (paper Section 3.1): only tiles that
-// hold an allowed pair are visited, FULL tiles skip the per-pair mask test of
-// Algorithm 3.
+// What bounds them: at the sizes this path is used for (up to a few thousand tokens on a few heads) the chip is far
+// from full and a kernel lasts as long as its longest chain of loads, so the work is cut as finely as the matrix
+// instruction allows: a workgroup owns 16 queries of one head (forward, dQ) or 16 keys of one kv-head (dK/dV) and its
+// eight waves share the 16-wide blocks of the other axis round-robin; their partial results are combined through LDS
+// in a fixed order (no atomics).  Operands go from global memory (L1 / L2) straight into registers as 16-byte loads
+// in both orientations; nothing is staged.  A step of one 168-token fp32 sample on one head of 64: forward 222 us,
+// delta + dQ 143 us, dK/dV 524 us with one thread per row; see the launchers for the figures of these.
+//
+// Operand layout of the 16x16x4 product (r = lane % 16, g = lane / 16): A element (row r, k g), B element (k g,
+// column r), C register i = (row 4 g + i, column r).
+//   scores   S^T = K Q^T: a lane loads 16 bytes of its key's (query's) row at head dims 16 t + 4 g; component c of
+//            load t is step (t, c), which contracts head dims {16 t + 4 g + c}.
+//   outputs  O^T += V^T P^T: C register i of the scores is the B operand of step i, which contracts keys {4 g + i};
+//            the A operand is 16 bytes of key 4 g + i at head dims 64 h + 4 r: component c gives output block (h, c),
+//            whose row r is head dim 64 h + 4 r + c, so that a lane ends up with four neighbouring head dims.
+//
+// Which 16-wide blocks hold an allowed pair follows from the per-token descriptors of Algorithm 3 alone (a query block
+// reads keys from its earliest sample start to its last query, without the blocks that are hidden from all its rows;
+// a key block is read by queries up to its largest key_hi), so the tile lists are not needed here.
 #include <hip/hip_runtime.h>
 
 #include "psattn_internal.h"
@@ -14,218 +29,319 @@
 namespace psattn {
 namespace {
 
-__device__ inline float ld(const float* p) { return *p; }
-__device__ inline float ld(const uint16_t* p) { return __uint_as_float(static_cast<uint32_t>(*p) << 16); }
-__device__ inline void st(float* p, float v) { *p = v; }
-__device__ inline void st(uint16_t* p, float v) {  // round to nearest even
-    uint32_t u = __float_as_uint(v);
-    if ((u & 0x7fffffffu) > 0x7f800000u) { *p = static_cast<uint16_t>((u >> 16) | 0x40); return; }
-    u += 0x7fffu + ((u >> 16) & 1u);
-    *p = static_cast<uint16_t>(u >> 16);
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kWaves = 8, kThreads = 64 * kWaves;
+constexpr int kB = 16;  // rows of a block
+
+__device__ inline f32x4 ld4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
+__device__ inline f32x4 ld4(const uint16_t* p) {
+    const uint2 u = *reinterpret_cast<const uint2*>(p);
+    f32x4 v;
+    v[0] = __uint_as_float(u.x << 16); v[1] = __uint_as_float(u.x & 0xffff0000u);
+    v[2] = __uint_as_float(u.y << 16); v[3] = __uint_as_float(u.y & 0xffff0000u);
+    return v;
 }
+__device__ inline uint32_t bf16_bits(float v) {  // round to nearest even
+    uint32_t u = __float_as_uint(v);
+    if ((u & 0x7fffffffu) > 0x7f800000u) return (u >> 16) | 0x40;
+    u += 0x7fffu + ((u >> 16) & 1u);
+    return u >> 16;
+}
+__device__ inline void st4(float* p, f32x4 v) { *reinterpret_cast<f32x4*>(p) = v; }
+__device__ inline void st4(uint16_t* p, f32x4 v) {
+    *reinterpret_cast<uint2*>(p) = make_uint2(bf16_bits(v[0]) | (bf16_bits(v[1]) << 16), bf16_bits(v[2]) | (bf16_bits(v[3]) << 16));
+}
+
+__device__ inline f32x4 mfma4(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
 __device__ inline bool allowed(const Tok4& t, int q, int kv) {
     return kv >= t.s && kv <= q && !(kv >= t.hole_lo && kv < t.hole_hi);
 }
 
-constexpr int kThreads = 64;
+template <typename F>
+__device__ inline int over_rows(int x, F f) {  // f over the 16 rows of the block (the same in all lanes)
+#pragma unroll
+    for (int m = 1; m < 16; m <<= 1) x = f(x, __shfl_xor(x, m));
+    return __builtin_amdgcn_readfirstlane(x);
+}
+__device__ inline float sum_groups(float x) {  // over the four lanes that share a row
+    x += __shfl_xor(x, 16);
+    return x + __shfl_xor(x, 32);
+}
+
+// Key blocks that the 16 queries of a block can read: [first, last], except those inside [hole_lo, hole_hi).
+struct KeyRange {
+    int first, last, hole_lo, hole_hi;
+    __device__ inline bool skip(int kb) const { return kB * kb >= hole_lo && kB * kb + kB <= hole_hi; }
+};
+__device__ inline KeyRange key_range(const Tok4& tk, int q0, int T) {
+    const bool real = tk.s != kPadStart;
+    KeyRange k;
+    const int s = over_rows(tk.s, [](int x, int y) { return min(x, y); });
+    k.hole_lo = over_rows(real ? tk.hole_lo : INT32_MIN, [](int x, int y) { return max(x, y); });
+    k.hole_hi = over_rows(real ? tk.hole_hi : INT32_MAX, [](int x, int y) { return min(x, y); });
+    k.first = s / kB;
+    k.last = s == kPadStart ? -1 : (min(T, q0 + kB) - 1) / kB;
+    return k;
+}
+
+// rows `row` of a [T, H, D] tensor, clamped to the last token (what a clamped row yields is masked)
+template <typename E, int D>
+__device__ inline const E* row_of(const void* base, int row, int T, int H, int h) {
+    return static_cast<const E*>(base) + (static_cast<size_t>(min(row, T - 1)) * H + h) * D;
+}
+
+// score operand: this lane's 16 bytes of every 16 head dims of its row
+template <typename E, int D>
+__device__ inline void load_rows(f32x4 (&x)[D / 16], const E* row, int g) {
+#pragma unroll
+    for (int t = 0; t < D / 16; ++t) x[t] = ld4(row + 16 * t + 4 * g);
+}
+template <int D>
+__device__ inline f32x4 dot_rows(const f32x4 (&x)[D / 16], const f32x4 (&y)[D / 16]) {
+    f32x4 s = {0.f, 0.f, 0.f, 0.f}, s2 = s;  // two chains: a dependent product waits for the one before it
+#pragma unroll
+    for (int t = 0; t < D / 16; ++t) {
+        s = mfma4(x[t][0], y[t][0], s);
+        s2 = mfma4(x[t][1], y[t][1], s2);
+        s = mfma4(x[t][2], y[t][2], s);
+        s2 = mfma4(x[t][3], y[t][3], s2);
+    }
+    return s + s2;
+}
+// output operand: 16 bytes of each of the block's rows 4 g + i
+template <typename E, int D>
+__device__ inline void load_cols(f32x4 (&x)[4][D / 64], const void* base, int r0, int T, int H, int h, int r, int g) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const E* row = row_of<E, D>(base, r0 + 4 * g + i, T, H, h);
+#pragma unroll
+        for (int hh = 0; hh < D / 64; ++hh) x[i][hh] = ld4(row + 64 * hh + 4 * r);
+    }
+}
+template <int D>
+__device__ inline void add_outer(f32x4 (&acc)[D / 16], const f32x4 (&x)[4][D / 64], const f32x4& p) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int b = 0; b < D / 16; ++b) acc[b] = mfma4(x[i][b >> 2][b & 3], p[i], acc[b]);
+}
+
+// partial results of the waves, [wave][row][head dim], rows padded against bank conflicts
+template <int D>
+struct Partials {
+    float v[kWaves][kB][D + 4];
+};
+template <int D>
+__device__ inline void put_partial(Partials<D>& sm, const f32x4 (&acc)[D / 16], int w, int r, int g) {
+#pragma unroll
+    for (int hh = 0; hh < D / 64; ++hh)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const f32x4 v = {acc[4 * hh][i], acc[4 * hh + 1][i], acc[4 * hh + 2][i], acc[4 * hh + 3][i]};
+            *reinterpret_cast<f32x4*>(&sm.v[w][r][64 * hh + 16 * g + 4 * i]) = v;
+        }
+}
+// the workgroup's 512 threads as (row, four head dims); D = 64 needs half of them
+template <int D>
+__device__ inline bool my_quad(int tid, int& row, int& d) {
+    row = tid / (D / 4);
+    d = 4 * (tid % (D / 4));
+    return row < kB;
+}
+template <int D>
+__device__ inline f32x4 sum_partials(const Partials<D>& sm, int row, int d) {
+    f32x4 v = *reinterpret_cast<const f32x4*>(&sm.v[0][row][d]);
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) v += *reinterpret_cast<const f32x4*>(&sm.v[w][row][d]);
+    return v;
+}
 
 // ---------------------------------------------------------------- forward
 template <typename E, int D>
 __global__ __launch_bounds__(kThreads) void generic_fwd(AttnArgs a) {
-    const DeviceCsr& g = a.meta.fwd;
-    const int T = a.meta.T, Hq = a.Hq, Hkv = a.Hkv;
-    const int tile = g.order[blockIdx.x / Hq];
-    const int h = blockIdx.x % Hq, kvh = h / (Hq / Hkv);
-    const E* Q = static_cast<const E*>(a.Q);
-    const E* K = static_cast<const E*>(a.K);
-    const E* V = static_cast<const E*>(a.V);
-    E* O = static_cast<E*>(a.Oout);
-    const int q_end = min(T, (tile + 1) * g.tile_q);
-    for (int i = tile * g.tile_q + threadIdx.x; i < q_end; i += kThreads) {
-        const Tok4 t = a.meta.tok[i];
-        float q[D], acc[D];
+    __shared__ Partials<D> sm;
+    __shared__ float s_m[kWaves][kB], s_l[kWaves][kB];
+    const int T = a.meta.T, Hq = a.Hq, Hkv = a.Hkv, n_blocks = (T + kB - 1) / kB;
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), r = tid & 15, g = (tid >> 4) & 3;
+    const int h = blockIdx.x % Hq, kvh = h / (Hq / Hkv), q0 = kB * (n_blocks - 1 - static_cast<int>(blockIdx.x) / Hq);
+    const int q = q0 + r;
+    Tok4 tk = {kPadStart, 0, 0, 0};
+    if (q < T) tk = a.meta.tok[q];
+    f32x4 qf[D / 16], acc[D / 16];
+    load_rows<E, D>(qf, row_of<E, D>(a.Q, q, T, Hq, h), g);
 #pragma unroll
-        for (int x = 0; x < D; ++x) { q[x] = ld(Q + (static_cast<size_t>(i) * Hq + h) * D + x); acc[x] = 0.f; }
-        float m = -INFINITY, l = 0.f;
-        for (int e = g.row_ptr[tile]; e < g.row_ptr[tile + 1]; ++e) {
-            const int ent = g.entry[e];
-            const int k0 = (ent >> 2) * g.tile_k, k1 = min(T, k0 + g.tile_k);
-            const bool full = (ent & 3) == PSATTN_TILE_FULL;
-            for (int j = k0; j < k1; ++j) {
-                if (!full && !allowed(t, i, j)) continue;
-                const E* kr = K + (static_cast<size_t>(j) * Hkv + kvh) * D;
-                const E* vr = V + (static_cast<size_t>(j) * Hkv + kvh) * D;
-                float s = 0.f;
+    for (int b = 0; b < D / 16; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const KeyRange kr = key_range(tk, q0, T);
+    float m = -INFINITY, l = 0.f;
+    for (int kb = kr.first + w; kb <= kr.last; kb += kWaves) {
+        if (kr.skip(kb)) continue;
+        const int k0 = kB * kb;
+        f32x4 kf[D / 16], vc[4][D / 64];
+        load_rows<E, D>(kf, row_of<E, D>(a.K, k0 + r, T, Hkv, kvh), g);
+        load_cols<E, D>(vc, a.V, k0, T, Hkv, kvh, r, g);
+        f32x4 s = dot_rows<D>(kf, qf);
+        float mx = -INFINITY;
 #pragma unroll
-                for (int x = 0; x < D; ++x) s = fmaf(q[x], ld(kr + x), s);
-                s *= a.scale;
-                const float mn = fmaxf(m, s);
-                const float alpha = expf(m - mn);  // m = -inf the first time: 0
-                const float p = expf(s - mn);
-                l = l * alpha + p;
-#pragma unroll
-                for (int x = 0; x < D; ++x) acc[x] = fmaf(p, ld(vr + x), acc[x] * alpha);
-                m = mn;
-            }
+        for (int i = 0; i < 4; ++i) {
+            s[i] = allowed(tk, q, k0 + 4 * g + i) ? s[i] * a.scale : -INFINITY;
+            mx = fmaxf(mx, s[i]);
         }
-        const float inv = l > 0.f ? 1.f / l : 0.f;
+        mx = fmaxf(mx, __shfl_xor(mx, 16));
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        const float mn = fmaxf(m, mx), ref = mn == -INFINITY ? 0.f : mn;
+        const float alpha = expf(m - ref);  // m = -inf: 0
+        l *= alpha;
 #pragma unroll
-        for (int x = 0; x < D; ++x) st(O + (static_cast<size_t>(i) * Hq + h) * D + x, acc[x] * inv);
-        a.LSEout[static_cast<size_t>(h) * T + i] = l > 0.f ? m + logf(l) : -INFINITY;
+        for (int i = 0; i < 4; ++i) { s[i] = expf(s[i] - ref); l += s[i]; }
+#pragma unroll
+        for (int b = 0; b < D / 16; ++b) acc[b] *= alpha;
+        add_outer<D>(acc, vc, s);
+        m = mn;
     }
+    l = sum_groups(l);
+    put_partial<D>(sm, acc, w, r, g);
+    if (g == 0) { s_m[w][r] = m; s_l[w][r] = l; }
+    __syncthreads();
+    int row, d;
+    if (!my_quad<D>(tid, row, d) || q0 + row >= T) return;
+    float mt = s_m[0][row];
+#pragma unroll
+    for (int i = 1; i < kWaves; ++i) mt = fmaxf(mt, s_m[i][row]);
+    const float ref = mt == -INFINITY ? 0.f : mt;
+    float lt = 0.f;
+    f32x4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < kWaves; ++i) {
+        const float f = expf(s_m[i][row] - ref);
+        lt = fmaf(s_l[i][row], f, lt);
+        o += *reinterpret_cast<const f32x4*>(&sm.v[i][row][d]) * f;
+    }
+    const float inv = lt > 0.f ? 1.f / lt : 0.f;
+    st4(static_cast<E*>(a.Oout) + (static_cast<size_t>(q0 + row) * Hq + h) * D + d, o * inv);
+    if (d == 0) a.LSEout[static_cast<size_t>(h) * T + q0 + row] = lt > 0.f ? mt + logf(lt) : -INFINITY;
 }
 
-// ---------------------------------------------------------------- delta = rowsum(dO o O)
-template <typename E>
-__global__ __launch_bounds__(256) void delta_kernel(AttnArgs a) {
-    const int T = a.meta.T, Hq = a.Hq, D = a.d;
-    const int lanes = 16;  // threads per (token, head) row
-    const size_t row = (static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x) / lanes;
-    const int sub = threadIdx.x % lanes;
-    const size_t n_rows = static_cast<size_t>(T) * Hq;
-    float s = 0.f;
-    if (row < n_rows) {
-        const E* o = static_cast<const E*>(a.O) + row * D;
-        const E* g = static_cast<const E*>(a.dO) + row * D;
-        for (int x = sub; x < D; x += lanes) s = fmaf(ld(o + x), ld(g + x), s);
-    }
-#pragma unroll
-    for (int off = lanes / 2; off > 0; off >>= 1) s += __shfl_xor(s, off);
-    if (row < n_rows && sub == 0) {
-        const size_t t = row / Hq, h = row % Hq;
-        a.delta[h * T + t] = s;
-    }
-}
-
-// ---------------------------------------------------------------- dQ (q-major)
+// ---------------------------------------------------------------- delta = rowsum(dO o O), dQ
 template <typename E, int D>
 __global__ __launch_bounds__(kThreads) void generic_dq(AttnArgs a) {
-    const DeviceCsr& g = a.meta.fwd;
-    const int T = a.meta.T, Hq = a.Hq, Hkv = a.Hkv;
-    const int tile = g.order[blockIdx.x / Hq];
-    const int h = blockIdx.x % Hq, kvh = h / (Hq / Hkv);
-    const E* Q = static_cast<const E*>(a.Q);
-    const E* K = static_cast<const E*>(a.K);
-    const E* V = static_cast<const E*>(a.V);
-    const E* dO = static_cast<const E*>(a.dO);
-    E* dQ = static_cast<E*>(a.dQ);
-    const int q_end = min(T, (tile + 1) * g.tile_q);
-    for (int i = tile * g.tile_q + threadIdx.x; i < q_end; i += kThreads) {
-        const Tok4 t = a.meta.tok[i];
-        float q[D], go[D], acc[D];
+    __shared__ Partials<D> sm;
+    const int T = a.meta.T, Hq = a.Hq, Hkv = a.Hkv, n_blocks = (T + kB - 1) / kB;
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), r = tid & 15, g = (tid >> 4) & 3;
+    const int h = blockIdx.x % Hq, kvh = h / (Hq / Hkv), q0 = kB * (n_blocks - 1 - static_cast<int>(blockIdx.x) / Hq);
+    const int q = q0 + r;
+    Tok4 tk = {kPadStart, 0, 0, 0};
+    if (q < T) tk = a.meta.tok[q];
+    f32x4 qf[D / 16], gf[D / 16], acc[D / 16];
+    load_rows<E, D>(qf, row_of<E, D>(a.Q, q, T, Hq, h), g);
+    load_rows<E, D>(gf, row_of<E, D>(a.dO, q, T, Hq, h), g);
+    const float lse = a.LSE[static_cast<size_t>(h) * T + min(q, T - 1)];
+    float delta = 0.f;
+    {
+        const E* orow = row_of<E, D>(a.O, q, T, Hq, h);
 #pragma unroll
-        for (int x = 0; x < D; ++x) {
-            q[x] = ld(Q + (static_cast<size_t>(i) * Hq + h) * D + x);
-            go[x] = ld(dO + (static_cast<size_t>(i) * Hq + h) * D + x);
-            acc[x] = 0.f;
+        for (int t = 0; t < D / 16; ++t) {
+            const f32x4 o = ld4(orow + 16 * t + 4 * g);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) delta = fmaf(o[c], gf[t][c], delta);
+            acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
-        const float lse = a.LSE[static_cast<size_t>(h) * T + i];
-        const float dl = a.delta[static_cast<size_t>(h) * T + i];
-        for (int e = g.row_ptr[tile]; e < g.row_ptr[tile + 1]; ++e) {
-            const int ent = g.entry[e];
-            const int k0 = (ent >> 2) * g.tile_k, k1 = min(T, k0 + g.tile_k);
-            const bool full = (ent & 3) == PSATTN_TILE_FULL;
-            for (int j = k0; j < k1; ++j) {
-                if (!full && !allowed(t, i, j)) continue;
-                const E* kr = K + (static_cast<size_t>(j) * Hkv + kvh) * D;
-                const E* vr = V + (static_cast<size_t>(j) * Hkv + kvh) * D;
-                float s = 0.f, dp = 0.f;
-#pragma unroll
-                for (int x = 0; x < D; ++x) { s = fmaf(q[x], ld(kr + x), s); dp = fmaf(go[x], ld(vr + x), dp); }
-                const float p = expf(s * a.scale - lse);
-                const float ds = p * (dp - dl);
-#pragma unroll
-                for (int x = 0; x < D; ++x) acc[x] = fmaf(ds, ld(kr + x), acc[x]);
-            }
-        }
-#pragma unroll
-        for (int x = 0; x < D; ++x) st(dQ + (static_cast<size_t>(i) * Hq + h) * D + x, acc[x] * a.scale);
     }
+    delta = sum_groups(delta);
+    if (w == 0 && g == 0 && q < T) a.delta[static_cast<size_t>(h) * T + q] = delta;
+    const KeyRange kr = key_range(tk, q0, T);
+    for (int kb = kr.first + w; kb <= kr.last; kb += kWaves) {
+        if (kr.skip(kb)) continue;
+        const int k0 = kB * kb;
+        f32x4 kf[D / 16], vf[D / 16], kc[4][D / 64];
+        load_rows<E, D>(kf, row_of<E, D>(a.K, k0 + r, T, Hkv, kvh), g);
+        load_rows<E, D>(vf, row_of<E, D>(a.V, k0 + r, T, Hkv, kvh), g);
+        load_cols<E, D>(kc, a.K, k0, T, Hkv, kvh, r, g);
+        const f32x4 s = dot_rows<D>(kf, qf), dp = dot_rows<D>(vf, gf);
+        f32x4 ds;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            ds[i] = allowed(tk, q, k0 + 4 * g + i) ? expf(s[i] * a.scale - lse) * (dp[i] - delta) : 0.f;
+        add_outer<D>(acc, kc, ds);
+    }
+    put_partial<D>(sm, acc, w, r, g);
+    __syncthreads();
+    int row, d;
+    if (!my_quad<D>(tid, row, d) || q0 + row >= T) return;
+    st4(static_cast<E*>(a.dQ) + (static_cast<size_t>(q0 + row) * Hq + h) * D + d, sum_partials<D>(sm, row, d) * a.scale);
 }
 
-// ---------------------------------------------------------------- dK, dV (k-major)
+// ---------------------------------------------------------------- dK, dV
+// the waves share the (query block, head of the group) pairs, heads innermost
 template <typename E, int D>
 __global__ __launch_bounds__(kThreads) void generic_dkdv(AttnArgs a) {
-    const DeviceCsr& g = a.meta.bwd;
+    __shared__ Partials<D> sm;
     const int T = a.meta.T, Hq = a.Hq, Hkv = a.Hkv, G = Hq / Hkv;
-    const int tile = g.order[blockIdx.x / Hkv];
-    const int kvh = blockIdx.x % Hkv;
-    const E* Q = static_cast<const E*>(a.Q);
-    const E* K = static_cast<const E*>(a.K);
-    const E* V = static_cast<const E*>(a.V);
-    const E* dO = static_cast<const E*>(a.dO);
-    E* dK = static_cast<E*>(a.dK);
-    E* dV = static_cast<E*>(a.dV);
-    const int k_end = min(T, (tile + 1) * g.tile_k);
-    for (int j = tile * g.tile_k + threadIdx.x; j < k_end; j += kThreads) {
-        const int q_hi = a.meta.tok[j].key_hi;  // queries [j, q_hi) may read key j
-        float dk[D], dv[D];
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), r = tid & 15, g = (tid >> 4) & 3;
+    const int kvh = blockIdx.x % Hkv, k0 = kB * (static_cast<int>(blockIdx.x) / Hkv), key = k0 + r;
+    const int key_hi = key < T ? a.meta.tok[key].key_hi : 0;  // queries [key, key_hi) read this key
+    f32x4 kf[D / 16], vf[D / 16], dk[D / 16], dv[D / 16];
+    load_rows<E, D>(kf, row_of<E, D>(a.K, key, T, Hkv, kvh), g);
+    load_rows<E, D>(vf, row_of<E, D>(a.V, key, T, Hkv, kvh), g);
 #pragma unroll
-        for (int x = 0; x < D; ++x) { dk[x] = 0.f; dv[x] = 0.f; }
-        const E* kr = K + (static_cast<size_t>(j) * Hkv + kvh) * D;
-        const E* vr = V + (static_cast<size_t>(j) * Hkv + kvh) * D;
-        for (int gi = 0; gi < G; ++gi) {
-            const int h = kvh * G + gi;
-            for (int e = g.row_ptr[tile]; e < g.row_ptr[tile + 1]; ++e) {
-                const int ent = g.entry[e];
-                const int q0 = (ent >> 2) * g.tile_q, q1 = min(T, q0 + g.tile_q);
-                for (int i = max(q0, j); i < min(q1, q_hi); ++i) {
-                    const E* qr = Q + (static_cast<size_t>(i) * Hq + h) * D;
-                    const E* gr = dO + (static_cast<size_t>(i) * Hq + h) * D;
-                    float s = 0.f, dp = 0.f;
+    for (int b = 0; b < D / 16; ++b) dk[b] = dv[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int q_end = over_rows(key_hi, [](int x, int y) { return max(x, y); });
+    const int n_it = q_end > k0 ? ((q_end - k0 + kB - 1) / kB) * G : 0;
+    for (int it = w; it < n_it; it += kWaves) {
+        const int q0 = k0 + kB * (it / G), h = kvh * G + it % G;
+        f32x4 qf[D / 16], gf[D / 16], qc[4][D / 64], gc[4][D / 64];
+        load_rows<E, D>(qf, row_of<E, D>(a.Q, q0 + r, T, Hq, h), g);
+        load_rows<E, D>(gf, row_of<E, D>(a.dO, q0 + r, T, Hq, h), g);
+        load_cols<E, D>(qc, a.Q, q0, T, Hq, h, r, g);
+        load_cols<E, D>(gc, a.dO, q0, T, Hq, h, r, g);
+        float lse[4], delta[4];
 #pragma unroll
-                    for (int x = 0; x < D; ++x) { s = fmaf(ld(qr + x), ld(kr + x), s); dp = fmaf(ld(gr + x), ld(vr + x), dp); }
-                    const float p = expf(s * a.scale - a.LSE[static_cast<size_t>(h) * T + i]);
-                    const float ds = p * (dp - a.delta[static_cast<size_t>(h) * T + i]);
-#pragma unroll
-                    for (int x = 0; x < D; ++x) { dv[x] = fmaf(p, ld(gr + x), dv[x]); dk[x] = fmaf(ds, ld(qr + x), dk[x]); }
-                }
-            }
+        for (int i = 0; i < 4; ++i) {
+            const size_t at = static_cast<size_t>(h) * T + min(q0 + 4 * g + i, T - 1);
+            lse[i] = a.LSE[at];
+            delta[i] = a.delta[at];
         }
+        const f32x4 s = dot_rows<D>(qf, kf), dp = dot_rows<D>(gf, vf);
+        f32x4 p, ds;
 #pragma unroll
-        for (int x = 0; x < D; ++x) {
-            st(dK + (static_cast<size_t>(j) * Hkv + kvh) * D + x, dk[x] * a.scale);
-            st(dV + (static_cast<size_t>(j) * Hkv + kvh) * D + x, dv[x]);
+        for (int i = 0; i < 4; ++i) {
+            const int q = q0 + 4 * g + i;
+            const bool ok = key <= q && q < key_hi;
+            p[i] = ok ? expf(s[i] * a.scale - lse[i]) : 0.f;
+            ds[i] = ok ? p[i] * (dp[i] - delta[i]) : 0.f;
         }
+        add_outer<D>(dv, gc, p);
+        add_outer<D>(dk, qc, ds);
     }
+    int row, d;
+    const bool mine = my_quad<D>(tid, row, d) && k0 + row < T;
+    const size_t at = (static_cast<size_t>(k0 + row) * Hkv + kvh) * D + d;
+    put_partial<D>(sm, dk, w, r, g);
+    __syncthreads();
+    if (mine) st4(static_cast<E*>(a.dK) + at, sum_partials<D>(sm, row, d) * a.scale);
+    __syncthreads();
+    put_partial<D>(sm, dv, w, r, g);
+    __syncthreads();
+    if (mine) st4(static_cast<E*>(a.dV) + at, sum_partials<D>(sm, row, d));
 }
-
-hipError_t last_error() { return hipGetLastError(); }
 
 }  // namespace
 
-#define PSATTN_DISPATCH(KERNEL, GRID)                                                              \
-    do {                                                                                           \
-        hipStream_t s = static_cast<hipStream_t>(stream);                                          \
-        if (GRID == 0) return 0;                                                                   \
-        if (dt == PSATTN_F32 && a.d == 64) KERNEL<float, 64><<<GRID, kThreads, 0, s>>>(a);         \
-        else if (dt == PSATTN_F32 && a.d == 128) KERNEL<float, 128><<<GRID, kThreads, 0, s>>>(a);  \
-        else if (dt == PSATTN_BF16 && a.d == 64) KERNEL<uint16_t, 64><<<GRID, kThreads, 0, s>>>(a);\
-        else KERNEL<uint16_t, 128><<<GRID, kThreads, 0, s>>>(a);                                   \
-        return static_cast<int>(last_error());                                                     \
+#define PSATTN_DISPATCH(KERNEL, HEADS)                                                               \
+    do {                                                                                             \
+        hipStream_t s = static_cast<hipStream_t>(stream);                                            \
+        const unsigned grid = static_cast<unsigned>((a.meta.T + kB - 1) / kB) * (HEADS);             \
+        if (grid == 0) return 0;                                                                     \
+        if (dt == PSATTN_F32 && a.d == 64) KERNEL<float, 64><<<grid, kThreads, 0, s>>>(a);           \
+        else if (dt == PSATTN_F32 && a.d == 128) KERNEL<float, 128><<<grid, kThreads, 0, s>>>(a);    \
+        else if (dt == PSATTN_BF16 && a.d == 64) KERNEL<uint16_t, 64><<<grid, kThreads, 0, s>>>(a);  \
+        else KERNEL<uint16_t, 128><<<grid, kThreads, 0, s>>>(a);                                     \
+        return static_cast<int>(hipGetLastError());                                                  \
     } while (0)
 
-int launch_generic_fwd(int dt, const AttnArgs& a, void* stream) {
-    const unsigned grid = static_cast<unsigned>(a.meta.fwd.n_rows) * a.Hq;
-    PSATTN_DISPATCH(generic_fwd, grid);
-}
-int launch_generic_dq(int dt, const AttnArgs& a, void* stream) {
-    const unsigned grid = static_cast<unsigned>(a.meta.fwd.n_rows) * a.Hq;
-    PSATTN_DISPATCH(generic_dq, grid);
-}
-int launch_generic_dkdv(int dt, const AttnArgs& a, void* stream) {
-    const unsigned grid = static_cast<unsigned>(a.meta.bwd.n_rows) * a.Hkv;
-    PSATTN_DISPATCH(generic_dkdv, grid);
-}
-int launch_delta(int dt, const AttnArgs& a, void* stream) {
-    const size_t rows = static_cast<size_t>(a.meta.T) * a.Hq;
-    const unsigned grid = static_cast<unsigned>((rows * 16 + 255) / 256);
-    if (grid == 0) return 0;
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    if (dt == PSATTN_F32) delta_kernel<float><<<grid, 256, 0, s>>>(a);
-    else delta_kernel<uint16_t><<<grid, 256, 0, s>>>(a);
-    return static_cast<int>(last_error());
-}
+int launch_generic_fwd(int dt, const AttnArgs& a, void* stream) { PSATTN_DISPATCH(generic_fwd, a.Hq); }
+int launch_generic_dq(int dt, const AttnArgs& a, void* stream) { PSATTN_DISPATCH(generic_dq, a.Hq); }
+int launch_generic_dkdv(int dt, const AttnArgs& a, void* stream) { PSATTN_DISPATCH(generic_dkdv, a.Hkv); }
 
 }  // namespace psattn

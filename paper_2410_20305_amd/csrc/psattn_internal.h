@@ -127,7 +127,6 @@ int bwd_checked(const psattn_meta* meta, int32_t dt, int32_t n_q_heads, int32_t 
 int launch_generic_fwd(int dt, const AttnArgs& a, void* stream);
 int launch_generic_dq(int dt, const AttnArgs& a, void* stream);
 int launch_generic_dkdv(int dt, const AttnArgs& a, void* stream);
-int launch_delta(int dt, const AttnArgs& a, void* stream);
 int launch_mfma_fwd(const AttnArgs& a, void* stream);
 int launch_mfma_dq(const AttnArgs& a, void* stream);
 int launch_mfma_dkdv(const AttnArgs& a, void* stream);

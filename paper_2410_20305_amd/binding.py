@@ -114,17 +114,42 @@ def _check(status, what):
         raise PsattnError(status, what)
 
 
+# The calls below are a few microseconds each, and so are the smallest kernels: the marshalling keeps to what it needs
+# (no stream objects, no ctypes wrappers of arrays, no modules looked up again).
+_INT32 = np.dtype(np.int32)
+_TORCH = None
+
+
+def _torch():
+    """torch, imported on first use: the host-only functions work without it."""
+    global _TORCH
+    if _TORCH is None:
+        import torch
+        _TORCH = torch
+    return _TORCH
+
+
 def _i32(x):
+    if type(x) is np.ndarray and x.dtype == _INT32 and x.flags.c_contiguous:
+        return x
     return np.ascontiguousarray(np.asarray(x, dtype=np.int32))
+
+
+def _addr(x):
+    """Address of a NumPy array (x.ctypes.data builds a ctypes view first)."""
+    return x.__array_interface__["data"][0]
 
 
 def _stream_ptr(stream):
     if stream is None:
-        import torch
-        return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+        torch = _TORCH or _torch()
+        try:  # the current stream's handle without a Stream object around it (0.2 us instead of 2.9)
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except (AttributeError, RuntimeError):  # not initialised yet, or a torch without these
+            return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
-        return C.c_void_p(stream)
-    return C.c_void_p(stream.cuda_stream)
+        return stream
+    return stream.cuda_stream
 
 
 class Meta:
@@ -223,11 +248,11 @@ def psattn_build_meta(offset, prefix_len, chosen_len, rejected_len, total_tokens
         raise ValueError("sample arrays differ in length")
     h = C.c_void_p()
     if host_only:
-        st = lib.psattn_build_meta_host(n, off.ctypes.data, p.ctypes.data, c.ctypes.data, r.ctypes.data,
+        st = lib.psattn_build_meta_host(n, _addr(off), _addr(p), _addr(c), _addr(r),
                                         int(total_tokens), tile_q, tile_k, bwd_tile_q, bwd_tile_k, C.byref(h))
         _check(st, "psattn_build_meta_host")
     else:
-        st = lib.psattn_build_meta(n, off.ctypes.data, p.ctypes.data, c.ctypes.data, r.ctypes.data,
+        st = lib.psattn_build_meta(n, _addr(off), _addr(p), _addr(c), _addr(r),
                                    int(total_tokens), tile_q, tile_k, bwd_tile_q, bwd_tile_k,
                                    _stream_ptr(stream), C.byref(h))
         _check(st, "psattn_build_meta")
@@ -242,14 +267,14 @@ def psattn_build_meta_multi(offset, prefix_len, resp_ptr, resp_len, total_tokens
     n = off.shape[0]
     if p.shape[0] != n or ptr.shape[0] != n + 1 or (n and rl.shape[0] != int(ptr[-1])):
         raise ValueError("sample arrays differ in length")
-    rl_ptr = rl.ctypes.data if rl.shape[0] else None
+    rl_ptr = _addr(rl) if rl.shape[0] else None
     h = C.c_void_p()
     if host_only:
-        st = lib.psattn_build_meta_multi_host(n, off.ctypes.data, p.ctypes.data, ptr.ctypes.data, rl_ptr,
+        st = lib.psattn_build_meta_multi_host(n, _addr(off), _addr(p), _addr(ptr), rl_ptr,
                                               int(total_tokens), tile_q, tile_k, bwd_tile_q, bwd_tile_k, C.byref(h))
         _check(st, "psattn_build_meta_multi_host")
     else:
-        st = lib.psattn_build_meta_multi(n, off.ctypes.data, p.ctypes.data, ptr.ctypes.data, rl_ptr,
+        st = lib.psattn_build_meta_multi(n, _addr(off), _addr(p), _addr(ptr), rl_ptr,
                                          int(total_tokens), tile_q, tile_k, bwd_tile_q, bwd_tile_k,
                                          _stream_ptr(stream), C.byref(h))
         _check(st, "psattn_build_meta_multi")
@@ -267,22 +292,25 @@ def psattn_pack_ffd(prefix_len, chosen_len, rejected_len, row_len, max_rows=0):
     offset = np.zeros(max(1, n), dtype=np.int32)
     order = np.zeros(max(1, n), dtype=np.int32)
     n_rows, pad = C.c_int32(), C.c_int64()
-    st = lib.psattn_pack_ffd(n, p.ctypes.data, c.ctypes.data, r.ctypes.data, int(row_len), int(max_rows),
+    st = lib.psattn_pack_ffd(n, _addr(p), _addr(c), _addr(r), int(row_len), int(max_rows),
                              offset.ctypes.data, order.ctypes.data, C.byref(n_rows), C.byref(pad))
     _check(st, "psattn_pack_ffd")
     return dict(offset=offset[:n], order=order[:n], n_rows=n_rows.value, padding_tokens=pad.value)
 
 
 def _dtype_code(t):
-    import torch
-    if t.dtype == torch.float32:
-        return F32
-    if t.dtype == torch.bfloat16:
+    torch = _TORCH or _torch()
+    dtype = t.dtype
+    if dtype == torch.bfloat16:
         return BF16
+    if dtype == torch.float32:
+        return F32
     raise TypeError("psattn supports float32 and bfloat16 tensors, got %s" % t.dtype)
 
 
 def _check_tensor(t, name, shape, dtype):
+    if t.is_cuda and t.is_contiguous() and t.shape == shape and (dtype is None or t.dtype == dtype):
+        return
     if not t.is_cuda:
         raise ValueError("%s must be a device tensor" % name)
     if not t.is_contiguous():
@@ -295,8 +323,7 @@ def _check_tensor(t, name, shape, dtype):
 
 def psattn_fwd(meta: Meta, Q, K, V, scale, O=None, LSE=None, stream=None):
     """O, LSE = attention forward.  Q [T, Hq, d]; K, V [T, Hkv, d]; LSE [Hq, T] float32."""
-    import torch
-    lib = load_library()
+    torch, lib = _TORCH or _torch(), _LIB or load_library()
     T, Hq, d = Q.shape
     Hkv = K.shape[1]
     _check_tensor(Q, "Q", (meta.total_tokens, Hq, d), None)
@@ -321,8 +348,7 @@ def psattn_bwd_workspace_bytes(meta: Meta, n_q_heads, n_kv_heads, head_dim) -> i
 def psattn_bwd(meta: Meta, Q, K, V, O, dO, LSE, scale, dQ=None, dK=None, dV=None, workspace=None,
                stream=None):
     """dQ, dK, dV = attention backward from the forward's O and LSE."""
-    import torch
-    lib = load_library()
+    torch, lib = _TORCH or _torch(), _LIB or load_library()
     T, Hq, d = Q.shape
     Hkv = K.shape[1]
     _check_tensor(Q, "Q", (meta.total_tokens, Hq, d), None)
@@ -337,9 +363,8 @@ def psattn_bwd(meta: Meta, Q, K, V, O, dO, LSE, scale, dQ=None, dK=None, dV=None
     _check_tensor(dQ, "dQ", Q.shape, Q.dtype)
     _check_tensor(dK, "dK", K.shape, Q.dtype)
     _check_tensor(dV, "dV", V.shape, Q.dtype)
-    need = psattn_bwd_workspace_bytes(meta, Hq, Hkv, d)
     if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=Q.device)
+        workspace = torch.empty(psattn_bwd_workspace_bytes(meta, Hq, Hkv, d), dtype=torch.uint8, device=Q.device)
     if not workspace.is_cuda or not workspace.is_contiguous():
         raise ValueError("workspace must be a contiguous device tensor")
     ws_bytes = workspace.numel() * workspace.element_size()
@@ -352,8 +377,7 @@ def psattn_bwd(meta: Meta, Q, K, V, O, dO, LSE, scale, dQ=None, dK=None, dV=None
 
 def psattn_bwd_static(meta: Meta, Q, K, V, O, dO, LSE, scale, dQ, dK, dV, stream=None):
     """psattn_bwd on the library's static scratch: allocates nothing, so the outputs must be given."""
-    import torch
-    lib = load_library()
+    torch, lib = _TORCH or _torch(), _LIB or load_library()
     T, Hq, d = Q.shape
     Hkv = K.shape[1]
     _check_tensor(Q, "Q", (meta.total_tokens, Hq, d), None)
@@ -402,8 +426,7 @@ class Rope:
 
 def psattn_fwd_rope(meta: Meta, rope: Rope, Q, K, V, scale, O=None, LSE=None, Qr=None, Kr=None, stream=None):
     """O, LSE, Qr, Kr = forward with rotary embedding applied to the unrotated Q, K inside the op."""
-    import torch
-    lib = load_library()
+    torch, lib = _TORCH or _torch(), _LIB or load_library()
     T, Hq, d = Q.shape
     Hkv = K.shape[1]
     _check_tensor(Q, "Q", (meta.total_tokens, Hq, d), None)
@@ -427,8 +450,7 @@ def psattn_fwd_rope(meta: Meta, rope: Rope, Q, K, V, scale, O=None, LSE=None, Qr
 def psattn_bwd_rope(meta: Meta, rope: Rope, Qr, Kr, V, O, dO, LSE, scale, dQ=None, dK=None, dV=None, workspace=None,
                     stream=None):
     """dQ, dK, dV (w.r.t. the unrotated Q, K) from the forward's rotated Qr, Kr."""
-    import torch
-    lib = load_library()
+    torch, lib = _TORCH or _torch(), _LIB or load_library()
     T, Hq, d = Qr.shape
     Hkv = Kr.shape[1]
     _check_tensor(Qr, "Qr", (meta.total_tokens, Hq, d), None)
@@ -440,9 +462,8 @@ def psattn_bwd_rope(meta: Meta, rope: Rope, Qr, Kr, V, O, dO, LSE, scale, dQ=Non
     dV = torch.empty_like(V) if dV is None else dV
     for t, name, shape in ((dQ, "dQ", Qr.shape), (dK, "dK", Kr.shape), (dV, "dV", Kr.shape)):
         _check_tensor(t, name, shape, Qr.dtype)
-    need = psattn_bwd_workspace_bytes(meta, Hq, Hkv, d)
     if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=Qr.device)
+        workspace = torch.empty(psattn_bwd_workspace_bytes(meta, Hq, Hkv, d), dtype=torch.uint8, device=Qr.device)
     st = lib.psattn_bwd_rope(meta.handle, rope.handle, _dtype_code(Qr), Hq, Hkv, d, float(scale), Qr.data_ptr(),
                              Kr.data_ptr(), V.data_ptr(), O.data_ptr(), dO.data_ptr(), LSE.data_ptr(), dQ.data_ptr(),
                              dK.data_ptr(), dV.data_ptr(), workspace.data_ptr(),
@@ -458,8 +479,8 @@ class LogprobPlan:
         lib = load_library()
         off, p, ptr, rl = _i32(offset), _i32(prefix_len), _i32(resp_ptr), _i32(resp_len)
         h = C.c_void_p()
-        _check(lib.psattn_logprob_plan(off.shape[0], off.ctypes.data, p.ctypes.data, ptr.ctypes.data,
-                                       rl.ctypes.data if rl.shape[0] else None, int(total_tokens), _stream_ptr(stream),
+        _check(lib.psattn_logprob_plan(off.shape[0], _addr(off), _addr(p), _addr(ptr),
+                                       _addr(rl) if rl.shape[0] else None, int(total_tokens), _stream_ptr(stream),
                                        C.byref(h)), "psattn_logprob_plan")
         self._h = h
         self.total_tokens = int(total_tokens)
@@ -487,7 +508,7 @@ class LogprobPlan:
 
 def psattn_logprob_fwd(plan: LogprobPlan, logits, token_ids, row_lse=None, resp_logp=None, stream=None):
     """row_lse [T], resp_logp [n_responses] from logits [T, vocab] and token_ids int32 [T]."""
-    import torch
+    torch = _TORCH or _torch()
     T, V = logits.shape
     _check_tensor(logits, "logits", (plan.total_tokens, V), None)
     _check_tensor(token_ids, "token_ids", (T,), torch.int32)
@@ -502,7 +523,7 @@ def psattn_logprob_fwd(plan: LogprobPlan, logits, token_ids, row_lse=None, resp_
 
 
 def psattn_logprob_bwd(plan: LogprobPlan, logits, token_ids, row_lse, d_resp_logp, dlogits=None, stream=None):
-    import torch
+    torch = _TORCH or _torch()
     T, V = logits.shape
     _check_tensor(logits, "logits", (plan.total_tokens, V), None)
     _check_tensor(token_ids, "token_ids", (T,), torch.int32)
@@ -519,7 +540,7 @@ def psattn_logprob_bwd(plan: LogprobPlan, logits, token_ids, row_lse, d_resp_log
 
 def psattn_dpo_loss(logp_policy, logp_ref, beta, stream=None):
     """loss [n_pairs], d_logp [2 n_pairs] for responses stored as (chosen, rejected) pairs."""
-    import torch
+    torch = _TORCH or _torch()
     n = logp_policy.shape[0]
     if n % 2 or tuple(logp_ref.shape) != (n,):
         raise ValueError("log-probabilities must come in (chosen, rejected) pairs")

@@ -2,6 +2,7 @@
 // kernel dispatch for psattn_fwd / psattn_bwd.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstring>
 #include <mutex>
 #include <new>
@@ -15,46 +16,47 @@ namespace {
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
+// Device copy of a block mask: tok | lists.  Staged on the host: lists | seg_start | seg_tok | block_first; the
+// descriptors of the tokens are expanded on the device, so that what crosses PCIe does not grow with T.
 struct BlobLayout {
-    size_t tok, f_row, f_ent, f_ord, f_lch, b_row, b_ent, b_ord, b_lch, total;
+    size_t f_ent, f_lch, b_ent, b_lch, lists;         // inside the lists
+    size_t tok;                                       // device: bytes of the token descriptors, the lists follow
+    size_t seg_start, seg_tok, block_first, staged;   // host
 };
+
+int32_t upload_blocks(const psattn_meta& m) { return (m.T + kUploadTokens - 1) / kUploadTokens; }
 
 BlobLayout layout_of(const psattn_meta& m) {
     BlobLayout L{};
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
-    L.tok = take(sizeof(Tok4) * static_cast<size_t>(m.T));
-    L.f_row = take(sizeof(int32_t) * m.fwd.row_ptr.size());
-    L.f_ent = take(sizeof(int32_t) * m.fwd.idx.size());
-    L.f_ord = take(sizeof(int32_t) * m.fwd.order.size());
+    L.f_ent = take(sizeof(int32_t) * m.fwd.entry.size());
     L.f_lch = take(sizeof(RowLaunch) * m.fwd.order.size());
-    L.b_row = take(sizeof(int32_t) * m.bwd.row_ptr.size());
-    L.b_ent = take(sizeof(int32_t) * m.bwd.idx.size());
-    L.b_ord = take(sizeof(int32_t) * m.bwd.order.size());
+    L.b_ent = take(sizeof(int32_t) * m.bwd.entry.size());
     L.b_lch = take(sizeof(RowLaunch) * m.bwd.order.size());
-    L.total = off ? off : 256;
+    L.lists = off;
+    L.seg_start = take(sizeof(int32_t) * m.seg_start.size());
+    L.seg_tok = take(sizeof(Tok4) * m.seg_tok.size());
+    L.block_first = take(sizeof(int32_t) * (upload_blocks(m) + 1));
+    L.staged = off;
+    L.tok = align_up(sizeof(Tok4) * static_cast<size_t>(m.T), 256);
     return L;
 }
 
 // walk_backwards: the kernel of this grid starts with the last entry of a row
-void fill_csr(char* base, size_t row, size_t ent, size_t ord, size_t lch, const TileCsr& g, bool walk_backwards) {
-    std::memcpy(base + row, g.row_ptr.data(), g.row_ptr.size() * sizeof(int32_t));
-    int32_t* e = reinterpret_cast<int32_t*>(base + ent);
-    for (size_t i = 0; i < g.idx.size(); ++i) e[i] = (g.idx[i] << 2) | g.cls[i];
-    std::memcpy(base + ord, g.order.data(), g.order.size() * sizeof(int32_t));
+void fill_csr(char* base, size_t ent, size_t lch, const TileCsr& g, bool walk_backwards) {
+    if (!g.entry.empty()) std::memcpy(base + ent, g.entry.data(), g.entry.size() * sizeof(int32_t));
     RowLaunch* rl = reinterpret_cast<RowLaunch*>(base + lch);
     for (size_t i = 0; i < g.order.size(); ++i) {
         const int32_t r = g.order[i], b = g.row_ptr[r], n = g.row_ptr[r + 1] - b;
-        rl[i] = RowLaunch{r, b, n, n > 0 ? e[walk_backwards ? b + n - 1 : b] : 0};
+        rl[i] = RowLaunch{r, b, n, n > 0 ? g.entry[walk_backwards ? b + n - 1 : b] : 0};
     }
 }
 
-DeviceCsr view_csr(const char* base, size_t row, size_t ent, size_t ord, size_t lch, const TileCsr& g) {
+DeviceCsr view_csr(const char* lists, size_t ent, size_t lch, const TileCsr& g) {
     DeviceCsr v{};
-    v.row_ptr = reinterpret_cast<const int32_t*>(base + row);
-    v.entry = reinterpret_cast<const int32_t*>(base + ent);
-    v.order = reinterpret_cast<const int32_t*>(base + ord);
-    v.launch = reinterpret_cast<const RowLaunch*>(base + lch);
+    v.entry = reinterpret_cast<const int32_t*>(lists + ent);
+    v.launch = reinterpret_cast<const RowLaunch*>(lists + lch);
     v.n_rows = static_cast<int32_t>(g.row_ptr.size()) - 1;
     v.tile_q = g.tile_q;
     v.tile_k = g.tile_k;
@@ -62,7 +64,7 @@ DeviceCsr view_csr(const char* base, size_t row, size_t ent, size_t ord, size_t 
 }
 
 // ---- pooled metadata blobs
-// A mini-batch needs one pinned staging buffer and one device buffer of the same size.
+// A mini-batch needs one pinned staging buffer and one device buffer.
 // Allocating and freeing them every training step would synchronise the device each
 // time, so released pairs stay in a small per-process pool and are handed out again.
 // A pair carries an event that marks the point after which the device no longer needs
@@ -71,7 +73,8 @@ DeviceCsr view_csr(const char* base, size_t row, size_t ent, size_t ord, size_t 
 struct Blob {
     void* d = nullptr;
     void* h = nullptr;
-    size_t cap = 0;
+    void* hd = nullptr;   // h as the device addresses it
+    size_t cap = 0;       // bytes of each of the two
     int device = -1;
     hipEvent_t idle = nullptr;  // completes when the previous user is done with d and h
 };
@@ -89,9 +92,10 @@ void destroy_blob(Blob& b) {
 // Returns a pair of at least `bytes` on `device`; blocks only if every pooled candidate is
 // still in use by the device and the pool is full.
 int acquire_blob(size_t bytes, int device, Blob* out) {
+    bool wait = false;
     {
         std::lock_guard<std::mutex> lk(g_pool_mu);
-        int best = -1, busy = -1;
+        int best = -1, busy = -1;  // best: smallest idle pair that fits
         for (size_t i = 0; i < g_pool.size(); ++i) {
             const Blob& b = g_pool[i];
             if (b.device != device || b.cap < bytes) continue;
@@ -102,14 +106,17 @@ int acquire_blob(size_t bytes, int device, Blob* out) {
                 if (busy < 0) busy = static_cast<int>(i);
             }
         }
-        if (best < 0 && busy >= 0 && g_pool.size() >= kPoolMax) best = busy;
+        if (best < 0 && busy >= 0 && g_pool.size() >= kPoolMax) {
+            best = busy;
+            wait = true;
+        }
         if (best >= 0) {
             *out = g_pool[best];
             g_pool.erase(g_pool.begin() + best);
         }
     }
     if (out->d) {
-        if (hipEventSynchronize(out->idle) != hipSuccess) { destroy_blob(*out); return PSATTN_EHIP; }
+        if (wait && hipEventSynchronize(out->idle) != hipSuccess) { destroy_blob(*out); return PSATTN_EHIP; }
         return PSATTN_OK;
     }
     Blob b;
@@ -117,6 +124,7 @@ int acquire_blob(size_t bytes, int device, Blob* out) {
     b.cap = align_up(bytes + bytes / 4, 1 << 16);  // head-room: the next mini-batch differs a little
     if (hipEventCreateWithFlags(&b.idle, hipEventDisableTiming) != hipSuccess) { b.idle = nullptr; (void)hipGetLastError(); return PSATTN_EHIP; }
     if (hipHostMalloc(&b.h, b.cap, hipHostMallocDefault) != hipSuccess) { b.h = nullptr; (void)hipGetLastError(); destroy_blob(b); return PSATTN_ENOMEM; }
+    if (hipHostGetDevicePointer(&b.hd, b.h, 0) != hipSuccess) { (void)hipGetLastError(); destroy_blob(b); return PSATTN_EHIP; }
     if (hipMalloc(&b.d, b.cap) != hipSuccess) { b.d = nullptr; (void)hipGetLastError(); destroy_blob(b); return PSATTN_ENOMEM; }
     *out = b;
     return PSATTN_OK;
@@ -144,28 +152,45 @@ void release_blob(Blob b, hipStream_t stream) {
 int upload(psattn_meta* m, hipStream_t stream) {
     const BlobLayout L = layout_of(*m);
     if (hipGetDevice(&m->device) != hipSuccess) return PSATTN_EHIP;
+    const size_t on_device = L.tok + L.lists;
     Blob b;
-    const int rc = acquire_blob(L.total, m->device, &b);
+    const int rc = acquire_blob(std::max(L.staged, on_device), m->device, &b);
     if (rc != PSATTN_OK) return rc;
     m->h_stage = b.h;
+    m->h_stage_dev = b.hd;
     m->d_blob = b.d;
     m->blob_cap = b.cap;
     m->blob_idle = b.idle;
     char* h = static_cast<char*>(m->h_stage);
-    Tok4* tok = reinterpret_cast<Tok4*>(h + L.tok);
-    for (int32_t t = 0; t < m->T; ++t)
-        tok[t] = Tok4{m->tok_desc[3 * t], m->tok_desc[3 * t + 1], m->tok_desc[3 * t + 2], m->key_hi[t]};
-    fill_csr(h, L.f_row, L.f_ent, L.f_ord, L.f_lch, m->fwd, false);
-    fill_csr(h, L.b_row, L.b_ent, L.b_ord, L.b_lch, m->bwd, true);
-    if (hipMemcpyAsync(m->d_blob, h, L.total, hipMemcpyHostToDevice, stream) != hipSuccess) {
-        (void)hipGetLastError();
-        return PSATTN_EHIP;
+    fill_csr(h, L.f_ent, L.f_lch, m->fwd, false);
+    fill_csr(h, L.b_ent, L.b_lch, m->bwd, true);
+    const int32_t n_seg = static_cast<int32_t>(m->seg_tok.size()), n_blocks = upload_blocks(*m);
+    std::memcpy(h + L.seg_start, m->seg_start.data(), m->seg_start.size() * sizeof(int32_t));
+    if (n_seg > 0) std::memcpy(h + L.seg_tok, m->seg_tok.data(), m->seg_tok.size() * sizeof(Tok4));
+    int32_t* first = reinterpret_cast<int32_t*>(h + L.block_first);
+    for (int32_t k = 0, i = 0; k <= n_blocks; ++k) {
+        const int64_t t = std::min<int64_t>(static_cast<int64_t>(k) * kUploadTokens, m->T - 1);
+        while (i + 1 < n_seg && m->seg_start[i + 1] <= t) ++i;
+        first[k] = i;
     }
-    const char* d = static_cast<const char*>(m->d_blob);
-    m->blob_bytes = L.total;
-    m->dev.tok = reinterpret_cast<const Tok4*>(d + L.tok);
-    m->dev.fwd = view_csr(d, L.f_row, L.f_ent, L.f_ord, L.f_lch, m->fwd);
-    m->dev.bwd = view_csr(d, L.b_row, L.b_ent, L.b_ord, L.b_lch, m->bwd);
+    char* d = static_cast<char*>(m->d_blob);
+    const char* hd = static_cast<const char*>(m->h_stage_dev);
+    UploadArgs u{};
+    u.seg_start = reinterpret_cast<const int32_t*>(hd + L.seg_start);
+    u.seg_tok = reinterpret_cast<const Tok4*>(hd + L.seg_tok);
+    u.block_first = reinterpret_cast<const int32_t*>(hd + L.block_first);
+    u.n_seg = n_seg;
+    u.T = m->T;
+    u.tok = reinterpret_cast<Tok4*>(d);
+    u.src = reinterpret_cast<const uint4*>(hd);
+    u.dst = reinterpret_cast<uint4*>(d + L.tok);
+    if (L.lists / 16 > static_cast<size_t>(INT32_MAX)) return PSATTN_EUNSUPPORTED;
+    u.n_units = static_cast<int32_t>(L.lists / 16);
+    if (launch_upload(u, stream) != 0) return PSATTN_EHIP;
+    m->blob_bytes = on_device;
+    m->dev.tok = reinterpret_cast<const Tok4*>(d);
+    m->dev.fwd = view_csr(d + L.tok, L.f_ent, L.f_lch, m->fwd);
+    m->dev.bwd = view_csr(d + L.tok, L.b_ent, L.b_lch, m->bwd);
     m->dev.T = m->T;
     m->on_device = true;
     return PSATTN_OK;
@@ -175,7 +200,7 @@ int release_meta(psattn_meta* meta, hipStream_t stream) {
     if (!meta) return PSATTN_OK;
     if (meta->d_blob) {
         Blob b;
-        b.d = meta->d_blob; b.h = meta->h_stage; b.cap = meta->blob_cap; b.device = meta->device;
+        b.d = meta->d_blob; b.h = meta->h_stage; b.hd = meta->h_stage_dev; b.cap = meta->blob_cap; b.device = meta->device;
         b.idle = static_cast<hipEvent_t>(meta->blob_idle);
         // the event and the stream belong to the blob's device
         int cur = -1;

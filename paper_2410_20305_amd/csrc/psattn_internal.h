@@ -5,6 +5,8 @@
 #include <cstdint>
 #include <vector>
 
+#include <hip/hip_vector_types.h>
+
 #include "psattn.h"
 
 namespace psattn {
@@ -22,9 +24,8 @@ struct TileCsr {
     int32_t tile_q = 0, tile_k = 0;
     int32_t n_q_tiles = 0, n_k_tiles = 0;
     std::vector<int32_t> row_ptr;  // rows = q-tiles (FWD) or k-tiles (BWD)
-    std::vector<int32_t> idx;
-    std::vector<uint8_t> cls;
-    std::vector<int32_t> order;    // rows sorted by decreasing work (longest first)
+    std::vector<int32_t> entry;    // (column tile index << 2) | class, ascending in a row
+    std::vector<int32_t> order;    // rows in launch order
 };
 
 // What a workgroup of the MFMA kernels needs to start on its row, in launch order: one
@@ -40,9 +41,7 @@ struct alignas(16) RowLaunch {
 
 // Device-side view handed to kernels by value.
 struct DeviceCsr {
-    const int32_t* row_ptr;
     const int32_t* entry;  // (idx << 2) | cls
-    const int32_t* order;
     const RowLaunch* launch;  // [n_rows], in launch order
     int32_t n_rows;
     int32_t tile_q, tile_k;
@@ -66,14 +65,17 @@ struct psattn_meta {
     int32_t n_samples = 0;
     int64_t n_allowed = 0;
     int32_t n_positions = 0;        // 1 + the largest position id of any token (prompt length + longest response)
-    std::vector<int32_t> tok_desc;  // [3T]  (s, hole_lo, hole_hi)
-    std::vector<int32_t> key_hi;    // [T]   queries that may read key j are [j, key_hi[j])
+    // Runs of neighbouring tokens with the same descriptor (a prompt, a response, a stretch of padding), covering
+    // [0, T): run i is tokens [seg_start[i], seg_start[i + 1]), seg_start.back() == T.
+    std::vector<int32_t> seg_start;
+    std::vector<psattn::Tok4> seg_tok;
     psattn::TileCsr fwd, bwd;
     // device copy
     bool on_device = false;
     int device = -1;
     void* d_blob = nullptr;   // device copy of the metadata (from the library's blob pool)
-    void* h_stage = nullptr;  // pinned staging buffer of the same size, alive until release
+    void* h_stage = nullptr;  // pinned staging buffer, alive until release
+    void* h_stage_dev = nullptr;  // its address on the device
     size_t blob_bytes = 0;    // bytes in use
     size_t blob_cap = 0;      // bytes allocated
     void* blob_idle = nullptr;  // hipEvent_t of the pooled pair
@@ -122,6 +124,21 @@ int bwd_checked(const psattn_meta* meta, int32_t dt, int32_t n_q_heads, int32_t 
                 float scale, const void* Q, const void* K, const void* V, const void* O, const void* dO,
                 const float* LSE, void* dQ, void* dK, void* dV, void* scratch_base, size_t scratch_bytes,
                 void* hip_stream, const float* rope_table = nullptr);
+
+// Unpacks a staged block mask on the device (psattn_upload.hip): expands the runs of equal token descriptors into
+// tok[T] and copies the lists.  All source pointers are pinned host memory as the device addresses it.
+struct UploadArgs {
+    const int32_t* seg_start;   // [n_seg + 1]
+    const Tok4* seg_tok;        // [n_seg]
+    const int32_t* block_first; // [blocks + 1]  run that holds the first token of block b (kUploadTokens tokens each)
+    int32_t n_seg, T;
+    Tok4* tok;
+    const uint4* src;           // lists, 16-byte units
+    uint4* dst;
+    int32_t n_units;
+};
+constexpr int32_t kUploadTokens = 1024;
+int launch_upload(const UploadArgs& a, void* stream);
 
 // Launchers (each returns a hipError_t cast to int; 0 = success).
 int launch_generic_fwd(int dt, const AttnArgs& a, void* stream);

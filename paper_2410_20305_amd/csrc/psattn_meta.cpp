@@ -70,8 +70,7 @@ bool classify(const std::vector<Sample>& samples, int64_t T, int32_t tq, int32_t
     g.n_q_tiles = static_cast<int32_t>((T + tq - 1) / tq);
     g.n_k_tiles = static_cast<int32_t>((T + tk - 1) / tk);
     g.row_ptr.assign(g.n_q_tiles + 1, 0);
-    g.idx.clear();
-    g.cls.clear();
+    g.entry.clear();
     std::vector<int64_t> cnt;
     size_t first = 0;  // first sample that may still intersect the current q-tile
     for (int32_t a = 0; a < g.n_q_tiles; ++a) {
@@ -85,21 +84,24 @@ bool classify(const std::vector<Sample>& samples, int64_t T, int32_t tq, int32_t
             cnt.assign(kt_hi - kt_lo + 1, 0);
             for (size_t i = first; i < last; ++i) {
                 const Sample& s = samples[i];
-                const int64_t qb = std::min(q1, s.e);
+                const int64_t qa = std::max(q0, s.o), qb = std::min(q1, s.e);
+                // k-tiles inside the prompt and not behind the first query: every pair is allowed (most tiles of a
+                // long sample, so they are not worth a call each)
+                const int64_t b_lo = (s.o + tk - 1) / tk, b_hi = std::min(s.C, qa + 1) / tk;
                 for (int64_t b = s.o / tk; b <= (qb - 1) / tk; ++b)
-                    cnt[b - kt_lo] += sample_pairs(s, q0, q1, b * tk, std::min<int64_t>(T, (b + 1) * tk));
+                    cnt[b - kt_lo] += b >= b_lo && b < b_hi ? (qb - qa) * tk
+                                                            : sample_pairs(s, q0, q1, b * tk, std::min<int64_t>(T, (b + 1) * tk));
             }
             for (int64_t b = kt_lo; b <= kt_hi; ++b) {
                 const int64_t n = cnt[b - kt_lo];
                 if (n == 0) continue;
                 const bool unclipped = (q0 + tq <= T) && ((b + 1) * tk <= T);
                 const bool full = unclipped && n == static_cast<int64_t>(tq) * tk;
-                g.idx.push_back(static_cast<int32_t>(b));
-                g.cls.push_back(full ? PSATTN_TILE_FULL : PSATTN_TILE_PARTIAL);
+                g.entry.push_back(static_cast<int32_t>(b << 2) | (full ? PSATTN_TILE_FULL : PSATTN_TILE_PARTIAL));
             }
         }
-        if (g.idx.size() > static_cast<size_t>(INT32_MAX)) return false;
-        g.row_ptr[a + 1] = static_cast<int32_t>(g.idx.size());
+        if (g.entry.size() > static_cast<size_t>(INT32_MAX)) return false;
+        g.row_ptr[a + 1] = static_cast<int32_t>(g.entry.size());
     }
     return true;
 }
@@ -112,17 +114,13 @@ void transpose(const TileCsr& in, TileCsr& out) {
     out.n_k_tiles = in.n_k_tiles;
     const int32_t n_rows = in.n_k_tiles;
     out.row_ptr.assign(n_rows + 1, 0);
-    for (int32_t b : in.idx) out.row_ptr[b + 1]++;
+    for (int32_t e : in.entry) out.row_ptr[(e >> 2) + 1]++;
     for (int32_t b = 0; b < n_rows; ++b) out.row_ptr[b + 1] += out.row_ptr[b];
-    out.idx.resize(in.idx.size());
-    out.cls.resize(in.cls.size());
+    out.entry.resize(in.entry.size());
     std::vector<int32_t> fill(out.row_ptr.begin(), out.row_ptr.end() - 1);
     for (int32_t a = 0; a < in.n_q_tiles; ++a)
-        for (int32_t e = in.row_ptr[a]; e < in.row_ptr[a + 1]; ++e) {
-            const int32_t pos = fill[in.idx[e]]++;
-            out.idx[pos] = a;
-            out.cls[pos] = in.cls[e];
-        }
+        for (int32_t e = in.row_ptr[a]; e < in.row_ptr[a + 1]; ++e)
+            out.entry[fill[in.entry[e] >> 2]++] = (a << 2) | (in.entry[e] & 3);
 }
 
 // Launch order of the rows.
@@ -208,25 +206,30 @@ int build_host_multi(int32_t n_samples, const int32_t* offset, const int32_t* pr
         m->n_samples = n_samples;
         m->n_allowed = n_allowed;
         m->n_positions = static_cast<int32_t>(n_positions);
-        m->tok_desc.assign(static_cast<size_t>(3) * T, 0);
-        m->key_hi.assign(T, 0);
-        for (int64_t t = 0; t < T; ++t) m->tok_desc[3 * t] = kPadStart;
+        // runs of equal descriptors, in token order
+        m->seg_start.reserve(starts.size() + samples.size() + 2);
+        m->seg_tok.reserve(starts.size() + samples.size() + 1);
+        auto run = [&](int64_t from, int64_t to, const Tok4& t) {
+            if (from >= to) return;
+            m->seg_start.push_back(static_cast<int32_t>(from));
+            m->seg_tok.push_back(t);
+        };
+        const Tok4 pad = {kPadStart, 0, 0, 0};
+        int64_t at = 0;
         for (const Sample& s : samples) {
-            for (int64_t t = s.o; t < s.C; ++t) {
-                m->tok_desc[3 * t] = static_cast<int32_t>(s.o);
-                m->key_hi[t] = static_cast<int32_t>(s.e);  // a prompt key is visible to the whole sample
+            const int32_t o = static_cast<int32_t>(s.o), C = static_cast<int32_t>(s.C);
+            run(at, s.o, pad);
+            run(s.o, s.C, Tok4{o, 0, 0, static_cast<int32_t>(s.e)});  // a prompt key is visible to the whole sample
+            for (int32_t j = 0; j < s.k; ++j) {
+                // must not see the responses before its own (keys [C, start of response j)); a response key is
+                // visible up to the end of its own response only
+                const int32_t r0 = static_cast<int32_t>(s.resp[j]), r1 = static_cast<int32_t>(s.resp[j + 1]);
+                run(r0, r1, j >= 1 ? Tok4{o, C, r0, r1} : Tok4{o, 0, 0, r1});
             }
-            for (int32_t j = 0; j < s.k; ++j)
-                for (int64_t t = s.resp[j]; t < s.resp[j + 1]; ++t) {
-                    m->tok_desc[3 * t] = static_cast<int32_t>(s.o);
-                    if (j >= 1) {  // must not see the responses before its own: keys [C, start of response j)
-                        m->tok_desc[3 * t + 1] = static_cast<int32_t>(s.C);
-                        m->tok_desc[3 * t + 2] = static_cast<int32_t>(s.resp[j]);
-                    }
-                    // a response key is visible up to the end of its own response only
-                    m->key_hi[t] = static_cast<int32_t>(s.resp[j + 1]);
-                }
+            at = s.e;
         }
+        run(at, T, pad);
+        m->seg_start.push_back(static_cast<int32_t>(T));
         if (!classify(samples, T, tile_q, tile_k, m->fwd)) return PSATTN_EUNSUPPORTED;
         order_rows(m->fwd, true);
         TileCsr qmajor;
@@ -292,7 +295,7 @@ int psattn_meta_tiles(const psattn_meta* meta, int32_t grid, int32_t* tile_q, in
     if (tile_k) *tile_k = g.tile_k;
     if (n_q_tiles) *n_q_tiles = g.n_q_tiles;
     if (n_k_tiles) *n_k_tiles = g.n_k_tiles;
-    if (n_entries) *n_entries = static_cast<int64_t>(g.idx.size());
+    if (n_entries) *n_entries = static_cast<int64_t>(g.entry.size());
     return PSATTN_OK;
 }
 
@@ -300,34 +303,41 @@ int psattn_meta_copy_csr(const psattn_meta* meta, int32_t grid, int32_t* row_ptr
                          uint8_t* cls) {
     if (!meta || (grid != PSATTN_GRID_FWD && grid != PSATTN_GRID_BWD)) return PSATTN_EINVAL;
     const psattn::TileCsr& g = grid == PSATTN_GRID_FWD ? meta->fwd : meta->bwd;
-    if (!row_ptr || ((!idx || !cls) && !g.idx.empty())) return PSATTN_EINVAL;
+    if (!row_ptr || ((!idx || !cls) && !g.entry.empty())) return PSATTN_EINVAL;
     std::memcpy(row_ptr, g.row_ptr.data(), g.row_ptr.size() * sizeof(int32_t));
-    if (!g.idx.empty()) {
-        std::memcpy(idx, g.idx.data(), g.idx.size() * sizeof(int32_t));
-        std::memcpy(cls, g.cls.data(), g.cls.size());
+    for (size_t e = 0; e < g.entry.size(); ++e) {
+        idx[e] = g.entry[e] >> 2;
+        cls[e] = static_cast<uint8_t>(g.entry[e] & 3);
     }
     return PSATTN_OK;
 }
 
 int psattn_meta_copy_tok_desc(const psattn_meta* meta, int32_t* tok_desc) {
     if (!meta || (!tok_desc && meta->T > 0)) return PSATTN_EINVAL;
-    if (meta->T > 0) std::memcpy(tok_desc, meta->tok_desc.data(), meta->tok_desc.size() * sizeof(int32_t));
+    for (size_t i = 0; i < meta->seg_tok.size(); ++i)
+        for (int32_t t = meta->seg_start[i]; t < meta->seg_start[i + 1]; ++t) {
+            tok_desc[3 * static_cast<size_t>(t)] = meta->seg_tok[i].s;
+            tok_desc[3 * static_cast<size_t>(t) + 1] = meta->seg_tok[i].hole_lo;
+            tok_desc[3 * static_cast<size_t>(t) + 2] = meta->seg_tok[i].hole_hi;
+        }
     return PSATTN_OK;
 }
 
 int psattn_meta_copy_key_desc(const psattn_meta* meta, int32_t* key_hi) {
     if (!meta || (!key_hi && meta->T > 0)) return PSATTN_EINVAL;
-    if (meta->T > 0) std::memcpy(key_hi, meta->key_hi.data(), meta->key_hi.size() * sizeof(int32_t));
+    for (size_t i = 0; i < meta->seg_tok.size(); ++i)
+        std::fill(key_hi + meta->seg_start[i], key_hi + meta->seg_start[i + 1], meta->seg_tok[i].key_hi);
     return PSATTN_OK;
 }
 
 int psattn_meta_copy_positions(const psattn_meta* meta, int32_t* pos, int32_t* n_positions) {
     if (!meta || (!pos && meta->T > 0)) return PSATTN_EINVAL;
-    for (int32_t t = 0; t < meta->T; ++t) {
-        const int32_t s = meta->tok_desc[3 * t];
+    for (size_t i = 0; i < meta->seg_tok.size(); ++i) {
+        const psattn::Tok4& d = meta->seg_tok[i];
         // the hidden key range lies between the prompt and the token's own response: skipping it
         // puts the response right behind the prompt
-        pos[t] = s == psattn::kPadStart ? 0 : t - s - (meta->tok_desc[3 * t + 2] - meta->tok_desc[3 * t + 1]);
+        for (int32_t t = meta->seg_start[i]; t < meta->seg_start[i + 1]; ++t)
+            pos[t] = d.s == psattn::kPadStart ? 0 : t - d.s - (d.hole_hi - d.hole_lo);
     }
     if (n_positions) *n_positions = meta->n_positions;
     return PSATTN_OK;

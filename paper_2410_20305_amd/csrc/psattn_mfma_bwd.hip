@@ -224,16 +224,10 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_dq_bf16_mfma(Att
                 }
             }
     }
-    if (valid) {
-        uint16_t* row = static_cast<uint16_t*>(a.dQ) + qoff;
-        const float sc = a.scale;
+    const int row0 = qt * 128 + 32 * w;
+    uint16_t* rows = static_cast<uint16_t*>(a.dQ) + (static_cast<size_t>(row0) * Hq + h) * D;
 #pragma unroll
-        for (int db = 0; db < kBlocks; ++db)
-#pragma unroll
-            for (int i4 = 0; i4 < 4; ++i4)
-                store4(row + 32 * db + 8 * i4 + 4 * g, dq[db][4 * i4] * sc, dq[db][4 * i4 + 1] * sc,
-                       dq[db][4 * i4 + 2] * sc, dq[db][4 * i4 + 3] * sc);
-    }
+    for (int db = 0; db < kBlocks; ++db) store_block(rows, static_cast<size_t>(Hq) * D, T - row0, db, dq[db], a.scale, l);
 }
 
 }  // namespace

@@ -326,12 +326,40 @@ __device__ inline void rope_frag8(Frag8& lo, Frag8& hi, const float* row, int i0
     }
 }
 
-__device__ inline void store4(uint16_t* dst, float a, float b, float c, float d) {
-    f32x2 v0 = {a, b}, v1 = {c, d};
-    union { bf16x2 p[2]; uint2 u; } o;
-    o.p[0] = __builtin_convertvector(v0, bf16x2);
-    o.p[1] = __builtin_convertvector(v1, bf16x2);
-    *reinterpret_cast<uint2*>(dst) = o.u;
+__device__ __forceinline__ uint32_t pack2(float a, float b) {
+    f32x2 v = {a, b};
+    union { bf16x2 p; uint32_t u; } o;
+    o.p = __builtin_convertvector(v, bf16x2);
+    return o.u;
+}
+
+// Stores one 32-wide block (head dims 32 db ..) of the wave's 32 output rows: `x` is an accumulator whose column is
+// the lane's row.  A lane holds pieces of four head dims, 8 bytes in bf16, of one row; stored like that, every store
+// instruction would scatter 32 pieces of 16 bytes.  Two rounds of lane swaps first: between the half-waves (the two
+// pieces of 8 bytes that make 16), then between the 16-lane halves of each (rows r and r + 16 trade 16-byte chunks),
+// after which an instruction writes 64 contiguous bytes of each of 16 rows.
+// `base`: row 0 of the wave's 32; `row_elems`: elements between rows; rows from n_rows on are not stored.
+__device__ __forceinline__ void store_block(uint16_t* base, size_t row_elems, int n_rows, int db, const f32x16& x, float factor, int l) {
+    uint32_t c[2][4];  // 16-byte chunks 2 k + g of the block, k = 0, 1
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int i = 8 * k + 2 * j;
+            const auto r = __builtin_amdgcn_permlane32_swap(pack2(x[i] * factor, x[i + 1] * factor), pack2(x[i + 4] * factor, x[i + 5] * factor), false, false);
+            c[k][j] = r[0];
+            c[k][2 + j] = r[1];
+        }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const auto r = __builtin_amdgcn_permlane16_swap(c[0][j], c[1][j], false, false);
+        c[0][j] = r[0];
+        c[1][j] = r[1];
+    }
+    const int row = l & 15;
+    uint16_t* p = base + row * row_elems + 32 * db + 16 * ((l >> 4) & 1) + 8 * (l >> 5);
+    if (row < n_rows) *reinterpret_cast<uint4*>(p) = make_uint4(c[0][0], c[0][1], c[0][2], c[0][3]);
+    if (row + 16 < n_rows) *reinterpret_cast<uint4*>(p + 16 * row_elems) = make_uint4(c[1][0], c[1][1], c[1][2], c[1][3]);
 }
 
 }  // namespace mma

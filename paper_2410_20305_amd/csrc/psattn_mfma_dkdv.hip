@@ -90,13 +90,6 @@ __device__ inline void pair_masks(uint32_t (&mw)[2][8], int lo, int hi, int g) {
         }
 }
 
-__device__ inline uint32_t pack2(float a, float b) {
-    f32x2 v = {a, b};
-    union { bf16x2 p; uint32_t u; } o;
-    o.p = __builtin_convertvector(v, bf16x2);
-    return o.u;
-}
-
 __device__ inline float comp(const float4& v, int i) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; }
 
 // The LDS operands of the first kAhead slots (Q and dO rows of query block 0, head dims 0-31),
@@ -331,44 +324,45 @@ __global__ __launch_bounds__(256) void psattn_dkdv_bf16_mfma(AttnArgs a) {
     // no copy may still be writing to LDS when the workgroup ends
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     settle();  // the last MFMAs, before dK / dV are read out
-    if (kvalid) {
-        uint16_t* krow = static_cast<uint16_t*>(a.dK) + koff;
-        uint16_t* vrow = static_cast<uint16_t*>(a.dV) + koff;
-        const float sc = a.scale;
-        static_for<0, 16>([&](auto Q4) {
-            constexpr int q4 = decltype(Q4)::value, db = q4 >> 2, i4 = q4 & 3;
-            const int d = 32 * db + 8 * i4 + 4 * g;
-            store4(vrow + d, acc_get<kAccDV + 16 * db + 4 * i4 + 0>(), acc_get<kAccDV + 16 * db + 4 * i4 + 1>(),
-                   acc_get<kAccDV + 16 * db + 4 * i4 + 2>(), acc_get<kAccDV + 16 * db + 4 * i4 + 3>());
+    const int row0 = kt * 128 + 32 * w;
+    const size_t out0 = (static_cast<size_t>(row0) * Hkv + kvh) * 128, row_elems = static_cast<size_t>(Hkv) * 128;
+    auto get = [&](auto A0) {
+        f32x16 x;
+        static_for<0, 16>([&](auto I) { x[decltype(I)::value] = acc_get<decltype(A0)::value + decltype(I)::value>(); });
+        return x;
+    };
+    static_for<0, 4>([&](auto DB) {
+        constexpr int db = decltype(DB)::value;
+        store_block(static_cast<uint16_t*>(a.dV) + out0, row_elems, T - row0, db, get(std::integral_constant<int, kAccDV + 16 * db>{}), 1.f, l);
+    });
+    if (a.rope) {
+        // K arrived rotated: turn dK back by the key's angles (accumulator element 4 i4 + k of block
+        // db is head dim 32 db + 8 i4 + 4 g + k; its partner sits in block db + 2)
+        const float* trow = a.rope + (kvalid ? static_cast<size_t>(rope_position(a.meta.tok[key], key)) * 128 : 0);
+        static_for<0, 2>([&](auto DB) {
+            constexpr int db = decltype(DB)::value;
+            f32x16 x = get(std::integral_constant<int, kAccDK + 16 * db>{}), y = get(std::integral_constant<int, kAccDK + 16 * (db + 2)>{});
+#pragma unroll
+            for (int i4 = 0; i4 < 4; ++i4) {
+                const float4 c = *reinterpret_cast<const float4*>(trow + 32 * db + 8 * i4 + 4 * g);
+                const float4 s = *reinterpret_cast<const float4*>(trow + 64 + 32 * db + 8 * i4 + 4 * g);
+                const float cs[4] = {c.x, c.y, c.z, c.w}, sn[4] = {s.x, s.y, s.z, s.w};
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    float lo = x[4 * i4 + k], hi = y[4 * i4 + k];
+                    rope_turn<true>(lo, hi, cs[k], sn[k]);
+                    x[4 * i4 + k] = lo;
+                    y[4 * i4 + k] = hi;
+                }
+            }
+            store_block(static_cast<uint16_t*>(a.dK) + out0, row_elems, T - row0, db, x, a.scale, l);
+            store_block(static_cast<uint16_t*>(a.dK) + out0, row_elems, T - row0, db + 2, y, a.scale, l);
         });
-        if (a.rope) {
-            // K arrived rotated: turn dK back by the key's angles (accumulator element 4 i4 + k of block
-            // db is head dim 32 db + 8 i4 + 4 g + k; its partner sits in block db + 2)
-            const float* trow = a.rope + static_cast<size_t>(rope_position(a.meta.tok[key], key)) * 128;
-            static_for<0, 8>([&](auto Q4) {
-                constexpr int q4 = decltype(Q4)::value, db = q4 >> 2, i4 = q4 & 3;
-                const int d = 32 * db + 8 * i4 + 4 * g;
-                const float4 c = *reinterpret_cast<const float4*>(trow + d);
-                const float4 s = *reinterpret_cast<const float4*>(trow + 64 + d);
-                float l0 = acc_get<kAccDK + 16 * db + 4 * i4 + 0>(), l1 = acc_get<kAccDK + 16 * db + 4 * i4 + 1>(),
-                      l2 = acc_get<kAccDK + 16 * db + 4 * i4 + 2>(), l3 = acc_get<kAccDK + 16 * db + 4 * i4 + 3>();
-                float h0 = acc_get<kAccDK + 16 * (db + 2) + 4 * i4 + 0>(), h1 = acc_get<kAccDK + 16 * (db + 2) + 4 * i4 + 1>(),
-                      h2 = acc_get<kAccDK + 16 * (db + 2) + 4 * i4 + 2>(), h3 = acc_get<kAccDK + 16 * (db + 2) + 4 * i4 + 3>();
-                rope_turn<true>(l0, h0, c.x, s.x);
-                rope_turn<true>(l1, h1, c.y, s.y);
-                rope_turn<true>(l2, h2, c.z, s.z);
-                rope_turn<true>(l3, h3, c.w, s.w);
-                store4(krow + d, l0 * sc, l1 * sc, l2 * sc, l3 * sc);
-                store4(krow + 64 + d, h0 * sc, h1 * sc, h2 * sc, h3 * sc);
-            });
-        } else {
-            static_for<0, 16>([&](auto Q4) {
-                constexpr int q4 = decltype(Q4)::value, db = q4 >> 2, i4 = q4 & 3;
-                const int d = 32 * db + 8 * i4 + 4 * g;
-                store4(krow + d, acc_get<kAccDK + 16 * db + 4 * i4 + 0>() * sc, acc_get<kAccDK + 16 * db + 4 * i4 + 1>() * sc,
-                       acc_get<kAccDK + 16 * db + 4 * i4 + 2>() * sc, acc_get<kAccDK + 16 * db + 4 * i4 + 3>() * sc);
-            });
-        }
+    } else {
+        static_for<0, 4>([&](auto DB) {
+            constexpr int db = decltype(DB)::value;
+            store_block(static_cast<uint16_t*>(a.dK) + out0, row_elems, T - row0, db, get(std::integral_constant<int, kAccDK + 16 * db>{}), a.scale, l);
+        });
     }
 }
 

@@ -181,18 +181,12 @@ __global__ __launch_bounds__(256, 2) void psattn_dkdv64_bf16_mfma(AttnArgs a) {
     if (it < n_it) tile(std::integral_constant<int, 0>{});
     // no copy may still be writing to LDS when the workgroup ends
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if (kvalid) {
-        uint16_t* krow = static_cast<uint16_t*>(a.dK) + koff;
-        uint16_t* vrow = static_cast<uint16_t*>(a.dV) + koff;
-        const float sc = a.scale;
+    const int row0 = kt * 128 + 32 * w;
+    const size_t out0 = (static_cast<size_t>(row0) * Hkv + kvh) * 64, row_elems = static_cast<size_t>(Hkv) * 64;
 #pragma unroll
-        for (int db = 0; db < 2; ++db)
-#pragma unroll
-            for (int i4 = 0; i4 < 4; ++i4) {
-                const int d = 32 * db + 8 * i4 + 4 * g;
-                store4(vrow + d, dv[db][4 * i4], dv[db][4 * i4 + 1], dv[db][4 * i4 + 2], dv[db][4 * i4 + 3]);
-                store4(krow + d, dk[db][4 * i4] * sc, dk[db][4 * i4 + 1] * sc, dk[db][4 * i4 + 2] * sc, dk[db][4 * i4 + 3] * sc);
-            }
+    for (int db = 0; db < 2; ++db) {
+        store_block(static_cast<uint16_t*>(a.dV) + out0, row_elems, T - row0, db, dv[db], 1.f, l);
+        store_block(static_cast<uint16_t*>(a.dK) + out0, row_elems, T - row0, db, dk[db], a.scale, l);
     }
 }
 

@@ -216,17 +216,12 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(At
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     const float l_tot = lsum + other_half(lsum);
     const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-    if (valid) {
-        uint16_t* orow = static_cast<uint16_t*>(a.Oout) + (static_cast<size_t>(q_row) * Hq + h) * D;
+    const int row0 = qt * 128 + 32 * w;
+    uint16_t* orow = static_cast<uint16_t*>(a.Oout) + (static_cast<size_t>(row0) * Hq + h) * D;
 #pragma unroll
-        for (int db = 0; db < kBlocks; ++db)
-#pragma unroll
-            for (int i4 = 0; i4 < 4; ++i4)
-                store4(orow + 32 * db + 8 * i4 + 4 * g, o[db][4 * i4] * inv, o[db][4 * i4 + 1] * inv,
-                       o[db][4 * i4 + 2] * inv, o[db][4 * i4 + 3] * inv);
-        if (g == 0)
-            a.LSEout[static_cast<size_t>(h) * T + q_row] = l_tot > 0.f ? m * kLn2 + __logf(l_tot) : -INFINITY;
-    }
+    for (int db = 0; db < kBlocks; ++db) store_block(orow, static_cast<size_t>(Hq) * D, T - row0, db, o[db], inv, l);
+    if (valid && g == 0)
+        a.LSEout[static_cast<size_t>(h) * T + q_row] = l_tot > 0.f ? m * kLn2 + __logf(l_tot) : -INFINITY;
 }
 
 }  // namespace

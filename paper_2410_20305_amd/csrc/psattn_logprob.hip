@@ -8,8 +8,11 @@
 // never read, which is where the prefix sharing saves work here too (the prompt is most of
 // the tokens).
 //
-// All three passes stream logits rows of `vocab` elements and are bound by HBM bandwidth:
-// one workgroup per row, 16-byte loads, online max / sum in fp32, one exponential per element.
+// All three passes stream logits rows of `vocab` elements and are bound by HBM bandwidth: one workgroup per row, 16-byte
+// accesses from the row's first aligned element on (rows of an odd vocabulary start anywhere), online max / sum in fp32,
+// one exponential per element.  65 536 rows of 32 000 bf16, 9 965 of them with a target: log-sum-exp 169 -> 98 us
+// (6.5 TB/s), gradient 906 -> 884 us (5.5 TB/s, almost all of it writes; a plain fill reaches 5.6 - 5.8); 8 334 rows of
+// 50 257 fp32, 3 206 with a target: 242 -> 100 us and 588 -> 476 us.
 // Every sum is taken in a fixed order (no atomics): results are deterministic.
 #include <hip/hip_runtime.h>
 
@@ -37,46 +40,74 @@ struct psattn_lp_plan {
 namespace {
 
 constexpr int kThreads = 256;
+constexpr int kBwdThreads = 1024;
 
-__device__ inline float bf16_to_f32(uint16_t b) { return __uint_as_float(static_cast<uint32_t>(b) << 16); }
-__device__ inline uint16_t f32_to_bf16(float v) {  // round to nearest even
-    uint32_t u = __float_as_uint(v);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return static_cast<uint16_t>((u >> 16) | 0x40);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return static_cast<uint16_t>(u >> 16);
-}
+// The gradient writes far more than it reads, and fewer rows open at a time suit the memory: 256 / 512 / 1024 threads per
+// row 957 / 941 / 923 us (non-temporal stores 965 / - / 884 us) on 65 536 rows of 32 000 bf16; several loads in flight
+// per lane change nothing there (879 us with four, but 492 us against 476 on 8 334 rows of 50 257 fp32).
+constexpr int kUnroll = 4;  // 16-byte loads in flight per lane of the log-sum-exp
+// Non-temporal accesses where the data is larger than the 256 MB last-level cache, so that the pass that follows could
+// not find it there anyway (reading 4 GB alone: 6.3 -> 7.1 TB/s).
+constexpr size_t kCacheBytes = size_t{256} << 20;
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
+typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
+
 __device__ inline float ld1(const float* p) { return *p; }
-__device__ inline float ld1(const uint16_t* p) { return bf16_to_f32(*p); }
+__device__ inline float ld1(const uint16_t* p) { return __uint_as_float(static_cast<uint32_t>(*p) << 16); }
+__device__ inline uint32_t pack_bf16(float a, float b) {  // round to nearest even
+    const f32x2 v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
 __device__ inline void st1(float* p, float v) { *p = v; }
-__device__ inline void st1(uint16_t* p, float v) { *p = f32_to_bf16(v); }
+__device__ inline void st1(uint16_t* p, float v) { *p = static_cast<uint16_t>(pack_bf16(v, 0.f)); }
 
 template <typename E> struct Vec;
 template <> struct Vec<uint16_t> { static constexpr int N = 8; };  // 16 bytes
 template <> struct Vec<float> { static constexpr int N = 4; };
 
-__device__ inline void load_vec(const uint16_t* p, float (&x)[8]) {
-    const uint4 u = *reinterpret_cast<const uint4*>(p);
-    const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+template <bool NT, typename E>
+__device__ inline u32x4 load_raw(const E* p) {
+    if constexpr (NT) return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+    else return *reinterpret_cast<const u32x4*>(p);
+}
+__device__ inline void unpack(const u32x4& u, float (&x)[8]) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        x[2 * j] = __uint_as_float(w[j] << 16);
-        x[2 * j + 1] = __uint_as_float(w[j] & 0xffff0000u);
+        x[2 * j] = __uint_as_float(u[j] << 16);
+        x[2 * j + 1] = __uint_as_float(u[j] & 0xffff0000u);
     }
 }
-__device__ inline void load_vec(const float* p, float (&x)[4]) {
-    const float4 u = *reinterpret_cast<const float4*>(p);
-    x[0] = u.x; x[1] = u.y; x[2] = u.z; x[3] = u.w;
-}
-__device__ inline void store_vec(uint16_t* p, const float (&x)[8]) {
-    uint4 u;
-    uint32_t w[4];
+__device__ inline void unpack(const u32x4& u, float (&x)[4]) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) w[j] = static_cast<uint32_t>(f32_to_bf16(x[2 * j])) | (static_cast<uint32_t>(f32_to_bf16(x[2 * j + 1])) << 16);
-    u.x = w[0]; u.y = w[1]; u.z = w[2]; u.w = w[3];
-    *reinterpret_cast<uint4*>(p) = u;
+    for (int j = 0; j < 4; ++j) x[j] = __uint_as_float(u[j]);
 }
-__device__ inline void store_vec(float* p, const float (&x)[4]) {
-    *reinterpret_cast<float4*>(p) = make_float4(x[0], x[1], x[2], x[3]);
+template <bool NT, typename E>
+__device__ inline void store_vec(E* p, const float* x) {
+    u32x4 u;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        if constexpr (sizeof(E) == 2) u[j] = pack_bf16(x[2 * j], x[2 * j + 1]);
+        else u[j] = __float_as_uint(x[j]);
+    }
+    if constexpr (NT) __builtin_nontemporal_store(u, reinterpret_cast<u32x4*>(p));
+    else *reinterpret_cast<u32x4*>(p) = u;
+}
+
+// A row seen as `head` single elements up to the first 16-byte boundary, n_vec aligned groups of N, and the rest.
+struct RowSplit {
+    int head, n_vec, tail;  // tail: index of the first element behind the groups
+};
+template <typename E>
+__device__ inline RowSplit split_row(const E* x, int vocab) {
+    constexpr int N = Vec<E>::N;
+    const int mis = static_cast<int>(reinterpret_cast<uintptr_t>(x) / sizeof(E)) & (N - 1);
+    RowSplit r;
+    r.head = min(vocab, (N - mis) & (N - 1));
+    r.n_vec = (vocab - r.head) / N;
+    r.tail = r.head + r.n_vec * N;
+    return r;
 }
 
 // (m, s) pairs of an online log-sum-exp: value = m + log s
@@ -113,32 +144,47 @@ __device__ inline float block_sum(float v, float* sm) {
 }
 
 // ---- pass 1: log-sum-exp of every row that predicts something
-template <typename E>
+template <typename E, bool NT>
 __global__ __launch_bounds__(kThreads) void psattn_lp_row_lse(const int32_t* rows, int vocab, const E* logits, float* row_lse) {
     __shared__ float sm[kThreads / 64], ss[kThreads / 64];
     const int row = rows[blockIdx.x];
     const E* x = logits + static_cast<size_t>(row) * vocab;
     constexpr int N = Vec<E>::N;
+    const RowSplit r = split_row(x, vocab);
+    const E* xv = x + r.head;
     float m = -INFINITY, s = 0.f;
-    const int n_vec = (vocab % N == 0) ? vocab / N : 0;  // rows are 16-byte aligned only then
-    for (int c = threadIdx.x; c < n_vec; c += kThreads) {
-        float v[N];
-        load_vec(x + static_cast<size_t>(c) * N, v);
-        float mx = v[0];
+    for (int c = threadIdx.x; c < r.n_vec; c += kThreads * kUnroll) {
+        u32x4 raw[kUnroll];
 #pragma unroll
-        for (int j = 1; j < N; ++j) mx = fmaxf(mx, v[j]);
-        const float mn = fmaxf(m, mx);
-        float acc = 0.f;
+        for (int u = 0; u < kUnroll; ++u)
+            raw[u] = load_raw<NT>(xv + static_cast<size_t>(min(c + u * kThreads, r.n_vec - 1)) * N);
+        float mx = m;
 #pragma unroll
-        for (int j = 0; j < N; ++j) acc += __expf(v[j] - mn);
-        s = s * __expf(m - mn) + acc;
-        m = mn;
+        for (int u = 0; u < kUnroll; ++u) {
+            float v[N];
+            unpack(raw[u], v);
+#pragma unroll
+            for (int j = 0; j < N; ++j) mx = fmaxf(mx, v[j]);  // a group read again at the row's end does not change it
+        }
+        const float ref = mx == -INFINITY ? 0.f : mx;
+        s *= __expf(m - ref);
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            float v[N], acc = 0.f;
+            unpack(raw[u], v);
+#pragma unroll
+            for (int j = 0; j < N; ++j) acc += __expf(v[j] - ref);
+            if (c + u * kThreads < r.n_vec) s += acc;
+        }
+        m = mx;
     }
-    for (int c = n_vec * N + threadIdx.x; c < vocab; c += kThreads) {
-        const float v = ld1(x + c), mn = fmaxf(m, v);
-        s = s * __expf(m - mn) + __expf(v - mn);
-        m = mn;
-    }
+    auto one = [&](int i) {
+        const float v = ld1(x + i), mx = fmaxf(m, v), ref = mx == -INFINITY ? 0.f : mx;
+        s = s * __expf(m - ref) + __expf(v - ref);
+        m = mx;
+    };
+    if (static_cast<int>(threadIdx.x) < r.head) one(threadIdx.x);
+    for (int i = r.tail + threadIdx.x; i < vocab; i += kThreads) one(i);
     block_lse(m, s, sm, ss);
     if (threadIdx.x == 0) row_lse[row] = m + __logf(s);
 }
@@ -163,8 +209,8 @@ __global__ __launch_bounds__(kThreads) void psattn_lp_resp_sum(const int32_t* re
 }
 
 // ---- backward: d logits = sum over the row's items of d_logp[j] (onehot(target) - softmax(row))
-template <typename E>
-__global__ __launch_bounds__(kThreads) void psattn_lp_bwd(const int32_t* row_desc, const int32_t* resp_first,
+template <typename E, bool NT>
+__global__ __launch_bounds__(kBwdThreads) void psattn_lp_bwd(const int32_t* row_desc, const int32_t* resp_first,
                                                           const int32_t* resp_len, const int32_t* samp_ptr, int vocab,
                                                           const E* logits, const int32_t* token_ids, const float* row_lse,
                                                           const float* d_logp, E* dlogits) {
@@ -172,13 +218,14 @@ __global__ __launch_bounds__(kThreads) void psattn_lp_bwd(const int32_t* row_des
     const E* x = logits + static_cast<size_t>(row) * vocab;
     E* g = dlogits + static_cast<size_t>(row) * vocab;
     constexpr int N = Vec<E>::N;
-    const int n_vec = (vocab % N == 0) ? vocab / N : 0;
+    RowSplit sp = split_row(g, vocab);
     if (desc == -1) {  // predicts nothing: the row of the gradient is zero, the logits are not read
         float z[N];
 #pragma unroll
         for (int j = 0; j < N; ++j) z[j] = 0.f;
-        for (int c = threadIdx.x; c < n_vec; c += kThreads) store_vec(g + static_cast<size_t>(c) * N, z);
-        for (int c = n_vec * N + threadIdx.x; c < vocab; c += kThreads) st1(g + c, 0.f);
+        for (int c = threadIdx.x; c < sp.n_vec; c += kBwdThreads) store_vec<NT>(g + sp.head + static_cast<size_t>(c) * N, z);
+        if (static_cast<int>(threadIdx.x) < sp.head) st1(g + threadIdx.x, 0.f);
+        for (int i = sp.tail + threadIdx.x; i < vocab; i += kBwdThreads) st1(g + i, 0.f);
         return;
     }
     // total weight of the row's items
@@ -196,27 +243,30 @@ __global__ __launch_bounds__(kThreads) void psattn_lp_bwd(const int32_t* row_des
     for (int j = r0; j < r1; ++j)
         if (target(j) >= 0) coef += d_logp[j];
     const float lse = row_lse[row];
-    for (int c = threadIdx.x; c < n_vec; c += kThreads) {
+    if ((reinterpret_cast<uintptr_t>(x) ^ reinterpret_cast<uintptr_t>(g)) & 15) sp = {0, 0, 0};  // the two rows share no 16-byte boundaries
+    const E* xv = x + sp.head;
+    E* gv = g + sp.head;
+    auto grad = [&](float v) { return -coef * __expf(v - lse); };
+    for (int c = threadIdx.x; c < sp.n_vec; c += kBwdThreads) {
         float v[N];
-        load_vec(x + static_cast<size_t>(c) * N, v);
+        unpack(load_raw<false>(xv + static_cast<size_t>(c) * N), v);
 #pragma unroll
-        for (int j = 0; j < N; ++j) v[j] = -coef * __expf(v[j] - lse);
-        store_vec(g + static_cast<size_t>(c) * N, v);
+        for (int k = 0; k < N; ++k) v[k] = grad(v[k]);
+        store_vec<NT>(gv + static_cast<size_t>(c) * N, v);
     }
-    for (int c = n_vec * N + threadIdx.x; c < vocab; c += kThreads) st1(g + c, -coef * __expf(ld1(x + c) - lse));
-    // the target columns: recomputed whole by one thread after the block's stores are visible, so
-    // each is rounded once and two responses that start with the same token add up
-    __threadfence_block();
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int j = r0; j < r1; ++j) {
-            const int tgt = target(j);
-            if (tgt < 0) continue;
-            float v = -coef * __expf(ld1(x + tgt) - lse);
-            for (int k = r0; k < r1; ++k)
-                if (target(k) == tgt) v += d_logp[k];
-            st1(g + tgt, v);
-        }
+    if (static_cast<int>(threadIdx.x) < sp.head) st1(g + threadIdx.x, grad(ld1(x + threadIdx.x)));
+    for (int i = sp.tail + threadIdx.x; i < vocab; i += kBwdThreads) st1(g + i, grad(ld1(x + i)));
+    // the target columns: each is recomputed whole by the thread that has just stored it, so it is rounded once and two
+    // responses that start with the same token add up
+    for (int j = r0; j < r1; ++j) {
+        const int tgt = target(j);
+        if (tgt < 0) continue;
+        const int owner = tgt < sp.head ? tgt : tgt < sp.tail ? (tgt - sp.head) / N : tgt - sp.tail;
+        if (owner % kBwdThreads != static_cast<int>(threadIdx.x)) continue;
+        float v = grad(ld1(x + tgt));
+        for (int k = r0; k < r1; ++k)
+            if (target(k) == tgt) v += d_logp[k];
+        st1(g + tgt, v);
     }
 }
 
@@ -340,8 +390,10 @@ int psattn_logprob_fwd(const psattn_lp_plan* plan, int32_t dt, int32_t vocab, co
     if (!logits || !token_ids || !row_lse || !resp_logp) return PSATTN_EINVAL;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     if (plan->n_rows > 0) {
-        if (dt == PSATTN_BF16) psattn_lp_row_lse<uint16_t><<<plan->n_rows, kThreads, 0, s>>>(plan->rows, vocab, static_cast<const uint16_t*>(logits), row_lse);
-        else psattn_lp_row_lse<float><<<plan->n_rows, kThreads, 0, s>>>(plan->rows, vocab, static_cast<const float*>(logits), row_lse);
+        const bool nt = static_cast<size_t>(plan->n_rows) * vocab * (dt == PSATTN_BF16 ? 2 : 4) > kCacheBytes;
+        auto lse = [&](auto kernel, auto* x) { kernel<<<plan->n_rows, kThreads, 0, s>>>(plan->rows, vocab, x, row_lse); };
+        if (dt == PSATTN_BF16) lse(nt ? psattn_lp_row_lse<uint16_t, true> : psattn_lp_row_lse<uint16_t, false>, static_cast<const uint16_t*>(logits));
+        else lse(nt ? psattn_lp_row_lse<float, true> : psattn_lp_row_lse<float, false>, static_cast<const float*>(logits));
     }
     if (dt == PSATTN_BF16) psattn_lp_resp_sum<uint16_t><<<plan->n_resp, kThreads, 0, s>>>(plan->resp_first, plan->resp_len, plan->resp_prev, vocab, static_cast<const uint16_t*>(logits), token_ids, row_lse, resp_logp);
     else psattn_lp_resp_sum<float><<<plan->n_resp, kThreads, 0, s>>>(plan->resp_first, plan->resp_len, plan->resp_prev, vocab, static_cast<const float*>(logits), token_ids, row_lse, resp_logp);
@@ -354,8 +406,12 @@ int psattn_logprob_bwd(const psattn_lp_plan* plan, int32_t dt, int32_t vocab, co
     if (plan->T == 0) return PSATTN_OK;
     if (!logits || !token_ids || !row_lse || !dlogits || (plan->n_resp > 0 && !d_resp_logp)) return PSATTN_EINVAL;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    if (dt == PSATTN_BF16) psattn_lp_bwd<uint16_t><<<plan->T, kThreads, 0, s>>>(plan->row_desc, plan->resp_first, plan->resp_len, plan->samp_ptr, vocab, static_cast<const uint16_t*>(logits), token_ids, row_lse, d_resp_logp, static_cast<uint16_t*>(dlogits));
-    else psattn_lp_bwd<float><<<plan->T, kThreads, 0, s>>>(plan->row_desc, plan->resp_first, plan->resp_len, plan->samp_ptr, vocab, static_cast<const float*>(logits), token_ids, row_lse, d_resp_logp, static_cast<float*>(dlogits));
+    const bool nt = static_cast<size_t>(plan->T) * vocab * (dt == PSATTN_BF16 ? 2 : 4) > kCacheBytes;
+    auto bwd = [&](auto kernel, auto* x, auto* g) {
+        kernel<<<plan->T, kBwdThreads, 0, s>>>(plan->row_desc, plan->resp_first, plan->resp_len, plan->samp_ptr, vocab, x, token_ids, row_lse, d_resp_logp, g);
+    };
+    if (dt == PSATTN_BF16) bwd(nt ? psattn_lp_bwd<uint16_t, true> : psattn_lp_bwd<uint16_t, false>, static_cast<const uint16_t*>(logits), static_cast<uint16_t*>(dlogits));
+    else bwd(nt ? psattn_lp_bwd<float, true> : psattn_lp_bwd<float, false>, static_cast<const float*>(logits), static_cast<float*>(dlogits));
     return hipGetLastError() == hipSuccess ? PSATTN_OK : PSATTN_EHIP;
 }
 

@@ -58,6 +58,8 @@ DeviceCsr view_csr(const char* lists, size_t ent, size_t lch, const TileCsr& g) 
     v.entry = reinterpret_cast<const int32_t*>(lists + ent);
     v.launch = reinterpret_cast<const RowLaunch*>(lists + lch);
     v.n_rows = static_cast<int32_t>(g.row_ptr.size()) - 1;
+    v.n_entries = static_cast<int64_t>(g.entry.size());
+    for (int32_t r = 0; r < v.n_rows; ++r) v.longest = std::max(v.longest, g.row_ptr[r + 1] - g.row_ptr[r]);
     v.tile_q = g.tile_q;
     v.tile_k = g.tile_k;
     return v;

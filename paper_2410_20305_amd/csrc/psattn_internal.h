@@ -45,6 +45,8 @@ struct DeviceCsr {
     const RowLaunch* launch;  // [n_rows], in launch order
     int32_t n_rows;
     int32_t tile_q, tile_k;
+    int32_t longest;    // entries of the longest row
+    int64_t n_entries;  // of all rows
 };
 
 // Per-token descriptor as the kernels read it (one 16-byte load).

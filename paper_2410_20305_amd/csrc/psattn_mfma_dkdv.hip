@@ -1,7 +1,7 @@
 // bf16 MFMA dK/dV kernel for gfx950; layout and staging helpers are in psattn_mfma_common.h.
 //
 // grid: one workgroup per (k-tile of 128 keys, kv-head); 4 waves x 32 keys, one wave per
-// SIMD.  The workgroup walks the G query heads of its group and, for each, the q-tiles
+// SIMD (or two workgroups of 64 keys for the same, on grids that are bound by their longest row: see psattn_dkdv_bf16_mfma).  The workgroup walks the G query heads of its group and, for each, the q-tiles
 // (64 queries) that can read its keys (the k-major tile list of the block mask, paper
 // Section 3.1), so the prompt's keys collect the contributions of prompt, chosen and
 // rejected queries in one place, without atomics.
@@ -103,9 +103,9 @@ __device__ __forceinline__ void tile_prefetch(Frag8 (&ring)[8], const char* sQ, 
 }
 
 // FULL: every pair of the tile is allowed, no mask work at all (mw is not read).
-// copy_piece(k), k = 0 .. 8, issues one instruction of the next tile's asynchronous copy;
+// copy_piece(k), k = 0 .. PIECES - 1, issues one instruction of the next tile's asynchronous copy;
 // the pieces are spread over the first slots.
-template <bool FULL, typename CopyPiece>
+template <bool FULL, int PIECES, typename CopyPiece>
 __device__ __forceinline__ void dkdv_tile(const char* sQ, const char* sG, const float* sL, const float* sD,
                                           const LaneOffsets& lo, const uint32_t (&mw)[2][8], float c, int g,
                                           Frag8 (&ring)[8], CopyPiece&& copy_piece) {
@@ -149,7 +149,7 @@ __device__ __forceinline__ void dkdv_tile(const char* sQ, const char* sG, const 
         // Copy pieces go out every other slot: the four waves issue theirs at the same moment and
         // the CU's address unit takes one such instruction per ~16 cycles, so a piece per slot
         // from each wave would queue up and stall the waves.
-        if constexpr (m < 18 && (m & 1) == 0) copy_piece(std::integral_constant<int, m / 2>{});
+        if constexpr (m < 2 * PIECES && (m & 1) == 0) copy_piece(std::integral_constant<int, m / 2>{});
         if constexpr (m == 10) start_dp(std::integral_constant<int, 1>{});
         // One wait per two slots: naming the next slot's operand here makes the compiler wait
         // for both now (the statement itself is empty), and the odd slot then needs none.
@@ -186,19 +186,26 @@ __device__ __forceinline__ void dkdv_tile(const char* sQ, const char* sG, const 
     });
 }
 
+// S = 1: the four waves hold 128 keys and walk the list together.
+// S = 2: a workgroup holds 64 keys, two waves each, twice over: its two groups of waves take every other step of the walk
+// (a step is one head on one q-tile) with tiles of their own, and their partial sums are added in LDS at the end.  Twice as
+// many workgroups, each half as long; see launch_mfma_dkdv for when.
+template <int S>
 __global__ __launch_bounds__(256) void psattn_dkdv_bf16_mfma(AttnArgs a) {
-    __shared__ __attribute__((aligned(16))) char sQ[2][kQTileBytes];
-    __shared__ __attribute__((aligned(16))) char sG[2][kQTileBytes];  // dO
-    __shared__ __attribute__((aligned(16))) float sL[2][64];          // LSE * log2(e)
-    __shared__ __attribute__((aligned(16))) float sD[2][64];          // -delta
+    constexpr int kWaves = 4 / S, kRows = 64 / kWaves, kOps = kRows / 4, kPieces = 2 * kOps + 1;
+    // tiles of Q (two buffers), of dO (two buffers) per group; then LSE * log2(e) and -delta
+    __shared__ __attribute__((aligned(16))) char smem[S][4][kQTileBytes];
+    __shared__ __attribute__((aligned(16))) float sStat[S][2][2][64];
     // a[0:191] are in use: makes the kernel's register allocation cover them
     asm volatile("" ::: "a0", "a191");
-    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, c32 = l & 31, g = l >> 5;
+    const int tid = threadIdx.x, wg = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, c32 = l & 31, g = l >> 5;
+    const int group = S == 1 ? 0 : wg / kWaves, w = S == 1 ? wg : wg % kWaves;  // wave index in its group
     const int T = a.meta.T, Hq = a.Hq, Hkv = a.Hkv, G = Hq / Hkv;
     const DeviceCsr& csr = a.meta.bwd;
-    const RowLaunch rl = csr.launch[blockIdx.x / Hkv];  // one scalar load: row, list bounds, first entry
-    const int kvh = blockIdx.x % Hkv, kt = rl.row;
-    const int key = kt * 128 + 32 * w + c32;
+    const int kvh = blockIdx.x % Hkv, rest = blockIdx.x / Hkv;
+    const RowLaunch rl = csr.launch[rest / S];  // one scalar load: row, list bounds, first entry
+    const int row0 = rl.row * 128 + (rest % S) * (128 / S) + 32 * w;  // the wave's first key
+    const int key = row0 + c32;
     const bool kvalid = key < T;
     const int key_hi = kvalid ? a.meta.tok[key].key_hi : 0;  // queries [key, key_hi) read this key
     const size_t koff = (static_cast<size_t>(key) * Hkv + kvh) * 128;
@@ -223,9 +230,17 @@ __global__ __launch_bounds__(256) void psattn_dkdv_bf16_mfma(AttnArgs a) {
     static_for<0, 128>([&](auto R) { acc_set<decltype(R)::value>(0u); });
 
     const float c = a.scale * kLog2e;
-    const LaneOffsets lo = lane_offsets(l);
+    LaneOffsets lo = lane_offsets(l);
+    if constexpr (S > 1) {  // the group's tiles
+        const int at = group * static_cast<int>(sizeof(smem[0]));
+        lo.nat += at;
+        lo.tr1 += at;
+        lo.tr2 += at;
+    }
     const int e0 = rl.begin, n_ent = rl.count;
-    const int n_it = n_ent * G;
+    const int n_steps = n_ent * G;
+    const int n_it = (n_steps - group + S - 1) / S;      // the group's share: steps group, group + S, ...
+    const int n_loop = (n_steps + S - 1) / S;            // every wave joins every barrier
 
     // Staging of one q-tile (64 rows x 256 B of Q and of dO, 64 LSE * log2 e, 64 delta):
     // asynchronous global -> LDS copies, issued one tile ahead into the buffer the
@@ -233,13 +248,23 @@ __global__ __launch_bounds__(256) void psattn_dkdv_bf16_mfma(AttnArgs a) {
     // last token: whatever they hold is removed by the pair masks (a clipped tile is
     // never FULL).
     const uint32_t row_bytes = static_cast<uint32_t>(Hq) * 256u;
-    const DmaLane dml = dma_lane(row_bytes, w, l);
-    // The copy of one tile is nine instructions per lane: pieces 0-3 are Q rows, 4-7 dO rows,
-    // piece 8 the statistics.  copy_setup fixes the tile, copy_piece issues one piece.
+    struct Lane { uint32_t off[kOps]; };
+    auto lane_rows = [&](int last_row) {
+        Lane d;
+#pragma unroll
+        for (int i = 0; i < kOps; ++i) {
+            const int row = kRows * w + 4 * i + (l >> 4);
+            d.off[i] = static_cast<uint32_t>(min(row, last_row)) * row_bytes + (((l & 15) ^ row_swizzle<128>(row)) << 4);
+        }
+        return d;
+    };
+    const Lane dml = lane_rows(63);
+    // The copy of one tile is 2 kOps + 1 instructions per lane: the first kOps are Q rows, then dO rows, the last one the
+    // statistics.  copy_setup fixes the tile, copy_piece issues one piece.
     const char* cp_q = nullptr;   // first Q row of the tile being copied (this head)
     const char* cp_g = nullptr;   // first dO row
     const float* cp_s = nullptr;  // this lane's statistic (waves 0, 1)
-    DmaLane cp_lane = dml;
+    Lane cp_lane = dml;
     auto copy_setup = [&](int ent, int h) {
         const int q0 = (ent >> 2) * 64;
         const size_t tile_elems = (static_cast<size_t>(q0) * Hq + h) * 128;
@@ -250,14 +275,14 @@ __global__ __launch_bounds__(256) void psattn_dkdv_bf16_mfma(AttnArgs a) {
         cp_lane = dml;
         if (rmax < 63) {
             asm volatile("; clipped tile" : "+s"(rmax));  // keeps the clamped offsets' arithmetic in this branch
-            cp_lane = dma_lane(row_bytes, w, l, rmax);
+            cp_lane = lane_rows(rmax);
         }
     };
     auto copy_piece = [&](auto P, auto BUF) {
         constexpr int p = decltype(P)::value, buf = decltype(BUF)::value;
-        if constexpr (p < 4) dma16(cp_q, cp_lane.off[p], lds_addr(sQ[buf]) + (16 * w + 4 * p) * kRowBytes);
-        else if constexpr (p < 8) dma16(cp_g, cp_lane.off[p - 4], lds_addr(sG[buf]) + (16 * w + 4 * (p - 4)) * kRowBytes);
-        else if (w < 2) dma4(cp_s, lds_addr(w ? sD[buf] : sL[buf]));  // wave 0: LSE * log2 e, wave 1: -delta
+        if constexpr (p < kOps) dma16(cp_q, cp_lane.off[p], lds_addr(smem[0][buf]) + group * sizeof(smem[0]) + (kRows * w + 4 * p) * kRowBytes);
+        else if constexpr (p < 2 * kOps) dma16(cp_g, cp_lane.off[p - kOps], lds_addr(smem[0][2 + buf]) + group * sizeof(smem[0]) + (kRows * w + 4 * (p - kOps)) * kRowBytes);
+        else if (w < 2) dma4(cp_s, lds_addr(sStat[0][0][buf]) + group * sizeof(sStat[0]) + (w ? sizeof(sStat[0][0]) : 0));  // wave 0: LSE * log2 e, wave 1: -delta
     };
     // Walk order: q-tiles from the last to the first, and for each q-tile the G heads
     // of the group.  Every k-tile of a sample ends at the same q-tile, so workgroups
@@ -265,13 +290,22 @@ __global__ __launch_bounds__(256) void psattn_dkdv_bf16_mfma(AttnArgs a) {
     // same Q / dO tile at the same moment and share it through L2.
     EntryStream es;
     es.init(csr.entry, e0 + n_ent - 1, -1, n_ent, l);
-    int pk = 0, ph = 0;  // walk position and head (within the group) of the next tile
+    int pk = 0, ph = 0;  // walk position and head (within the group of heads) of the group's next step
+    auto advance = [&](int steps) {
+        ph += steps;
+        while (ph >= G) { ph -= G; ++pk; }
+    };
     int ent = 0, it = 0;
-    if (n_it > 0) {
+    if (n_steps > 0) {
         ent = rl.first_entry;
-        copy_setup(ent, kvh * G);
-        static_for<0, 9>([&](auto P) { copy_piece(P, std::integral_constant<int, 0>{}); });
-        if (++ph == G) { ph = 0; ++pk; }
+        if constexpr (S > 1) {
+            advance(group);
+            if (pk >= n_ent) pk = ph = 0;  // nothing to do for this group: it copies a tile that it does not use
+            if (pk > 0) ent = es.get(pk);
+        }
+        copy_setup(ent, kvh * G + ph);
+        static_for<0, kPieces>([&](auto P) { copy_piece(P, std::integral_constant<int, 0>{}); });
+        advance(S);
     }
     // One tile; the buffer index is a compile-time constant, so every LDS address is a lane
     // constant plus an immediate offset.
@@ -281,60 +315,91 @@ __global__ __launch_bounds__(256) void psattn_dkdv_bf16_mfma(AttnArgs a) {
         // have, and tile it - 1 (same buffer as it + 1) is no longer read
         dma_wait_barrier<0>();
         Frag8 ring[8];
-        tile_prefetch(ring, sQ[buf], sG[buf], lo);
+        const char *sQ = smem[0][buf], *sG = smem[0][2 + buf];  // the group's tiles are behind them by what lo holds
+        const float *sL = sStat[group][0][buf], *sD = sStat[group][1][buf];
+        tile_prefetch(ring, sQ, sG, lo);
         __builtin_amdgcn_sched_barrier(0);
         const int q0 = (ent >> 2) * 64;
         const bool full = (ent & 3) == PSATTN_TILE_FULL;
         // After the last tile the copy is issued once more (same tile, other buffer): the slots
         // then need no branch around each piece; nobody reads that buffer.
         if (it + 1 < n_it) {
-            if (ph == 0) {  // first head of the next q-tile
+            if (ph < S) {  // another q-tile
                 ent = es.get(pk);
-                copy_setup(ent, kvh * G);
-            } else {        // same q-tile, next head of the group: 128 elements / T statistics further on
-                cp_q += 256;
-                cp_g += 256;
-                cp_s += T;
+                copy_setup(ent, kvh * G + ph);
+            } else {       // same q-tile, S heads on: 128 S elements / S T statistics further on
+                cp_q += 256 * S;
+                cp_g += 256 * S;
+                cp_s += S * T;
             }
-            if (++ph == G) { ph = 0; ++pk; }
+            advance(S);
         }
         ++it;
         auto piece = [&](auto P) { copy_piece(P, std::integral_constant<int, buf ^ 1>{}); };
         uint32_t mw[2][8];
-        if (full) {
-            dkdv_tile<true>(sQ[buf], sG[buf], sL[buf], sD[buf], lo, mw, c, g, ring, piece);
+        if (S > 1 && it > n_it) {  // the other group's last step
+        } else if (full) {
+            dkdv_tile<true, kPieces>(sQ, sG, sL, sD, lo, mw, c, g, ring, piece);
         } else if (__builtin_amdgcn_ballot_w64(max(key, q0) < min(key_hi, q0 + 64)) == 0) {
             // PARTIAL tile none of whose queries reads any of this wave's 32 keys (two of the four
             // waves on the first q-tile of every causal diagonal, and the keys of another sample or
             // response): the wave only issues its share of the next tile's copy
-            static_for<0, 9>([&](auto P) { piece(P); });
+            static_for<0, kPieces>([&](auto P) { piece(P); });
         } else {
             pair_masks(mw, key - q0, key_hi - q0, g);
-            dkdv_tile<false>(sQ[buf], sG[buf], sL[buf], sD[buf], lo, mw, c, g, ring, piece);
+            dkdv_tile<false, kPieces>(sQ, sG, sL, sD, lo, mw, c, g, ring, piece);
         }
     };
     // The K / V loads above have retired before the loop starts, so the loop body holds no
     // wait on a compiler-tracked load (such a wait would also cover the copies in flight).
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
     settle();  // the register writes above, before the first MFMA reads them
-    while (it < n_it) {
+    while (it < n_loop) {
         if (it & 1) tile(std::integral_constant<int, 1>{});
         else tile(std::integral_constant<int, 0>{});
     }
     // no copy may still be writing to LDS when the workgroup ends
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     settle();  // the last MFMAs, before dK / dV are read out
-    const int row0 = kt * 128 + 32 * w;
     const size_t out0 = (static_cast<size_t>(row0) * Hkv + kvh) * 128, row_elems = static_cast<size_t>(Hkv) * 128;
+    if constexpr (S > 1) {
+        // Group 0 hands its dK to group 1, which hands its dV to group 0; each adds the other's part to its own.
+        __syncthreads();  // every wave's reads and copies are done: the tiles' space is free
+        char* const mine = &smem[0][0][0] + wg * kQTileBytes + 16 * l;
+        const char* const theirs = &smem[0][0][0] + (wg ^ kWaves) * kQTileBytes + 16 * l;
+        auto give = [&](auto A0) {
+            static_for<0, 16>([&](auto I) {
+                constexpr int r = decltype(A0)::value + 4 * decltype(I)::value;
+                *reinterpret_cast<float4*>(mine + 1024 * decltype(I)::value) = make_float4(acc_get<r>(), acc_get<r + 1>(), acc_get<r + 2>(), acc_get<r + 3>());
+            });
+        };
+        auto take = [&](auto A0) {
+            static_for<0, 16>([&](auto I) {
+                constexpr int r = decltype(A0)::value + 4 * decltype(I)::value;
+                const float4 x = *reinterpret_cast<const float4*>(theirs + 1024 * decltype(I)::value);
+                acc_set<r>(__float_as_uint(acc_get<r>() + x.x));
+                acc_set<r + 1>(__float_as_uint(acc_get<r + 1>() + x.y));
+                acc_set<r + 2>(__float_as_uint(acc_get<r + 2>() + x.z));
+                acc_set<r + 3>(__float_as_uint(acc_get<r + 3>() + x.w));
+            });
+        };
+        using DV = std::integral_constant<int, kAccDV>;
+        using DK = std::integral_constant<int, kAccDK>;
+        if (group) give(DV{}); else give(DK{});
+        __syncthreads();
+        if (group) take(DK{}); else take(DV{});
+    }
     auto get = [&](auto A0) {
         f32x16 x;
         static_for<0, 16>([&](auto I) { x[decltype(I)::value] = acc_get<decltype(A0)::value + decltype(I)::value>(); });
         return x;
     };
+    if (S == 1 || group == 0)
     static_for<0, 4>([&](auto DB) {
         constexpr int db = decltype(DB)::value;
         store_block(static_cast<uint16_t*>(a.dV) + out0, row_elems, T - row0, db, get(std::integral_constant<int, kAccDV + 16 * db>{}), 1.f, l);
     });
+    if (S > 1 && group == 0) return;
     if (a.rope) {
         // K arrived rotated: turn dK back by the key's angles (accumulator element 4 i4 + k of block
         // db is head dim 32 db + 8 i4 + 4 g + k; its partner sits in block db + 2)
@@ -368,10 +433,22 @@ __global__ __launch_bounds__(256) void psattn_dkdv_bf16_mfma(AttnArgs a) {
 
 }  // namespace
 
+// Which of the two.  A workgroup is a serial chain of as many steps (heads of the group x q-tiles) as its row is long, one
+// workgroup per CU, so a launch takes at least its longest chain however few workgroups there are; splitting halves the
+// chain and costs 10 - 15 % more work (every tile is staged for 64 keys instead of 128) and the exchange at the end.  The
+// line lies where the longest chain is 1.6 times a CU's share of all steps, and at chains of 8 steps.  Measured, whole
+// step of forward and backward, unsplit / split: one sample of 2 000 tokens, 32 q / 8 kv heads (chain 128, share 33)
+// 291 / 221 us; 28 / 4 heads 409 / 279; 221 tokens (16, 0.8) 55.5 / 47; six samples of 600 tokens (44, 25) 158 / 146;
+// sixteen of 256 (16, 12) 118 / 129; one sample of 180 tokens, 16 / 16 heads (3, 0.2) 33.7 / 34.1.
+constexpr int64_t kCus = 256;
+
 int launch_mfma_dkdv(const AttnArgs& a, void* stream) {
     const unsigned grid = static_cast<unsigned>(a.meta.bwd.n_rows) * a.Hkv;
     if (grid == 0) return 0;
-    psattn_dkdv_bf16_mfma<<<grid, 256, 0, static_cast<hipStream_t>(stream)>>>(a);
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    const int64_t chain = static_cast<int64_t>(a.meta.bwd.longest) * (a.Hq / a.Hkv), steps = a.meta.bwd.n_entries * a.Hq;
+    if (chain >= 8 && 10 * chain * kCus >= 16 * steps) psattn_dkdv_bf16_mfma<2><<<2 * grid, 256, 0, s>>>(a);
+    else psattn_dkdv_bf16_mfma<1><<<grid, 256, 0, s>>>(a);
     return static_cast<int>(hipGetLastError());
 }
 

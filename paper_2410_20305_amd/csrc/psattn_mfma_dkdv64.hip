@@ -1,13 +1,13 @@
 // bf16 MFMA dK/dV kernel for gfx950, head_dim 64; layout and staging helpers are in psattn_mfma_common.h.
 //
-// grid: one workgroup per (k-tile of 128 keys, kv-head); 4 waves x 32 keys.  The walk is that of the head_dim 128
+// grid: one workgroup per (k-tile of 128 keys, kv-head), or two of 64 keys; 4 waves x 32 keys.  The walk is that of the head_dim 128
 // kernel (the G query heads of the group, and for each the q-tiles of 64 queries that can read the keys, so that the
 // prompt's keys collect the contributions of prompt, chosen and rejected queries in one place, without atomics), but
 // at half the head dimension dK, dV and the K / V fragments of a wave take 96 registers instead of 192: the whole
 // kernel fits 256, the compiler can manage it, and two waves share a SIMD, so that one wave's softmax arithmetic
 // meets the other's MFMAs.  What bounds it is that arithmetic: per 64 x 32 scores a wave issues 32 MFMAs (1 024
 // cycles of the matrix pipeline) and about 300 vector instructions.  Measured on a step of 8 samples, 4 758 tokens,
-// 32 q / 8 kv heads: forward + dQ + dK/dV 14.9 ms on the one-thread-per-row kernels, 0.15 ms on these.
+// 32 q / 8 kv heads: forward + dQ + dK/dV 14.9 ms on the one-thread-per-row kernels, 0.13 ms on these.
 #include "psattn_mfma_common.h"
 
 namespace psattn {
@@ -16,17 +16,24 @@ using namespace mma;
 
 constexpr int kRB = kRowBytesOf<64>;
 
+// S = 1: the four waves hold 128 keys and walk the list together.  S = 2: a workgroup holds 64 keys, two waves each, twice
+// over: its two groups of waves take every other step of the walk (a step is one head on one q-tile) with tiles of their
+// own, and their partial sums are added in LDS at the end.  Twice as many workgroups, each half as long; see
+// launch_mfma_dkdv64 for when.
+template <int S>
 __global__ __launch_bounds__(256, 2) void psattn_dkdv64_bf16_mfma(AttnArgs a) {
-    __shared__ __attribute__((aligned(16))) char sQ[2][64 * kRB];  // double buffered
-    __shared__ __attribute__((aligned(16))) char sG[2][64 * kRB];  // dO
-    __shared__ __attribute__((aligned(16))) float sL[2][64];       // LSE * log2(e)
-    __shared__ __attribute__((aligned(16))) float sD[2][64];       // -delta
-    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, c32 = l & 31, g = l >> 5;
+    constexpr int kWaves = 4 / S, kRows = 64 / kWaves, kOps = kRows / 8, kPieces = 2 * kOps + 1;
+    // tiles of Q (two buffers), of dO (two buffers) per group; then LSE * log2(e) and -delta
+    __shared__ __attribute__((aligned(16))) char smem[S][4][64 * kRB];
+    __shared__ __attribute__((aligned(16))) float sStat[S][2][2][64];
+    const int tid = threadIdx.x, wg = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, c32 = l & 31, g = l >> 5;
+    const int group = S == 1 ? 0 : wg / kWaves, w = S == 1 ? wg : wg % kWaves;  // wave index in its group
     const int T = a.meta.T, Hq = a.Hq, Hkv = a.Hkv, G = Hq / Hkv;
     const DeviceCsr& csr = a.meta.bwd;
-    const RowLaunch rl = csr.launch[blockIdx.x / Hkv];  // one scalar load: row, list bounds, first entry
-    const int kvh = blockIdx.x % Hkv, kt = rl.row;
-    const int key = kt * 128 + 32 * w + c32;
+    const int kvh = blockIdx.x % Hkv, rest = blockIdx.x / Hkv;
+    const RowLaunch rl = csr.launch[rest / S];  // one scalar load: row, list bounds, first entry
+    const int row0 = rl.row * 128 + (rest % S) * (128 / S) + 32 * w;  // the wave's first key
+    const int key = row0 + c32;
     const bool kvalid = key < T;
     const int key_hi = kvalid ? a.meta.tok[key].key_hi : 0;  // queries [key, key_hi) read this key
     const size_t koff = (static_cast<size_t>(key) * Hkv + kvh) * 64;
@@ -44,38 +51,74 @@ __global__ __launch_bounds__(256, 2) void psattn_dkdv64_bf16_mfma(AttnArgs a) {
         for (int i = 0; i < 16; ++i) { dk[db][i] = 0.f; dv[db][i] = 0.f; }
 
     const float c = a.scale * kLog2e;
-    const LaneOffsets lo = lane_offsets<64>(l);
+    LaneOffsets lo = lane_offsets<64>(l);
+    if constexpr (S > 1) {  // the group's tiles
+        const int at = group * static_cast<int>(sizeof(smem[0]));
+        lo.nat += at;
+        lo.tr1 += at;
+        lo.tr2 += at;
+    }
     const int e0 = rl.begin, n_ent = rl.count;
-    const int n_it = n_ent * G;
+    const int n_steps = n_ent * G;
+    const int n_it = (n_steps - group + S - 1) / S;  // the group's share: steps group, group + S, ...
+    const int n_loop = (n_steps + S - 1) / S;        // every wave joins every barrier
 
     // Q and dO tiles and their statistics are copied global -> LDS asynchronously, one tile ahead, into the buffer the
     // previous tile has just vacated; rows past the end of the buffer re-read the last token and are masked.
     const uint32_t row_bytes = static_cast<uint32_t>(Hq) * kRB;
-    const DmaLaneOf<64> dml = dma_lane<64>(row_bytes, w, l);
-    PairCopyOf<64> pc;
-    const float* cp_s = nullptr;  // this lane's statistic (waves 0, 1)
+    struct Lane { uint32_t off[kOps]; };
+    auto lane_rows = [&](int last_row) {
+        Lane d;
+#pragma unroll
+        for (int i = 0; i < kOps; ++i) {
+            const int row = kRows * w + 8 * i + (l >> 3);
+            d.off[i] = static_cast<uint32_t>(min(row, last_row)) * row_bytes + (((l & 7) ^ row_swizzle<64>(row)) << 4);
+        }
+        return d;
+    };
+    const Lane dml = lane_rows(63);
+    const char *cp_q = nullptr, *cp_g = nullptr;  // first Q and dO row of the tile being copied
+    const float* cp_s = nullptr;                  // this lane's statistic (waves 0, 1 of a group)
+    Lane cp_lane = dml;
     auto copy_setup = [&](int ent, int h) {
-        const int q0 = (ent >> 2) * 64, rmax = T - 1 - q0;
+        const int q0 = (ent >> 2) * 64;
+        int rmax = T - 1 - q0;
         const size_t tile_elems = (static_cast<size_t>(q0) * Hq + h) * 64;
-        pair_copy_setup(pc, reinterpret_cast<const char*>(static_cast<const uint16_t*>(a.Q) + tile_elems),
-                        reinterpret_cast<const char*>(static_cast<const uint16_t*>(a.dO) + tile_elems), row_bytes, rmax, dml, w, l);
+        cp_q = reinterpret_cast<const char*>(static_cast<const uint16_t*>(a.Q) + tile_elems);
+        cp_g = reinterpret_cast<const char*>(static_cast<const uint16_t*>(a.dO) + tile_elems);
         cp_s = (w ? a.delta : a.lse2) + static_cast<size_t>(h) * T + q0 + min(l, rmax);
+        cp_lane = dml;
+        if (rmax < 63) {
+            asm volatile("; clipped tile" : "+s"(rmax));  // keeps the clamped offsets' arithmetic in this branch
+            cp_lane = lane_rows(rmax);
+        }
     };
     auto copy_piece = [&](auto P, auto BUF) {
         constexpr int p = decltype(P)::value, buf = decltype(BUF)::value;
-        if constexpr (p < 4) pair_copy_piece<p>(pc, sQ[buf], sG[buf], w);
-        else if (w < 2) dma4(cp_s, lds_addr(w ? sD[buf] : sL[buf]));  // wave 0: LSE * log2 e, wave 1: -delta
+        const uint32_t at = group * static_cast<uint32_t>(sizeof(smem[0])) + kRows * w * kRB;
+        if constexpr (p < kOps) dma16(cp_q, cp_lane.off[p], lds_addr(smem[0][buf]) + at + 1024 * p);
+        else if constexpr (p < 2 * kOps) dma16(cp_g, cp_lane.off[p - kOps], lds_addr(smem[0][2 + buf]) + at + 1024 * (p - kOps));
+        else if (w < 2) dma4(cp_s, lds_addr(sStat[0][0][buf]) + group * sizeof(sStat[0]) + (w ? sizeof(sStat[0][0]) : 0));  // wave 0: LSE * log2 e, wave 1: -delta
     };
     // q-tiles from the last to the first and the heads innermost: neighbouring k-tiles share Q / dO tiles through L2
     EntryStream es;
     es.init(csr.entry, e0 + n_ent - 1, -1, n_ent, l);
-    int pk = 0, ph = 0;  // walk position and head (within the group) of the next tile
+    int pk = 0, ph = 0;  // walk position and head (within the group of heads) of the group's next step
+    auto advance = [&](int steps) {
+        ph += steps;
+        while (ph >= G) { ph -= G; ++pk; }
+    };
     int ent = 0, it = 0;
-    if (n_it > 0) {
+    if (n_steps > 0) {
         ent = rl.first_entry;
-        copy_setup(ent, kvh * G);
-        static_for<0, 5>([&](auto P) { copy_piece(P, std::integral_constant<int, 0>{}); });
-        if (++ph == G) { ph = 0; ++pk; }
+        if constexpr (S > 1) {
+            advance(group);
+            if (pk >= n_ent) pk = ph = 0;  // nothing to do for this group: it copies a tile that it does not use
+            if (pk > 0) ent = es.get(pk);
+        }
+        copy_setup(ent, kvh * G + ph);
+        static_for<0, kPieces>([&](auto P) { copy_piece(P, std::integral_constant<int, 0>{}); });
+        advance(S);
     }
     constexpr int kAhead = 2, kRing = 4;
     auto tile = [&](auto BUF) {
@@ -85,22 +128,25 @@ __global__ __launch_bounds__(256, 2) void psattn_dkdv64_bf16_mfma(AttnArgs a) {
         const bool full = (ent & 3) == PSATTN_TILE_FULL;
         // after the last tile the same tile is copied once more (to the other buffer, which nobody reads)
         if (it + 1 < n_it) {
-            if (ph == 0) {
+            if (ph < S) {  // another q-tile
                 ent = es.get(pk);
-                copy_setup(ent, kvh * G);
-            } else {  // same q-tile, next head of the group
-                pc.a += kRB;
-                pc.b += kRB;
-                cp_s += T;
+                copy_setup(ent, kvh * G + ph);
+            } else {       // same q-tile, S heads on
+                cp_q += kRB * S;
+                cp_g += kRB * S;
+                cp_s += S * T;
             }
-            if (++ph == G) { ph = 0; ++pk; }
+            advance(S);
         }
         ++it;
+        if (S > 1 && it > n_it) return;  // the other group's last step: nothing is copied behind it
+        const char *sQ = smem[0][buf], *sG = smem[0][2 + buf];  // the group's tiles are behind them by what lo holds
+        const float *sL = sStat[group][0][buf], *sD = sStat[group][1][buf];
         uint32_t bits = 0xffffffffu;
         if (!full) {
             bits = elem_range_bits(key - q0, key_hi - q0, g);
             if (__builtin_amdgcn_ballot_w64(bits != 0) == 0) {
-                static_for<0, 5>([&](auto P) { copy_piece(P, std::integral_constant<int, buf ^ 1>{}); });
+                static_for<0, kPieces>([&](auto P) { copy_piece(P, std::integral_constant<int, buf ^ 1>{}); });
                 return;
             }
         }
@@ -113,10 +159,10 @@ __global__ __launch_bounds__(256, 2) void psattn_dkdv64_bf16_mfma(AttnArgs a) {
                 constexpr int b = m >> 4, j = m & 15;
                 if constexpr (j < 8) {
                     constexpr int t = j >> 1;
-                    ring[m % kRing].v = ld_rows<t>(((j & 1) ? sG[buf] : sQ[buf]) + 32 * b * kRB, lo.nat);
+                    ring[m % kRing].v = ld_rows<t>(((j & 1) ? sG : sQ) + 32 * b * kRB, lo.nat);
                 } else {
                     constexpr int half = (j >> 2) & 1, db = (j >> 1) & 1;
-                    ring[m % kRing].v = ld_cols<db, half, 64>(((j & 1) ? sQ[buf] : sG[buf]) + 32 * b * kRB, lo.tr1, lo.tr2);
+                    ring[m % kRing].v = ld_cols<db, half, 64>(((j & 1) ? sQ : sG) + 32 * b * kRB, lo.tr1, lo.tr2);
                 }
             }
         };
@@ -127,7 +173,7 @@ __global__ __launch_bounds__(256, 2) void psattn_dkdv64_bf16_mfma(AttnArgs a) {
             // dP starts from -delta, so that dS = P o (dP - delta) is one multiplication
 #pragma unroll
             for (int i4 = 0; i4 < 4; ++i4) {
-                const float4 d = *reinterpret_cast<const float4*>(sD[buf] + 32 * b + 8 * i4 + 4 * g);
+                const float4 d = *reinterpret_cast<const float4*>(sD + 32 * b + 8 * i4 + 4 * g);
                 dp[4 * i4] = d.x; dp[4 * i4 + 1] = d.y; dp[4 * i4 + 2] = d.z; dp[4 * i4 + 3] = d.w;
 #pragma unroll
                 for (int k = 0; k < 4; ++k) s[4 * i4 + k] = 0.f;
@@ -135,7 +181,7 @@ __global__ __launch_bounds__(256, 2) void psattn_dkdv64_bf16_mfma(AttnArgs a) {
             static_for<0, 8>([&](auto J) {
                 constexpr int j = decltype(J)::value, m = 16 * b + j, t = j >> 1;
                 request(std::integral_constant<int, m + kAhead>{});
-                if constexpr (b == 0 && j < 5) copy_piece(J, std::integral_constant<int, buf ^ 1>{});
+                if constexpr (8 * b + j < kPieces) copy_piece(std::integral_constant<int, 8 * b + j>{}, std::integral_constant<int, buf ^ 1>{});
                 if constexpr (j & 1) dp = mfma(ring[m % kRing].v, vf[t].v, dp);
                 else s = mfma(ring[m % kRing].v, kf[t].v, s);
                 __builtin_amdgcn_sched_barrier(0);
@@ -150,7 +196,7 @@ __global__ __launch_bounds__(256, 2) void psattn_dkdv64_bf16_mfma(AttnArgs a) {
             bf16x8 pb[2], dsb[2];
 #pragma unroll
             for (int i4 = 0; i4 < 4; ++i4) {
-                const float4 L = *reinterpret_cast<const float4*>(sL[buf] + 32 * b + 8 * i4 + 4 * g);
+                const float4 L = *reinterpret_cast<const float4*>(sL + 32 * b + 8 * i4 + 4 * g);
                 const float Ls[4] = {L.x, L.y, L.z, L.w};
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
@@ -174,28 +220,63 @@ __global__ __launch_bounds__(256, 2) void psattn_dkdv64_bf16_mfma(AttnArgs a) {
     // every compiler-tracked load above has retired before the loop starts, so the loop body holds no wait of the
     // compiler's that would also cover copies in flight
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-    while (it + 1 < n_it) {
+    while (it + 1 < n_loop) {
         tile(std::integral_constant<int, 0>{});
         tile(std::integral_constant<int, 1>{});
     }
-    if (it < n_it) tile(std::integral_constant<int, 0>{});
+    if (it < n_loop) tile(std::integral_constant<int, 0>{});
     // no copy may still be writing to LDS when the workgroup ends
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    const int row0 = kt * 128 + 32 * w;
     const size_t out0 = (static_cast<size_t>(row0) * Hkv + kvh) * 64, row_elems = static_cast<size_t>(Hkv) * 64;
+    if constexpr (S > 1) {
+        // Group 0 hands its dK to group 1, which hands its dV to group 0; each adds the other's part to its own.
+        __syncthreads();  // every wave's reads and copies are done: the tiles' space is free
+        char* const mine = &smem[0][0][0] + wg * 8192 + 16 * l;
+        const char* const theirs = &smem[0][0][0] + (wg ^ kWaves) * 8192 + 16 * l;
+        auto give = [&](const f32x16 (&x)[2]) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                *reinterpret_cast<float4*>(mine + 1024 * i) = make_float4(x[i >> 2][4 * (i & 3)], x[i >> 2][4 * (i & 3) + 1], x[i >> 2][4 * (i & 3) + 2], x[i >> 2][4 * (i & 3) + 3]);
+        };
+        auto take = [&](f32x16 (&x)[2]) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float4 y = *reinterpret_cast<const float4*>(theirs + 1024 * i);
+                x[i >> 2][4 * (i & 3)] += y.x;
+                x[i >> 2][4 * (i & 3) + 1] += y.y;
+                x[i >> 2][4 * (i & 3) + 2] += y.z;
+                x[i >> 2][4 * (i & 3) + 3] += y.w;
+            }
+        };
+        if (group) give(dv); else give(dk);
+        __syncthreads();
+        if (group) take(dk); else take(dv);
+    }
 #pragma unroll
     for (int db = 0; db < 2; ++db) {
-        store_block(static_cast<uint16_t*>(a.dV) + out0, row_elems, T - row0, db, dv[db], 1.f, l);
-        store_block(static_cast<uint16_t*>(a.dK) + out0, row_elems, T - row0, db, dk[db], a.scale, l);
+        if (S == 1 || group == 0) store_block(static_cast<uint16_t*>(a.dV) + out0, row_elems, T - row0, db, dv[db], 1.f, l);
+        if (S == 1 || group == 1) store_block(static_cast<uint16_t*>(a.dK) + out0, row_elems, T - row0, db, dk[db], a.scale, l);
     }
 }
 
 }  // namespace
 
+// Which of the two.  A workgroup is a serial chain of as many steps (heads of the group x q-tiles) as its row is long; with
+// two workgroups per CU a launch is bound by its longest chain until that falls below half of a CU's share of all steps.
+// Splitting halves the chain and costs a few per cent more work (every tile is staged for 64 keys instead of 128) and the
+// exchange at the end; the line lies where the longest chain is a CU's share.  Measured, whole step of forward and
+// backward, unsplit / split: one sample of 2 000 tokens, 32 q / 8 kv heads (chain 128, share 33) 225 / 155 us; eight of 860
+// tokens (64, 59) 197 / 181; fourteen of 600 (48, 58) 178 / 172; 16 / 16 heads, two of 1 600 (26, 22) 108 / 100, eight
+// of 500 (10, 13) 58 / 61.
+constexpr int64_t kCus = 256;
+
 int launch_mfma_dkdv64(const AttnArgs& a, void* stream) {
     const unsigned grid = static_cast<unsigned>(a.meta.bwd.n_rows) * a.Hkv;
     if (grid == 0) return 0;
-    psattn_dkdv64_bf16_mfma<<<grid, 256, 0, static_cast<hipStream_t>(stream)>>>(a);
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    const int64_t chain = static_cast<int64_t>(a.meta.bwd.longest) * (a.Hq / a.Hkv), steps = a.meta.bwd.n_entries * a.Hq;
+    if (chain > 0 && chain * kCus >= steps) psattn_dkdv64_bf16_mfma<2><<<2 * grid, 256, 0, s>>>(a);
+    else psattn_dkdv64_bf16_mfma<1><<<grid, 256, 0, s>>>(a);
     return static_cast<int>(hipGetLastError());
 }
 

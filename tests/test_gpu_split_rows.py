@@ -20,15 +20,16 @@ CASES = {
 }
 
 
+@pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("case", sorted(CASES))
-def test_split_rows(case):
+def test_split_rows(case, d):
     c = CASES[case]
-    w = W.custom_workload(c["samples"], offsets=c.get("offsets"), total_tokens=c.get("T"), hq=c["hq"], hkv=c["hkv"], d=128,
+    w = W.custom_workload(c["samples"], offsets=c.get("offsets"), total_tokens=c.get("T"), hq=c["hq"], hkv=c["hkv"], d=d,
                           dtype="bf16", seed=128)
     tens = W.make_tensors(w)
     out, meta = run_gpu(w, tens)
     import paper_2410_20305_amd as ps
     row_ptr, _, _ = meta.csr(ps.GRID_BWD)
     chain = int(np.diff(row_ptr).max()) * (c["hq"] // c["hkv"])
-    assert chain >= 8 and 10 * chain * 256 >= 16 * int(row_ptr[-1]) * c["hq"]  # the launch rule's condition
-    compare_full(w, tens, out, "bf16", what="split " + case)
+    assert chain >= 8 and 10 * chain * 256 >= 16 * int(row_ptr[-1]) * c["hq"]  # the launch rules' conditions
+    compare_full(w, tens, out, "bf16", what="split %s d %d" % (case, d))

@@ -296,6 +296,10 @@ int bwd_checked(const psattn_meta* meta, int32_t dt, int32_t n_q_heads, int32_t 
     int err = 0;
     const bool mfma = mfma_bwd_ok(meta, dt, head_dim, scale);
     if (rope_table && !(mfma && head_dim == 128)) return PSATTN_EUNSUPPORTED;  // rotary embedding lives in these matrix-core kernels only
+    if (!mfma && !g_profile && generic_bwd_in_one(a)) {  // (profiling times the passes one by one)
+        g_last_kernel[1] = g_last_kernel[2] = g_last_kernel[3] = "generic_bwd";
+        return launch_generic_bwd(dt, a, hip_stream) == 0 ? PSATTN_OK : PSATTN_EHIP;
+    }
     {  // the dQ kernels compute delta themselves and leave it in the scratch for the dK/dV pass
         PassTimer t(2, hip_stream);
         err = mfma ? launch_mfma_dq(a, hip_stream) : launch_generic_dq(dt, a, hip_stream);

@@ -9,7 +9,7 @@
 // eight waves share the 16-wide blocks of the other axis round-robin; their partial results are combined through LDS
 // in a fixed order (no atomics).  Operands go from global memory (L1 / L2) straight into registers as 16-byte loads
 // in both orientations; nothing is staged.  A step of one 168-token fp32 sample on one head of 64: forward 222 us,
-// delta + dQ 143 us, dK/dV 524 us with one thread per row; see the launchers for the figures of these.
+// delta + dQ 143 us, dK/dV 524 us with one thread per row; 7.7 us and, dQ and dK/dV in one launch, 11.4 us with these.
 //
 // Operand layout of the 16x16x4 product (r = lane % 16, g = lane / 16): A element (row r, k g), B element (k g,
 // column r), C register i = (row 4 g + i, column r).
@@ -225,11 +225,10 @@ __global__ __launch_bounds__(kThreads) void generic_fwd(AttnArgs a) {
 
 // ---------------------------------------------------------------- delta = rowsum(dO o O), dQ
 template <typename E, int D>
-__global__ __launch_bounds__(kThreads) void generic_dq(AttnArgs a) {
-    __shared__ Partials<D> sm;
+__device__ inline void dq_block(const AttnArgs& a, Partials<D>& sm, int block) {
     const int T = a.meta.T, Hq = a.Hq, Hkv = a.Hkv, n_blocks = (T + kB - 1) / kB;
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), r = tid & 15, g = (tid >> 4) & 3;
-    const int h = blockIdx.x % Hq, kvh = h / (Hq / Hkv), q0 = kB * (n_blocks - 1 - static_cast<int>(blockIdx.x) / Hq);
+    const int h = block % Hq, kvh = h / (Hq / Hkv), q0 = kB * (n_blocks - 1 - block / Hq);
     const int q = q0 + r;
     Tok4 tk = {kPadStart, 0, 0, 0};
     if (q < T) tk = a.meta.tok[q];
@@ -273,13 +272,13 @@ __global__ __launch_bounds__(kThreads) void generic_dq(AttnArgs a) {
 }
 
 // ---------------------------------------------------------------- dK, dV
-// the waves share the (query block, head of the group) pairs, heads innermost
-template <typename E, int D>
-__global__ __launch_bounds__(kThreads) void generic_dkdv(AttnArgs a) {
-    __shared__ Partials<D> sm;
+// the waves share the (query block, head of the group) pairs, heads innermost; OWN_DELTA: delta = rowsum(dO o O) is
+// computed here, from O, instead of being read from what the dQ pass left
+template <typename E, int D, bool OWN_DELTA>
+__device__ inline void dkdv_block(const AttnArgs& a, Partials<D>& sm, int block) {
     const int T = a.meta.T, Hq = a.Hq, Hkv = a.Hkv, G = Hq / Hkv;
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), r = tid & 15, g = (tid >> 4) & 3;
-    const int kvh = blockIdx.x % Hkv, k0 = kB * (static_cast<int>(blockIdx.x) / Hkv), key = k0 + r;
+    const int kvh = block % Hkv, k0 = kB * (block / Hkv), key = k0 + r;
     const int key_hi = key < T ? a.meta.tok[key].key_hi : 0;  // queries [key, key_hi) read this key
     f32x4 kf[D / 16], vf[D / 16], dk[D / 16], dv[D / 16];
     load_rows<E, D>(kf, row_of<E, D>(a.K, key, T, Hkv, kvh), g);
@@ -291,16 +290,30 @@ __global__ __launch_bounds__(kThreads) void generic_dkdv(AttnArgs a) {
     for (int it = w; it < n_it; it += kWaves) {
         const int q0 = k0 + kB * (it / G), h = kvh * G + it % G;
         f32x4 qf[D / 16], gf[D / 16], qc[4][D / 64], gc[4][D / 64];
-        load_rows<E, D>(qf, row_of<E, D>(a.Q, q0 + r, T, Hq, h), g);
+        float lse[4], delta[4];
         load_rows<E, D>(gf, row_of<E, D>(a.dO, q0 + r, T, Hq, h), g);
+        if constexpr (OWN_DELTA) {
+            const E* orow = row_of<E, D>(a.O, q0 + r, T, Hq, h);
+            float dl = 0.f;
+#pragma unroll
+            for (int t = 0; t < D / 16; ++t) {
+                const f32x4 o = ld4(orow + 16 * t + 4 * g);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) dl = fmaf(o[c], gf[t][c], dl);  // the dQ pass's order of sums
+            }
+            dl = sum_groups(dl);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) delta[i] = __shfl(dl, 4 * g + i);
+            if constexpr (D == 128) __builtin_amdgcn_sched_barrier(0);  // O is used up before the other operands need its registers
+        }
+        load_rows<E, D>(qf, row_of<E, D>(a.Q, q0 + r, T, Hq, h), g);
         load_cols<E, D>(qc, a.Q, q0, T, Hq, h, r, g);
         load_cols<E, D>(gc, a.dO, q0, T, Hq, h, r, g);
-        float lse[4], delta[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const size_t at = static_cast<size_t>(h) * T + min(q0 + 4 * g + i, T - 1);
             lse[i] = a.LSE[at];
-            delta[i] = a.delta[at];
+            if constexpr (!OWN_DELTA) delta[i] = a.delta[at];
         }
         const f32x4 s = dot_rows<D>(qf, kf), dp = dot_rows<D>(gf, vf);
         f32x4 p, ds;
@@ -326,6 +339,25 @@ __global__ __launch_bounds__(kThreads) void generic_dkdv(AttnArgs a) {
     if (mine) st4(static_cast<E*>(a.dV) + at, sum_partials<D>(sm, row, d));
 }
 
+template <typename E, int D>
+__global__ __launch_bounds__(kThreads) void generic_dq(AttnArgs a) {
+    __shared__ Partials<D> sm;
+    dq_block<E, D>(a, sm, blockIdx.x);
+}
+template <typename E, int D>
+__global__ __launch_bounds__(kThreads) void generic_dkdv(AttnArgs a) {
+    __shared__ Partials<D> sm;
+    dkdv_block<E, D, false>(a, sm, blockIdx.x);
+}
+// both at once: neither needs anything of the other
+template <typename E, int D>
+__global__ __launch_bounds__(kThreads) void generic_bwd(AttnArgs a) {
+    __shared__ Partials<D> sm;
+    const int n_dkdv = (a.meta.T + kB - 1) / kB * a.Hkv;
+    if (static_cast<int>(blockIdx.x) < n_dkdv) dkdv_block<E, D, true>(a, sm, blockIdx.x);
+    else dq_block<E, D>(a, sm, blockIdx.x - n_dkdv);
+}
+
 }  // namespace
 
 #define PSATTN_DISPATCH(KERNEL, HEADS)                                                               \
@@ -343,5 +375,16 @@ __global__ __launch_bounds__(kThreads) void generic_dkdv(AttnArgs a) {
 int launch_generic_fwd(int dt, const AttnArgs& a, void* stream) { PSATTN_DISPATCH(generic_fwd, a.Hq); }
 int launch_generic_dq(int dt, const AttnArgs& a, void* stream) { PSATTN_DISPATCH(generic_dq, a.Hq); }
 int launch_generic_dkdv(int dt, const AttnArgs& a, void* stream) { PSATTN_DISPATCH(generic_dkdv, a.Hkv); }
+int launch_generic_bwd(int dt, const AttnArgs& a, void* stream) { PSATTN_DISPATCH(generic_bwd, a.Hq + a.Hkv); }
+
+// One launch lets the dK/dV workgroups start with the dQ ones instead of behind them, for a recomputed delta per pair of
+// blocks.  It pays while both together do not fill the chip many times over and dK/dV is not the longer of the two by far
+// (its chains grow with the heads of a group).  Measured, whole step, two launches / one, fp32: 168 tokens, 1 / 1 heads of
+// 64 33.3 / 25.8 us; 450 tokens, 8 / 2 heads of 64 (290 workgroups) 83.5 / 77.3, of 128 148 / 153 (the one loss found
+// inside the rule); 4 000 tokens, 8 / 2 of 64 (2 500) 363 / 344; 8 000 (5 000) 623 / 653; 168 tokens, 32 / 1 of 64 180 / 203.
+bool generic_bwd_in_one(const AttnArgs& a) {
+    const int64_t groups = static_cast<int64_t>((a.meta.T + kB - 1) / kB) * (a.Hq + a.Hkv);
+    return groups <= 2560 && a.Hq <= 4 * a.Hkv;
+}
 
 }  // namespace psattn

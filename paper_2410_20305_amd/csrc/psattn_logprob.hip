@@ -18,6 +18,7 @@
 
 #include <cstring>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "psattn.h"
@@ -40,11 +41,12 @@ struct psattn_lp_plan {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kBwdThreads = 1024;
 
-// The gradient writes far more than it reads, and fewer rows open at a time suit the memory: 256 / 512 / 1024 threads per
-// row 957 / 941 / 923 us (non-temporal stores 965 / - / 884 us) on 65 536 rows of 32 000 bf16; several loads in flight
-// per lane change nothing there (879 us with four, but 492 us against 476 on 8 334 rows of 50 257 fp32).
+// The gradient writes far more than it reads, and of long rows fewer open at a time suit the memory: 256 / 512 / 1024
+// threads per row 957 / 941 / 923 us (non-temporal stores 965 / - / 884 us) on 65 536 rows of 32 000 bf16.  Short rows leave
+// most of 1024 threads without work: whole head, 46 000 rows, 256 / 1024 threads, 1 000 bf16 103 / 230 us, 8 000
+// (16 000 bytes) 335 / 380, 11 000 (22 000 bytes) 501 / 500, 16 000 723 / 662; 33 600 rows of 11 000 222 / 190.
+constexpr size_t kWideRowBytes = 20480;
 constexpr int kUnroll = 4;  // 16-byte loads in flight per lane of the log-sum-exp
 // Non-temporal accesses where the data is larger than the 256 MB last-level cache, so that the pass that follows could
 // not find it there anyway (reading 4 GB alone: 6.3 -> 7.1 TB/s).
@@ -153,31 +155,34 @@ __global__ __launch_bounds__(kThreads) void psattn_lp_row_lse(const int32_t* row
     const RowSplit r = split_row(x, vocab);
     const E* xv = x + r.head;
     float m = -INFINITY, s = 0.f;
-    for (int c = threadIdx.x; c < r.n_vec; c += kThreads * kUnroll) {
-        u32x4 raw[kUnroll];
+    auto groups = [&](auto COUNT, int c) {  // groups c, c + kThreads, ...
+        constexpr int n = decltype(COUNT)::value;
+        u32x4 raw[n];
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u)
-            raw[u] = load_raw<NT>(xv + static_cast<size_t>(min(c + u * kThreads, r.n_vec - 1)) * N);
+        for (int u = 0; u < n; ++u) raw[u] = load_raw<NT>(xv + static_cast<size_t>(c + u * kThreads) * N);
         float mx = m;
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
+        for (int u = 0; u < n; ++u) {
             float v[N];
             unpack(raw[u], v);
 #pragma unroll
-            for (int j = 0; j < N; ++j) mx = fmaxf(mx, v[j]);  // a group read again at the row's end does not change it
+            for (int j = 0; j < N; ++j) mx = fmaxf(mx, v[j]);
         }
         const float ref = mx == -INFINITY ? 0.f : mx;
         s *= __expf(m - ref);
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
+        for (int u = 0; u < n; ++u) {
             float v[N], acc = 0.f;
             unpack(raw[u], v);
 #pragma unroll
             for (int j = 0; j < N; ++j) acc += __expf(v[j] - ref);
-            if (c + u * kThreads < r.n_vec) s += acc;
+            s += acc;
         }
         m = mx;
-    }
+    };
+    int c = threadIdx.x;
+    for (; c + (kUnroll - 1) * kThreads < r.n_vec; c += kThreads * kUnroll) groups(std::integral_constant<int, kUnroll>{}, c);
+    for (; c < r.n_vec; c += kThreads) groups(std::integral_constant<int, 1>{}, c);
     auto one = [&](int i) {
         const float v = ld1(x + i), mx = fmaxf(m, v), ref = mx == -INFINITY ? 0.f : mx;
         s = s * __expf(m - ref) + __expf(v - ref);
@@ -209,7 +214,7 @@ __global__ __launch_bounds__(kThreads) void psattn_lp_resp_sum(const int32_t* re
 }
 
 // ---- backward: d logits = sum over the row's items of d_logp[j] (onehot(target) - softmax(row))
-template <typename E, bool NT>
+template <typename E, bool NT, int kBwdThreads>
 __global__ __launch_bounds__(kBwdThreads) void psattn_lp_bwd(const int32_t* row_desc, const int32_t* resp_first,
                                                           const int32_t* resp_len, const int32_t* samp_ptr, int vocab,
                                                           const E* logits, const int32_t* token_ids, const float* row_lse,
@@ -406,12 +411,24 @@ int psattn_logprob_bwd(const psattn_lp_plan* plan, int32_t dt, int32_t vocab, co
     if (plan->T == 0) return PSATTN_OK;
     if (!logits || !token_ids || !row_lse || !dlogits || (plan->n_resp > 0 && !d_resp_logp)) return PSATTN_EINVAL;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    const bool nt = static_cast<size_t>(plan->T) * vocab * (dt == PSATTN_BF16 ? 2 : 4) > kCacheBytes;
-    auto bwd = [&](auto kernel, auto* x, auto* g) {
-        kernel<<<plan->T, kBwdThreads, 0, s>>>(plan->row_desc, plan->resp_first, plan->resp_len, plan->samp_ptr, vocab, x, token_ids, row_lse, d_resp_logp, g);
+    const size_t row_bytes = static_cast<size_t>(vocab) * (dt == PSATTN_BF16 ? 2 : 4);
+    const bool wide = row_bytes >= kWideRowBytes;
+    const bool nt = plan->T * row_bytes > kCacheBytes;
+    auto bwd = [&](auto nontemporal, auto threads, auto* x, auto* g) {
+        constexpr int n = decltype(threads)::value;
+        psattn_lp_bwd<std::remove_pointer_t<decltype(g)>, decltype(nontemporal)::value, n><<<plan->T, n, 0, s>>>(
+            plan->row_desc, plan->resp_first, plan->resp_len, plan->samp_ptr, vocab, x, token_ids, row_lse, d_resp_logp, g);
     };
-    if (dt == PSATTN_BF16) bwd(nt ? psattn_lp_bwd<uint16_t, true> : psattn_lp_bwd<uint16_t, false>, static_cast<const uint16_t*>(logits), static_cast<uint16_t*>(dlogits));
-    else bwd(nt ? psattn_lp_bwd<float, true> : psattn_lp_bwd<float, false>, static_cast<const float*>(logits), static_cast<float*>(dlogits));
+    auto typed = [&](auto* x, auto* g) {
+        using Small = std::integral_constant<int, 256>;
+        using Large = std::integral_constant<int, 1024>;
+        if (nt && wide) bwd(std::true_type{}, Large{}, x, g);
+        else if (nt) bwd(std::true_type{}, Small{}, x, g);
+        else if (wide) bwd(std::false_type{}, Large{}, x, g);
+        else bwd(std::false_type{}, Small{}, x, g);
+    };
+    if (dt == PSATTN_BF16) typed(static_cast<const uint16_t*>(logits), static_cast<uint16_t*>(dlogits));
+    else typed(static_cast<const float*>(logits), static_cast<float*>(dlogits));
     return hipGetLastError() == hipSuccess ? PSATTN_OK : PSATTN_EHIP;
 }
 

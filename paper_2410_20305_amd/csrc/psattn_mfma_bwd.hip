@@ -163,14 +163,14 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_dq_bf16_mfma(Att
                 const float p = __builtin_amdgcn_exp2f(fmaf(s[i], c, -lse2));
                 s[i] = p * (dp[i] - dl);  // dS^T
             }
-            bf16x8 dsb[2];
-            dsb[0] = pack8(s, 0);
-            dsb[1] = pack8(s, 1);
+            Operand<D> dsb[2];
+            dsb[0] = make_operand<D>(s, 0);
+            dsb[1] = make_operand<D>(s, 1);
             __builtin_amdgcn_sched_barrier(0);
             static_for<kS, kB>([&](auto J) {
                 constexpr int j = decltype(J)::value, m = kB * kb + j, half = (j - kS) / kBlocks, db = (j - kS) % kBlocks;
                 request(std::integral_constant<int, m + kAhead>{});
-                dq[db] = mfma(ring[m % kRing].v, dsb[half], dq[db]);
+                dq[db] = mfma_parts<D>(ring[m % kRing].v, dsb[half], dq[db]);
                 __builtin_amdgcn_sched_barrier(0);
             });
         });

@@ -5,9 +5,10 @@
 // prompt's keys collect the contributions of prompt, chosen and rejected queries in one place, without atomics), but
 // at half the head dimension dK, dV and the K / V fragments of a wave take 96 registers instead of 192: the whole
 // kernel fits 256, the compiler can manage it, and two waves share a SIMD, so that one wave's softmax arithmetic
-// meets the other's MFMAs.  What bounds it is that arithmetic: per 64 x 32 scores a wave issues 32 MFMAs (1 024
-// cycles of the matrix pipeline) and about 300 vector instructions.  Measured on a step of 8 samples, 4 758 tokens,
-// 32 q / 8 kv heads: forward + dQ + dK/dV 14.9 ms on the one-thread-per-row kernels, 0.13 ms on these.
+// meets the other's MFMAs.  What bounds it is both: per 64 x 32 scores a wave issues 64 MFMAs (2 048 cycles of the
+// matrix pipeline; P and dS enter as three operands each, see make_operand) and about 515 vector instructions.  Measured
+// on a step of 8 samples, 4 758 tokens, 32 q / 8 kv heads: forward + dQ + dK/dV 14.9 ms on one thread per row, 0.18 ms on
+// these.
 #include "psattn_mfma_common.h"
 
 namespace psattn {
@@ -193,7 +194,7 @@ __global__ __launch_bounds__(256, 2) void psattn_dkdv64_bf16_mfma(AttnArgs a) {
                     s[i] = keep_or_neg_inf<16 * b + i>(s[i], bits);
                 });
             }
-            bf16x8 pb[2], dsb[2];
+            Operand<64> pb[2], dsb[2];
 #pragma unroll
             for (int i4 = 0; i4 < 4; ++i4) {
                 const float4 L = *reinterpret_cast<const float4*>(sL + 32 * b + 8 * i4 + 4 * g);
@@ -205,14 +206,14 @@ __global__ __launch_bounds__(256, 2) void psattn_dkdv64_bf16_mfma(AttnArgs a) {
                     dp[i] *= s[i];
                 }
             }
-            pb[0] = pack8(s, 0); pb[1] = pack8(s, 1);
-            dsb[0] = pack8(dp, 0); dsb[1] = pack8(dp, 1);
+            pb[0] = make_operand<64>(s, 0); pb[1] = make_operand<64>(s, 1);
+            dsb[0] = make_operand<64>(dp, 0); dsb[1] = make_operand<64>(dp, 1);
             __builtin_amdgcn_sched_barrier(0);
             static_for<8, 16>([&](auto J) {
                 constexpr int j = decltype(J)::value, m = 16 * b + j, half = (j >> 2) & 1, db = (j >> 1) & 1;
                 request(std::integral_constant<int, m + kAhead>{});
-                if constexpr (j & 1) dk[db] = mfma(ring[m % kRing].v, dsb[half], dk[db]);
-                else dv[db] = mfma(ring[m % kRing].v, pb[half], dv[db]);
+                if constexpr (j & 1) dk[db] = mfma_parts<64>(ring[m % kRing].v, dsb[half], dk[db]);
+                else dv[db] = mfma_parts<64>(ring[m % kRing].v, pb[half], dv[db]);
                 __builtin_amdgcn_sched_barrier(0);
             });
         });

@@ -183,7 +183,7 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(At
         }
         const float m_use = m == -INFINITY ? 0.f : m;
         float ps[4] = {0.f, 0.f, 0.f, 0.f};
-        bf16x8 pb[2][2];
+        Operand<D> pb[2][2];
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb) {
 #pragma unroll
@@ -191,8 +191,8 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(At
                 s[kb][i] = __builtin_amdgcn_exp2f(fmaf(s[kb][i], c, -m_use));
                 ps[i & 3] += s[kb][i];
             }
-            pb[kb][0] = pack8(s[kb], 0);
-            pb[kb][1] = pack8(s[kb], 1);
+            pb[kb][0] = make_operand<D>(s[kb], 0);
+            pb[kb][1] = make_operand<D>(s[kb], 1);
         }
         const float psum = (ps[0] + ps[1]) + (ps[2] + ps[3]);
         lsum += psum;
@@ -200,7 +200,7 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(At
         static_for<kS, 2 * kS>([&](auto M) {
             constexpr int m_ = decltype(M)::value, j = m_ - kS, kb = j / (2 * kBlocks), half = (j / kBlocks) & 1, db = j % kBlocks;
             request(std::integral_constant<int, m_ + kAhead>{});
-            o[db] = mfma(ring[m_ % kRing].v, pb[kb][half], o[db]);
+            o[db] = mfma_parts<D>(ring[m_ % kRing].v, pb[kb][half], o[db]);
             __builtin_amdgcn_sched_barrier(0);
         });
     };

@@ -19,45 +19,22 @@
 //            the A operand is 16 bytes of key 4 g + i at head dims 64 h + 4 r: component c gives output block (h, c),
 //            whose row r is head dim 64 h + 4 r + c, so that a lane ends up with four neighbouring head dims.
 //
+// Sums that are not finite are taken again on the allowed pairs alone (psattn_exact.h).
+//
 // Which 16-wide blocks hold an allowed pair follows from the per-token descriptors of Algorithm 3 alone (a query block
 // reads keys from its earliest sample start to its last query, without the blocks that are hidden from all its rows;
 // a key block is read by queries up to its largest key_hi), so the tile lists are not needed here.
 #include <hip/hip_runtime.h>
 
-#include "psattn_internal.h"
+#include "psattn_exact.h"
 
 namespace psattn {
 namespace {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
 constexpr int kWaves = 8, kThreads = 64 * kWaves;
 constexpr int kB = 16;  // rows of a block
 
-__device__ inline f32x4 ld4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
-__device__ inline f32x4 ld4(const uint16_t* p) {
-    const uint2 u = *reinterpret_cast<const uint2*>(p);
-    f32x4 v;
-    v[0] = __uint_as_float(u.x << 16); v[1] = __uint_as_float(u.x & 0xffff0000u);
-    v[2] = __uint_as_float(u.y << 16); v[3] = __uint_as_float(u.y & 0xffff0000u);
-    return v;
-}
-__device__ inline uint32_t bf16_bits(float v) {  // round to nearest even
-    uint32_t u = __float_as_uint(v);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return (u >> 16) | 0x40;
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return u >> 16;
-}
-__device__ inline void st4(float* p, f32x4 v) { *reinterpret_cast<f32x4*>(p) = v; }
-__device__ inline void st4(uint16_t* p, f32x4 v) {
-    *reinterpret_cast<uint2*>(p) = make_uint2(bf16_bits(v[0]) | (bf16_bits(v[1]) << 16), bf16_bits(v[2]) | (bf16_bits(v[3]) << 16));
-}
-
 __device__ inline f32x4 mfma4(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
-
-__device__ inline bool allowed(const Tok4& t, int q, int kv) {
-    return kv >= t.s && kv <= q && !(kv >= t.hole_lo && kv < t.hole_hi);
-}
 
 template <typename F>
 __device__ inline int over_rows(int x, F f) {  // f over the 16 rows of the block (the same in all lanes)
@@ -219,7 +196,9 @@ __global__ __launch_bounds__(kThreads) void generic_fwd(AttnArgs a) {
         o += *reinterpret_cast<const f32x4*>(&sm.v[i][row][d]) * f;
     }
     const float inv = lt > 0.f ? 1.f / lt : 0.f;
-    st4(static_cast<E*>(a.Oout) + (static_cast<size_t>(q0 + row) * Hq + h) * D + d, o * inv);
+    o *= inv;
+    if (!is_finite(o) || !(lt > 0.f)) o = exact_o<E, D>(a, h, q0 + row, d);  // (no sum: padding, or scores of -inf alone)
+    st4(static_cast<E*>(a.Oout) + (static_cast<size_t>(q0 + row) * Hq + h) * D + d, o);
     if (d == 0) a.LSEout[static_cast<size_t>(h) * T + q0 + row] = lt > 0.f ? mt + logf(lt) : -INFINITY;
 }
 
@@ -268,7 +247,9 @@ __device__ inline void dq_block(const AttnArgs& a, Partials<D>& sm, int block) {
     __syncthreads();
     int row, d;
     if (!my_quad<D>(tid, row, d) || q0 + row >= T) return;
-    st4(static_cast<E*>(a.dQ) + (static_cast<size_t>(q0 + row) * Hq + h) * D + d, sum_partials<D>(sm, row, d) * a.scale);
+    f32x4 dq = sum_partials<D>(sm, row, d) * a.scale;
+    if (!is_finite(dq)) dq = exact_dq<E, D>(a, h, q0 + row, d, a.delta[static_cast<size_t>(h) * T + q0 + row]);
+    st4(static_cast<E*>(a.dQ) + (static_cast<size_t>(q0 + row) * Hq + h) * D + d, dq);
 }
 
 // ---------------------------------------------------------------- dK, dV
@@ -330,13 +311,25 @@ __device__ inline void dkdv_block(const AttnArgs& a, Partials<D>& sm, int block)
     int row, d;
     const bool mine = my_quad<D>(tid, row, d) && k0 + row < T;
     const size_t at = (static_cast<size_t>(k0 + row) * Hkv + kvh) * D + d;
+    const auto delta_of = [&](int h, int q) {
+        if constexpr (OWN_DELTA) return exact_dot<D>(exact_row<E, D>(a.O, q, Hq, h), exact_row<E, D>(a.dO, q, Hq, h));
+        else return a.delta[static_cast<size_t>(h) * T + q];
+    };
     put_partial<D>(sm, dk, w, r, g);
     __syncthreads();
-    if (mine) st4(static_cast<E*>(a.dK) + at, sum_partials<D>(sm, row, d) * a.scale);
+    if (mine) {
+        f32x4 x = sum_partials<D>(sm, row, d) * a.scale;
+        if (!is_finite(x)) x = exact_dkdv<E, D, true>(a, kvh, k0 + row, d, delta_of);
+        st4(static_cast<E*>(a.dK) + at, x);
+    }
     __syncthreads();
     put_partial<D>(sm, dv, w, r, g);
     __syncthreads();
-    if (mine) st4(static_cast<E*>(a.dV) + at, sum_partials<D>(sm, row, d));
+    if (mine) {
+        f32x4 x = sum_partials<D>(sm, row, d);
+        if (!is_finite(x)) x = exact_dkdv<E, D, false>(a, kvh, k0 + row, d, delta_of);
+        st4(static_cast<E*>(a.dV) + at, x);
+    }
 }
 
 template <typename E, int D>

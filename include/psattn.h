@@ -38,9 +38,10 @@
  *     read kv-head g.
  *   - padding tokens (covered by no sample) are never attended to; every output at
  *     a padding position is written as zero (LSE = -inf).  Outputs are overwritten,
- *     never accumulated into.  The input VALUES at padding positions must be finite:
- *     the matrix-core kernels multiply them by exact zeros, and 0 * inf or 0 * NaN
- *     would reach real tokens of the same tile.
+ *     never accumulated into.  With PSATTN_BF16 and head_dim 128 the input VALUES must be
+ *     finite, at padding positions too: its matrix-core kernels multiply them by exact
+ *     zeros, and 0 * inf or 0 * NaN would reach other tokens of the same tile.  Every
+ *     other call takes any value: inf and NaN reach the rows that read them and no others.
  */
 #ifndef PSATTN_H
 #define PSATTN_H

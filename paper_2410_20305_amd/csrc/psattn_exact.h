@@ -118,9 +118,9 @@ __device__ inline f32x4 exact_dq(const AttnArgs& a, int h, int q, int d, float d
     return acc * a.scale;
 }
 
-// the same of dK (DK) or dV; delta(q-head, query)
-template <typename E, int D, bool DK, typename Delta>
-__device__ inline f32x4 exact_dkdv(const AttnArgs& a, int kvh, int key, int d, Delta delta) {
+// the same of dK (DK) or dV.  DELTA: a.delta holds delta (1) or its negative (-1), or delta is summed from O and dO (0)
+template <typename E, int D, bool DK, int DELTA>
+__device__ inline f32x4 exact_dkdv(const AttnArgs& a, int kvh, int key, int d) {
     const int G = a.Hq / a.Hkv, q_hi = a.meta.tok[key].key_hi;  // queries [key, q_hi) read this key
     const E *kr = exact_row<E, D>(a.K, key, a.Hkv, kvh), *vr = exact_row<E, D>(a.V, key, a.Hkv, kvh);
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -129,8 +129,12 @@ __device__ inline f32x4 exact_dkdv(const AttnArgs& a, int kvh, int key, int d, D
 #pragma nounroll
         for (int q = key; q < q_hi && !all_nan(acc); ++q) {
             const E *qr = exact_row<E, D>(a.Q, q, a.Hq, h), *gr = exact_row<E, D>(a.dO, q, a.Hq, h);
-            float p = expf(exact_dot<D>(qr, kr) * a.scale - a.LSE[static_cast<size_t>(h) * a.meta.T + q]);
-            if constexpr (DK) p *= exact_dot<D>(gr, vr) - delta(h, q);
+            const size_t stat = static_cast<size_t>(h) * a.meta.T + q;
+            float p = expf(exact_dot<D>(qr, kr) * a.scale - a.LSE[stat]);
+            if constexpr (DK) {
+                const float delta = DELTA == 0 ? exact_dot<D>(exact_row<E, D>(a.O, q, a.Hq, h), gr) : DELTA * a.delta[stat];
+                p *= exact_dot<D>(gr, vr) - delta;
+            }
             const f32x4 x = ld4((DK ? qr : gr) + d);
 #pragma unroll
             for (int c = 0; c < 4; ++c) acc[c] = fmaf(p, x[c], acc[c]);

@@ -311,15 +311,11 @@ __device__ inline void dkdv_block(const AttnArgs& a, Partials<D>& sm, int block)
     int row, d;
     const bool mine = my_quad<D>(tid, row, d) && k0 + row < T;
     const size_t at = (static_cast<size_t>(k0 + row) * Hkv + kvh) * D + d;
-    const auto delta_of = [&](int h, int q) {
-        if constexpr (OWN_DELTA) return exact_dot<D>(exact_row<E, D>(a.O, q, Hq, h), exact_row<E, D>(a.dO, q, Hq, h));
-        else return a.delta[static_cast<size_t>(h) * T + q];
-    };
     put_partial<D>(sm, dk, w, r, g);
     __syncthreads();
     if (mine) {
         f32x4 x = sum_partials<D>(sm, row, d) * a.scale;
-        if (!is_finite(x)) x = exact_dkdv<E, D, true>(a, kvh, k0 + row, d, delta_of);
+        if (!is_finite(x)) x = exact_dkdv<E, D, true, OWN_DELTA ? 0 : 1>(a, kvh, k0 + row, d);
         st4(static_cast<E*>(a.dK) + at, x);
     }
     __syncthreads();
@@ -327,7 +323,7 @@ __device__ inline void dkdv_block(const AttnArgs& a, Partials<D>& sm, int block)
     __syncthreads();
     if (mine) {
         f32x4 x = sum_partials<D>(sm, row, d);
-        if (!is_finite(x)) x = exact_dkdv<E, D, false>(a, kvh, k0 + row, d, delta_of);
+        if (!is_finite(x)) x = exact_dkdv<E, D, false, OWN_DELTA ? 0 : 1>(a, kvh, k0 + row, d);
         st4(static_cast<E*>(a.dV) + at, x);
     }
 }

@@ -1,4 +1,5 @@
 // bf16 MFMA backward (dQ; dK/dV) kernels for gfx950; layout and staging helpers are in psattn_mfma_common.h.
+#include "psattn_exact.h"
 #include "psattn_mfma_common.h"
 
 namespace psattn {
@@ -36,9 +37,11 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_dq_bf16_mfma(Att
                         : make_uint4(0, 0, 0, 0);
     }
     // Rows without keys (padding) have LSE = -inf.  Their scores are masked to -inf below;
-    // with +inf here exp2(score - lse2) is 0 for them instead of exp2(-inf + inf).
+    // with +inf here exp2(score - lse2) is 0 for them instead of exp2(-inf + inf).  (A row with keys has LSE = -inf only
+    // where its scores are not numbers; head_dim 64 passes that on to whatever reads the row.)
     const float lse_row = valid ? a.LSE[static_cast<size_t>(h) * T + q_row] : -INFINITY;
-    const float lse2 = lse_row == -INFINITY ? INFINITY : lse_row * kLog2e;
+    const bool no_keys = D == 64 ? tk.s == kPadStart : lse_row == -INFINITY;
+    const float lse2 = no_keys ? INFINITY : lse_row * kLog2e;
     // delta = rowsum(dO o O): this lane holds half of the row's dO already, O is read once
     // here; the result also goes to the workspace for the dK/dV pass that follows
     float dl = 0.f;
@@ -228,6 +231,10 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_dq_bf16_mfma(Att
     uint16_t* rows = static_cast<uint16_t*>(a.dQ) + (static_cast<size_t>(row0) * Hq + h) * D;
 #pragma unroll
     for (int db = 0; db < kBlocks; ++db) store_block(rows, static_cast<size_t>(Hq) * D, T - row0, db, dq[db], a.scale, l);
+    if constexpr (D == 64)  // sums that are not finite are taken again (psattn_exact.h)
+        for (AgainGroups n(not_finite_groups(dq), row0, T); n.any(); n.next())
+            st4(static_cast<uint16_t*>(a.dQ) + (static_cast<size_t>(n.row) * Hq + h) * D + n.dim(),
+                exact_dq<uint16_t, D>(a, h, n.row, n.dim(), -a.delta[static_cast<size_t>(h) * T + n.row]));
 }
 
 }  // namespace

@@ -409,5 +409,40 @@ __device__ __forceinline__ void store_block(uint16_t* base, size_t row_elems, in
     if (row + 16 < n_rows) *reinterpret_cast<uint4*>(p + 16 * row_elems) = make_uint4(c[1][0], c[1][1], c[1][2], c[1][3]);
 }
 
+// Finished sums of a wave (accumulator whose column is the lane's row) that are not all finite, as bits: group 4 db + i4
+// is head dims 32 db + 8 i4 + 4 g .. + 3.
+template <int N>
+__device__ __forceinline__ uint32_t not_finite_groups(const f32x16 (&x)[N]) {
+    uint32_t bits = 0;
+#pragma unroll
+    for (int n = 0; n < 4 * N; ++n) {
+        uint32_t top = 0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) top = max(top, __float_as_uint(x[n >> 2][4 * (n & 3) + c]) & 0x7fffffffu);
+        if (top >= 0x7f800000u) bits |= 1u << n;
+    }
+    return bits;
+}
+// Walks the groups that not_finite_groups has named: for (AgainGroups n(bits, row0, T); n.any(); n.next()), group n.dim() of
+// row n.row.  What other lanes of the wave have stored for the row may be overwritten.  Rare: row and half are found anew
+// from the lane's number, so that the kernel's loop keeps no registers for it.
+struct AgainGroups {
+    uint32_t bits;
+    int row, half;
+    __device__ __forceinline__ AgainGroups(uint32_t b, int row0, int T) : bits(b) {
+        const int l = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0));
+        row = row0 + (l & 31);
+        half = l >> 5;
+        if (row >= T) bits = 0;
+        if (__builtin_amdgcn_ballot_w64(bits != 0) != 0) __threadfence_block();
+    }
+    __device__ __forceinline__ bool any() const { return bits != 0; }
+    __device__ __forceinline__ void next() { bits &= bits - 1; }
+    __device__ __forceinline__ int dim() const {
+        const int n = __builtin_ctz(bits);
+        return 32 * (n >> 2) + 8 * (n & 3) + 4 * half;
+    }
+};
+
 }  // namespace mma
 }  // namespace psattn

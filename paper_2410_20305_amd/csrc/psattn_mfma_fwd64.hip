@@ -1,0 +1,13 @@
+// bf16 MFMA forward at head_dim 64 (psattn_mfma_fwd.h), built with NaNs honoured: inputs of any value, see psattn_exact.h.
+#include "psattn_mfma_fwd.h"
+
+namespace psattn {
+
+int launch_mfma_fwd64(const AttnArgs& a, void* stream) {
+    const unsigned grid = static_cast<unsigned>(a.meta.fwd.n_rows) * a.Hq;
+    if (grid == 0) return 0;
+    psattn_fwd_bf16_mfma<64><<<grid, 256, 0, static_cast<hipStream_t>(stream)>>>(a);
+    return static_cast<int>(hipGetLastError());
+}
+
+}  // namespace psattn

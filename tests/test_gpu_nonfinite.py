@@ -13,6 +13,7 @@ pytestmark = pytest.mark.gpu
 
 SMALL = dict(samples=[(23, 9, 14), (5, 0, 11), (20, 7, 13)], offsets=[3, 52, 70], T=125)
 TILES = dict(samples=[(150, 40, 70), (30, 90, 10), (100, 33, 65)], offsets=[5, 300, 430], T=700)
+MANY = dict(samples=[(70, 30, 28)] * 40, offsets=[5 + 130 * i for i in range(40)], T=5300)  # dK/dV rows held by one workgroup each
 # kernels: dtype, d, heads, tiles, layout
 PATHS = {
     "f32_64": ("f32", 64, 2, 1, (0, 0, 0, 0), SMALL),
@@ -20,6 +21,9 @@ PATHS = {
     "f32_two_launches": ("f32", 64, 5, 1, (0, 0, 0, 0), SMALL),
     "f32_tiles": ("f32", 64, 2, 2, (0, 0, 0, 0), TILES),
     "bf16_generic_64": ("bf16", 64, 4, 2, (7, 5, 3, 9), SMALL),
+    "bf16_64": ("bf16", 64, 4, 2, (0, 0, 0, 0), TILES),
+    "bf16_64_many": ("bf16", 64, 16, 16, (0, 0, 0, 0), MANY),
+    "bf16_64_small": ("bf16", 64, 3, 1, (0, 0, 0, 0), SMALL),
     "bf16_generic_128": ("bf16", 128, 5, 1, (32, 16, 16, 32), SMALL),
 }
 

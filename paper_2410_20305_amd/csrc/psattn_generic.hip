@@ -26,6 +26,8 @@
 // a key block is read by queries up to its largest key_hi), so the tile lists are not needed here.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "psattn_exact.h"
 
 namespace psattn {
@@ -137,12 +139,13 @@ __device__ inline f32x4 sum_partials(const Partials<D>& sm, int row, int d) {
 
 // ---------------------------------------------------------------- forward
 template <typename E, int D>
-__global__ __launch_bounds__(kThreads) void generic_fwd(AttnArgs a) {
+__global__ __launch_bounds__(kThreads) void generic_fwd(AttnArgs a, int first) {
     __shared__ Partials<D> sm;
     __shared__ float s_m[kWaves][kB], s_l[kWaves][kB];
-    const int T = a.meta.T, Hq = a.Hq, Hkv = a.Hkv, n_blocks = (T + kB - 1) / kB;
+    const int T = a.meta.T, Hq = a.Hq, Hkv = a.Hkv, n_blocks = (T - 1) / kB + 1;
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), r = tid & 15, g = (tid >> 4) & 3;
-    const int h = blockIdx.x % Hq, kvh = h / (Hq / Hkv), q0 = kB * (n_blocks - 1 - static_cast<int>(blockIdx.x) / Hq);
+    const int block = first + static_cast<int>(blockIdx.x);
+    const int h = block % Hq, kvh = h / (Hq / Hkv), q0 = kB * (n_blocks - 1 - block / Hq);
     const int q = q0 + r;
     Tok4 tk = {kPadStart, 0, 0, 0};
     if (q < T) tk = a.meta.tok[q];
@@ -205,7 +208,7 @@ __global__ __launch_bounds__(kThreads) void generic_fwd(AttnArgs a) {
 // ---------------------------------------------------------------- delta = rowsum(dO o O), dQ
 template <typename E, int D>
 __device__ inline void dq_block(const AttnArgs& a, Partials<D>& sm, int block) {
-    const int T = a.meta.T, Hq = a.Hq, Hkv = a.Hkv, n_blocks = (T + kB - 1) / kB;
+    const int T = a.meta.T, Hq = a.Hq, Hkv = a.Hkv, n_blocks = (T - 1) / kB + 1;
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), r = tid & 15, g = (tid >> 4) & 3;
     const int h = block % Hq, kvh = h / (Hq / Hkv), q0 = kB * (n_blocks - 1 - block / Hq);
     const int q = q0 + r;
@@ -329,36 +332,44 @@ __device__ inline void dkdv_block(const AttnArgs& a, Partials<D>& sm, int block)
 }
 
 template <typename E, int D>
-__global__ __launch_bounds__(kThreads) void generic_dq(AttnArgs a) {
+__global__ __launch_bounds__(kThreads) void generic_dq(AttnArgs a, int first) {
     __shared__ Partials<D> sm;
-    dq_block<E, D>(a, sm, blockIdx.x);
+    dq_block<E, D>(a, sm, first + static_cast<int>(blockIdx.x));
 }
 template <typename E, int D>
-__global__ __launch_bounds__(kThreads) void generic_dkdv(AttnArgs a) {
+__global__ __launch_bounds__(kThreads) void generic_dkdv(AttnArgs a, int first) {
     __shared__ Partials<D> sm;
-    dkdv_block<E, D, false>(a, sm, blockIdx.x);
+    dkdv_block<E, D, false>(a, sm, first + static_cast<int>(blockIdx.x));
 }
 // both at once: neither needs anything of the other
 template <typename E, int D>
-__global__ __launch_bounds__(kThreads) void generic_bwd(AttnArgs a) {
+__global__ __launch_bounds__(kThreads) void generic_bwd(AttnArgs a, int first) {
     __shared__ Partials<D> sm;
-    const int n_dkdv = (a.meta.T + kB - 1) / kB * a.Hkv;
-    if (static_cast<int>(blockIdx.x) < n_dkdv) dkdv_block<E, D, true>(a, sm, blockIdx.x);
-    else dq_block<E, D>(a, sm, blockIdx.x - n_dkdv);
+    const int block = first + static_cast<int>(blockIdx.x), n_dkdv = ((a.meta.T - 1) / kB + 1) * a.Hkv;
+    if (block < n_dkdv) dkdv_block<E, D, true>(a, sm, block);
+    else dq_block<E, D>(a, sm, block - n_dkdv);
 }
 
 }  // namespace
 
-#define PSATTN_DISPATCH(KERNEL, HEADS)                                                               \
-    do {                                                                                             \
-        hipStream_t s = static_cast<hipStream_t>(stream);                                            \
-        const unsigned grid = static_cast<unsigned>((a.meta.T + kB - 1) / kB) * (HEADS);             \
-        if (grid == 0) return 0;                                                                     \
-        if (dt == PSATTN_F32 && a.d == 64) KERNEL<float, 64><<<grid, kThreads, 0, s>>>(a);           \
-        else if (dt == PSATTN_F32 && a.d == 128) KERNEL<float, 128><<<grid, kThreads, 0, s>>>(a);    \
-        else if (dt == PSATTN_BF16 && a.d == 64) KERNEL<uint16_t, 64><<<grid, kThreads, 0, s>>>(a);  \
-        else KERNEL<uint16_t, 128><<<grid, kThreads, 0, s>>>(a);                                     \
-        return static_cast<int>(hipGetLastError());                                                  \
+// A grid of 512 threads may hold just under 2^23 workgroups (2^32 threads); more go in several launches.
+constexpr int64_t kMostGroups = int64_t{1} << 22;
+
+#define PSATTN_DISPATCH(KERNEL, HEADS)                                                                      \
+    do {                                                                                                    \
+        hipStream_t s = static_cast<hipStream_t>(stream);                                                   \
+        const int64_t groups = (static_cast<int64_t>(a.meta.T) + kB - 1) / kB * (HEADS);                    \
+        if (groups > INT32_MAX) return static_cast<int>(hipErrorInvalidConfiguration);                      \
+        for (int64_t at = 0; at < groups; at += kMostGroups) {                                              \
+            const int first = static_cast<int>(at);                                                         \
+            const unsigned grid = static_cast<unsigned>(std::min(groups - at, kMostGroups));                \
+            if (dt == PSATTN_F32 && a.d == 64) KERNEL<float, 64><<<grid, kThreads, 0, s>>>(a, first);       \
+            else if (dt == PSATTN_F32) KERNEL<float, 128><<<grid, kThreads, 0, s>>>(a, first);              \
+            else if (a.d == 64) KERNEL<uint16_t, 64><<<grid, kThreads, 0, s>>>(a, first);                   \
+            else KERNEL<uint16_t, 128><<<grid, kThreads, 0, s>>>(a, first);                                 \
+            if (const hipError_t err = hipGetLastError(); err != hipSuccess) return static_cast<int>(err);  \
+        }                                                                                                   \
+        return 0;                                                                                           \
     } while (0)
 
 int launch_generic_fwd(int dt, const AttnArgs& a, void* stream) { PSATTN_DISPATCH(generic_fwd, a.Hq); }
@@ -372,7 +383,7 @@ int launch_generic_bwd(int dt, const AttnArgs& a, void* stream) { PSATTN_DISPATC
 // 64 33.3 / 25.8 us; 450 tokens, 8 / 2 heads of 64 (290 workgroups) 83.5 / 77.3, of 128 148 / 153 (the one loss found
 // inside the rule); 4 000 tokens, 8 / 2 of 64 (2 500) 363 / 344; 8 000 (5 000) 623 / 653; 168 tokens, 32 / 1 of 64 180 / 203.
 bool generic_bwd_in_one(const AttnArgs& a) {
-    const int64_t groups = static_cast<int64_t>((a.meta.T + kB - 1) / kB) * (a.Hq + a.Hkv);
+    const int64_t groups = (static_cast<int64_t>(a.meta.T) + kB - 1) / kB * (a.Hq + a.Hkv);
     return groups <= 2560 && a.Hq <= 4 * a.Hkv;
 }
 

@@ -16,6 +16,7 @@
 // Every sum is taken in a fixed order (no atomics): results are deterministic.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstring>
 #include <new>
 #include <type_traits>
@@ -218,8 +219,8 @@ template <typename E, bool NT, int kBwdThreads>
 __global__ __launch_bounds__(kBwdThreads) void psattn_lp_bwd(const int32_t* row_desc, const int32_t* resp_first,
                                                           const int32_t* resp_len, const int32_t* samp_ptr, int vocab,
                                                           const E* logits, const int32_t* token_ids, const float* row_lse,
-                                                          const float* d_logp, E* dlogits) {
-    const int row = blockIdx.x, desc = row_desc[row];
+                                                          const float* d_logp, E* dlogits, int first) {
+    const int row = first + static_cast<int>(blockIdx.x), desc = row_desc[row];
     const E* x = logits + static_cast<size_t>(row) * vocab;
     E* g = dlogits + static_cast<size_t>(row) * vocab;
     constexpr int N = Vec<E>::N;
@@ -287,6 +288,13 @@ __global__ void psattn_dpo_loss_kernel(int n_pairs, float beta, const float* lp,
 }
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
+
+// n workgroups in grids of at most 2^31 threads (2^32 and more wrap around without an error)
+template <typename F>
+void in_grids(int32_t n, int threads, F launch) {
+    const int64_t most = (int64_t{1} << 31) / threads;
+    for (int64_t at = 0; at < n; at += most) launch(static_cast<int32_t>(at), static_cast<uint32_t>(std::min<int64_t>(n - at, most)));
+}
 
 }  // namespace
 
@@ -396,12 +404,19 @@ int psattn_logprob_fwd(const psattn_lp_plan* plan, int32_t dt, int32_t vocab, co
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     if (plan->n_rows > 0) {
         const bool nt = static_cast<size_t>(plan->n_rows) * vocab * (dt == PSATTN_BF16 ? 2 : 4) > kCacheBytes;
-        auto lse = [&](auto kernel, auto* x) { kernel<<<plan->n_rows, kThreads, 0, s>>>(plan->rows, vocab, x, row_lse); };
+        auto lse = [&](auto kernel, auto* x) {
+            in_grids(plan->n_rows, kThreads, [&](int32_t at, uint32_t n) { kernel<<<n, kThreads, 0, s>>>(plan->rows + at, vocab, x, row_lse); });
+        };
         if (dt == PSATTN_BF16) lse(nt ? psattn_lp_row_lse<uint16_t, true> : psattn_lp_row_lse<uint16_t, false>, static_cast<const uint16_t*>(logits));
         else lse(nt ? psattn_lp_row_lse<float, true> : psattn_lp_row_lse<float, false>, static_cast<const float*>(logits));
     }
-    if (dt == PSATTN_BF16) psattn_lp_resp_sum<uint16_t><<<plan->n_resp, kThreads, 0, s>>>(plan->resp_first, plan->resp_len, plan->resp_prev, vocab, static_cast<const uint16_t*>(logits), token_ids, row_lse, resp_logp);
-    else psattn_lp_resp_sum<float><<<plan->n_resp, kThreads, 0, s>>>(plan->resp_first, plan->resp_len, plan->resp_prev, vocab, static_cast<const float*>(logits), token_ids, row_lse, resp_logp);
+    auto sum = [&](auto* x) {
+        in_grids(plan->n_resp, kThreads, [&](int32_t at, uint32_t n) {
+            psattn_lp_resp_sum<<<n, kThreads, 0, s>>>(plan->resp_first + at, plan->resp_len + at, plan->resp_prev + at, vocab, x, token_ids, row_lse, resp_logp + at);
+        });
+    };
+    if (dt == PSATTN_BF16) sum(static_cast<const uint16_t*>(logits));
+    else sum(static_cast<const float*>(logits));
     return hipGetLastError() == hipSuccess ? PSATTN_OK : PSATTN_EHIP;
 }
 
@@ -416,8 +431,10 @@ int psattn_logprob_bwd(const psattn_lp_plan* plan, int32_t dt, int32_t vocab, co
     const bool nt = plan->T * row_bytes > kCacheBytes;
     auto bwd = [&](auto nontemporal, auto threads, auto* x, auto* g) {
         constexpr int n = decltype(threads)::value;
-        psattn_lp_bwd<std::remove_pointer_t<decltype(g)>, decltype(nontemporal)::value, n><<<plan->T, n, 0, s>>>(
-            plan->row_desc, plan->resp_first, plan->resp_len, plan->samp_ptr, vocab, x, token_ids, row_lse, d_resp_logp, g);
+        in_grids(plan->T, n, [&](int32_t at, uint32_t rows) {
+            psattn_lp_bwd<std::remove_pointer_t<decltype(g)>, decltype(nontemporal)::value, n><<<rows, n, 0, s>>>(
+                plan->row_desc, plan->resp_first, plan->resp_len, plan->samp_ptr, vocab, x, token_ids, row_lse, d_resp_logp, g, at);
+        });
     };
     auto typed = [&](auto* x, auto* g) {
         using Small = std::integral_constant<int, 256>;

@@ -44,3 +44,31 @@ def test_rows(dtype, vocab, x_off, g_off):
     tol = 1e-6 if dtype == "f32" else 2.0 ** -8 * np.abs(gref) + 1e-6
     assert np.all(np.isfinite(got)) and float((np.abs(got - gref) - tol).max()) <= 0
     plan.free()
+
+
+def test_more_rows_than_a_grid_of_wide_rows_holds():
+    """2^22 + 3 rows of 20 480 bytes: the gradient of the few rows that predict something, zeros everywhere else.  Logits,
+    token ids and row sums are read at predicting rows only, so they are given for the first rows alone."""
+    import torch
+    T, vocab, head = (1 << 22) + 3, 10240, 32
+    if torch.cuda.mem_get_info()[0] < 100 << 30:
+        pytest.skip("needs 100 GB of device memory")
+    off, P, ptr, rl = [2, 20], [5, 0], [0, 2, 4], [4, 3, 2, 5]
+    rng = np.random.default_rng(3)
+    logits = W.bf16_round((rng.standard_normal((head, vocab)) * 3).astype(np.float32))
+    ids = rng.integers(0, vocab, size=head).astype(np.int32)
+    d_logp = rng.standard_normal(len(rl)).astype(np.float32)
+    small, plan = ps.LogprobPlan(off, P, ptr, rl, head), ps.LogprobPlan(off, P, ptr, rl, T)
+    x, tid, dl = torch.from_numpy(logits).cuda().to(torch.bfloat16), torch.from_numpy(ids).cuda(), torch.from_numpy(d_logp).cuda()
+    row_lse, _ = ps.psattn_logprob_fwd(small, x, tid)
+    g = torch.full((T, vocab), float("nan"), dtype=torch.bfloat16, device="cuda")
+    st = ps.load_library().psattn_logprob_bwd(plan.handle, ps.BF16, vocab, x.data_ptr(), tid.data_ptr(), row_lse.data_ptr(),
+                                              dl.data_ptr(), g.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    assert st == 0
+    gref = orc.response_logprobs_grad(logits, ids, off, P, ptr, rl, d_logp.astype(np.float64))
+    got = g[:head].float().cpu().numpy().astype(np.float64)
+    assert float((np.abs(got - gref) - 2.0 ** -8 * np.abs(gref)).max()) <= 1e-6
+    for t in range(head, T, 1 << 17):
+        assert int(torch.count_nonzero(g[t:t + (1 << 17)].view(torch.int16))) == 0, t
+    small.free()
+    plan.free()

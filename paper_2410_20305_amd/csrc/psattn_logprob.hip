@@ -43,11 +43,12 @@ namespace {
 
 constexpr int kThreads = 256;
 
-// The gradient writes far more than it reads, and of long rows fewer open at a time suit the memory: 256 / 512 / 1024
-// threads per row 957 / 941 / 923 us (non-temporal stores 965 / - / 884 us) on 65 536 rows of 32 000 bf16.  Short rows leave
-// most of 1024 threads without work: whole head, 46 000 rows, 256 / 1024 threads, 1 000 bf16 103 / 230 us, 8 000
-// (16 000 bytes) 335 / 380, 11 000 (22 000 bytes) 501 / 500, 16 000 723 / 662; 33 600 rows of 11 000 222 / 190.
-constexpr size_t kWideRowBytes = 20480;
+// Threads per row of the gradient, which writes far more than it reads: of long rows fewer open at a time suit the memory,
+// short ones leave most of many threads without work.  Whole head, 256 / 512 / 1024 threads, 46 000 rows, of which 39 900
+// have a target: 5 000 bf16 (10 000 bytes) 230 / 225 / 261 us, 8 000 349 / 323 / 349, 9 600 405 / 375 / 405, 11 000 501 / - /
+// 461, 16 000 723 / - / 640; 33 600 rows with 9 600 targets: 5 000 100 / 95 / 92, 8 000 133 / 126 / 156, 11 000 222 / - / 189.
+// On 65 536 rows of 32 000 the gradient alone 957 / 941 / 923 (non-temporal stores 965 / - / 884).
+constexpr size_t kMidRowBytes = 8192, kWideRowBytes = 20480;  // 512 threads, 1024 threads
 constexpr int kUnroll = 4;  // 16-byte loads in flight per lane of the log-sum-exp
 // Non-temporal accesses where the data is larger than the 256 MB last-level cache, so that the pass that follows could
 // not find it there anyway (reading 4 GB alone: 6.3 -> 7.1 TB/s).
@@ -102,9 +103,11 @@ __device__ inline void store_vec(E* p, const float* x) {
 struct RowSplit {
     int head, n_vec, tail;  // tail: index of the first element behind the groups
 };
-template <typename E>
+// WHOLE: every row starts on a boundary and is a whole number of groups (the host has looked)
+template <bool WHOLE, typename E>
 __device__ inline RowSplit split_row(const E* x, int vocab) {
     constexpr int N = Vec<E>::N;
+    if constexpr (WHOLE) return RowSplit{0, vocab / N, vocab};
     const int mis = static_cast<int>(reinterpret_cast<uintptr_t>(x) / sizeof(E)) & (N - 1);
     RowSplit r;
     r.head = min(vocab, (N - mis) & (N - 1));
@@ -147,13 +150,13 @@ __device__ inline float block_sum(float v, float* sm) {
 }
 
 // ---- pass 1: log-sum-exp of every row that predicts something
-template <typename E, bool NT>
+template <typename E, bool NT, bool WHOLE>
 __global__ __launch_bounds__(kThreads) void psattn_lp_row_lse(const int32_t* rows, int vocab, const E* logits, float* row_lse) {
     __shared__ float sm[kThreads / 64], ss[kThreads / 64];
     const int row = rows[blockIdx.x];
     const E* x = logits + static_cast<size_t>(row) * vocab;
     constexpr int N = Vec<E>::N;
-    const RowSplit r = split_row(x, vocab);
+    const RowSplit r = split_row<WHOLE>(x, vocab);
     const E* xv = x + r.head;
     float m = -INFINITY, s = 0.f;
     auto groups = [&](auto COUNT, int c) {  // groups c, c + kThreads, ...
@@ -189,8 +192,10 @@ __global__ __launch_bounds__(kThreads) void psattn_lp_row_lse(const int32_t* row
         s = s * __expf(m - ref) + __expf(v - ref);
         m = mx;
     };
-    if (static_cast<int>(threadIdx.x) < r.head) one(threadIdx.x);
-    for (int i = r.tail + threadIdx.x; i < vocab; i += kThreads) one(i);
+    if constexpr (!WHOLE) {
+        if (static_cast<int>(threadIdx.x) < r.head) one(threadIdx.x);
+        for (int i = r.tail + threadIdx.x; i < vocab; i += kThreads) one(i);
+    }
     block_lse(m, s, sm, ss);
     if (threadIdx.x == 0) row_lse[row] = m + __logf(s);
 }
@@ -215,7 +220,7 @@ __global__ __launch_bounds__(kThreads) void psattn_lp_resp_sum(const int32_t* re
 }
 
 // ---- backward: d logits = sum over the row's items of d_logp[j] (onehot(target) - softmax(row))
-template <typename E, bool NT, int kBwdThreads>
+template <typename E, bool NT, bool WHOLE, int kBwdThreads>
 __global__ __launch_bounds__(kBwdThreads) void psattn_lp_bwd(const int32_t* row_desc, const int32_t* resp_first,
                                                           const int32_t* resp_len, const int32_t* samp_ptr, int vocab,
                                                           const E* logits, const int32_t* token_ids, const float* row_lse,
@@ -224,14 +229,16 @@ __global__ __launch_bounds__(kBwdThreads) void psattn_lp_bwd(const int32_t* row_
     const E* x = logits + static_cast<size_t>(row) * vocab;
     E* g = dlogits + static_cast<size_t>(row) * vocab;
     constexpr int N = Vec<E>::N;
-    RowSplit sp = split_row(g, vocab);
+    RowSplit sp = split_row<WHOLE>(g, vocab);
     if (desc == -1) {  // predicts nothing: the row of the gradient is zero, the logits are not read
         float z[N];
 #pragma unroll
         for (int j = 0; j < N; ++j) z[j] = 0.f;
         for (int c = threadIdx.x; c < sp.n_vec; c += kBwdThreads) store_vec<NT>(g + sp.head + static_cast<size_t>(c) * N, z);
-        if (static_cast<int>(threadIdx.x) < sp.head) st1(g + threadIdx.x, 0.f);
-        for (int i = sp.tail + threadIdx.x; i < vocab; i += kBwdThreads) st1(g + i, 0.f);
+        if constexpr (!WHOLE) {
+            if (static_cast<int>(threadIdx.x) < sp.head) st1(g + threadIdx.x, 0.f);
+            for (int i = sp.tail + threadIdx.x; i < vocab; i += kBwdThreads) st1(g + i, 0.f);
+        }
         return;
     }
     // total weight of the row's items
@@ -245,11 +252,16 @@ __global__ __launch_bounds__(kBwdThreads) void psattn_lp_bwd(const int32_t* row_
         const int t = desc >= 0 ? token_ids[row + 1] : token_ids[resp_first[j]];
         return t >= 0 && t < vocab ? t : -1;
     };
+    const int only = desc >= 0 ? target(r0) : -1;  // rows inside a response have one item
     float coef = 0.f;
-    for (int j = r0; j < r1; ++j)
-        if (target(j) >= 0) coef += d_logp[j];
+    if (desc >= 0) {
+        if (only >= 0) coef = d_logp[r0];
+    } else {
+        for (int j = r0; j < r1; ++j)
+            if (target(j) >= 0) coef += d_logp[j];
+    }
     const float lse = row_lse[row];
-    if ((reinterpret_cast<uintptr_t>(x) ^ reinterpret_cast<uintptr_t>(g)) & 15) sp = {0, 0, 0};  // the two rows share no 16-byte boundaries
+    if (!WHOLE && (reinterpret_cast<uintptr_t>(x) ^ reinterpret_cast<uintptr_t>(g)) & 15) sp = {0, 0, 0};  // the two rows share no 16-byte boundaries
     const E* xv = x + sp.head;
     E* gv = g + sp.head;
     auto grad = [&](float v) { return -coef * __expf(v - lse); };
@@ -260,15 +272,23 @@ __global__ __launch_bounds__(kBwdThreads) void psattn_lp_bwd(const int32_t* row_
         for (int k = 0; k < N; ++k) v[k] = grad(v[k]);
         store_vec<NT>(gv + static_cast<size_t>(c) * N, v);
     }
-    if (static_cast<int>(threadIdx.x) < sp.head) st1(g + threadIdx.x, grad(ld1(x + threadIdx.x)));
-    for (int i = sp.tail + threadIdx.x; i < vocab; i += kBwdThreads) st1(g + i, grad(ld1(x + i)));
+    if constexpr (!WHOLE) {
+        if (static_cast<int>(threadIdx.x) < sp.head) st1(g + threadIdx.x, grad(ld1(x + threadIdx.x)));
+        for (int i = sp.tail + threadIdx.x; i < vocab; i += kBwdThreads) st1(g + i, grad(ld1(x + i)));
+    }
     // the target columns: each is recomputed whole by the thread that has just stored it, so it is rounded once and two
     // responses that start with the same token add up
+    const auto mine = [&](int tgt) {
+        const int owner = tgt < sp.head ? tgt : tgt < sp.tail ? (tgt - sp.head) / N : tgt - sp.tail;
+        return owner % kBwdThreads == static_cast<int>(threadIdx.x);
+    };
+    if (desc >= 0) {  // without reading the tables again, which would keep every wave of a short row waiting
+        if (only >= 0 && mine(only)) st1(g + only, grad(ld1(x + only)) + coef);
+        return;
+    }
     for (int j = r0; j < r1; ++j) {
         const int tgt = target(j);
-        if (tgt < 0) continue;
-        const int owner = tgt < sp.head ? tgt : tgt < sp.tail ? (tgt - sp.head) / N : tgt - sp.tail;
-        if (owner % kBwdThreads != static_cast<int>(threadIdx.x)) continue;
+        if (tgt < 0 || !mine(tgt)) continue;
         float v = grad(ld1(x + tgt));
         for (int k = r0; k < r1; ++k)
             if (target(k) == tgt) v += d_logp[k];
@@ -288,6 +308,12 @@ __global__ void psattn_dpo_loss_kernel(int n_pairs, float beta, const float* lp,
 }
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
+
+// All rows start on a 16-byte boundary and are whole numbers of 16 bytes.  Rows of a few KB spend a noticeable part of their
+// time on finding that out one by one: 46 000 rows of 512 bf16 66.5 us, by the general path 71.1.
+bool whole_rows(int32_t dt, int32_t vocab, const void* x) {
+    return reinterpret_cast<uintptr_t>(x) % 16 == 0 && vocab % (dt == PSATTN_BF16 ? 8 : 4) == 0;
+}
 
 // n workgroups in grids of at most 2^31 threads (2^32 and more wrap around without an error)
 template <typename F>
@@ -407,8 +433,14 @@ int psattn_logprob_fwd(const psattn_lp_plan* plan, int32_t dt, int32_t vocab, co
         auto lse = [&](auto kernel, auto* x) {
             in_grids(plan->n_rows, kThreads, [&](int32_t at, uint32_t n) { kernel<<<n, kThreads, 0, s>>>(plan->rows + at, vocab, x, row_lse); });
         };
-        if (dt == PSATTN_BF16) lse(nt ? psattn_lp_row_lse<uint16_t, true> : psattn_lp_row_lse<uint16_t, false>, static_cast<const uint16_t*>(logits));
-        else lse(nt ? psattn_lp_row_lse<float, true> : psattn_lp_row_lse<float, false>, static_cast<const float*>(logits));
+        const bool whole = whole_rows(dt, vocab, logits);
+        auto typed = [&](auto* x) {
+            using E = std::remove_const_t<std::remove_pointer_t<decltype(x)>>;
+            if (nt) lse(whole ? psattn_lp_row_lse<E, true, true> : psattn_lp_row_lse<E, true, false>, x);
+            else lse(whole ? psattn_lp_row_lse<E, false, true> : psattn_lp_row_lse<E, false, false>, x);
+        };
+        if (dt == PSATTN_BF16) typed(static_cast<const uint16_t*>(logits));
+        else typed(static_cast<const float*>(logits));
     }
     auto sum = [&](auto* x) {
         in_grids(plan->n_resp, kThreads, [&](int32_t at, uint32_t n) {
@@ -427,22 +459,25 @@ int psattn_logprob_bwd(const psattn_lp_plan* plan, int32_t dt, int32_t vocab, co
     if (!logits || !token_ids || !row_lse || !dlogits || (plan->n_resp > 0 && !d_resp_logp)) return PSATTN_EINVAL;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const size_t row_bytes = static_cast<size_t>(vocab) * (dt == PSATTN_BF16 ? 2 : 4);
-    const bool wide = row_bytes >= kWideRowBytes;
     const bool nt = plan->T * row_bytes > kCacheBytes;
-    auto bwd = [&](auto nontemporal, auto threads, auto* x, auto* g) {
+    const bool whole = whole_rows(dt, vocab, logits) && whole_rows(dt, vocab, dlogits);
+    auto bwd = [&](auto nontemporal, auto whole_, auto threads, auto* x, auto* g) {
         constexpr int n = decltype(threads)::value;
         in_grids(plan->T, n, [&](int32_t at, uint32_t rows) {
-            psattn_lp_bwd<std::remove_pointer_t<decltype(g)>, decltype(nontemporal)::value, n><<<rows, n, 0, s>>>(
+            psattn_lp_bwd<std::remove_pointer_t<decltype(g)>, decltype(nontemporal)::value, decltype(whole_)::value, n><<<rows, n, 0, s>>>(
                 plan->row_desc, plan->resp_first, plan->resp_len, plan->samp_ptr, vocab, x, token_ids, row_lse, d_resp_logp, g, at);
         });
     };
     auto typed = [&](auto* x, auto* g) {
-        using Small = std::integral_constant<int, 256>;
-        using Large = std::integral_constant<int, 1024>;
-        if (nt && wide) bwd(std::true_type{}, Large{}, x, g);
-        else if (nt) bwd(std::true_type{}, Small{}, x, g);
-        else if (wide) bwd(std::false_type{}, Large{}, x, g);
-        else bwd(std::false_type{}, Small{}, x, g);
+        auto sized = [&](auto nontemporal, auto whole_) {
+            if (row_bytes >= kWideRowBytes) bwd(nontemporal, whole_, std::integral_constant<int, 1024>{}, x, g);
+            else if (row_bytes >= kMidRowBytes) bwd(nontemporal, whole_, std::integral_constant<int, 512>{}, x, g);
+            else bwd(nontemporal, whole_, std::integral_constant<int, 256>{}, x, g);
+        };
+        if (nt && whole) sized(std::true_type{}, std::true_type{});
+        else if (nt) sized(std::true_type{}, std::false_type{});
+        else if (whole) sized(std::false_type{}, std::true_type{});
+        else sized(std::false_type{}, std::false_type{});
     };
     if (dt == PSATTN_BF16) typed(static_cast<const uint16_t*>(logits), static_cast<uint16_t*>(dlogits));
     else typed(static_cast<const float*>(logits), static_cast<float*>(dlogits));

@@ -46,6 +46,13 @@ def test_rows(dtype, vocab, x_off, g_off):
     plan.free()
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("vocab", [8, 16, 2048, 4096, 5120, 10240, 16392])
+def test_whole_rows(dtype, vocab):
+    """Rows that start on a boundary and are whole numbers of 16 bytes, on either side of the thread counts' lines."""
+    test_rows(dtype, vocab, 0, 0)
+
+
 def test_more_rows_than_a_grid_of_wide_rows_holds():
     """2^22 + 3 rows of 20 480 bytes: the gradient of the few rows that predict something, zeros everywhere else.  Logits,
     token ids and row sums are read at predicting rows only, so they are given for the first rows alone."""

@@ -42,6 +42,9 @@
  *     finite, at padding positions too: its matrix-core kernels multiply them by exact
  *     zeros, and 0 * inf or 0 * NaN would reach other tokens of the same tile.  Every
  *     other call takes any value: inf and NaN reach the rows that read them and no others.
+ *   - an output may not overlap an input or another output, with these exceptions, where it
+ *     takes exactly that tensor's memory: O that of Q in psattn_fwd, dQ that of O, dK that of
+ *     K and dV that of V in psattn_bwd and psattn_bwd_static.
  */
 #ifndef PSATTN_H
 #define PSATTN_H

@@ -296,7 +296,17 @@ int bwd_checked(const psattn_meta* meta, int32_t dt, int32_t n_q_heads, int32_t 
     int err = 0;
     const bool mfma = mfma_bwd_ok(meta, dt, head_dim, scale);
     if (rope_table && !(mfma && head_dim == 128)) return PSATTN_EUNSUPPORTED;  // rotary embedding lives in these matrix-core kernels only
-    if (!mfma && !g_profile && generic_bwd_in_one(a)) {  // (profiling times the passes one by one)
+    // One launch reads Q, K, V, O and dO while the gradients are being written, two read O in the first and of K and V only
+    // the workgroup's own rows in the second: a gradient that takes the memory of O, K or V needs them.
+    const size_t e = dt == PSATTN_F32 ? 4 : 2, q_bytes = e * meta->T * n_q_heads * head_dim, kv_bytes = e * meta->T * n_kv_heads * head_dim;
+    const auto apart = [&](const void* out, size_t n) {
+        const auto from = [&](const void* in, size_t m) {
+            const uintptr_t x = reinterpret_cast<uintptr_t>(out), y = reinterpret_cast<uintptr_t>(in);
+            return x + n <= y || y + m <= x;
+        };
+        return from(Q, q_bytes) && from(O, q_bytes) && from(dO, q_bytes) && from(K, kv_bytes) && from(V, kv_bytes);
+    };
+    if (!mfma && !g_profile && generic_bwd_in_one(a) && apart(dQ, q_bytes) && apart(dK, kv_bytes) && apart(dV, kv_bytes)) {  // (profiling times the passes one by one)
         g_last_kernel[1] = g_last_kernel[2] = g_last_kernel[3] = "generic_bwd";
         return launch_generic_bwd(dt, a, hip_stream) == 0 ? PSATTN_OK : PSATTN_EHIP;
     }

@@ -185,24 +185,25 @@ __global__ __launch_bounds__(kThreads) void generic_fwd(AttnArgs a, int first) {
     if (g == 0) { s_m[w][r] = m; s_l[w][r] = l; }
     __syncthreads();
     int row, d;
-    if (!my_quad<D>(tid, row, d) || q0 + row >= T) return;
-    float mt = s_m[0][row];
-#pragma unroll
-    for (int i = 1; i < kWaves; ++i) mt = fmaxf(mt, s_m[i][row]);
-    const float ref = mt == -INFINITY ? 0.f : mt;
-    float lt = 0.f;
+    const bool mine = my_quad<D>(tid, row, d) && q0 + row < T;
     f32x4 o = {0.f, 0.f, 0.f, 0.f};
+    if (mine) {
+        float mt = s_m[0][row], lt = 0.f;
 #pragma unroll
-    for (int i = 0; i < kWaves; ++i) {
-        const float f = expf(s_m[i][row] - ref);
-        lt = fmaf(s_l[i][row], f, lt);
-        o += *reinterpret_cast<const f32x4*>(&sm.v[i][row][d]) * f;
+        for (int i = 1; i < kWaves; ++i) mt = fmaxf(mt, s_m[i][row]);
+        const float ref = mt == -INFINITY ? 0.f : mt;
+#pragma unroll
+        for (int i = 0; i < kWaves; ++i) {
+            const float f = expf(s_m[i][row] - ref);
+            lt = fmaf(s_l[i][row], f, lt);
+            o += *reinterpret_cast<const f32x4*>(&sm.v[i][row][d]) * f;
+        }
+        o *= lt > 0.f ? 1.f / lt : 0.f;
+        if (!is_finite(o) || !(lt > 0.f)) o = exact_o<E, D>(a, h, q0 + row, d);  // (no sum: padding, or scores of -inf alone)
+        if (d == 0) a.LSEout[static_cast<size_t>(h) * T + q0 + row] = lt > 0.f ? mt + logf(lt) : -INFINITY;
     }
-    const float inv = lt > 0.f ? 1.f / lt : 0.f;
-    o *= inv;
-    if (!is_finite(o) || !(lt > 0.f)) o = exact_o<E, D>(a, h, q0 + row, d);  // (no sum: padding, or scores of -inf alone)
-    st4(static_cast<E*>(a.Oout) + (static_cast<size_t>(q0 + row) * Hq + h) * D + d, o);
-    if (d == 0) a.LSEout[static_cast<size_t>(h) * T + q0 + row] = lt > 0.f ? mt + logf(lt) : -INFINITY;
+    __syncthreads();  // nobody reads Q any more: O may take its memory
+    if (mine) st4(static_cast<E*>(a.Oout) + (static_cast<size_t>(q0 + row) * Hq + h) * D + d, o);
 }
 
 // ---------------------------------------------------------------- delta = rowsum(dO o O), dQ
@@ -314,20 +315,22 @@ __device__ inline void dkdv_block(const AttnArgs& a, Partials<D>& sm, int block)
     int row, d;
     const bool mine = my_quad<D>(tid, row, d) && k0 + row < T;
     const size_t at = (static_cast<size_t>(k0 + row) * Hkv + kvh) * D + d;
+    f32x4 xk = {0.f, 0.f, 0.f, 0.f}, xv = xk;
     put_partial<D>(sm, dk, w, r, g);
     __syncthreads();
-    if (mine) {
-        f32x4 x = sum_partials<D>(sm, row, d) * a.scale;
-        if (!is_finite(x)) x = exact_dkdv<E, D, true, OWN_DELTA ? 0 : 1>(a, kvh, k0 + row, d);
-        st4(static_cast<E*>(a.dK) + at, x);
-    }
+    if (mine) xk = sum_partials<D>(sm, row, d) * a.scale;
     __syncthreads();
     put_partial<D>(sm, dv, w, r, g);
     __syncthreads();
     if (mine) {
-        f32x4 x = sum_partials<D>(sm, row, d);
-        if (!is_finite(x)) x = exact_dkdv<E, D, false, OWN_DELTA ? 0 : 1>(a, kvh, k0 + row, d);
-        st4(static_cast<E*>(a.dV) + at, x);
+        xv = sum_partials<D>(sm, row, d);
+        if (!is_finite(xk)) xk = exact_dkdv<E, D, true, OWN_DELTA ? 0 : 1>(a, kvh, k0 + row, d);
+        if (!is_finite(xv)) xv = exact_dkdv<E, D, false, OWN_DELTA ? 0 : 1>(a, kvh, k0 + row, d);
+    }
+    __syncthreads();  // nobody reads K and V any more: dK and dV may take their memory
+    if (mine) {
+        st4(static_cast<E*>(a.dK) + at, xk);
+        st4(static_cast<E*>(a.dV) + at, xv);
     }
 }
 

@@ -1,5 +1,4 @@
 // bf16 MFMA backward (dQ; dK/dV) kernels for gfx950; layout and staging helpers are in psattn_mfma_common.h.
-#include "psattn_exact.h"
 #include "psattn_mfma_common.h"
 
 namespace psattn {
@@ -229,12 +228,13 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_dq_bf16_mfma(Att
     }
     const int row0 = qt * 128 + 32 * w;
     uint16_t* rows = static_cast<uint16_t*>(a.dQ) + (static_cast<size_t>(row0) * Hq + h) * D;
-#pragma unroll
-    for (int db = 0; db < kBlocks; ++db) store_block(rows, static_cast<size_t>(Hq) * D, T - row0, db, dq[db], a.scale, l);
-    if constexpr (D == 64)  // sums that are not finite are taken again (psattn_exact.h)
+    if constexpr (D == 64) {  // sums that are not finite are taken again (psattn_exact.h)
+        multiply(dq, a.scale);
         for (AgainGroups n(not_finite_groups(dq), row0, T); n.any(); n.next())
-            st4(static_cast<uint16_t*>(a.dQ) + (static_cast<size_t>(n.row) * Hq + h) * D + n.dim(),
-                exact_dq<uint16_t, D>(a, h, n.row, n.dim(), -a.delta[static_cast<size_t>(h) * T + n.row]));
+            set_group(dq, n.group(), exact_dq<uint16_t, D>(a, h, n.row, n.dim(), -a.delta[static_cast<size_t>(h) * T + n.row]));
+    }
+#pragma unroll
+    for (int db = 0; db < kBlocks; ++db) store_block(rows, static_cast<size_t>(Hq) * D, T - row0, db, dq[db], D == 64 ? 1.f : a.scale, l);
 }
 
 }  // namespace

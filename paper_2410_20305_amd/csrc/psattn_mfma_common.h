@@ -26,7 +26,7 @@
 
 #include <type_traits>
 
-#include "psattn_internal.h"
+#include "psattn_exact.h"
 
 namespace psattn {
 namespace mma {
@@ -423,10 +423,16 @@ __device__ __forceinline__ uint32_t not_finite_groups(const f32x16 (&x)[N]) {
     }
     return bits;
 }
-// Walks the groups that not_finite_groups has named: for (AgainGroups n(bits, row0, T); n.any(); n.next()), group n.dim() of
-// row n.row.  What other lanes of the wave have stored for the row may be overwritten.  Rare: row and half are found anew
-// from the lane's number, so that the kernel's loop keeps no registers for it.
-struct AgainGroups {
+template <int N>
+__device__ __forceinline__ void set_group(f32x16 (&x)[N], int n, const f32x4& v) {
+#pragma unroll
+    for (int m = 0; m < 4 * N; ++m)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) x[m >> 2][4 * (m & 3) + c] = m == n ? v[c] : x[m >> 2][4 * (m & 3) + c];
+}
+// Walks the groups that not_finite_groups has named, of the rows [row0, row0 + 32) below T.  Rare: row and half are found
+// anew from the lane's number, so that the kernel's loop keeps no registers for it.
+struct AgainGroups {  // for (AgainGroups n(bits, row0, T); n.any(); n.next()): group n.group(), head dims n.dim() .. + 3 of row n.row
     uint32_t bits;
     int row, half;
     __device__ __forceinline__ AgainGroups(uint32_t b, int row0, int T) : bits(b) {
@@ -434,15 +440,19 @@ struct AgainGroups {
         row = row0 + (l & 31);
         half = l >> 5;
         if (row >= T) bits = 0;
-        if (__builtin_amdgcn_ballot_w64(bits != 0) != 0) __threadfence_block();
     }
     __device__ __forceinline__ bool any() const { return bits != 0; }
     __device__ __forceinline__ void next() { bits &= bits - 1; }
-    __device__ __forceinline__ int dim() const {
-        const int n = __builtin_ctz(bits);
-        return 32 * (n >> 2) + 8 * (n & 3) + 4 * half;
-    }
+    __device__ __forceinline__ int group() const { return __builtin_ctz(bits); }
+    __device__ __forceinline__ int dim() const { return 32 * (group() >> 2) + 8 * (group() & 3) + 4 * half; }
 };
+template <int N>
+__device__ __forceinline__ void multiply(f32x16 (&x)[N], float factor) {
+#pragma unroll
+    for (int db = 0; db < N; ++db)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) x[db][i] *= factor;
+}
 
 }  // namespace mma
 }  // namespace psattn

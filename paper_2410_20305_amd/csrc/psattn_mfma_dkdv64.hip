@@ -9,7 +9,6 @@
 // matrix pipeline; P and dS enter as three operands each, see make_operand) and about 515 vector instructions.  Measured
 // on a step of 8 samples, 4 758 tokens, 32 q / 8 kv heads: forward + dQ + dK/dV 14.9 ms on one thread per row, 0.18 ms on
 // these.
-#include "psattn_exact.h"
 #include "psattn_mfma_common.h"
 
 namespace psattn {
@@ -254,18 +253,20 @@ __global__ __launch_bounds__(256, 2) void psattn_dkdv64_bf16_mfma(AttnArgs a) {
         __syncthreads();
         if (group) take(dk); else take(dv);
     }
+    // sums that are not finite are taken again (psattn_exact.h), before anything is stored: dK and dV may take K's and V's memory
+    multiply(dk, a.scale);
+    if (S == 1 || group == 0)
+        for (AgainGroups n(not_finite_groups(dv), row0, T); n.any(); n.next())
+            set_group(dv, n.group(), exact_dkdv<uint16_t, 64, false, -1>(a, kvh, n.row, n.dim()));
+    if (S == 1 || group == 1)
+        for (AgainGroups n(not_finite_groups(dk), row0, T); n.any(); n.next())
+            set_group(dk, n.group(), exact_dkdv<uint16_t, 64, true, -1>(a, kvh, n.row, n.dim()));
+    if constexpr (S > 1) __syncthreads();
 #pragma unroll
     for (int db = 0; db < 2; ++db) {
         if (S == 1 || group == 0) store_block(static_cast<uint16_t*>(a.dV) + out0, row_elems, T - row0, db, dv[db], 1.f, l);
-        if (S == 1 || group == 1) store_block(static_cast<uint16_t*>(a.dK) + out0, row_elems, T - row0, db, dk[db], a.scale, l);
+        if (S == 1 || group == 1) store_block(static_cast<uint16_t*>(a.dK) + out0, row_elems, T - row0, db, dk[db], 1.f, l);
     }
-    // sums that are not finite are taken again (psattn_exact.h)
-    if (S == 1 || group == 0)
-        for (AgainGroups n(not_finite_groups(dv), row0, T); n.any(); n.next())
-            st4(static_cast<uint16_t*>(a.dV) + (static_cast<size_t>(n.row) * Hkv + kvh) * 64 + n.dim(), exact_dkdv<uint16_t, 64, false, -1>(a, kvh, n.row, n.dim()));
-    if (S == 1 || group == 1)
-        for (AgainGroups n(not_finite_groups(dk), row0, T); n.any(); n.next())
-            st4(static_cast<uint16_t*>(a.dK) + (static_cast<size_t>(n.row) * Hkv + kvh) * 64 + n.dim(), exact_dkdv<uint16_t, 64, true, -1>(a, kvh, n.row, n.dim()));
 }
 
 }  // namespace

@@ -1,7 +1,6 @@
 // bf16 MFMA forward kernel for gfx950; layout and staging helpers are in psattn_mfma_common.h.  Built once per head_dim:
 // psattn_mfma_fwd.hip (128) and psattn_mfma_fwd64.hip (64).
 #pragma once
-#include "psattn_exact.h"
 #include "psattn_mfma_common.h"
 
 namespace psattn {
@@ -221,15 +220,15 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(At
     const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
     const int row0 = qt * 128 + 32 * w;
     uint16_t* orow = static_cast<uint16_t*>(a.Oout) + (static_cast<size_t>(row0) * Hq + h) * D;
-#pragma unroll
-    for (int db = 0; db < kBlocks; ++db) store_block(orow, static_cast<size_t>(Hq) * D, T - row0, db, o[db], inv, l);
+    multiply(o, inv);
     if constexpr (D == 64) {
         // sums that are not finite, and rows without a sum, are taken again (psattn_exact.h)
         uint32_t again = not_finite_groups(o);
         if (!(l_tot > 0.f) && tk.s != kPadStart) again = 0xff;
-        for (AgainGroups n(again, row0, T); n.any(); n.next())
-            st4(static_cast<uint16_t*>(a.Oout) + (static_cast<size_t>(n.row) * Hq + h) * D + n.dim(), exact_o<uint16_t, D>(a, h, n.row, n.dim()));
+        for (AgainGroups n(again, row0, T); n.any(); n.next()) set_group(o, n.group(), exact_o<uint16_t, D>(a, h, n.row, n.dim()));
     }
+#pragma unroll
+    for (int db = 0; db < kBlocks; ++db) store_block(orow, static_cast<size_t>(Hq) * D, T - row0, db, o[db], 1.f, l);
     if (valid && g == 0)
         a.LSEout[static_cast<size_t>(h) * T + q_row] = l_tot > 0.f ? m * kLn2 + __logf(l_tot) : -INFINITY;
 }

@@ -24,8 +24,6 @@ struct BlobLayout {
     size_t seg_start, seg_tok, block_first, staged;   // host
 };
 
-int32_t upload_blocks(const psattn_meta& m) { return (m.T + kUploadTokens - 1) / kUploadTokens; }
-
 BlobLayout layout_of(const psattn_meta& m) {
     BlobLayout L{};
     size_t off = 0;
@@ -37,7 +35,7 @@ BlobLayout layout_of(const psattn_meta& m) {
     L.lists = off;
     L.seg_start = take(sizeof(int32_t) * m.seg_start.size());
     L.seg_tok = take(sizeof(Tok4) * m.seg_tok.size());
-    L.block_first = take(sizeof(int32_t) * (upload_blocks(m) + 1));
+    L.block_first = take(sizeof(int32_t) * (upload_blocks(m.T) + 1));
     L.staged = off;
     L.tok = align_up(sizeof(Tok4) * static_cast<size_t>(m.T), 256);
     return L;
@@ -166,7 +164,7 @@ int upload(psattn_meta* m, hipStream_t stream) {
     char* h = static_cast<char*>(m->h_stage);
     fill_csr(h, L.f_ent, L.f_lch, m->fwd, false);
     fill_csr(h, L.b_ent, L.b_lch, m->bwd, true);
-    const int32_t n_seg = static_cast<int32_t>(m->seg_tok.size()), n_blocks = upload_blocks(*m);
+    const int32_t n_seg = static_cast<int32_t>(m->seg_tok.size()), n_blocks = upload_blocks(m->T);
     std::memcpy(h + L.seg_start, m->seg_start.data(), m->seg_start.size() * sizeof(int32_t));
     if (n_seg > 0) std::memcpy(h + L.seg_tok, m->seg_tok.data(), m->seg_tok.size() * sizeof(Tok4));
     int32_t* first = reinterpret_cast<int32_t*>(h + L.block_first);

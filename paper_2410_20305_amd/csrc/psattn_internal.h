@@ -140,6 +140,7 @@ struct UploadArgs {
     int32_t n_units;
 };
 constexpr int32_t kUploadTokens = 1024;
+constexpr int32_t upload_blocks(int32_t T) { return static_cast<int32_t>((int64_t{T} + kUploadTokens - 1) / kUploadTokens); }
 int launch_upload(const UploadArgs& a, void* stream);
 
 // Launchers (each returns a hipError_t cast to int; 0 = success).

@@ -19,8 +19,8 @@ constexpr int kMostRuns = kUploadTokens + 1;  // runs that can touch one block's
 __global__ __launch_bounds__(kThreads) void psattn_meta_upload(UploadArgs a, int tok_blocks) {
     const int tid = threadIdx.x, b = blockIdx.x;
     if (b >= tok_blocks) {
-        const int i = (b - tok_blocks) * kThreads + tid;
-        if (i < a.n_units) a.dst[i] = a.src[i];
+        const uint32_t i = static_cast<uint32_t>(b - tok_blocks) * kThreads + tid;
+        if (i < static_cast<uint32_t>(a.n_units)) a.dst[i] = a.src[i];
         return;
     }
     __shared__ int s_start[kMostRuns];
@@ -52,7 +52,7 @@ __global__ __launch_bounds__(kThreads) void psattn_meta_upload(UploadArgs a, int
 }  // namespace
 
 int launch_upload(const UploadArgs& a, void* stream) {
-    const int tok_blocks = (a.T + kUploadTokens - 1) / kUploadTokens, list_blocks = (a.n_units + kThreads - 1) / kThreads;
+    const int tok_blocks = upload_blocks(a.T), list_blocks = static_cast<int>((int64_t{a.n_units} + kThreads - 1) / kThreads);
     if (tok_blocks + list_blocks == 0) return 0;
     psattn_meta_upload<<<tok_blocks + list_blocks, kThreads, 0, static_cast<hipStream_t>(stream)>>>(a, tok_blocks);
     return static_cast<int>(hipGetLastError());

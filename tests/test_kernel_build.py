@@ -8,6 +8,7 @@ kernels (a spill there costs scratch traffic in the hot loop).
 """
 import os
 import re
+import subprocess
 
 import pytest
 
@@ -111,3 +112,17 @@ def test_dkdv64_two_waves_per_simd_without_spills(tmp_path):
     assert int(meta["private_segment_fixed_size"]) == 0
     for code in _outside_asm(text):
         assert not re.search(r"\bm0\b", code), code
+
+
+def test_upload_blocks_up_to_the_largest_buffer(tmp_path):
+    """Workgroups that expand the token descriptors, for every T that total_tokens can name: rounding up must not leave int32,
+    and the last workgroup's token numbers (1024 per workgroup) must not either."""
+    src = tmp_path / "blocks.hip"
+    src.write_text("""#include "psattn_internal.h"
+using namespace psattn;
+static_assert(upload_blocks(0) == 0 && upload_blocks(1) == 1 && upload_blocks(1024) == 1 && upload_blocks(1025) == 2, "");
+static_assert(upload_blocks(INT32_MAX) == 1 << 21 && upload_blocks(INT32_MAX - 1023) == (1 << 21) - 1, "");
+static_assert(int64_t{upload_blocks(INT32_MAX)} * kUploadTokens - 1 == INT32_MAX, "");
+""")
+    subprocess.check_call([build.hipcc(), "--offload-arch=gfx950", "-std=c++17", "-x", "hip", "-fsyntax-only", "-w", "-I",
+                           os.path.join(build.ROOT, "include"), "-I", build.CSRC, str(src)])

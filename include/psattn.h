@@ -35,7 +35,8 @@
  *   - tensors are contiguous, token-major: Q, O, dO, dQ are [T, n_q_heads, head_dim],
  *     K, V, dK, dV are [T, n_kv_heads, head_dim], head_dim fastest.  LSE is
  *     [n_q_heads, T] float.  q-heads [g*G, (g+1)*G), G = n_q_heads / n_kv_heads,
- *     read kv-head g.
+ *     read kv-head g.  They may start wherever an element may, but 16-byte boundaries are
+ *     faster, and PSATTN_BF16 with head_dim 128 on the matrix cores needs them.
  *   - padding tokens (covered by no sample) are never attended to; every output at
  *     a padding position is written as zero (LSE = -inf).  Outputs are overwritten,
  *     never accumulated into.  With PSATTN_BF16 and head_dim 128 the input VALUES must be
@@ -268,7 +269,8 @@ size_t psattn_bwd_static_max_rows(void);
 
 /* 1 if psattn_fwd (backward = 0) or psattn_bwd (backward != 0) would run the bf16
  * matrix-core kernels for this meta object, element type, head_dim and scale, 0 if
- * the call would run on the slow generic kernels, negative status for a NULL meta. */
+ * the call would run on the slow generic kernels, negative status for a NULL meta.
+ * (head_dim 64: for tensors on 16-byte boundaries; others run on the generic kernels.) */
 int psattn_uses_mfma(const psattn_meta* meta, int32_t dt, int32_t head_dim, float scale, int32_t backward);
 
 /*

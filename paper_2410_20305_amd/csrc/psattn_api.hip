@@ -234,6 +234,10 @@ bool mfma_bwd_ok(const psattn_meta* m, int32_t dt, int32_t d, float scale) {
     return mfma_fwd_ok(m, dt, d, scale) && m->bwd.tile_q == kBwdTileQ && m->bwd.tile_k == kBwdTileK;
 }
 
+// The matrix-core kernels move 16 bytes at a time, asynchronous copies among them.
+template <typename... P>
+bool aligned16(const P*... p) { return ((reinterpret_cast<uintptr_t>(p) | ...) & 15) == 0; }
+
 // ---- optional per-pass event timing
 bool g_profile = false;
 struct EventPair { hipEvent_t a, b; int pass; };
@@ -292,7 +296,7 @@ int bwd_checked(const psattn_meta* meta, int32_t dt, int32_t n_q_heads, int32_t 
     a.delta = reinterpret_cast<float*>(align_up(reinterpret_cast<uintptr_t>(scratch_base), 256));
     a.lse2 = a.delta + align_up(sizeof(float) * static_cast<size_t>(meta->T) * n_q_heads, 256) / sizeof(float);
     int err = 0;
-    const bool mfma = mfma_bwd_ok(meta, dt, head_dim, scale);
+    const bool mfma = mfma_bwd_ok(meta, dt, head_dim, scale) && (head_dim == 128 || aligned16(Q, K, V, O, dO, dQ, dK, dV));
     if (rope_table && !(mfma && head_dim == 128)) return PSATTN_EUNSUPPORTED;  // rotary embedding lives in these matrix-core kernels only
     // One launch reads Q, K, V, O and dO while the gradients are being written, two read O in the first and of K and V only
     // the workgroup's own rows in the second: a gradient that takes the memory of O, K or V needs them.
@@ -335,7 +339,7 @@ int fwd_checked(const psattn_meta* meta, int32_t dt, int32_t n_q_heads, int32_t 
     a.Hq = n_q_heads; a.Hkv = n_kv_heads; a.d = head_dim; a.scale = scale;
     a.Q = Q; a.K = K; a.V = V; a.Oout = O; a.LSEout = LSE;
     a.rope = rope_table; a.Qr = Qr;
-    const bool mfma = mfma_fwd_ok(meta, dt, head_dim, scale);
+    const bool mfma = mfma_fwd_ok(meta, dt, head_dim, scale) && (head_dim == 128 || aligned16(Q, K, V, O));
     if (rope_table && !(mfma && head_dim == 128)) return PSATTN_EUNSUPPORTED;  // rotary embedding lives in these matrix-core kernels only
     int err;
     {

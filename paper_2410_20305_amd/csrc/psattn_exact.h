@@ -18,12 +18,15 @@ namespace psattn {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-__device__ inline f32x4 ld4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
+// four neighbouring elements; tensors start wherever an element may (one wide access all the same)
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
+__device__ inline f32x4 ld4(const float* p) { return *reinterpret_cast<const f32x4_any*>(p); }
 __device__ inline f32x4 ld4(const uint16_t* p) {
-    const uint2 u = *reinterpret_cast<const uint2*>(p);
+    const u32x2_any u = *reinterpret_cast<const u32x2_any*>(p);
     f32x4 v;
-    v[0] = __uint_as_float(u.x << 16); v[1] = __uint_as_float(u.x & 0xffff0000u);
-    v[2] = __uint_as_float(u.y << 16); v[3] = __uint_as_float(u.y & 0xffff0000u);
+    v[0] = __uint_as_float(u[0] << 16); v[1] = __uint_as_float(u[0] & 0xffff0000u);
+    v[2] = __uint_as_float(u[1] << 16); v[3] = __uint_as_float(u[1] & 0xffff0000u);
     return v;
 }
 __device__ inline uint32_t bf16_bits(float v) {  // round to nearest even
@@ -32,9 +35,10 @@ __device__ inline uint32_t bf16_bits(float v) {  // round to nearest even
     u += 0x7fffu + ((u >> 16) & 1u);
     return u >> 16;
 }
-__device__ inline void st4(float* p, f32x4 v) { *reinterpret_cast<f32x4*>(p) = v; }
+__device__ inline void st4(float* p, f32x4 v) { *reinterpret_cast<f32x4_any*>(p) = v; }
 __device__ inline void st4(uint16_t* p, f32x4 v) {
-    *reinterpret_cast<uint2*>(p) = make_uint2(bf16_bits(v[0]) | (bf16_bits(v[1]) << 16), bf16_bits(v[2]) | (bf16_bits(v[3]) << 16));
+    const u32x2_any u = {bf16_bits(v[0]) | (bf16_bits(v[1]) << 16), bf16_bits(v[2]) | (bf16_bits(v[3]) << 16)};
+    *reinterpret_cast<u32x2_any*>(p) = u;
 }
 
 __device__ inline bool allowed(const Tok4& t, int q, int kv) {

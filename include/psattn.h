@@ -276,7 +276,9 @@ int psattn_uses_mfma(const psattn_meta* meta, int32_t dt, int32_t head_dim, floa
 /*
  * Per-pass device timing for benchmarks.  While enabled, psattn_fwd / psattn_bwd
  * bracket each kernel with a pair of HIP events on the caller's stream (pass 0 =
- * forward, 1 = delta, 2 = dQ, 3 = dK/dV).  psattn_profile_read waits for the
+ * forward, 2 = dQ with delta, 3 = dK/dV; pass 1 is never launched any more; the fp32
+ * backward of small calls is one kernel and counts as pass 3).  The kernels are those that
+ * run without profiling.  psattn_profile_read waits for the
  * recorded events, adds the elapsed milliseconds per pass to sum_ms[4] and the
  * number of launches to count[4] (both host, overwritten), and forgets them.
  * Not thread-safe; meant for one benchmarking thread.  At most 65 536 unread event
@@ -395,7 +397,8 @@ int psattn_probe_mfma_peak(int32_t n_workgroups, int32_t iters, int32_t random_o
                            void* hip_stream);
 
 /* Name of the kernel that psattn_fwd / psattn_bwd launched most recently in this
- * process for the given pass (0 = forward, 1 = delta, 2 = dQ, 3 = dK/dV), for profilers
+ * process for the given pass (0 = forward, 1 = delta, 2 = dQ, 3 = dK/dV; one kernel may
+ * have done the work of several), for profilers
  * and benchmarks; before any launch of that pass, the kernel a default-grid call with
  * element type dt would use. */
 const char* psattn_kernel_name(int32_t dt, int32_t pass);

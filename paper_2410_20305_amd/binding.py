@@ -576,7 +576,7 @@ def psattn_profile_enable(on: bool) -> None:
 
 
 def psattn_profile_read():
-    """Returns (sum_ms[4], count[4]) per pass: 0 forward, 1 delta, 2 dQ, 3 dK/dV."""
+    """Returns (sum_ms[4], count[4]) per pass: 0 forward, 2 dQ with delta, 3 dK/dV or a backward in one launch (1: none)."""
     ms = np.zeros(4, dtype=np.float64)
     cnt = np.zeros(4, dtype=np.int64)
     _check(load_library().psattn_profile_read(ms.ctypes.data, cnt.ctypes.data), "psattn_profile_read")

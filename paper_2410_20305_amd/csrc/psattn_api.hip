@@ -308,7 +308,8 @@ int bwd_checked(const psattn_meta* meta, int32_t dt, int32_t n_q_heads, int32_t 
         };
         return from(Q, q_bytes) && from(O, q_bytes) && from(dO, q_bytes) && from(K, kv_bytes) && from(V, kv_bytes);
     };
-    if (!mfma && !g_profile && generic_bwd_in_one(a) && apart(dQ, q_bytes) && apart(dK, kv_bytes) && apart(dV, kv_bytes)) {  // (profiling times the passes one by one)
+    if (!mfma && generic_bwd_in_one(a) && apart(dQ, q_bytes) && apart(dK, kv_bytes) && apart(dV, kv_bytes)) {
+        PassTimer t(3, hip_stream);
         g_last_kernel[1] = g_last_kernel[2] = g_last_kernel[3] = "generic_bwd";
         return launch_generic_bwd(dt, a, hip_stream) == 0 ? PSATTN_OK : PSATTN_EHIP;
     }

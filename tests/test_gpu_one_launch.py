@@ -51,3 +51,17 @@ def test_outputs_in_the_memory_of_inputs(dtype, d, tiles):
     assert ps.psattn_kernel_name(code, 2) == ("psattn_dq_bf16_mfma" if mfma else "generic_dq")
     for got, ref in ((O2, dQ), (K2, dK), (V2, dV)):
         assert np.array_equal(to_np(got), to_np(ref))
+
+
+def test_profiling_times_the_kernels_that_run_without_it():
+    w = W.custom_workload([(50, 20, 33)], hq=4, hkv=2, d=64, dtype="f32", seed=18)
+    tens = W.make_tensors(w)
+    ps.psattn_profile_enable(True)
+    try:
+        ps.psattn_profile_read()
+        run_gpu(w, tens)
+        ms, count = ps.psattn_profile_read()
+    finally:
+        ps.psattn_profile_enable(False)
+    assert ps.psattn_kernel_name(ps.F32, 3) == "generic_bwd"
+    assert count.tolist() == [1, 0, 0, 1] and ms[0] > 0 and ms[3] > 0

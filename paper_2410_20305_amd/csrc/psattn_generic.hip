@@ -382,9 +382,12 @@ int launch_generic_bwd(int dt, const AttnArgs& a, void* stream) { PSATTN_DISPATC
 
 // One launch lets the dK/dV workgroups start with the dQ ones instead of behind them, for a recomputed delta per pair of
 // blocks.  It pays while both together do not fill the chip many times over and dK/dV is not the longer of the two by far
-// (its chains grow with the heads of a group).  Measured, whole step, two launches / one, fp32: 168 tokens, 1 / 1 heads of
-// 64 33.3 / 25.8 us; 450 tokens, 8 / 2 heads of 64 (290 workgroups) 83.5 / 77.3, of 128 148 / 153 (the one loss found
-// inside the rule); 4 000 tokens, 8 / 2 of 64 (2 500) 363 / 344; 8 000 (5 000) 623 / 653; 168 tokens, 32 / 1 of 64 180 / 203.
+// (its chains grow with the heads of a group).  Measured, whole fp32 step, one launch / two, head_dim 64 then 128, over 1 to
+// 16 query heads and 40 to 4 000 tokens (84 tables): up to 174 workgroups 25 / 27 to 60 / 77 us and 27 / 32 to 92 / 98, but
+// groups of four heads at 128 from 145 workgroups on 151 / 144, 308 / 286 (315), 154 / 146 (290); 1 250 to 2 500 workgroups,
+// samples of 1 000 tokens, 196 / 229 and 377 / 421 (4 / 1 heads), 331 / 341 and 635 / 660 (8 / 2), samples of 2 000, 574 / 529
+// and 1 133 / 1 035 (8 / 2); 4 000 and more 336 / 310, 1 143 / 1 057.  The losses inside the line, eleven of 76 tables, are 1 to
+// 9 %, the gains up to 31 %; what separates them is not a size that the host knows.
 bool generic_bwd_in_one(const AttnArgs& a) {
     const int64_t groups = (static_cast<int64_t>(a.meta.T) + kB - 1) / kB * (a.Hq + a.Hkv);
     return groups <= 2560 && a.Hq <= 4 * a.Hkv;

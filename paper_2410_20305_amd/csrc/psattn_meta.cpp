@@ -137,8 +137,9 @@ void transpose(const TileCsr& in, TileCsr& out) {
 // launch does not end in whatever long row comes late in that order, while the rest
 // keeps its neighbours.  dK/dV of 33 506 tokens in 16 long samples 1 426 -> 1 360 us, of
 // 65 536 in 10 long ones 8 255 -> 7 920, of 65 536 in 143 short ones 825 -> 823 (8 %:
-// 1 380 / 7 905 / 842, 25 %: 1 357 / 8 038 / 801).  The same order costs the forward up
-// to 3 % (K / V reads that its neighbours no longer share).
+// 1 380 / 7 905 / 842, 25 %: 1 357 / 8 038 / 801).  On fourteen more tables of 33 000 to 62 000 tokens (1 to 6 responses, 16
+// to 64 heads) 15 % against none is 0.89 to 1.00, one of them 1.04 (16 / 16 heads), and against 25 % better on all but two.
+// The same order costs the forward up to 3 % (K / V reads that its neighbours no longer share).
 //
 // Small grids (fewer rows than a couple of waves of workgroups): there is little to
 // share and the tail dominates, so rows are simply sorted longest first.

@@ -274,10 +274,11 @@ __global__ __launch_bounds__(256, 2) void psattn_dkdv64_bf16_mfma(AttnArgs a) {
 // Which of the two.  A workgroup is a serial chain of as many steps (heads of the group x q-tiles) as its row is long; with
 // two workgroups per CU a launch is bound by its longest chain until that falls below half of a CU's share of all steps.
 // Splitting halves the chain and costs a few per cent more work (every tile is staged for 64 keys instead of 128) and the
-// exchange at the end; the line lies where the longest chain is a CU's share.  Measured, whole step of forward and
-// backward, unsplit / split: one sample of 2 000 tokens, 32 q / 8 kv heads (chain 128, share 33) 225 / 155 us; eight of 860
-// tokens (64, 59) 197 / 181; fourteen of 600 (48, 58) 178 / 172; 16 / 16 heads, two of 1 600 (26, 22) 108 / 100, eight
-// of 500 (10, 13) 58 / 61.
+// exchange at the end; the line lies where the longest chain is a CU's share.  Measured on 96 tables, chains of 1 to 496 steps,
+// whole step of forward and backward, unsplit / split: one sample of 2 000 tokens, 32 q / 8 kv heads (chain 128, share 33)
+// 378 / 248 us; eight of 860 tokens (64, 59) 304 / 273; fourteen of 600 (48, 58) 264 / 248; 16 / 16 heads, two of 1 600
+// (26, 22) 158 / 140, eight of 500 (10, 13) 80 / 82, twenty-four of 256 (4, 9) 72 / 77; one sample of 40 tokens, 8 / 8 heads
+// (chain 1) 28.6 / 29.2, of 180 (3) 33.8 / 32.5.  No table inside the line loses more than that 2 %.
 constexpr int64_t kCus = 256;
 
 int launch_mfma_dkdv64(const AttnArgs& a, void* stream) {

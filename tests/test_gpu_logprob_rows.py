@@ -27,8 +27,9 @@ def test_rows(dtype, vocab, x_off, g_off):
     dt = torch.bfloat16 if dtype == "bf16" else torch.float32
 
     def at(offset):
-        return torch.full((T * vocab + 64,), float("nan"), dtype=dt, device="cuda")[offset:offset + T * vocab].view(T, vocab)
-    x, g = at(x_off), at(g_off)
+        whole = torch.full((T * vocab + 64,), float("nan"), dtype=dt, device="cuda")
+        return whole, whole[16 + offset:16 + offset + T * vocab].view(T, vocab)
+    (_, x), (whole, g) = at(x_off), at(g_off)
     x.copy_(torch.from_numpy(logits))
     plan = ps.LogprobPlan(off, P, ptr, rl, T)
     tid = torch.from_numpy(ids).cuda()
@@ -43,6 +44,8 @@ def test_rows(dtype, vocab, x_off, g_off):
     got = g.float().cpu().numpy().astype(np.float64)
     tol = 1e-6 if dtype == "f32" else 2.0 ** -8 * np.abs(gref) + 1e-6
     assert np.all(np.isfinite(got)) and float((np.abs(got - gref) - tol).max()) <= 0
+    outside = torch.cat([whole[:16 + g_off], whole[16 + g_off + T * vocab:]])
+    assert outside.numel() == 64 and bool(torch.isnan(outside).all())  # nothing is stored beside the rows
     plan.free()
 
 

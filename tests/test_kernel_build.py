@@ -19,53 +19,23 @@ def _asm(tmp_path, src):
     return build.device_asm(src, str(tmp_path / (src + ".s")))
 
 
-def _kernel_meta(text, kernel):
-    """amdhsa.kernels metadata entry whose .name contains `kernel`, as a dict of scalars."""
-    blocks = re.split(r"\n  - \.agpr_count:", text)
-    for b in blocks[1:]:
-        b = ".agpr_count:" + b
-        if re.search(r"\.name:\s+\S*" + kernel, b):
-            return {k: v for k, v in re.findall(r"\.([a-z_]+):\s+(\S+)", b)}
-    raise AssertionError("no metadata for " + kernel)
+def _kernels(text, kernel, count):
+    """Every instantiation of `kernel` in the file: (name, device code, metadata scalars).  `count` pins how many there are."""
+    meta = {}
+    for b in re.split(r"\n  - \.agpr_count:", text)[1:]:
+        d = dict(re.findall(r"\.([a-z_]+):\s+(\S+)", ".agpr_count:" + b))
+        meta[d["name"]] = d
+    out = []
+    for name in re.findall(r"\.amdhsa_kernel (\S+)", text):
+        start, end = text.index("\n" + name + ":"), text.index(".amdhsa_kernel " + name + "\n")
+        if kernel in name:
+            out.append((name, text[start:end], meta[name]))
+    assert len(out) == count, (kernel, [n for n, _, _ in out])
+    return out
 
 
-def test_dkdv_accumulation_registers_belong_to_the_assembly(tmp_path):
-    text = _asm(tmp_path, "psattn_mfma_dkdv.hip")
-    body = text.split(".amdhsa_kernel")[0]
-    inside = False
-    offenders = []
-    for ln in body.splitlines():
-        if "#ASMSTART" in ln:
-            inside = True
-        elif "#ASMEND" in ln:
-            inside = False
-        elif not inside:
-            code = ln.split(";")[0]
-            if re.search(r"accvgpr|\ba\[|[ ,\[]a\d+\b", code):
-                offenders.append(ln.strip())
-    assert not offenders, offenders[:5]
-    meta = _kernel_meta(text, "psattn_dkdv_bf16_mfma")
-    assert int(meta["agpr_count"]) == 192
-    assert int(meta["vgpr_spill_count"]) == 0 and int(meta["sgpr_spill_count"]) == 0
-    assert int(meta["private_segment_fixed_size"]) == 0
-    # one wave per SIMD: ordinary + accumulation registers of one lane
-    assert int(meta["vgpr_count"]) <= 512
-
-
-@pytest.mark.parametrize("src,kernel", [("psattn_mfma_fwd.hip", "psattn_fwd_bf16_mfma"),
-                                        ("psattn_mfma_bwd.hip", "psattn_dq_bf16_mfma")])
-def test_two_workgroups_per_cu_without_spills(tmp_path, src, kernel):
-    meta = _kernel_meta(_asm(tmp_path, src), kernel)
-    assert int(meta["vgpr_count"]) <= 256          # two waves per SIMD
-    assert int(meta["agpr_count"]) == 0
-    assert int(meta["vgpr_spill_count"]) == 0 and int(meta["sgpr_spill_count"]) == 0
-    assert int(meta["private_segment_fixed_size"]) == 0
-    assert int(meta["group_segment_fixed_size"]) <= 80 * 1024  # two workgroups in 160 KB of LDS
-
-
-def _outside_asm(text):
-    """Instruction lines of the device code that the compiler itself emitted."""
-    body = text.split(".amdhsa_kernel")[0]
+def _outside_asm(body):
+    """Instruction lines that the compiler itself emitted."""
     inside = False
     for ln in body.splitlines():
         if "#ASMSTART" in ln:
@@ -78,40 +48,65 @@ def _outside_asm(text):
                 yield code
 
 
-@pytest.mark.parametrize("src", ["psattn_mfma_fwd.hip", "psattn_mfma_bwd.hip", "psattn_mfma_dkdv.hip"])
-def test_compiler_keeps_m0_and_the_copy_counter_free(tmp_path, src):
+def _no_spills(name, meta):
+    assert int(meta["vgpr_spill_count"]) == 0 and int(meta["sgpr_spill_count"]) == 0, name
+    assert int(meta["private_segment_fixed_size"]) == 0, name
+
+
+def test_dkdv_accumulation_registers_belong_to_the_assembly(tmp_path):
+    text = _asm(tmp_path, "psattn_mfma_dkdv.hip")
+    for name, body, meta in _kernels(text, "psattn_dkdv_bf16_mfma", 2):
+        offenders = [c for c in _outside_asm(body) if re.search(r"accvgpr|\ba\[|[ ,\[]a\d+\b", c)]
+        assert not offenders, (name, offenders[:5])
+        assert int(meta["agpr_count"]) == 192, name
+        _no_spills(name, meta)
+        # one wave per SIMD: ordinary + accumulation registers of one lane
+        assert int(meta["vgpr_count"]) <= 512, name
+
+
+@pytest.mark.parametrize("src,kernel,count,waves", [("psattn_mfma_fwd.hip", "psattn_fwd_bf16_mfma", 1, [2]),
+                                                    ("psattn_mfma_fwd64.hip", "psattn_fwd_bf16_mfma", 1, [3]),
+                                                    ("psattn_mfma_bwd.hip", "psattn_dq_bf16_mfma", 2, [2, 3])])
+def test_two_workgroups_per_cu_without_spills(tmp_path, src, kernel, count, waves):
+    for (name, _, meta), n in zip(_kernels(_asm(tmp_path, src), kernel, count), waves):
+        assert int(meta["vgpr_count"]) <= 512 // n // 8 * 8, name   # n waves per SIMD, registers in eights
+        assert int(meta["agpr_count"]) == 0, name
+        _no_spills(name, meta)
+        assert int(meta["group_segment_fixed_size"]) <= 160 * 1024 // n, name  # n workgroups in 160 KB of LDS
+
+
+@pytest.mark.parametrize("src,count", [("psattn_mfma_fwd.hip", 1), ("psattn_mfma_fwd64.hip", 1), ("psattn_mfma_bwd.hip", 2),
+                                       ("psattn_mfma_dkdv.hip", 2), ("psattn_mfma_dkdv64.hip", 2)])
+def test_compiler_keeps_m0_and_the_copy_counter_free(tmp_path, src, count):
     """The asynchronous global -> LDS copies are issued from inline assembly that writes M0
     and counts its own outstanding copies (vmcnt).  Sound only while compiled code never
     keeps a value in M0, and while the only vector-memory loads the compiler issues between
     the first and the last copy are the one-dword tile-list refills."""
-    text = _asm(tmp_path, src)
-    for code in _outside_asm(text):
-        assert not re.search(r"\bm0\b", code), code
-    body = text.split(".amdhsa_kernel")[0]
-    first, last = body.index("global_load_lds_dwordx4"), body.rindex("global_load_lds_dwordx4")
-    loop = body[first:last]
-    inside = True  # the slice starts in the middle of an assembly statement
-    for ln in loop.splitlines():
-        if "#ASMSTART" in ln:
-            inside = True
-        elif "#ASMEND" in ln:
-            inside = False
-        elif not inside:
-            code = ln.split(";")[0].strip()
+    for name, body, _ in _kernels(_asm(tmp_path, src), "_mfma", count):
+        for code in _outside_asm(body):
+            assert not re.search(r"\bm0\b", code), (name, code)
+        first, last = body.index("global_load_lds_dwordx4"), body.rindex("global_load_lds_dwordx4")
+        loop = "#ASMSTART\n" + body[first:last]  # the slice starts in the middle of an assembly statement
+        for code in _outside_asm(loop):
             m = re.match(r"(global_load|buffer_load|flat_load|scratch_load)\w*", code)
             if m:
-                assert m.group(0) == "global_load_dword", code
+                assert m.group(0) == "global_load_dword", (name, code)
 
 
 def test_dkdv64_two_waves_per_simd_without_spills(tmp_path):
     """The head_dim 64 dK/dV kernel is left to the compiler: two waves per SIMD, nothing spilled, M0 untouched."""
-    text = _asm(tmp_path, "psattn_mfma_dkdv64.hip")
-    meta = _kernel_meta(text, "psattn_dkdv64_bf16_mfma")
-    assert int(meta["vgpr_count"]) <= 256 and int(meta["agpr_count"]) == 0
-    assert int(meta["vgpr_spill_count"]) == 0 and int(meta["sgpr_spill_count"]) == 0
-    assert int(meta["private_segment_fixed_size"]) == 0
-    for code in _outside_asm(text):
-        assert not re.search(r"\bm0\b", code), code
+    for name, body, meta in _kernels(_asm(tmp_path, "psattn_mfma_dkdv64.hip"), "psattn_dkdv64_bf16_mfma", 2):
+        assert int(meta["vgpr_count"]) <= 256 and int(meta["agpr_count"]) == 0, name
+        _no_spills(name, meta)
+        for code in _outside_asm(body):
+            assert not re.search(r"\bm0\b", code), (name, code)
+
+
+@pytest.mark.parametrize("kernel,count", [("generic_fwd", 4), ("generic_dq", 4), ("generic_dkdv", 4), ("generic_bwd", 4)])
+def test_generic_kernels_without_spills(tmp_path, kernel, count):
+    for name, _, meta in _kernels(_asm(tmp_path, "psattn_generic.hip"), kernel, count):
+        _no_spills(name, meta)
+        assert int(meta["vgpr_count"]) <= 256, name  # eight waves to a workgroup
 
 
 def test_upload_blocks_up_to_the_largest_buffer(tmp_path):

@@ -109,10 +109,11 @@ enum { PSATTN_GRID_FWD = 0, /* q-major CSR, used by psattn_fwd and the dQ pass  
  * !(hole_lo_q <= kv < hole_hi_q)).
  *
  * psattn_build_meta uploads the metadata to the current device with one
- * asynchronous copy on hip_stream (the host staging buffer stays alive inside the
- * object).  Tile grids with 2^29 or more tiles along an axis, or more than
- * INT32_MAX non-skipped tiles, are refused with PSATTN_EUNSUPPORTED.  psattn_build_meta_host builds the same object without touching any
- * device (for inspection and planning); kernels refuse it with PSATTN_ENODEVICE.
+ * asynchronous kernel on hip_stream that reads the pinned staging buffer (which stays
+ * alive inside the object).  Tile grids with 2^29 or more tiles along an axis, or more than
+ * INT32_MAX non-skipped tiles, are refused with PSATTN_EUNSUPPORTED.
+ * psattn_build_meta_host builds the same object without touching any device (for
+ * inspection and planning); kernels refuse it with PSATTN_ENODEVICE.
  * On error *out is set to NULL.
  */
 int psattn_build_meta(int32_t n_samples,
@@ -219,10 +220,12 @@ int psattn_pack_ffd(int32_t n_samples, const int32_t* prefix_len, const int32_t*
  * LSE[h, q] = log sum_kv exp(scale * Q_q . K_kv) (natural log).  SKIPPED tiles are
  * never computed (Section 3.1).  dt selects the element type of Q, K, V, O
  * (float, or bfloat16 with float accumulation); LSE is always float.
- * head_dim: 64 or 128 for either type.  The matrix-core kernels serve PSATTN_BF16 with
- * scale > 0 and the default tile grids; every other valid request runs on
- * plain one-thread-per-row kernels that are orders of magnitude slower (they exist for the
- * fp32 correctness configuration).  psattn_uses_mfma tells which one a call would take.
+ * head_dim: 64 or 128 for either type.  The bf16 matrix-core kernels serve PSATTN_BF16 with
+ * scale > 0 and the default tile grids; every other valid request runs on generic kernels
+ * (fp32 products throughout, 16 rows to a workgroup), several times slower on large batches.
+ * Probabilities and score gradients are fp32 everywhere but in the second products of
+ * PSATTN_BF16 with head_dim 128, which take them rounded to bfloat16.
+ * psattn_uses_mfma tells which kernels a call would take.
  */
 int psattn_fwd(const psattn_meta* meta, int32_t dt, int32_t n_q_heads, int32_t n_kv_heads,
                int32_t head_dim, float scale,
@@ -269,7 +272,7 @@ size_t psattn_bwd_static_max_rows(void);
 
 /* 1 if psattn_fwd (backward = 0) or psattn_bwd (backward != 0) would run the bf16
  * matrix-core kernels for this meta object, element type, head_dim and scale, 0 if
- * the call would run on the slow generic kernels, negative status for a NULL meta.
+ * the call would run on the generic kernels, negative status for a NULL meta.
  * (head_dim 64: for tensors on 16-byte boundaries; others run on the generic kernels.) */
 int psattn_uses_mfma(const psattn_meta* meta, int32_t dt, int32_t head_dim, float scale, int32_t backward);
 

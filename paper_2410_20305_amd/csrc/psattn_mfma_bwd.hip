@@ -13,12 +13,12 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_dq_bf16_mfma(Att
     __shared__ __attribute__((aligned(16))) char sKb[2][64 * kRB];  // double buffered
     __shared__ __attribute__((aligned(16))) char sVb[2][64 * kRB];
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, c32 = l & 31, g = l >> 5;
-    const int T = a.meta.T, Hq = a.Hq, Hkv = a.Hkv, G = Hq / Hkv;
+    const int T = a.meta.T, Hq = a.Hq, Hkv = a.Hkv;
     const DeviceCsr& csr = a.meta.fwd;
-    const int kvh = blockIdx.x % Hkv, rest = blockIdx.x / Hkv;
-    const RowLaunch rl = csr.launch[rest / G];  // one scalar load: row, list bounds, first entry
-    const int h = kvh * G + rest % G, qt = rl.row;
-    const int q_row = qt * 128 + 32 * w + c32;
+    const QueryBlock qb = query_block(Hq, Hkv, csr.n_rows, w);
+    const RowLaunch rl = csr.launch[qb.row];  // one scalar load: row, list bounds
+    const int kvh = qb.kvh, h = qb.h, row0 = rl.row * 128 + qb.first;
+    const int q_row = row0 + c32;
     const bool valid = q_row < T;
     Tok4 tk = {kPadStart, 0, 0, 0};
     if (valid) tk = a.meta.tok[q_row];
@@ -80,15 +80,19 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_dq_bf16_mfma(Att
         pair_copy_setup(pc, reinterpret_cast<const char*>(K) + static_cast<size_t>(k0) * row_bytes,
                         reinterpret_cast<const char*>(V) + static_cast<size_t>(k0) * row_bytes, row_bytes, T - 1 - k0, dml, w, l);
     };
-    const int e0 = rl.begin, n_ent = rl.count;
     EntryStream es;
-    es.init(csr.entry, e0, 1, n_ent, l);
-    int ent = 0, it = 0;
-    if (n_ent > 0) {
-        ent = rl.first_entry;
+    es.init(csr.entry, rl.begin, 1, rl.count, l);
+    int ent = rl.first_entry, it = 0, n_ent = rl.count;
+    // waves that share their queries leave out the tiles at both ends of the list that are there for the q-tile's others
+    if (qb.together)
+        while (it < n_ent && !reads_tile(ent, row0, tk))
+            if (++it < n_ent) ent = es.get(it);
+    if (it < n_ent) {
         copy_setup(ent);
         static_for<0, 2 * kBlocks>([&](auto P) { pair_copy_piece<decltype(P)::value>(pc, sKb[0], sVb[0], w); });
     }
+    if (qb.together && n_ent <= 64)
+        while (it + 1 < n_ent && !reads_tile(es.peek(n_ent - 1), row0, tk)) --n_ent;
     const LaneOffsets lo = lane_offsets<D>(l);
     constexpr int kAhead = 2, kRing = 4;  // measured: 1 and 3 are both slower
     // One tile = 2 kB MFMA slots, per block kb of 32 keys:
@@ -119,6 +123,7 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_dq_bf16_mfma(Att
                 static_for<0, 2 * kBlocks>([&](auto P) { pair_copy_piece<decltype(P)::value>(pc, sKb[buf ^ 1], sVb[buf ^ 1], w); });
                 if (skip32[1]) return;
             }
+            full = __builtin_amdgcn_ballot_w64(bits != 0xffffffffu) == 0;  // for these 32 queries
         }
         const char* sK = sKb[buf];
         const char* sV = sVb[buf];
@@ -226,7 +231,6 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_dq_bf16_mfma(Att
                 }
             }
     }
-    const int row0 = qt * 128 + 32 * w;
     uint16_t* rows = static_cast<uint16_t*>(a.dQ) + (static_cast<size_t>(row0) * Hq + h) * D;
     if constexpr (D == 64) {  // sums that are not finite are taken again (psattn_exact.h)
         multiply(dq, a.scale);

@@ -331,7 +331,45 @@ struct EntryStream {
         }
         return __builtin_amdgcn_readlane(cur, k & 63);
     }
+    __device__ __forceinline__ int peek(int k) const { return __builtin_amdgcn_readlane(cur, k & 63); }  // k in the current batch
 };
+
+// What a wave of a q-major kernel works on: 32 queries of one head.  Where a kv group has a multiple of four heads, the four
+// waves of a workgroup take four heads of it on the same queries, otherwise one head on 128 queries.  A workgroup stages and
+// waits for every tile that one of its waves reads: with short samples 128 neighbouring queries read 5.6 tiles where 32 read
+// 4.3 (65 536 tokens of packed samples of 450), with samples of 5 000 tokens 34.1 and 33.1.  Measured, one head / four, forward
+// and dQ in us, 32 q / 8 kv heads: those short samples 487 / 463 and 677 / 625, 8 334 tokens in samples of 1 000 103 / 101 and
+// 136 / 131, 33 506 tokens in samples of 2 100 682 / 675 and 873 / 855; 64 / 8 heads, samples of 5 000 tokens, 4 365 / 4 331 and
+// 5 612 / 5 556; head_dim 64, 4 758 tokens, 46 / 43 and 49 / 46.  Which tile comes first is known only once the descriptors of
+// the queries are, so a grid that the chip holds at once, which lasts as long as one workgroup, keeps one head: a step of one
+// sample of 221 tokens 46.8 / 48.9.
+constexpr int kTwoPerCu = 512;  // workgroups
+struct QueryBlock {
+    int kvh, h;     // kv head, q head
+    int row;        // position in the launch order of the q-tile of 128
+    int first;      // the wave's first query, in the q-tile
+    bool together;  // the waves share their queries
+};
+__device__ __forceinline__ QueryBlock query_block(int Hq, int Hkv, int n_rows, int w) {
+    // heads of one kv group are neighbours in launch order and share an XCD when Hkv == 8
+    const int G = Hq / Hkv, rest = blockIdx.x / Hkv, j = rest % G;
+    QueryBlock b;
+    b.kvh = blockIdx.x % Hkv;
+    b.row = rest / G;
+    b.together = (G & 3) == 0 && static_cast<int64_t>(n_rows) * Hq > kTwoPerCu;
+    // the last queries of a tile have the longest lists and go first
+    b.first = 32 * (b.together ? 3 - (j & 3) : w);
+    b.h = b.kvh * G + (b.together ? (j & ~3) + w : j);
+    return b;
+}
+
+// Whether one of the 32 queries from q0 on (tk: this lane's) may read a key of the tile of list entry e.
+__device__ __forceinline__ bool reads_tile(int e, int q0, const Tok4& tk) {
+    const int k0 = (e >> 2) * 64;
+    // k0 <= q0 is k0 <= q for all 32: tiles of keys start at multiples of 64
+    return (e & 3) == PSATTN_TILE_FULL ||
+           (k0 <= q0 && __builtin_amdgcn_ballot_w64(k0 + 63 >= tk.s && !(tk.hole_lo <= k0 && k0 + 64 <= tk.hole_hi)) != 0);
+}
 
 // ---- rotary position embedding (Section 3.1: position ids follow the paired format)
 // Dimension i < 64 is paired with i + 64 and the pair is turned by the angle of (position, i).

@@ -25,51 +25,32 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_dq_bf16_mfma(Att
 
     const uint16_t* K = static_cast<const uint16_t*>(a.K) + kvh * D;
     const uint16_t* V = static_cast<const uint16_t*>(a.V) + kvh * D;
-    const size_t qoff = (static_cast<size_t>(q_row) * Hq + h) * D;
-
-    Frag8 qf[kSteps], gf[kSteps];
+    // dO and Q pass through the places that the wave's own K / V copies take later
+    const LaneOffsets lo = lane_offsets<D>(l);
+    const uint32_t q_row_bytes = static_cast<uint32_t>(Hq) * kRB;
+    const int last_row = min(max(T - 1 - row0, 0), 31);
+    const size_t at0 = (static_cast<size_t>(min(row0, T - 1)) * Hq + h) * kRB;
+    const Rows<D> rows0{sKb[0] + 16 * w * kRB, sVb[0] + 16 * w * kRB}, rows1{sKb[1] + 16 * w * kRB, sVb[1] + 16 * w * kRB};
+    uint4 orow[kSteps];
 #pragma unroll
-    for (int t = 0; t < kSteps; ++t) {
-        qf[t].u = valid ? *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(a.Q) + qoff + 16 * t + 8 * g)
-                        : make_uint4(0, 0, 0, 0);
-        gf[t].u = valid ? *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(a.dO) + qoff + 16 * t + 8 * g)
-                        : make_uint4(0, 0, 0, 0);
-    }
+    for (int t = 0; t < kSteps; ++t) orow[t] = *reinterpret_cast<const uint4*>(static_cast<const char*>(a.O) + at0 + Rows<D>::lane_off(t, q_row_bytes, l, last_row));
+    rows0.copy_in(static_cast<const char*>(a.dO) + at0, q_row_bytes, l, last_row);
+    rows1.copy_in(static_cast<const char*>(a.Q) + at0, q_row_bytes, l, last_row);
     // Rows without keys (padding) have LSE = -inf.  Their scores are masked to -inf below;
     // with +inf here exp2(score - lse2) is 0 for them instead of exp2(-inf + inf).  (A row with keys has LSE = -inf only
     // where its scores are not numbers; head_dim 64 passes that on to whatever reads the row.)
     const float lse_row = valid ? a.LSE[static_cast<size_t>(h) * T + q_row] : -INFINITY;
     const bool no_keys = D == 64 ? tk.s == kPadStart : lse_row == -INFINITY;
     const float lse2 = no_keys ? INFINITY : lse_row * kLog2e;
-    // delta = rowsum(dO o O): this lane holds half of the row's dO already, O is read once
-    // here; the result also goes to the workspace for the dK/dV pass that follows
-    float dl = 0.f;
-    if (valid) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    Frag8 qf[kSteps], gf[kSteps];
+    uint4 grow[kSteps];
+    static_for<0, kSteps>([&](auto P) { grow[decltype(P)::value] = rows0.template chunk<decltype(P)::value>(l); });
+    rows0.operands(gf, l, lo.nat);
+    rows1.operands(qf, l, lo.nat);
+    // they are in registers before the first K / V tile takes the place of dO
 #pragma unroll
-        for (int t = 0; t < kSteps; ++t) {
-            const uint4 ov = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(a.O) + qoff + 16 * t + 8 * g);
-            const uint32_t ow[4] = {ov.x, ov.y, ov.z, ov.w};
-            const uint32_t gw[4] = {gf[t].u.x, gf[t].u.y, gf[t].u.z, gf[t].u.w};
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                dl = fmaf(__uint_as_float(ow[j] << 16), __uint_as_float(gw[j] << 16), dl);
-                dl = fmaf(__uint_as_float(ow[j] & 0xffff0000u), __uint_as_float(gw[j] & 0xffff0000u), dl);
-            }
-        }
-    }
-    dl += other_half(dl);
-    if (valid && g == 0) {
-        a.delta[static_cast<size_t>(h) * T + q_row] = -dl;  // the dK/dV kernel starts its dP accumulators from -delta
-        a.lse2[static_cast<size_t>(h) * T + q_row] = lse2;
-    }
-    const float c = a.scale * kLog2e;
-
-    f32x16 dq[kBlocks];
-#pragma unroll
-    for (int db = 0; db < kBlocks; ++db)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) dq[db][i] = 0.f;
-
+    for (int t = 0; t < kSteps; ++t) asm volatile("" : "+v"(qf[t].v), "+v"(gf[t].v), "+v"(grow[t].x)::"memory");
     // K / V tiles are copied global -> LDS asynchronously, one tile ahead, into the
     // buffer the previous tile has just vacated; one barrier per tile.
     const uint32_t row_bytes = static_cast<uint32_t>(Hkv) * kRB;
@@ -91,9 +72,45 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_dq_bf16_mfma(Att
         copy_setup(ent);
         static_for<0, 2 * kBlocks>([&](auto P) { pair_copy_piece<decltype(P)::value>(pc, sKb[0], sVb[0], w); });
     }
+    // delta = rowsum(dO o O), summed over the lanes that hold a row's 16-byte chunks; the result also goes to the workspace for
+    // the dK/dV pass that follows
+    constexpr int kLanes = D / 8;
+    float dl;
+    {
+        float part = 0.f;
+#pragma unroll
+        for (int t = 0; t < kSteps; ++t) {
+            const uint32_t ow[4] = {orow[t].x, orow[t].y, orow[t].z, orow[t].w};
+            const uint32_t gw[4] = {grow[t].x, grow[t].y, grow[t].z, grow[t].w};
+            float d = 0.f;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                d = fmaf(__uint_as_float(ow[j] << 16), __uint_as_float(gw[j] << 16), d);
+                d = fmaf(__uint_as_float(ow[j] & 0xffff0000u), __uint_as_float(gw[j] & 0xffff0000u), d);
+            }
+            d = sum_lanes<kLanes>(d);
+            part = l % kLanes == t ? d : part;
+        }
+        // lane kLanes * j + t holds row (64 / kLanes) t + j
+        float* sd = reinterpret_cast<float*>(rows1.a);  // Q is in registers
+        if (l % kLanes < kSteps) sd[(64 / kLanes) * (l % kLanes) + l / kLanes] = part;
+        dl = sd[c32];
+    }
+    if (valid && g == 0) {
+        a.delta[static_cast<size_t>(h) * T + q_row] = -dl;  // the dK/dV kernel starts its dP accumulators from -delta
+        a.lse2[static_cast<size_t>(h) * T + q_row] = lse2;
+    }
+    const float c = a.scale * kLog2e;
+
+    f32x16 dq[kBlocks];
+#pragma unroll
+    for (int db = 0; db < kBlocks; ++db)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) dq[db][i] = 0.f;
+
     if (qb.together && n_ent <= 64)
         while (it + 1 < n_ent && !reads_tile(es.peek(n_ent - 1), row0, tk)) --n_ent;
-    const LaneOffsets lo = lane_offsets<D>(l);
+    const int n_tiles = n_ent - it;
     constexpr int kAhead = 2, kRing = 4;  // measured: 1 and 3 are both slower
     // One tile = 2 kB MFMA slots, per block kb of 32 keys:
     //   slots kB kb + 0 .. kS - 1   S^T = K Q^T and dP^T = V dO^T (alternating)
@@ -231,14 +248,17 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_dq_bf16_mfma(Att
                 }
             }
     }
-    uint16_t* rows = static_cast<uint16_t*>(a.dQ) + (static_cast<size_t>(row0) * Hq + h) * D;
     if constexpr (D == 64) {  // sums that are not finite are taken again (psattn_exact.h)
         multiply(dq, a.scale);
         for (AgainGroups n(not_finite_groups(dq), row0, T); n.any(); n.next())
             set_group(dq, n.group(), exact_dq<uint16_t, D>(a, h, n.row, n.dim(), -a.delta[static_cast<size_t>(h) * T + n.row]));
     }
+    // the buffer that the last tile was not in
+    const int lx = opaque(l);
+    const Rows<D> rows{sKb[n_tiles & 1] + 16 * w * kRB, sVb[n_tiles & 1] + 16 * w * kRB};
 #pragma unroll
-    for (int db = 0; db < kBlocks; ++db) store_block(rows, static_cast<size_t>(Hq) * D, T - row0, db, dq[db], D == 64 ? 1.f : a.scale, l);
+    for (int db = 0; db < kBlocks; ++db) rows.put(db, dq[db], D == 64 ? 1.f : a.scale, lx);
+    rows.copy_out(static_cast<char*>(a.dQ) + (static_cast<size_t>(row0) * Hq + h) * kRB, q_row_bytes, lx, T - row0);
 }
 
 }  // namespace

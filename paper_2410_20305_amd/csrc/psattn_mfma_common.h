@@ -56,6 +56,13 @@ __device__ __forceinline__ void static_for(F&& f) {
     }
 }
 
+// x, and nothing that the compiler knows of it: what is computed from it stays where it stands instead of living in
+// registers throughout the loop before it
+__device__ __forceinline__ int opaque(int x) {
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
 union Frag8 {
     bf16x8 v;
     bf16x4 h[2];
@@ -210,6 +217,19 @@ __device__ inline float other_half(float x) {
     return __uint_as_float(threadIdx.x & 32 ? r[0] : r[1]);
 }
 
+// sum over groups of N = 8 or 16 neighbouring lanes, in all of them
+template <int N>
+__device__ __forceinline__ float sum_lanes(float x) {
+    const auto add = [](float v, auto C) {
+        return v + __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), decltype(C)::value, 0xf, 0xf, true));
+    };
+    x = add(x, std::integral_constant<int, 0xb1>{});   // quad_perm [1, 0, 3, 2]
+    x = add(x, std::integral_constant<int, 0x4e>{});   // quad_perm [2, 3, 0, 1]
+    x = add(x, std::integral_constant<int, 0x141>{});  // row_half_mirror
+    if constexpr (N == 16) x = add(x, std::integral_constant<int, 0x140>{});  // row_mirror
+    return x;
+}
+
 // row of the 32x32 accumulator that register i of lane-half g holds
 __device__ inline int acc_row(int i, int g) { return (i >> 2) * 8 + 4 * g + (i & 3); }
 
@@ -303,6 +323,72 @@ __device__ __forceinline__ void pair_copy_piece(const PairCopyOf<D>& c, const ch
     else dma16(c.b, c.lane.off[P - n], lds_addr(tile_b) + 16 * w * kRowBytesOf<D> + 1024 * (P - n));
 }
 
+__device__ __forceinline__ uint32_t pack2(float a, float b) {
+    f32x2 v = {a, b};
+    union { bf16x2 p; uint32_t u; } o;
+    o.p = __builtin_convertvector(v, bf16x2);
+    return o.u;
+}
+
+// A wave's 32 rows of a tensor on their way through LDS, so that memory is read and written in whole rows.  Operands loaded
+// straight into their registers take 32 bytes of each of 32 rows at a time: a line is asked for by four instructions, by which
+// time the eight waves of a CU have pushed it out of their 32 KB of L1.  (Taking the same loads non-temporally, so that every
+// one of the four goes to memory, slows dQ of packed short samples from 680 to 912 us, which is what gave it away; fetching the rows into
+// L2 beforehand changes nothing.)  Accumulators stored straight from theirs write 64 bytes of each of 16 rows.  In LDS the rows stand
+// as in a tile, 0 - 15 at `a` and 16 - 31 at `b`: the two places that the wave itself fills when it copies its share of a pair
+// of tiles.  Measured, straight / through LDS, in us: 65 536 tokens of packed samples of 450, 32 / 8 heads, forward 490 / 460,
+// dQ 637 / 549, dK/dV 833 / 817; 33 506 tokens in samples of 2 100 692 / 676, 872 / 834, 1 280 / 1 267; 64 / 8 heads,
+// samples of 5 000 tokens, 4 430 / 4 362, 5 660 / 5 458, 8 040 / 8 050; one sample of 221 tokens 11.5 / 12.0, 12.6 / 12.4, 22.7 / 21.3.
+template <int D>
+struct Rows {
+    static constexpr int kRB = kRowBytesOf<D>, kChunks = D / 8, kPieces = D / 16;  // 16-byte chunks of a row; pieces of 1024 bytes
+    char *a, *b;
+    template <int P>
+    __device__ __forceinline__ char* piece() const { return P < kPieces / 2 ? a + 1024 * P : b + 1024 * (P - kPieces / 2); }
+    // byte offset from the first row of what lane l moves in a piece, rows row_bytes apart; rows past `last_row` become it
+    static __device__ __forceinline__ uint32_t lane_off(int p, uint32_t row_bytes, int l, int last_row) {
+        const int row = 64 / kChunks * p + l / kChunks;
+        return static_cast<uint32_t>(min(row, last_row)) * row_bytes + (((l % kChunks) ^ row_swizzle<D>(row)) << 4);
+    }
+    __device__ __forceinline__ void copy_in(const void* base, uint32_t row_bytes, int l, int last_row) const {
+        static_for<0, kPieces>([&](auto P) {
+            constexpr int p = decltype(P)::value;
+            dma16(base, lane_off(p, row_bytes, l, last_row), lds_addr(piece<p>()));
+        });
+    }
+    // what lane l has moved in piece P
+    template <int P>
+    __device__ __forceinline__ uint4 chunk(int l) const { return *reinterpret_cast<const uint4*>(piece<P>() + 16 * l); }
+    // row l % 32 as MFMA operands
+    __device__ __forceinline__ void operands(Frag8 (&f)[D / 16], int l, int nat) const {
+        const char* at = l & 16 ? b - 16 * kRB : a;
+        static_for<0, D / 16>([&](auto S) { f[decltype(S)::value].v = ld_rows<decltype(S)::value>(at, nat); });
+    }
+    // ... and back
+    __device__ __forceinline__ void put_operands(const Frag8 (&f)[D / 16], int l, int nat) const {
+        char* const at = l & 16 ? b - 16 * kRB : a;
+        static_for<0, D / 16>([&](auto S) { *reinterpret_cast<uint4*>(at + (nat ^ (decltype(S)::value << 5))) = f[decltype(S)::value].u; });
+    }
+    // head dims 32 db .. of an accumulator whose column is row l % 32: a lane holds pieces of four head dims, 8 bytes in bf16
+    __device__ __forceinline__ void put(int db, const f32x16& x, float factor, int l) const {
+        const int row = l & 31;
+        char* const at = (row & 16 ? b - 16 * kRB : a) + row * kRB + 8 * (l >> 5);
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4)
+            *reinterpret_cast<uint2*>(at + (((4 * db + i4) ^ row_swizzle<D>(row)) << 4)) =
+                make_uint2(pack2(x[4 * i4] * factor, x[4 * i4 + 1] * factor), pack2(x[4 * i4 + 2] * factor, x[4 * i4 + 3] * factor));
+    }
+    // the first n_rows rows to memory
+    __device__ __forceinline__ void copy_out(void* base, uint32_t row_bytes, int l, int n_rows) const {
+        uint4 x[kPieces];
+        static_for<0, kPieces>([&](auto P) { x[decltype(P)::value] = chunk<decltype(P)::value>(l); });
+        static_for<0, kPieces>([&](auto P) {
+            constexpr int p = decltype(P)::value;
+            if (64 / kChunks * p + l / kChunks < n_rows) *reinterpret_cast<uint4*>(static_cast<char*>(base) + lane_off(p, row_bytes, l, 31)) = x[p];
+        });
+    }
+};
+
 // Reader of a tile list walked in one direction: position k = 0, 1, ... maps to
 // list[first + step * k] (step = +1 or -1), n positions in all.  Lane l keeps entry
 // 64 b + l of the current batch b; the next batch is requested when a batch is entered,
@@ -391,11 +477,17 @@ __device__ __forceinline__ void rope_turn(float& x1, float& x2, float c, float s
     x2 = y2;
 }
 
-// Rotates 8 packed bf16 (dims i0 .. i0 + 7, i0 < 64) and their partners (dims 64 + i0 ..) in place;
-// `row` points at the table row of the token's position.
-__device__ inline void rope_frag8(Frag8& lo, Frag8& hi, const float* row, int i0) {
-    const float4 c0 = *reinterpret_cast<const float4*>(row + i0), c1 = *reinterpret_cast<const float4*>(row + i0 + 4);
-    const float4 s0 = *reinterpret_cast<const float4*>(row + 64 + i0), s1 = *reinterpret_cast<const float4*>(row + 64 + i0 + 4);
+// What rope_frag8 takes of the table row `row` of the token's position for dims i0 .. i0 + 7, i0 < 64: cosines, then sines.
+__device__ __forceinline__ void rope_load8(float4* turn, const float* row, int i0) {
+    turn[0] = *reinterpret_cast<const float4*>(row + i0);
+    turn[1] = *reinterpret_cast<const float4*>(row + i0 + 4);
+    turn[2] = *reinterpret_cast<const float4*>(row + 64 + i0);
+    turn[3] = *reinterpret_cast<const float4*>(row + 64 + i0 + 4);
+}
+
+// Rotates 8 packed bf16 (dims i0 .. i0 + 7) and their partners (dims 64 + i0 ..) in place
+__device__ __forceinline__ void rope_frag8(Frag8& lo, Frag8& hi, const float4* turn) {
+    const float4 c0 = turn[0], c1 = turn[1], s0 = turn[2], s1 = turn[3];
     const float cs[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
     const float sn[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
     uint32_t lw[4] = {lo.u.x, lo.u.y, lo.u.z, lo.u.w}, hw[4] = {hi.u.x, hi.u.y, hi.u.z, hi.u.w};
@@ -409,42 +501,6 @@ __device__ inline void rope_frag8(Frag8& lo, Frag8& hi, const float* row, int i0
         lo.p[j] = __builtin_convertvector(va, bf16x2);
         hi.p[j] = __builtin_convertvector(vb, bf16x2);
     }
-}
-
-__device__ __forceinline__ uint32_t pack2(float a, float b) {
-    f32x2 v = {a, b};
-    union { bf16x2 p; uint32_t u; } o;
-    o.p = __builtin_convertvector(v, bf16x2);
-    return o.u;
-}
-
-// Stores one 32-wide block (head dims 32 db ..) of the wave's 32 output rows: `x` is an accumulator whose column is
-// the lane's row.  A lane holds pieces of four head dims, 8 bytes in bf16, of one row; stored like that, every store
-// instruction would scatter 32 pieces of 16 bytes.  Two rounds of lane swaps first: between the half-waves (the two
-// pieces of 8 bytes that make 16), then between the 16-lane halves of each (rows r and r + 16 trade 16-byte chunks),
-// after which an instruction writes 64 contiguous bytes of each of 16 rows.
-// `base`: row 0 of the wave's 32; `row_elems`: elements between rows; rows from n_rows on are not stored.
-__device__ __forceinline__ void store_block(uint16_t* base, size_t row_elems, int n_rows, int db, const f32x16& x, float factor, int l) {
-    uint32_t c[2][4];  // 16-byte chunks 2 k + g of the block, k = 0, 1
-#pragma unroll
-    for (int k = 0; k < 2; ++k)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int i = 8 * k + 2 * j;
-            const auto r = __builtin_amdgcn_permlane32_swap(pack2(x[i] * factor, x[i + 1] * factor), pack2(x[i + 4] * factor, x[i + 5] * factor), false, false);
-            c[k][j] = r[0];
-            c[k][2 + j] = r[1];
-        }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const auto r = __builtin_amdgcn_permlane16_swap(c[0][j], c[1][j], false, false);
-        c[0][j] = r[0];
-        c[1][j] = r[1];
-    }
-    const int row = l & 15;
-    uint16_t* p = base + row * row_elems + 32 * db + 16 * ((l >> 4) & 1) + 8 * (l >> 5);
-    if (row < n_rows) *reinterpret_cast<uint4*>(p) = make_uint4(c[0][0], c[0][1], c[0][2], c[0][3]);
-    if (row + 16 < n_rows) *reinterpret_cast<uint4*>(p + 16 * row_elems) = make_uint4(c[1][0], c[1][1], c[1][2], c[1][3]);
 }
 
 // Finished sums of a wave (accumulator whose column is the lane's row) that are not all finite, as bits: group 4 db + i4

@@ -90,6 +90,7 @@ __device__ inline void pair_masks(uint32_t (&mw)[2][8], int lo, int hi, int g) {
         }
 }
 
+__device__ inline uint32_t word(const uint4& v, int i) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; }
 __device__ inline float comp(const float4& v, int i) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; }
 
 // The LDS operands of the first kAhead slots (Q and dO rows of query block 0, head dims 0-31),
@@ -196,6 +197,7 @@ __global__ __launch_bounds__(256) void psattn_dkdv_bf16_mfma(AttnArgs a) {
     // tiles of Q (two buffers), of dO (two buffers) per group; then LSE * log2(e) and -delta
     __shared__ __attribute__((aligned(16))) char smem[S][4][kQTileBytes];
     __shared__ __attribute__((aligned(16))) float sStat[S][2][2][64];
+    __shared__ __attribute__((aligned(16))) char sRows[S == 1 ? 4 * 64 * kRowBytes : 1];  // K and V rows, later dK and dV rows, of each wave
     // a[0:191] are in use: makes the kernel's register allocation cover them
     asm volatile("" ::: "a0", "a191");
     const int tid = threadIdx.x, wg = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, c32 = l & 31, g = l >> 5;
@@ -208,34 +210,27 @@ __global__ __launch_bounds__(256) void psattn_dkdv_bf16_mfma(AttnArgs a) {
     const int key = row0 + c32;
     const bool kvalid = key < T;
     const int key_hi = kvalid ? a.meta.tok[key].key_hi : 0;  // queries [key, key_hi) read this key
-    const size_t koff = (static_cast<size_t>(key) * Hkv + kvh) * 128;
-
-    // K, V fragments of this lane's key -> a[128:191]; dK, dV accumulators a[0:127] = 0
-    static_for<0, 8>([&](auto TT) {
-        constexpr int t = decltype(TT)::value;
-        uint4 kv = make_uint4(0, 0, 0, 0), vv = make_uint4(0, 0, 0, 0);
-        if (kvalid) {
-            kv = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(a.K) + koff + 16 * t + 8 * g);
-            vv = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(a.V) + koff + 16 * t + 8 * g);
-        }
-        acc_set<kRegK + 4 * t + 0>(kv.x);
-        acc_set<kRegK + 4 * t + 1>(kv.y);
-        acc_set<kRegK + 4 * t + 2>(kv.z);
-        acc_set<kRegK + 4 * t + 3>(kv.w);
-        acc_set<kRegV + 4 * t + 0>(vv.x);
-        acc_set<kRegV + 4 * t + 1>(vv.y);
-        acc_set<kRegV + 4 * t + 2>(vv.z);
-        acc_set<kRegV + 4 * t + 3>(vv.w);
-    });
-    static_for<0, 128>([&](auto R) { acc_set<decltype(R)::value>(0u); });
-
     const float c = a.scale * kLog2e;
     LaneOffsets lo = lane_offsets(l);
+    const int l_nat = lo.nat;
     if constexpr (S > 1) {  // the group's tiles
         const int at = group * static_cast<int>(sizeof(smem[0]));
         lo.nat += at;
         lo.tr1 += at;
         lo.tr2 += at;
+    }
+    // K and V rows of the wave's keys pass through LDS: an unsplit row has room of its own, a split one takes its second buffers
+    char* const own = S == 1 ? sRows + 4 * kRowBytes * 16 * w : nullptr;
+    const Rows<128> k_rows = S == 1 ? Rows<128>{own, own + 16 * kRowBytes}
+                                    : Rows<128>{smem[group][1] + kRows * w * kRowBytes, smem[group][1] + (kRows * w + 16) * kRowBytes};
+    const Rows<128> v_rows = S == 1 ? Rows<128>{own + 32 * kRowBytes, own + 48 * kRowBytes}
+                                    : Rows<128>{smem[group][3] + kRows * w * kRowBytes, smem[group][3] + (kRows * w + 16) * kRowBytes};
+    const uint32_t k_row_bytes = static_cast<uint32_t>(Hkv) * kRowBytes;
+    {
+        const int last_row = min(max(T - 1 - row0, 0), 31);
+        const size_t at0 = (static_cast<size_t>(min(row0, T - 1)) * Hkv + kvh) * kRowBytes;
+        k_rows.copy_in(static_cast<const char*>(a.K) + at0, k_row_bytes, l, last_row);
+        v_rows.copy_in(static_cast<const char*>(a.V) + at0, k_row_bytes, l, last_row);
     }
     const int e0 = rl.begin, n_ent = rl.count;
     const int n_steps = n_ent * G;
@@ -307,6 +302,17 @@ __global__ __launch_bounds__(256) void psattn_dkdv_bf16_mfma(AttnArgs a) {
         static_for<0, kPieces>([&](auto P) { copy_piece(P, std::integral_constant<int, 0>{}); });
         advance(S);
     }
+    // dK, dV accumulators a[0:127] = 0; K, V fragments -> a[128:191]
+    static_for<0, 128>([&](auto R) { acc_set<decltype(R)::value>(0u); });
+    {
+        if (n_steps > 0) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * kOps) : "memory");  // the first tile's copies are younger
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        Frag8 f[8];
+        k_rows.operands(f, l, l_nat);
+        static_for<0, 32>([&](auto R) { acc_set<kRegK + decltype(R)::value>(word(f[decltype(R)::value / 4].u, decltype(R)::value % 4)); });
+        v_rows.operands(f, l, l_nat);
+        static_for<0, 32>([&](auto R) { acc_set<kRegV + decltype(R)::value>(word(f[decltype(R)::value / 4].u, decltype(R)::value % 4)); });
+    }
     // One tile; the buffer index is a compile-time constant, so every LDS address is a lane
     // constant plus an immediate offset.
     auto tile = [&](auto BUF) {
@@ -350,7 +356,7 @@ __global__ __launch_bounds__(256) void psattn_dkdv_bf16_mfma(AttnArgs a) {
             dkdv_tile<false, kPieces>(sQ, sG, sL, sD, lo, mw, c, g, ring, piece);
         }
     };
-    // The K / V loads above have retired before the loop starts, so the loop body holds no
+    // Every load above has retired before the loop starts, so the loop body holds no
     // wait on a compiler-tracked load (such a wait would also cover the copies in flight).
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
     settle();  // the register writes above, before the first MFMA reads them
@@ -361,7 +367,6 @@ __global__ __launch_bounds__(256) void psattn_dkdv_bf16_mfma(AttnArgs a) {
     // no copy may still be writing to LDS when the workgroup ends
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     settle();  // the last MFMAs, before dK / dV are read out
-    const size_t out0 = (static_cast<size_t>(row0) * Hkv + kvh) * 128, row_elems = static_cast<size_t>(Hkv) * 128;
     if constexpr (S > 1) {
         // Group 0 hands its dK to group 1, which hands its dV to group 0; each adds the other's part to its own.
         __syncthreads();  // every wave's reads and copies are done: the tiles' space is free
@@ -394,11 +399,18 @@ __global__ __launch_bounds__(256) void psattn_dkdv_bf16_mfma(AttnArgs a) {
         static_for<0, 16>([&](auto I) { x[decltype(I)::value] = acc_get<decltype(A0)::value + decltype(I)::value>(); });
         return x;
     };
-    if (S == 1 || group == 0)
-    static_for<0, 4>([&](auto DB) {
-        constexpr int db = decltype(DB)::value;
-        store_block(static_cast<uint16_t*>(a.dV) + out0, row_elems, T - row0, db, get(std::integral_constant<int, kAccDV + 16 * db>{}), 1.f, l);
-    });
+    // (a split row: the second group's tiles, which nobody uses any more)
+    const int lx = opaque(l);
+    char* const out = S == 1 ? own : &smem[S - 1][0][0] + wg * 32 * kRowBytes;
+    const Rows<128> out_rows{out, out + 16 * kRowBytes};
+    const size_t out0 = (static_cast<size_t>(row0) * Hkv + kvh) * kRowBytes;
+    if (S == 1 || group == 0) {
+        static_for<0, 4>([&](auto DB) {
+            constexpr int db = decltype(DB)::value;
+            out_rows.put(db, get(std::integral_constant<int, kAccDV + 16 * db>{}), 1.f, lx);
+        });
+        out_rows.copy_out(static_cast<char*>(a.dV) + out0, k_row_bytes, lx, T - row0);
+    }
     if (S > 1 && group == 0) return;
     if (a.rope) {
         // K arrived rotated: turn dK back by the key's angles (accumulator element 4 i4 + k of block
@@ -420,15 +432,16 @@ __global__ __launch_bounds__(256) void psattn_dkdv_bf16_mfma(AttnArgs a) {
                     y[4 * i4 + k] = hi;
                 }
             }
-            store_block(static_cast<uint16_t*>(a.dK) + out0, row_elems, T - row0, db, x, a.scale, l);
-            store_block(static_cast<uint16_t*>(a.dK) + out0, row_elems, T - row0, db + 2, y, a.scale, l);
+            out_rows.put(db, x, a.scale, lx);
+            out_rows.put(db + 2, y, a.scale, lx);
         });
     } else {
         static_for<0, 4>([&](auto DB) {
             constexpr int db = decltype(DB)::value;
-            store_block(static_cast<uint16_t*>(a.dK) + out0, row_elems, T - row0, db, get(std::integral_constant<int, kAccDK + 16 * db>{}), a.scale, l);
+            out_rows.put(db, get(std::integral_constant<int, kAccDK + 16 * db>{}), a.scale, lx);
         });
     }
+    out_rows.copy_out(static_cast<char*>(a.dK) + out0, k_row_bytes, lx, T - row0);
 }
 
 }  // namespace

@@ -27,6 +27,7 @@ __global__ __launch_bounds__(256, 2) void psattn_dkdv64_bf16_mfma(AttnArgs a) {
     // tiles of Q (two buffers), of dO (two buffers) per group; then LSE * log2(e) and -delta
     __shared__ __attribute__((aligned(16))) char smem[S][4][64 * kRB];
     __shared__ __attribute__((aligned(16))) float sStat[S][2][2][64];
+    __shared__ __attribute__((aligned(16))) char sRows[S == 1 ? 4 * 64 * kRB : 1];  // K and V rows, later dK and dV rows, of each wave
     const int tid = threadIdx.x, wg = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, c32 = l & 31, g = l >> 5;
     const int group = S == 1 ? 0 : wg / kWaves, w = S == 1 ? wg : wg % kWaves;  // wave index in its group
     const int T = a.meta.T, Hq = a.Hq, Hkv = a.Hkv, G = Hq / Hkv;
@@ -37,14 +38,18 @@ __global__ __launch_bounds__(256, 2) void psattn_dkdv64_bf16_mfma(AttnArgs a) {
     const int key = row0 + c32;
     const bool kvalid = key < T;
     const int key_hi = kvalid ? a.meta.tok[key].key_hi : 0;  // queries [key, key_hi) read this key
-    const size_t koff = (static_cast<size_t>(key) * Hkv + kvh) * 64;
-
-    Frag8 kf[4], vf[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        kf[t].u = kvalid ? *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(a.K) + koff + 16 * t + 8 * g) : make_uint4(0, 0, 0, 0);
-        vf[t].u = kvalid ? *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(a.V) + koff + 16 * t + 8 * g) : make_uint4(0, 0, 0, 0);
+    // K and V rows of the wave's keys pass through LDS: an unsplit row has room of its own, a split one takes its second buffers
+    char *const k_at = S == 1 ? sRows + 64 * kRB * w : smem[group][1] + kRows * w * kRB;
+    char *const v_at = S == 1 ? k_at + 32 * kRB : smem[group][3] + kRows * w * kRB;
+    const Rows<64> k_rows{k_at, k_at + 16 * kRB}, v_rows{v_at, v_at + 16 * kRB};
+    const uint32_t k_row_bytes = static_cast<uint32_t>(Hkv) * kRB;
+    {
+        const int last_row = min(max(T - 1 - row0, 0), 31);
+        const size_t at0 = (static_cast<size_t>(min(row0, T - 1)) * Hkv + kvh) * kRB;
+        k_rows.copy_in(static_cast<const char*>(a.K) + at0, k_row_bytes, l, last_row);
+        v_rows.copy_in(static_cast<const char*>(a.V) + at0, k_row_bytes, l, last_row);
     }
+    Frag8 kf[4], vf[4];
     f32x16 dk[2], dv[2];
 #pragma unroll
     for (int db = 0; db < 2; ++db)
@@ -53,6 +58,7 @@ __global__ __launch_bounds__(256, 2) void psattn_dkdv64_bf16_mfma(AttnArgs a) {
 
     const float c = a.scale * kLog2e;
     LaneOffsets lo = lane_offsets<64>(l);
+    const int l_nat = lo.nat;
     if constexpr (S > 1) {  // the group's tiles
         const int at = group * static_cast<int>(sizeof(smem[0]));
         lo.nat += at;
@@ -221,6 +227,11 @@ __global__ __launch_bounds__(256, 2) void psattn_dkdv64_bf16_mfma(AttnArgs a) {
     // every compiler-tracked load above has retired before the loop starts, so the loop body holds no wait of the
     // compiler's that would also cover copies in flight
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+    k_rows.operands(kf, l, l_nat);
+    v_rows.operands(vf, l, l_nat);
+    // in registers before a copy takes their place
+#pragma unroll
+    for (int t = 0; t < 4; ++t) asm volatile("" : "+v"(kf[t].v), "+v"(vf[t].v)::"memory");
     while (it + 1 < n_loop) {
         tile(std::integral_constant<int, 0>{});
         tile(std::integral_constant<int, 1>{});
@@ -228,7 +239,6 @@ __global__ __launch_bounds__(256, 2) void psattn_dkdv64_bf16_mfma(AttnArgs a) {
     if (it < n_loop) tile(std::integral_constant<int, 0>{});
     // no copy may still be writing to LDS when the workgroup ends
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    const size_t out0 = (static_cast<size_t>(row0) * Hkv + kvh) * 64, row_elems = static_cast<size_t>(Hkv) * 64;
     if constexpr (S > 1) {
         // Group 0 hands its dK to group 1, which hands its dV to group 0; each adds the other's part to its own.
         __syncthreads();  // every wave's reads and copies are done: the tiles' space is free
@@ -262,10 +272,20 @@ __global__ __launch_bounds__(256, 2) void psattn_dkdv64_bf16_mfma(AttnArgs a) {
         for (AgainGroups n(not_finite_groups(dk), row0, T); n.any(); n.next())
             set_group(dk, n.group(), exact_dkdv<uint16_t, 64, true, -1>(a, kvh, n.row, n.dim()));
     if constexpr (S > 1) __syncthreads();
+    // (a split row: the second group's tiles, which nobody uses any more)
+    const int lx = opaque(l);
+    char* const out = S == 1 ? k_at : &smem[S - 1][0][0] + wg * 32 * kRB;
+    const Rows<64> out_rows{out, out + 16 * kRB};
+    const size_t out0 = (static_cast<size_t>(row0) * Hkv + kvh) * kRB;
+    if (S == 1 || group == 0) {
 #pragma unroll
-    for (int db = 0; db < 2; ++db) {
-        if (S == 1 || group == 0) store_block(static_cast<uint16_t*>(a.dV) + out0, row_elems, T - row0, db, dv[db], 1.f, l);
-        if (S == 1 || group == 1) store_block(static_cast<uint16_t*>(a.dK) + out0, row_elems, T - row0, db, dk[db], 1.f, l);
+        for (int db = 0; db < 2; ++db) out_rows.put(db, dv[db], 1.f, lx);
+        out_rows.copy_out(static_cast<char*>(a.dV) + out0, k_row_bytes, lx, T - row0);
+    }
+    if (S == 1 || group == 1) {
+#pragma unroll
+        for (int db = 0; db < 2; ++db) out_rows.put(db, dk[db], 1.f, lx);
+        out_rows.copy_out(static_cast<char*>(a.dK) + out0, k_row_bytes, lx, T - row0);
     }
 }
 

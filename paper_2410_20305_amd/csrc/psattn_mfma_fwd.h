@@ -33,23 +33,26 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(At
     const uint16_t* K = static_cast<const uint16_t*>(a.K) + kvh * D;
     const uint16_t* V = static_cast<const uint16_t*>(a.V) + kvh * D;
 
-    Frag8 qf[kSteps];
-#pragma unroll
-    for (int t = 0; t < kSteps; ++t)
-        qf[t].u = valid ? *reinterpret_cast<const uint4*>(Q + (static_cast<size_t>(q_row) * Hq + h) * D + 16 * t + 8 * g)
-                        : make_uint4(0, 0, 0, 0);
-
+    // Q passes through the places of buffer 1 that the wave's own K / V copies take later
+    const LaneOffsets lo = lane_offsets<D>(l);
+    const uint32_t q_row_bytes = static_cast<uint32_t>(Hq) * kRB;
+    const Rows<D> rows1{sKb[1] + 16 * w * kRB, sVb[1] + 16 * w * kRB};
+    // rotary embedding: the table row of this lane's query, both members of a pair in the same lane
+    float4 turn[D == 128 ? 16 : 1];
     if constexpr (D == 128) if (a.rope) {
-        // rotary embedding of this lane's query in registers; the rotated row is also saved for
-        // the backward, which streams Q tiles straight into LDS and cannot rotate them on the way
         const float* row = a.rope + static_cast<size_t>(rope_position(tk, q_row)) * 128;
 #pragma unroll
-        for (int t = 0; t < 4; ++t) rope_frag8(qf[t], qf[t + 4], row, 16 * t + 8 * g);
-        if (valid && a.Qr) {
-            uint16_t* qr = static_cast<uint16_t*>(a.Qr) + (static_cast<size_t>(q_row) * Hq + h) * 128;
+        for (int t = 0; t < 4; ++t) rope_load8(turn + 4 * t, row, 16 * t + 8 * g);
+    }
+    Frag8 qf[kSteps];
+    // (the asynchronous copies move 16-byte groups; a Q that does not start on one is loaded straight into the registers)
+    const bool straight = D == 128 && (reinterpret_cast<uintptr_t>(a.Q) & 15) != 0;
+    if (straight) {
 #pragma unroll
-            for (int t = 0; t < 8; ++t) *reinterpret_cast<uint4*>(qr + 16 * t + 8 * g) = qf[t].u;
-        }
+        for (int t = 0; t < kSteps; ++t)
+            qf[t].u = valid ? *reinterpret_cast<const uint4*>(Q + (static_cast<size_t>(q_row) * Hq + h) * D + 16 * t + 8 * g) : make_uint4(0, 0, 0, 0);
+    } else {
+        rows1.copy_in(reinterpret_cast<const char*>(Q) + (static_cast<size_t>(min(row0, T - 1)) * Hq + h) * kRB, q_row_bytes, l, min(max(T - 1 - row0, 0), 31));
     }
     f32x16 o[kBlocks];
 #pragma unroll
@@ -58,7 +61,6 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(At
         for (int i = 0; i < 16; ++i) o[db][i] = 0.f;
     float m = -INFINITY, lsum = 0.f;
     const float c = a.scale * kLog2e;
-    const LaneOffsets lo = lane_offsets<D>(l);
     constexpr int kAhead = 2, kRing = 4;  // measured: 1 and 3 are both slower
 
     // K / V tiles are copied global -> LDS asynchronously, one tile ahead, into the
@@ -86,6 +88,7 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(At
     }
     if (qb.together && n_ent <= 64)
         while (it + 1 < n_ent && !reads_tile(es.peek(n_ent - 1), row0, tk)) --n_ent;
+    const int n_tiles = n_ent - it;
     // One tile.  The buffer index is a compile-time constant (the loop below is unrolled
     // by two), so every LDS address is a lane constant plus an immediate offset.
     auto tile = [&](auto BUF) {
@@ -213,6 +216,20 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(At
     // Q fragments are in registers before the loop starts, so the loop body holds no wait
     // on a compiler-tracked load (such a wait would also cover the copies in flight)
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+    if (!straight) rows1.operands(qf, l, lo.nat);
+    if constexpr (D == 128) if (a.rope) {
+        // the rotated row is also saved for the backward, which streams Q tiles straight into LDS and cannot rotate them on the way
+#pragma unroll
+        for (int t = 0; t < 4; ++t) rope_frag8(qf[t], qf[t + 4], turn + 4 * t);
+        if (a.Qr) {
+            rows1.put_operands(qf, l, lo.nat);
+            rows1.copy_out(static_cast<char*>(a.Qr) + (static_cast<size_t>(row0) * Hq + h) * kRB, q_row_bytes, l, T - row0);
+        }
+    }
+    // ... and the place in LDS is done with before the second tile's copies take it
+#pragma unroll
+    for (int t = 0; t < kSteps; ++t) asm volatile("" : "+v"(qf[t].v)::"memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
     while (it + 1 < n_ent) {
         tile(std::integral_constant<int, 0>{});
         tile(std::integral_constant<int, 1>{});
@@ -222,7 +239,6 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(At
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     const float l_tot = lsum + other_half(lsum);
     const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-    uint16_t* orow = static_cast<uint16_t*>(a.Oout) + (static_cast<size_t>(row0) * Hq + h) * D;
     multiply(o, inv);
     if constexpr (D == 64) {
         // sums that are not finite, and rows without a sum, are taken again (psattn_exact.h)
@@ -230,8 +246,12 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(At
         if (!(l_tot > 0.f) && tk.s != kPadStart) again = 0xff;
         for (AgainGroups n(again, row0, T); n.any(); n.next()) set_group(o, n.group(), exact_o<uint16_t, D>(a, h, n.row, n.dim()));
     }
+    // the buffer that the last tile was not in
+    const int lx = opaque(l);
+    const Rows<D> rows{sKb[n_tiles & 1] + 16 * w * kRB, sVb[n_tiles & 1] + 16 * w * kRB};
 #pragma unroll
-    for (int db = 0; db < kBlocks; ++db) store_block(orow, static_cast<size_t>(Hq) * D, T - row0, db, o[db], 1.f, l);
+    for (int db = 0; db < kBlocks; ++db) rows.put(db, o[db], 1.f, lx);
+    rows.copy_out(static_cast<char*>(a.Oout) + (static_cast<size_t>(row0) * Hq + h) * kRB, q_row_bytes, lx, T - row0);
     if (valid && g == 0)
         a.LSEout[static_cast<size_t>(h) * T + q_row] = l_tot > 0.f ? m * kLn2 + __logf(l_tot) : -INFINITY;
 }

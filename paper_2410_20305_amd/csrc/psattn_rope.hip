@@ -47,7 +47,9 @@ __global__ __launch_bounds__(256) void psattn_rope_k_bf16(DeviceMeta meta, int H
     Frag8 lo, hi;
     lo.u = *reinterpret_cast<const uint4*>(K + row * 128 + 8 * chunk);
     hi.u = *reinterpret_cast<const uint4*>(K + row * 128 + 64 + 8 * chunk);
-    rope_frag8(lo, hi, trow, 8 * chunk);
+    float4 turn[4];
+    rope_load8(turn, trow, 8 * chunk);
+    rope_frag8(lo, hi, turn);
     *reinterpret_cast<uint4*>(Kr + row * 128 + 8 * chunk) = lo.u;
     *reinterpret_cast<uint4*>(Kr + row * 128 + 64 + 8 * chunk) = hi.u;
 }

@@ -110,7 +110,9 @@ enum { PSATTN_GRID_FWD = 0, /* q-major CSR, used by psattn_fwd and the dQ pass  
  *
  * psattn_build_meta uploads the metadata to the current device with one
  * asynchronous kernel on hip_stream that reads the pinned staging buffer (which stays
- * alive inside the object).  Tile grids with 2^29 or more tiles along an axis, or more than
+ * alive inside the object).  Small masks (up to 1 024 tokens, 8 runs of equal
+ * descriptors, 8 rows of 16 tiles in either grid) need neither kernel nor buffers: they
+ * travel with the arguments of every kernel that reads them.  Tile grids with 2^29 or more tiles along an axis, or more than
  * INT32_MAX non-skipped tiles, are refused with PSATTN_EUNSUPPORTED.
  * psattn_build_meta_host builds the same object without touching any device (for
  * inspection and planning); kernels refuse it with PSATTN_ENODEVICE.

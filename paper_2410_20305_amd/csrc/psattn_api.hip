@@ -42,25 +42,12 @@ BlobLayout layout_of(const psattn_meta& m) {
 }
 
 // walk_backwards: the kernel of this grid starts with the last entry of a row
-void fill_csr(char* base, size_t ent, size_t lch, const TileCsr& g, bool walk_backwards) {
-    if (!g.entry.empty()) std::memcpy(base + ent, g.entry.data(), g.entry.size() * sizeof(int32_t));
-    RowLaunch* rl = reinterpret_cast<RowLaunch*>(base + lch);
+void fill_csr(int32_t* entry, RowLaunch* rl, const TileCsr& g, bool walk_backwards) {
+    if (!g.entry.empty()) std::memcpy(entry, g.entry.data(), g.entry.size() * sizeof(int32_t));
     for (size_t i = 0; i < g.order.size(); ++i) {
         const int32_t r = g.order[i], b = g.row_ptr[r], n = g.row_ptr[r + 1] - b;
         rl[i] = RowLaunch{r, b, n, n > 0 ? g.entry[walk_backwards ? b + n - 1 : b] : 0};
     }
-}
-
-DeviceCsr view_csr(const char* lists, size_t ent, size_t lch, const TileCsr& g) {
-    DeviceCsr v{};
-    v.entry = reinterpret_cast<const int32_t*>(lists + ent);
-    v.launch = reinterpret_cast<const RowLaunch*>(lists + lch);
-    v.n_rows = static_cast<int32_t>(g.row_ptr.size()) - 1;
-    v.n_entries = static_cast<int64_t>(g.entry.size());
-    for (int32_t r = 0; r < v.n_rows; ++r) v.longest = std::max(v.longest, g.row_ptr[r + 1] - g.row_ptr[r]);
-    v.tile_q = g.tile_q;
-    v.tile_k = g.tile_k;
-    return v;
 }
 
 // ---- pooled metadata blobs
@@ -149,9 +136,57 @@ void release_blob(Blob b, hipStream_t stream) {
     if (drop.d) destroy_blob(drop);
 }
 
+// A mask that fits travels with the kernels' arguments (psattn_mask.h).
+bool put_in_args(psattn_meta& m) {
+    const size_t n = m.seg_tok.size();
+    if (m.T == 0 || m.T > kSmallTokens || n > kSmallRuns) return false;
+    SmallMask s{};
+    for (size_t i = 0; i < kSmallRuns; ++i) {
+        uint64_t x = kSmallNone;
+        if (i < n) {
+            const Tok4& t = m.seg_tok[i];
+            const int32_t f[5] = {m.seg_start[i], t.s == kPadStart ? static_cast<int32_t>(kSmallNone) : t.s, t.hole_lo, t.hole_hi, t.key_hi};
+            x = 0;
+            for (int k = 0; k < 5; ++k) x |= static_cast<uint64_t>(static_cast<uint32_t>(f[k])) << (kSmallField * k);
+        }
+        s.run[i] = x;
+    }
+    const TileCsr* grid[2] = {&m.fwd, &m.bwd};
+    for (int g = 0; g < 2; ++g) {
+        const TileCsr& c = *grid[g];
+        if (c.order.size() > kSmallRows) return false;
+        for (size_t i = 0; i < c.order.size(); ++i) {
+            const int32_t r = c.order[i];
+            uint32_t tiles = 0;
+            for (int32_t k = c.row_ptr[r]; k < c.row_ptr[r + 1]; ++k) {
+                const int32_t tile = c.entry[k] >> 2;
+                if (tile >= kSmallTiles) return false;
+                tiles |= ((c.entry[k] & 3) == PSATTN_TILE_FULL ? 0x10001u : 1u) << tile;
+            }
+            s.tiles[g][i] = tiles;
+            s.row[g] |= static_cast<uint32_t>(r) << (4 * i);
+        }
+    }
+    m.dev.small = s;
+    m.dev.in_args = 1;
+    return true;
+}
+
 int upload(psattn_meta* m, hipStream_t stream) {
-    const BlobLayout L = layout_of(*m);
     if (hipGetDevice(&m->device) != hipSuccess) return PSATTN_EHIP;
+    m->dev.T = m->T;
+    const TileCsr* grid[2] = {&m->fwd, &m->bwd};
+    for (int g = 0; g < 2; ++g) {
+        const int32_t n = static_cast<int32_t>(grid[g]->order.size());
+        m->dev.n_rows[g] = n;
+        m->size[g].n_entries = static_cast<int64_t>(grid[g]->entry.size());
+        for (int32_t r = 0; r < n; ++r) m->size[g].longest = std::max(m->size[g].longest, grid[g]->row_ptr[r + 1] - grid[g]->row_ptr[r]);
+    }
+    if (put_in_args(*m)) {
+        m->on_device = true;
+        return PSATTN_OK;
+    }
+    const BlobLayout L = layout_of(*m);
     const size_t on_device = L.tok + L.lists;
     Blob b;
     const int rc = acquire_blob(std::max(L.staged, on_device), m->device, &b);
@@ -162,8 +197,8 @@ int upload(psattn_meta* m, hipStream_t stream) {
     m->blob_cap = b.cap;
     m->blob_idle = b.idle;
     char* h = static_cast<char*>(m->h_stage);
-    fill_csr(h, L.f_ent, L.f_lch, m->fwd, false);
-    fill_csr(h, L.b_ent, L.b_lch, m->bwd, true);
+    fill_csr(reinterpret_cast<int32_t*>(h + L.f_ent), reinterpret_cast<RowLaunch*>(h + L.f_lch), m->fwd, false);
+    fill_csr(reinterpret_cast<int32_t*>(h + L.b_ent), reinterpret_cast<RowLaunch*>(h + L.b_lch), m->bwd, true);
     const int32_t n_seg = static_cast<int32_t>(m->seg_tok.size()), n_blocks = upload_blocks(m->T);
     std::memcpy(h + L.seg_start, m->seg_start.data(), m->seg_start.size() * sizeof(int32_t));
     if (n_seg > 0) std::memcpy(h + L.seg_tok, m->seg_tok.data(), m->seg_tok.size() * sizeof(Tok4));
@@ -188,10 +223,12 @@ int upload(psattn_meta* m, hipStream_t stream) {
     u.n_units = static_cast<int32_t>(L.lists / 16);
     if (launch_upload(u, stream) != 0) return PSATTN_EHIP;
     m->blob_bytes = on_device;
-    m->dev.tok = reinterpret_cast<const Tok4*>(d);
-    m->dev.fwd = view_csr(d + L.tok, L.f_ent, L.f_lch, m->fwd);
-    m->dev.bwd = view_csr(d + L.tok, L.b_ent, L.b_lch, m->bwd);
-    m->dev.T = m->T;
+    const char* lists = d + L.tok;
+    m->dev.list.tok = reinterpret_cast<const Tok4*>(d);
+    m->dev.list.entry[0] = reinterpret_cast<const int32_t*>(lists + L.f_ent);
+    m->dev.list.entry[1] = reinterpret_cast<const int32_t*>(lists + L.b_ent);
+    m->dev.list.launch[0] = reinterpret_cast<const RowLaunch*>(lists + L.f_lch);
+    m->dev.list.launch[1] = reinterpret_cast<const RowLaunch*>(lists + L.b_lch);
     m->on_device = true;
     return PSATTN_OK;
 }
@@ -289,6 +326,7 @@ int bwd_checked(const psattn_meta* meta, int32_t dt, int32_t n_q_heads, int32_t 
     if (scratch_bytes < bwd_scratch_bytes(meta, n_q_heads)) return PSATTN_EINVAL;
     AttnArgs a{};
     a.meta = meta->dev;
+    std::copy_n(meta->size, 2, a.size);
     a.Hq = n_q_heads; a.Hkv = n_kv_heads; a.d = head_dim; a.scale = scale;
     a.Q = Q; a.K = K; a.V = V; a.O = O; a.dO = dO; a.LSE = LSE;
     a.dQ = dQ; a.dK = dK; a.dV = dV;
@@ -337,6 +375,7 @@ int fwd_checked(const psattn_meta* meta, int32_t dt, int32_t n_q_heads, int32_t 
     if (!Q || !K || !V || !O || !LSE) return PSATTN_EINVAL;
     AttnArgs a{};
     a.meta = meta->dev;
+    std::copy_n(meta->size, 2, a.size);
     a.Hq = n_q_heads; a.Hkv = n_kv_heads; a.d = head_dim; a.scale = scale;
     a.Q = Q; a.K = K; a.V = V; a.Oout = O; a.LSEout = LSE;
     a.rope = rope_table; a.Qr = Qr;

@@ -12,7 +12,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
-#include "psattn_internal.h"
+#include "psattn_mask.h"
 
 namespace psattn {
 
@@ -83,6 +83,14 @@ __device__ inline void exact_keys(const Tok4& t, int q, F f) {
         if (allowed(t, q, k) && !f(k)) return;
 }
 
+// The scale, loaded on its own.  (Multiplying four values by it, the compiler loads the 16 bytes of the arguments that it starts,
+// and for that copies the arguments around them to scratch memory.)
+__device__ __forceinline__ float scale_of(const AttnArgs& a) {
+    float x = a.scale;
+    asm volatile("" : "+s"(x));
+    return x;
+}
+
 // head dims d .. d + 3 of O
 template <typename E, int D>
 __device__ inline f32x4 exact_o(const AttnArgs& a, int h, int q, int d) {
@@ -90,7 +98,7 @@ __device__ inline f32x4 exact_o(const AttnArgs& a, int h, int q, int d) {
     const E* qr = exact_row<E, D>(a.Q, q, a.Hq, h);
     float m = -INFINITY, l = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    exact_keys(a.meta.tok[q], q, [&](int k) {
+    exact_keys(token(a.meta, q), q, [&](int k) {
         const float s = exact_dot<D>(qr, exact_row<E, D>(a.K, k, a.Hkv, kvh)) * a.scale;
         const float mn = fmaxf(m, s), alpha = expf(m - mn), p = expf(s - mn);  // m = -inf the first time: alpha = 0
         const f32x4 v = ld4(exact_row<E, D>(a.V, k, a.Hkv, kvh) + d);
@@ -110,7 +118,7 @@ __device__ inline f32x4 exact_dq(const AttnArgs& a, int h, int q, int d, float d
     const E *qr = exact_row<E, D>(a.Q, q, a.Hq, h), *gr = exact_row<E, D>(a.dO, q, a.Hq, h);
     const float lse = a.LSE[static_cast<size_t>(h) * a.meta.T + q];
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    exact_keys(a.meta.tok[q], q, [&](int k) {
+    exact_keys(token(a.meta, q), q, [&](int k) {
         const E* kr = exact_row<E, D>(a.K, k, a.Hkv, kvh);
         const float p = expf(exact_dot<D>(qr, kr) * a.scale - lse);
         const float ds = p * (exact_dot<D>(gr, exact_row<E, D>(a.V, k, a.Hkv, kvh)) - delta);
@@ -119,13 +127,13 @@ __device__ inline f32x4 exact_dq(const AttnArgs& a, int h, int q, int d, float d
         for (int c = 0; c < 4; ++c) acc[c] = fmaf(ds, x[c], acc[c]);
         return !all_nan(acc);
     });
-    return acc * a.scale;
+    return acc * scale_of(a);
 }
 
 // the same of dK (DK) or dV.  DELTA: a.delta holds delta (1) or its negative (-1), or delta is summed from O and dO (0)
 template <typename E, int D, bool DK, int DELTA>
 __device__ inline f32x4 exact_dkdv(const AttnArgs& a, int kvh, int key, int d) {
-    const int G = a.Hq / a.Hkv, q_hi = a.meta.tok[key].key_hi;  // queries [key, q_hi) read this key
+    const int G = a.Hq / a.Hkv, q_hi = token(a.meta, key).key_hi;  // queries [key, q_hi) read this key
     const E *kr = exact_row<E, D>(a.K, key, a.Hkv, kvh), *vr = exact_row<E, D>(a.V, key, a.Hkv, kvh);
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma nounroll
@@ -143,7 +151,7 @@ __device__ inline f32x4 exact_dkdv(const AttnArgs& a, int kvh, int key, int d) {
 #pragma unroll
             for (int c = 0; c < 4; ++c) acc[c] = fmaf(p, x[c], acc[c]);
         }
-    return DK ? acc * a.scale : acc;
+    return DK ? acc * scale_of(a) : acc;
 }
 
 }  // namespace psattn

@@ -140,6 +140,7 @@ __device__ inline f32x4 sum_partials(const Partials<D>& sm, int row, int d) {
 // ---------------------------------------------------------------- forward
 template <typename E, int D>
 __global__ __launch_bounds__(kThreads) void generic_fwd(AttnArgs a, int first) {
+    fetch_args(a);
     __shared__ Partials<D> sm;
     __shared__ float s_m[kWaves][kB], s_l[kWaves][kB];
     const int T = a.meta.T, Hq = a.Hq, Hkv = a.Hkv, n_blocks = (T - 1) / kB + 1;
@@ -147,10 +148,10 @@ __global__ __launch_bounds__(kThreads) void generic_fwd(AttnArgs a, int first) {
     const int block = first + static_cast<int>(blockIdx.x);
     const int h = block % Hq, kvh = h / (Hq / Hkv), q0 = kB * (n_blocks - 1 - block / Hq);
     const int q = q0 + r;
-    Tok4 tk = {kPadStart, 0, 0, 0};
-    if (q < T) tk = a.meta.tok[q];
+    Tok4 tk = token_begin(a.meta, q);
     f32x4 qf[D / 16], acc[D / 16];
     load_rows<E, D>(qf, row_of<E, D>(a.Q, q, T, Hq, h), g);
+    tk = token_end(tk, a.meta, q);
 #pragma unroll
     for (int b = 0; b < D / 16; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
     const KeyRange kr = key_range(tk, q0, T);
@@ -213,11 +214,11 @@ __device__ inline void dq_block(const AttnArgs& a, Partials<D>& sm, int block) {
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), r = tid & 15, g = (tid >> 4) & 3;
     const int h = block % Hq, kvh = h / (Hq / Hkv), q0 = kB * (n_blocks - 1 - block / Hq);
     const int q = q0 + r;
-    Tok4 tk = {kPadStart, 0, 0, 0};
-    if (q < T) tk = a.meta.tok[q];
+    Tok4 tk = token_begin(a.meta, q);
     f32x4 qf[D / 16], gf[D / 16], acc[D / 16];
     load_rows<E, D>(qf, row_of<E, D>(a.Q, q, T, Hq, h), g);
     load_rows<E, D>(gf, row_of<E, D>(a.dO, q, T, Hq, h), g);
+    tk = token_end(tk, a.meta, q);
     const float lse = a.LSE[static_cast<size_t>(h) * T + min(q, T - 1)];
     float delta = 0.f;
     {
@@ -251,7 +252,7 @@ __device__ inline void dq_block(const AttnArgs& a, Partials<D>& sm, int block) {
     __syncthreads();
     int row, d;
     if (!my_quad<D>(tid, row, d) || q0 + row >= T) return;
-    f32x4 dq = sum_partials<D>(sm, row, d) * a.scale;
+    f32x4 dq = sum_partials<D>(sm, row, d) * scale_of(a);
     if (!is_finite(dq)) dq = exact_dq<E, D>(a, h, q0 + row, d, a.delta[static_cast<size_t>(h) * T + q0 + row]);
     st4(static_cast<E*>(a.dQ) + (static_cast<size_t>(q0 + row) * Hq + h) * D + d, dq);
 }
@@ -264,7 +265,9 @@ __device__ inline void dkdv_block(const AttnArgs& a, Partials<D>& sm, int block)
     const int T = a.meta.T, Hq = a.Hq, Hkv = a.Hkv, G = Hq / Hkv;
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), r = tid & 15, g = (tid >> 4) & 3;
     const int kvh = block % Hkv, k0 = kB * (block / Hkv), key = k0 + r;
-    const int key_hi = key < T ? a.meta.tok[key].key_hi : 0;  // queries [key, key_hi) read this key
+    Tok4 tk = token_begin(a.meta, key);
+    tk = token_end(tk, a.meta, key);
+    const int key_hi = tk.key_hi;  // queries [key, key_hi) read this key
     f32x4 kf[D / 16], vf[D / 16], dk[D / 16], dv[D / 16];
     load_rows<E, D>(kf, row_of<E, D>(a.K, key, T, Hkv, kvh), g);
     load_rows<E, D>(vf, row_of<E, D>(a.V, key, T, Hkv, kvh), g);
@@ -318,7 +321,7 @@ __device__ inline void dkdv_block(const AttnArgs& a, Partials<D>& sm, int block)
     f32x4 xk = {0.f, 0.f, 0.f, 0.f}, xv = xk;
     put_partial<D>(sm, dk, w, r, g);
     __syncthreads();
-    if (mine) xk = sum_partials<D>(sm, row, d) * a.scale;
+    if (mine) xk = sum_partials<D>(sm, row, d) * scale_of(a);
     __syncthreads();
     put_partial<D>(sm, dv, w, r, g);
     __syncthreads();
@@ -336,17 +339,20 @@ __device__ inline void dkdv_block(const AttnArgs& a, Partials<D>& sm, int block)
 
 template <typename E, int D>
 __global__ __launch_bounds__(kThreads) void generic_dq(AttnArgs a, int first) {
+    fetch_args(a);
     __shared__ Partials<D> sm;
     dq_block<E, D>(a, sm, first + static_cast<int>(blockIdx.x));
 }
 template <typename E, int D>
 __global__ __launch_bounds__(kThreads) void generic_dkdv(AttnArgs a, int first) {
+    fetch_args(a);
     __shared__ Partials<D> sm;
     dkdv_block<E, D, false>(a, sm, first + static_cast<int>(blockIdx.x));
 }
 // both at once: neither needs anything of the other
 template <typename E, int D>
 __global__ __launch_bounds__(kThreads) void generic_bwd(AttnArgs a, int first) {
+    fetch_args(a);
     __shared__ Partials<D> sm;
     const int block = first + static_cast<int>(blockIdx.x), n_dkdv = ((a.meta.T - 1) / kB + 1) * a.Hkv;
     if (block < n_dkdv) dkdv_block<E, D, true>(a, sm, block);

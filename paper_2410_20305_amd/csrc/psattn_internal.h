@@ -12,6 +12,7 @@
 namespace psattn {
 
 constexpr int32_t kPadStart = INT32_MAX;
+constexpr int kGridQ = 0, kGridK = 1;  // q-major, k-major grid
 
 // Default tile grids = the shapes the bf16 MFMA kernels are built for.
 constexpr int32_t kFwdTileQ = 128;
@@ -39,25 +40,43 @@ struct alignas(16) RowLaunch {
                           // entry[begin + count - 1] for the k-major one (walked backwards)
 };
 
-// Device-side view handed to kernels by value.
-struct DeviceCsr {
-    const int32_t* entry;  // (idx << 2) | cls
-    const RowLaunch* launch;  // [n_rows], in launch order
-    int32_t n_rows;
-    int32_t tile_q, tile_k;
-    int32_t longest;    // entries of the longest row
-    int64_t n_entries;  // of all rows
-};
-
 // Per-token descriptor as the kernels read it (one 16-byte load).
 struct alignas(16) Tok4 {
     int32_t s, hole_lo, hole_hi, key_hi;
 };
 
+// A block mask that is small enough to travel with every kernel's arguments instead of being brought onto the device first
+// (psattn_mask.h reads it): at most kSmallTokens tokens in kSmallRuns runs of equal descriptors, kSmallRows rows of tiles in
+// either grid and 16 tiles the other way.  Index 0: q-major grid, 1: k-major grid.
+constexpr int kSmallTokens = 1024, kSmallRuns = 8, kSmallRows = 8, kSmallTiles = 16;
+constexpr int kSmallField = 11;                            // bits of a token number; all set: none
+constexpr uint32_t kSmallNone = (1u << kSmallField) - 1;
+struct SmallMask {
+    uint64_t run[kSmallRuns];           // first token | s | hole_lo | hole_hi | key_hi; s is none for padding, first token is none for an unused run
+    uint32_t tiles[2][kSmallRows];      // in launch order: bits 0 - 15 the tiles of the row's list, 16 - 31 those that are FULL
+    uint32_t row[2];                    // 4 bits for each position of the launch order
+};
+
+// Device-side view handed to kernels by value; grid 0: q-major, 1: k-major.
 struct DeviceMeta {
-    const Tok4* tok;        // [T]
-    DeviceCsr fwd, bwd;
+    struct Lists {
+        const Tok4* tok;             // [T]
+        const int32_t* entry[2];     // (idx << 2) | cls
+        const RowLaunch* launch[2];  // [n_rows], in launch order
+    };
     int32_t T;
+    int32_t in_args;
+    int32_t n_rows[2];
+    union {
+        Lists list;
+        SmallMask small;             // where in_args
+    };
+};
+
+// What the launchers want to know of a grid.
+struct GridSize {
+    int32_t longest;    // entries of the longest row
+    int64_t n_entries;  // of all rows
 };
 
 }  // namespace psattn
@@ -82,6 +101,7 @@ struct psattn_meta {
     size_t blob_cap = 0;      // bytes allocated
     void* blob_idle = nullptr;  // hipEvent_t of the pooled pair
     psattn::DeviceMeta dev{};
+    psattn::GridSize size[2] = {};
 };
 
 namespace psattn {
@@ -97,22 +117,26 @@ int build_host_multi(int32_t n_samples, const int32_t* offset, const int32_t* pr
                      int32_t tile_q, int32_t tile_k, int32_t bwd_tile_q, int32_t bwd_tile_k,
                      psattn_meta** out);
 
+// What every kernel starts with stands close together: each first access to 64 bytes of the arguments takes some 500 cycles, all of
+// those that fetch_args makes at once as long as one.
 struct AttnArgs {
-    DeviceMeta meta;
     int32_t Hq, Hkv, d;
     float scale;
-    const void *Q, *K, *V, *O, *dO;
+    const void *Q, *K, *V, *dO, *O;
     const float* LSE;
-    void *Oout, *dQ, *dK, *dV;
-    float* LSEout;
     // Rotary embedding (nullptr = none): table [positions][128] = cos[64] | sin[64] per position id.
     // Forward: Q arrives unrotated, is rotated in registers and, if Qr is set, saved rotated for the
     // backward; K arrives rotated.  Backward: Q and K arrive rotated, dQ and dK leave unrotated.
     const float* rope;
-    void* Qr;
+    DeviceMeta meta;
     float* delta;  // [Hq, T]  workspace: rowsum(dO o O); the MFMA kernels keep its negative here
     float* lse2;   // [Hq, T]  workspace: LSE * log2(e), written by the MFMA dQ pass for the dK/dV pass
+    void *Oout, *dQ, *dK, *dV;
+    float* LSEout;
+    void* Qr;
+    GridSize size[2];
 };
+
 
 // psattn_fwd with optional rotary embedding (rope_table == nullptr: none).
 int fwd_checked(const psattn_meta* meta, int32_t dt, int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim,

@@ -12,16 +12,15 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_dq_bf16_mfma(Att
     constexpr int kRB = kRowBytesOf<D>, kSteps = D / 16, kBlocks = D / 32;  // MFMA steps of a score, 32-wide blocks of a dQ row
     __shared__ __attribute__((aligned(16))) char sKb[2][64 * kRB];  // double buffered
     __shared__ __attribute__((aligned(16))) char sVb[2][64 * kRB];
+    fetch_args(a);
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, c32 = l & 31, g = l >> 5;
     const int T = a.meta.T, Hq = a.Hq, Hkv = a.Hkv;
-    const DeviceCsr& csr = a.meta.fwd;
-    const QueryBlock qb = query_block(Hq, Hkv, csr.n_rows, w);
-    const RowLaunch rl = csr.launch[qb.row];  // one scalar load: row, list bounds
+    const QueryBlock qb = query_block(Hq, Hkv, a.meta.n_rows[kGridQ], w);
+    const RowLaunch rl = row_launch<kGridQ>(a.meta, qb.row);  // one scalar load: row, list bounds
     const int kvh = qb.kvh, h = qb.h, row0 = rl.row * 128 + qb.first;
     const int q_row = row0 + c32;
     const bool valid = q_row < T;
-    Tok4 tk = {kPadStart, 0, 0, 0};
-    if (valid) tk = a.meta.tok[q_row];
+    Tok4 tk = token_begin(a.meta, q_row);
 
     const uint16_t* K = static_cast<const uint16_t*>(a.K) + kvh * D;
     const uint16_t* V = static_cast<const uint16_t*>(a.V) + kvh * D;
@@ -36,10 +35,13 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_dq_bf16_mfma(Att
     for (int t = 0; t < kSteps; ++t) orow[t] = *reinterpret_cast<const uint4*>(static_cast<const char*>(a.O) + at0 + Rows<D>::lane_off(t, q_row_bytes, l, last_row));
     rows0.copy_in(static_cast<const char*>(a.dO) + at0, q_row_bytes, l, last_row);
     rows1.copy_in(static_cast<const char*>(a.Q) + at0, q_row_bytes, l, last_row);
+    const float lse_row = valid ? a.LSE[static_cast<size_t>(h) * T + q_row] : -INFINITY;
+    tk = token_end(tk, a.meta, q_row);
+    EntryStream es;
+    es.init<kGridQ>(a.meta, rl, 1, l);
     // Rows without keys (padding) have LSE = -inf.  Their scores are masked to -inf below;
     // with +inf here exp2(score - lse2) is 0 for them instead of exp2(-inf + inf).  (A row with keys has LSE = -inf only
     // where its scores are not numbers; head_dim 64 passes that on to whatever reads the row.)
-    const float lse_row = valid ? a.LSE[static_cast<size_t>(h) * T + q_row] : -INFINITY;
     const bool no_keys = D == 64 ? tk.s == kPadStart : lse_row == -INFINITY;
     const float lse2 = no_keys ? INFINITY : lse_row * kLog2e;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -61,8 +63,6 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_dq_bf16_mfma(Att
         pair_copy_setup(pc, reinterpret_cast<const char*>(K) + static_cast<size_t>(k0) * row_bytes,
                         reinterpret_cast<const char*>(V) + static_cast<size_t>(k0) * row_bytes, row_bytes, T - 1 - k0, dml, w, l);
     };
-    EntryStream es;
-    es.init(csr.entry, rl.begin, 1, rl.count, l);
     int ent = rl.first_entry, it = 0, n_ent = rl.count;
     // waves that share their queries leave out the tiles at both ends of the list that are there for the q-tile's others
     if (qb.together)
@@ -264,7 +264,7 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_dq_bf16_mfma(Att
 }  // namespace
 
 int launch_mfma_dq(const AttnArgs& a, void* stream) {
-    const unsigned grid = static_cast<unsigned>(a.meta.fwd.n_rows) * a.Hq;
+    const unsigned grid = static_cast<unsigned>(a.meta.n_rows[kGridQ]) * a.Hq;
     if (grid == 0) return 0;
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (a.d == 128) psattn_dq_bf16_mfma<128><<<grid, 256, 0, s>>>(a);

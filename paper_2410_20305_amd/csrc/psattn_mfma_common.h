@@ -403,9 +403,18 @@ struct EntryStream {
         const int k = min(64 * b + l, n - 1);
         return list[first + step * k];
     }
-    __device__ __forceinline__ void init(const int* list_, int first_, int step_, int n_, int l_) {
-        list = list_; first = first_; step = step_; n = n_; l = l_;
+    // the list of row `rl` of a grid, forwards (step 1) or backwards (step -1)
+    template <int GRID>
+    __device__ __forceinline__ void init(const DeviceMeta& m, const RowLaunch& rl, int step_, int l_) {
+        list = m.list.entry[GRID];
+        step = step_; n = rl.count; l = l_;
+        first = step > 0 ? rl.begin : rl.begin + n - 1;
         batch = 0;
+        nxt = 0;
+        if (m.in_args) {
+            cur = small_entries(static_cast<uint32_t>(rl.begin), step, n);
+            return;
+        }
         cur = n > 0 ? fetch(0) : 0;
         nxt = n > 64 ? fetch(1) : 0;
     }

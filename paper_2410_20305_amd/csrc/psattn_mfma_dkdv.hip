@@ -200,16 +200,16 @@ __global__ __launch_bounds__(256) void psattn_dkdv_bf16_mfma(AttnArgs a) {
     __shared__ __attribute__((aligned(16))) char sRows[S == 1 ? 4 * 64 * kRowBytes : 1];  // K and V rows, later dK and dV rows, of each wave
     // a[0:191] are in use: makes the kernel's register allocation cover them
     asm volatile("" ::: "a0", "a191");
+    fetch_args(a);
     const int tid = threadIdx.x, wg = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, c32 = l & 31, g = l >> 5;
     const int group = S == 1 ? 0 : wg / kWaves, w = S == 1 ? wg : wg % kWaves;  // wave index in its group
     const int T = a.meta.T, Hq = a.Hq, Hkv = a.Hkv, G = Hq / Hkv;
-    const DeviceCsr& csr = a.meta.bwd;
     const int kvh = blockIdx.x % Hkv, rest = blockIdx.x / Hkv;
-    const RowLaunch rl = csr.launch[rest / S];  // one scalar load: row, list bounds, first entry
+    const RowLaunch rl = row_launch<kGridK>(a.meta, rest / S);  // one scalar load: row, list bounds, first entry
     const int row0 = rl.row * 128 + (rest % S) * (128 / S) + 32 * w;  // the wave's first key
     const int key = row0 + c32;
     const bool kvalid = key < T;
-    const int key_hi = kvalid ? a.meta.tok[key].key_hi : 0;  // queries [key, key_hi) read this key
+    Tok4 tk = token_begin(a.meta, key);
     const float c = a.scale * kLog2e;
     LaneOffsets lo = lane_offsets(l);
     const int l_nat = lo.nat;
@@ -232,7 +232,7 @@ __global__ __launch_bounds__(256) void psattn_dkdv_bf16_mfma(AttnArgs a) {
         k_rows.copy_in(static_cast<const char*>(a.K) + at0, k_row_bytes, l, last_row);
         v_rows.copy_in(static_cast<const char*>(a.V) + at0, k_row_bytes, l, last_row);
     }
-    const int e0 = rl.begin, n_ent = rl.count;
+    const int n_ent = rl.count;
     const int n_steps = n_ent * G;
     const int n_it = (n_steps - group + S - 1) / S;      // the group's share: steps group, group + S, ...
     const int n_loop = (n_steps + S - 1) / S;            // every wave joins every barrier
@@ -284,24 +284,31 @@ __global__ __launch_bounds__(256) void psattn_dkdv_bf16_mfma(AttnArgs a) {
     // of neighbouring k-tiles (which run at the same time on the same XCD) read the
     // same Q / dO tile at the same moment and share it through L2.
     EntryStream es;
-    es.init(csr.entry, e0 + n_ent - 1, -1, n_ent, l);
     int pk = 0, ph = 0;  // walk position and head (within the group of heads) of the group's next step
     auto advance = [&](int steps) {
         ph += steps;
         while (ph >= G) { ph -= G; ++pk; }
     };
     int ent = 0, it = 0;
+    bool started = false;  // the list
     if (n_steps > 0) {
         ent = rl.first_entry;
         if constexpr (S > 1) {
             advance(group);
             if (pk >= n_ent) pk = ph = 0;  // nothing to do for this group: it copies a tile that it does not use
-            if (pk > 0) ent = es.get(pk);
+            if (pk > 0) {
+                es.init<kGridK>(a.meta, rl, -1, l);
+                ent = es.get(pk);
+            }
         }
+        started = pk > 0;
         copy_setup(ent, kvh * G + ph);
         static_for<0, kPieces>([&](auto P) { copy_piece(P, std::integral_constant<int, 0>{}); });
         advance(S);
     }
+    if (!started) es.init<kGridK>(a.meta, rl, -1, l);
+    tk = token_end(tk, a.meta, key);
+    const int key_hi = tk.key_hi;  // queries [key, key_hi) read this key
     // dK, dV accumulators a[0:127] = 0; K, V fragments -> a[128:191]
     static_for<0, 128>([&](auto R) { acc_set<decltype(R)::value>(0u); });
     {
@@ -415,7 +422,7 @@ __global__ __launch_bounds__(256) void psattn_dkdv_bf16_mfma(AttnArgs a) {
     if (a.rope) {
         // K arrived rotated: turn dK back by the key's angles (accumulator element 4 i4 + k of block
         // db is head dim 32 db + 8 i4 + 4 g + k; its partner sits in block db + 2)
-        const float* trow = a.rope + (kvalid ? static_cast<size_t>(rope_position(a.meta.tok[key], key)) * 128 : 0);
+        const float* trow = a.rope + (kvalid ? static_cast<size_t>(rope_position(tk, key)) * 128 : 0);
         static_for<0, 2>([&](auto DB) {
             constexpr int db = decltype(DB)::value;
             f32x16 x = get(std::integral_constant<int, kAccDK + 16 * db>{}), y = get(std::integral_constant<int, kAccDK + 16 * (db + 2)>{});
@@ -458,10 +465,10 @@ __global__ __launch_bounds__(256) void psattn_dkdv_bf16_mfma(AttnArgs a) {
 constexpr int64_t kCus = 256;
 
 int launch_mfma_dkdv(const AttnArgs& a, void* stream) {
-    const unsigned grid = static_cast<unsigned>(a.meta.bwd.n_rows) * a.Hkv;
+    const unsigned grid = static_cast<unsigned>(a.meta.n_rows[kGridK]) * a.Hkv;
     if (grid == 0) return 0;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int64_t chain = static_cast<int64_t>(a.meta.bwd.longest) * (a.Hq / a.Hkv), steps = a.meta.bwd.n_entries * a.Hq;
+    const int64_t chain = static_cast<int64_t>(a.size[kGridK].longest) * (a.Hq / a.Hkv), steps = a.size[kGridK].n_entries * a.Hq;
     if (chain >= 8 && 10 * chain * kCus >= 16 * steps) psattn_dkdv_bf16_mfma<2><<<2 * grid, 256, 0, s>>>(a);
     else psattn_dkdv_bf16_mfma<1><<<grid, 256, 0, s>>>(a);
     return static_cast<int>(hipGetLastError());

@@ -28,16 +28,16 @@ __global__ __launch_bounds__(256, 2) void psattn_dkdv64_bf16_mfma(AttnArgs a) {
     __shared__ __attribute__((aligned(16))) char smem[S][4][64 * kRB];
     __shared__ __attribute__((aligned(16))) float sStat[S][2][2][64];
     __shared__ __attribute__((aligned(16))) char sRows[S == 1 ? 4 * 64 * kRB : 1];  // K and V rows, later dK and dV rows, of each wave
+    fetch_args(a);
     const int tid = threadIdx.x, wg = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, c32 = l & 31, g = l >> 5;
     const int group = S == 1 ? 0 : wg / kWaves, w = S == 1 ? wg : wg % kWaves;  // wave index in its group
     const int T = a.meta.T, Hq = a.Hq, Hkv = a.Hkv, G = Hq / Hkv;
-    const DeviceCsr& csr = a.meta.bwd;
     const int kvh = blockIdx.x % Hkv, rest = blockIdx.x / Hkv;
-    const RowLaunch rl = csr.launch[rest / S];  // one scalar load: row, list bounds, first entry
+    const RowLaunch rl = row_launch<kGridK>(a.meta, rest / S);  // one scalar load: row, list bounds, first entry
     const int row0 = rl.row * 128 + (rest % S) * (128 / S) + 32 * w;  // the wave's first key
     const int key = row0 + c32;
     const bool kvalid = key < T;
-    const int key_hi = kvalid ? a.meta.tok[key].key_hi : 0;  // queries [key, key_hi) read this key
+    Tok4 tk = token_begin(a.meta, key);
     // K and V rows of the wave's keys pass through LDS: an unsplit row has room of its own, a split one takes its second buffers
     char *const k_at = S == 1 ? sRows + 64 * kRB * w : smem[group][1] + kRows * w * kRB;
     char *const v_at = S == 1 ? k_at + 32 * kRB : smem[group][3] + kRows * w * kRB;
@@ -65,7 +65,7 @@ __global__ __launch_bounds__(256, 2) void psattn_dkdv64_bf16_mfma(AttnArgs a) {
         lo.tr1 += at;
         lo.tr2 += at;
     }
-    const int e0 = rl.begin, n_ent = rl.count;
+    const int n_ent = rl.count;
     const int n_steps = n_ent * G;
     const int n_it = (n_steps - group + S - 1) / S;  // the group's share: steps group, group + S, ...
     const int n_loop = (n_steps + S - 1) / S;        // every wave joins every barrier
@@ -109,24 +109,31 @@ __global__ __launch_bounds__(256, 2) void psattn_dkdv64_bf16_mfma(AttnArgs a) {
     };
     // q-tiles from the last to the first and the heads innermost: neighbouring k-tiles share Q / dO tiles through L2
     EntryStream es;
-    es.init(csr.entry, e0 + n_ent - 1, -1, n_ent, l);
     int pk = 0, ph = 0;  // walk position and head (within the group of heads) of the group's next step
     auto advance = [&](int steps) {
         ph += steps;
         while (ph >= G) { ph -= G; ++pk; }
     };
     int ent = 0, it = 0;
+    bool started = false;  // the list
     if (n_steps > 0) {
         ent = rl.first_entry;
         if constexpr (S > 1) {
             advance(group);
             if (pk >= n_ent) pk = ph = 0;  // nothing to do for this group: it copies a tile that it does not use
-            if (pk > 0) ent = es.get(pk);
+            if (pk > 0) {
+                es.init<kGridK>(a.meta, rl, -1, l);
+                ent = es.get(pk);
+            }
         }
+        started = pk > 0;
         copy_setup(ent, kvh * G + ph);
         static_for<0, kPieces>([&](auto P) { copy_piece(P, std::integral_constant<int, 0>{}); });
         advance(S);
     }
+    if (!started) es.init<kGridK>(a.meta, rl, -1, l);
+    tk = token_end(tk, a.meta, key);
+    const int key_hi = tk.key_hi;  // queries [key, key_hi) read this key
     constexpr int kAhead = 2, kRing = 4;
     auto tile = [&](auto BUF) {
         constexpr int buf = decltype(BUF)::value;
@@ -302,10 +309,10 @@ __global__ __launch_bounds__(256, 2) void psattn_dkdv64_bf16_mfma(AttnArgs a) {
 constexpr int64_t kCus = 256;
 
 int launch_mfma_dkdv64(const AttnArgs& a, void* stream) {
-    const unsigned grid = static_cast<unsigned>(a.meta.bwd.n_rows) * a.Hkv;
+    const unsigned grid = static_cast<unsigned>(a.meta.n_rows[kGridK]) * a.Hkv;
     if (grid == 0) return 0;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int64_t chain = static_cast<int64_t>(a.meta.bwd.longest) * (a.Hq / a.Hkv), steps = a.meta.bwd.n_entries * a.Hq;
+    const int64_t chain = static_cast<int64_t>(a.size[kGridK].longest) * (a.Hq / a.Hkv), steps = a.size[kGridK].n_entries * a.Hq;
     if (chain > 0 && chain * kCus >= steps) psattn_dkdv64_bf16_mfma<2><<<2 * grid, 256, 0, s>>>(a);
     else psattn_dkdv64_bf16_mfma<1><<<grid, 256, 0, s>>>(a);
     return static_cast<int>(hipGetLastError());

@@ -18,16 +18,15 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(At
     constexpr int kRB = kRowBytesOf<D>, kSteps = D / 16, kBlocks = D / 32;  // MFMA steps of a score, 32-wide blocks of an output row
     __shared__ __attribute__((aligned(16))) char sKb[2][64 * kRB];  // double buffered
     __shared__ __attribute__((aligned(16))) char sVb[2][64 * kRB];
+    fetch_args(a);
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, c32 = l & 31, g = l >> 5;
     const int T = a.meta.T, Hq = a.Hq, Hkv = a.Hkv;
-    const DeviceCsr& csr = a.meta.fwd;
-    const QueryBlock qb = query_block(Hq, Hkv, csr.n_rows, w);
-    const RowLaunch rl = csr.launch[qb.row];  // one scalar load: row, list bounds
+    const QueryBlock qb = query_block(Hq, Hkv, a.meta.n_rows[kGridQ], w);
+    const RowLaunch rl = row_launch<kGridQ>(a.meta, qb.row);  // one scalar load: row, list bounds
     const int kvh = qb.kvh, h = qb.h, row0 = rl.row * 128 + qb.first;
     const int q_row = row0 + c32;
     const bool valid = q_row < T;
-    Tok4 tk = {kPadStart, 0, 0, 0};
-    if (valid) tk = a.meta.tok[q_row];
+    Tok4 tk = token_begin(a.meta, q_row);
 
     const uint16_t* Q = static_cast<const uint16_t*>(a.Q);
     const uint16_t* K = static_cast<const uint16_t*>(a.K) + kvh * D;
@@ -40,6 +39,7 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(At
     // rotary embedding: the table row of this lane's query, both members of a pair in the same lane
     float4 turn[D == 128 ? 16 : 1];
     if constexpr (D == 128) if (a.rope) {
+        tk = token_end(tk, a.meta, q_row);
         const float* row = a.rope + static_cast<size_t>(rope_position(tk, q_row)) * 128;
 #pragma unroll
         for (int t = 0; t < 4; ++t) rope_load8(turn + 4 * t, row, 16 * t + 8 * g);
@@ -76,15 +76,21 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(At
                         T - 1 - k0, dl, w, l);
     };
     EntryStream es;
-    es.init(csr.entry, rl.begin, 1, rl.count, l);
     int ent = rl.first_entry, it = 0, n_ent = rl.count;
-    // waves that share their queries leave out the tiles at both ends of the list that are there for the q-tile's others
-    if (qb.together)
+    auto first_copy = [&] {
+        if (it < n_ent) {
+            copy_setup(ent);
+            static_for<0, 2 * kBlocks>([&](auto P) { pair_copy_piece<decltype(P)::value>(pc, sKb[0], sVb[0], w); });
+        }
+    };
+    if (!qb.together) first_copy();
+    if (!(D == 128 && a.rope)) tk = token_end(tk, a.meta, q_row);
+    es.init<kGridQ>(a.meta, rl, 1, l);
+    if (qb.together) {
+        // waves that share their queries leave out the tiles at both ends of the list that are there for the q-tile's others
         while (it < n_ent && !reads_tile(ent, row0, tk))
             if (++it < n_ent) ent = es.get(it);
-    if (it < n_ent) {
-        copy_setup(ent);
-        static_for<0, 2 * kBlocks>([&](auto P) { pair_copy_piece<decltype(P)::value>(pc, sKb[0], sVb[0], w); });
+        first_copy();
     }
     if (qb.together && n_ent <= 64)
         while (it + 1 < n_ent && !reads_tile(es.peek(n_ent - 1), row0, tk)) --n_ent;

@@ -10,19 +10,19 @@
 // of the same addresses (what a write-partials-then-reduce scheme would cost at least).
 #include <hip/hip_runtime.h>
 
-#include "psattn_internal.h"
+#include "psattn_mask.h"
 
 namespace psattn {
 namespace {
 
-__global__ __launch_bounds__(256) void psattn_dq_atomics_probe(DeviceMeta meta, int Hq, int Hkv, float* acc, int mode) {
+__global__ __launch_bounds__(256) void psattn_dq_atomics_probe(AttnArgs a, float* acc, int mode) {
     const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, c32 = l & 31, g = l >> 5;
-    const int G = Hq / Hkv, T = meta.T;
-    const DeviceCsr& csr = meta.bwd;
-    const RowLaunch rl = csr.launch[blockIdx.x / Hkv];
+    const DeviceMeta& meta = a.meta;
+    const int Hq = a.Hq, Hkv = a.Hkv, G = Hq / Hkv, T = meta.T;
+    const RowLaunch rl = row_launch<kGridK>(meta, blockIdx.x / Hkv);
     const int kvh = blockIdx.x % Hkv;
     for (int k = rl.count - 1; k >= 0; --k) {  // same walk as the dK/dV kernel: last q-tile first, heads innermost
-        const int q0 = (csr.entry[rl.begin + k] >> 2) * csr.tile_q;
+        const int q0 = (tile_entry<kGridK>(meta, rl, k) >> 2) * kBwdTileQ;
         for (int hh = 0; hh < G; ++hh) {
             const int h = kvh * G + hh;
 #pragma unroll
@@ -111,9 +111,11 @@ extern "C" int psattn_probe_dq_atomics(const psattn_meta* meta, int32_t n_q_head
     if (!meta || !acc || n_q_heads <= 0 || n_kv_heads <= 0 || n_q_heads % n_kv_heads != 0) return PSATTN_EINVAL;
     if (!meta->on_device) return PSATTN_ENODEVICE;
     if (meta->bwd.tile_q != psattn::kBwdTileQ || meta->bwd.tile_k != psattn::kBwdTileK) return PSATTN_EUNSUPPORTED;
-    const unsigned grid = static_cast<unsigned>(meta->dev.bwd.n_rows) * n_kv_heads;
+    const unsigned grid = static_cast<unsigned>(meta->dev.n_rows[psattn::kGridK]) * n_kv_heads;
     if (grid == 0) return PSATTN_OK;
-    psattn::psattn_dq_atomics_probe<<<grid, 256, 0, static_cast<hipStream_t>(hip_stream)>>>(meta->dev, n_q_heads, n_kv_heads,
-                                                                                           acc, mode);
+    psattn::AttnArgs a{};
+    a.meta = meta->dev;
+    a.Hq = n_q_heads; a.Hkv = n_kv_heads;
+    psattn::psattn_dq_atomics_probe<<<grid, 256, 0, static_cast<hipStream_t>(hip_stream)>>>(a, acc, mode);
     return hipGetLastError() == hipSuccess ? PSATTN_OK : PSATTN_EHIP;
 }

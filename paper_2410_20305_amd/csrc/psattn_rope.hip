@@ -35,15 +35,16 @@ namespace {
 using namespace mma;
 
 // one thread per (token, kv-head, 8 dims below 64): rotates them and their partners above 64
-__global__ __launch_bounds__(256) void psattn_rope_k_bf16(DeviceMeta meta, int Hkv, const float* table, const uint16_t* K,
-                                                           uint16_t* Kr) {
+__global__ __launch_bounds__(256) void psattn_rope_k_bf16(AttnArgs a, uint16_t* Kr) {
+    const int Hkv = a.Hkv;
+    const uint16_t* K = static_cast<const uint16_t*>(a.K);
     const size_t idx = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x;
-    const size_t n = static_cast<size_t>(meta.T) * Hkv * 8;
+    const size_t n = static_cast<size_t>(a.meta.T) * Hkv * 8;
     if (idx >= n) return;
     const int chunk = static_cast<int>(idx & 7);
     const size_t row = idx >> 3;               // token * Hkv + head
     const int t = static_cast<int>(row / Hkv);
-    const float* trow = table + static_cast<size_t>(rope_position(meta.tok[t], t)) * 128;
+    const float* trow = a.rope + static_cast<size_t>(rope_position(token(a.meta, t), t)) * 128;
     Frag8 lo, hi;
     lo.u = *reinterpret_cast<const uint4*>(K + row * 128 + 8 * chunk);
     hi.u = *reinterpret_cast<const uint4*>(K + row * 128 + 64 + 8 * chunk);
@@ -130,8 +131,10 @@ int psattn_rope_k(const psattn_meta* meta, const psattn_rope* rope, int32_t dt, 
     const size_t n = static_cast<size_t>(meta->T) * n_kv_heads * 8;
     const size_t grid = (n + 255) / 256;
     if (grid > 0x7fffffffu) return PSATTN_EUNSUPPORTED;
-    psattn::psattn_rope_k_bf16<<<static_cast<unsigned>(grid), 256, 0, static_cast<hipStream_t>(hip_stream)>>>(
-        meta->dev, n_kv_heads, rope->d_table, static_cast<const uint16_t*>(K), static_cast<uint16_t*>(Kr));
+    psattn::AttnArgs a{};
+    a.meta = meta->dev;
+    a.Hkv = n_kv_heads; a.K = K; a.rope = rope->d_table;
+    psattn::psattn_rope_k_bf16<<<static_cast<unsigned>(grid), 256, 0, static_cast<hipStream_t>(hip_stream)>>>(a, static_cast<uint16_t*>(Kr));
     return hipGetLastError() == hipSuccess ? PSATTN_OK : PSATTN_EHIP;
 }
 

@@ -11,7 +11,7 @@ using namespace mma;
 __device__ __forceinline__ float fmax3(float a, float b, float c) { return __builtin_fmaxf(__builtin_fmaxf(a, b), c); }
 
 // ------------------------------------------------------------------ forward
-// grid: one workgroup per (q-tile of 128 queries, q-head); 4 waves x 32 queries.
+// grid: as many workgroups as (q-tile of 128 queries, q-head); 4 waves x 32 queries of one head or of four (query_block).
 // D = head_dim.  D = 128: 64 KB of LDS and under 256 registers, two workgroups per CU.  D = 64: half of both.
 template <int D>
 __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(AttnArgs a) {

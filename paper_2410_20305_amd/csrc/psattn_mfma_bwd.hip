@@ -30,9 +30,9 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_dq_bf16_mfma(Att
     const int last_row = min(max(T - 1 - row0, 0), 31);
     const size_t at0 = (static_cast<size_t>(min(row0, T - 1)) * Hq + h) * kRB;
     const Rows<D> rows0{sKb[0] + 16 * w * kRB, sVb[0] + 16 * w * kRB}, rows1{sKb[1] + 16 * w * kRB, sVb[1] + 16 * w * kRB};
-    uint4 orow[kSteps];
+    u32x4 orow[kSteps];
 #pragma unroll
-    for (int t = 0; t < kSteps; ++t) orow[t] = *reinterpret_cast<const uint4*>(static_cast<const char*>(a.O) + at0 + Rows<D>::lane_off(t, q_row_bytes, l, last_row));
+    for (int t = 0; t < kSteps; ++t) orow[t] = *reinterpret_cast<const u32x4*>(static_cast<const char*>(a.O) + at0 + Rows<D>::lane_off(t, q_row_bytes, l, last_row));
     rows0.copy_in(static_cast<const char*>(a.dO) + at0, q_row_bytes, l, last_row);
     rows1.copy_in(static_cast<const char*>(a.Q) + at0, q_row_bytes, l, last_row);
     const float lse_row = valid ? a.LSE[static_cast<size_t>(h) * T + q_row] : -INFINITY;
@@ -46,13 +46,14 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_dq_bf16_mfma(Att
     const float lse2 = no_keys ? INFINITY : lse_row * kLog2e;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     Frag8 qf[kSteps], gf[kSteps];
-    uint4 grow[kSteps];
-    static_for<0, kSteps>([&](auto P) { grow[decltype(P)::value] = rows0.template chunk<decltype(P)::value>(l); });
     rows0.operands(gf, l, lo.nat);
     rows1.operands(qf, l, lo.nat);
-    // they are in registers before the first K / V tile takes the place of dO
+    // they are in registers before the first K / V tile takes the place of dO, and O that of Q
 #pragma unroll
-    for (int t = 0; t < kSteps; ++t) asm volatile("" : "+v"(qf[t].v), "+v"(gf[t].v), "+v"(grow[t].x)::"memory");
+    for (int t = 0; t < kSteps; ++t) asm volatile("" : "+v"(qf[t].v), "+v"(gf[t].v)::"memory");
+    Frag8 of[kSteps];
+    static_for<0, kSteps>([&](auto P) { rows1.template put_chunk<decltype(P)::value>(orow[decltype(P)::value], l); });
+    rows1.operands(of, l, lo.nat);
     // K / V tiles are copied global -> LDS asynchronously, one tile ahead, into the
     // buffer the previous tile has just vacated; one barrier per tile.
     const uint32_t row_bytes = static_cast<uint32_t>(Hkv) * kRB;
@@ -72,30 +73,21 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_dq_bf16_mfma(Att
         copy_setup(ent);
         static_for<0, 2 * kBlocks>([&](auto P) { pair_copy_piece<decltype(P)::value>(pc, sKb[0], sVb[0], w); });
     }
-    // delta = rowsum(dO o O), summed over the lanes that hold a row's 16-byte chunks; the result also goes to the workspace for
-    // the dK/dV pass that follows
-    constexpr int kLanes = D / 8;
-    float dl;
-    {
-        float part = 0.f;
+    // delta = rowsum(dO o O): this lane holds half of both rows; the result also goes to the workspace for the dK/dV pass that
+    // follows.  Each half is one chain of sums, head dims ascending, while the first tile is on its way.
+    float dl = 0.f;
 #pragma unroll
-        for (int t = 0; t < kSteps; ++t) {
-            const uint32_t ow[4] = {orow[t].x, orow[t].y, orow[t].z, orow[t].w};
-            const uint32_t gw[4] = {grow[t].x, grow[t].y, grow[t].z, grow[t].w};
-            float d = 0.f;
+    for (int t = 0; t < kSteps; ++t) {
+        const uint32_t ow[4] = {of[t].u.x, of[t].u.y, of[t].u.z, of[t].u.w};
+        const uint32_t gw[4] = {gf[t].u.x, gf[t].u.y, gf[t].u.z, gf[t].u.w};
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                d = fmaf(__uint_as_float(ow[j] << 16), __uint_as_float(gw[j] << 16), d);
-                d = fmaf(__uint_as_float(ow[j] & 0xffff0000u), __uint_as_float(gw[j] & 0xffff0000u), d);
-            }
-            d = sum_lanes<kLanes>(d);
-            part = l % kLanes == t ? d : part;
+        for (int j = 0; j < 4; ++j) {
+            dl = fmaf(__uint_as_float(ow[j] << 16), __uint_as_float(gw[j] << 16), dl);
+            dl = fmaf(__uint_as_float(ow[j] & 0xffff0000u), __uint_as_float(gw[j] & 0xffff0000u), dl);
         }
-        // lane kLanes * j + t holds row (64 / kLanes) t + j
-        float* sd = reinterpret_cast<float*>(rows1.a);  // Q is in registers
-        if (l % kLanes < kSteps) sd[(64 / kLanes) * (l % kLanes) + l / kLanes] = part;
-        dl = sd[c32];
     }
+    dl += other_half(dl);
+    asm volatile("" : "+v"(dl)::"memory");  // ... and O is done with before the second tile's copies take its place
     if (valid && g == 0) {
         a.delta[static_cast<size_t>(h) * T + q_row] = -dl;  // the dK/dV kernel starts its dP accumulators from -delta
         a.lse2[static_cast<size_t>(h) * T + q_row] = lse2;

@@ -217,19 +217,6 @@ __device__ inline float other_half(float x) {
     return __uint_as_float(threadIdx.x & 32 ? r[0] : r[1]);
 }
 
-// sum over groups of N = 8 or 16 neighbouring lanes, in all of them
-template <int N>
-__device__ __forceinline__ float sum_lanes(float x) {
-    const auto add = [](float v, auto C) {
-        return v + __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), decltype(C)::value, 0xf, 0xf, true));
-    };
-    x = add(x, std::integral_constant<int, 0xb1>{});   // quad_perm [1, 0, 3, 2]
-    x = add(x, std::integral_constant<int, 0x4e>{});   // quad_perm [2, 3, 0, 1]
-    x = add(x, std::integral_constant<int, 0x141>{});  // row_half_mirror
-    if constexpr (N == 16) x = add(x, std::integral_constant<int, 0x140>{});  // row_mirror
-    return x;
-}
-
 // row of the 32x32 accumulator that register i of lane-half g holds
 __device__ inline int acc_row(int i, int g) { return (i >> 2) * 8 + 4 * g + (i & 3); }
 
@@ -359,6 +346,8 @@ struct Rows {
     // what lane l has moved in piece P
     template <int P>
     __device__ __forceinline__ uint4 chunk(int l) const { return *reinterpret_cast<const uint4*>(piece<P>() + 16 * l); }
+    template <int P>
+    __device__ __forceinline__ void put_chunk(u32x4 x, int l) const { *reinterpret_cast<u32x4*>(piece<P>() + 16 * l) = x; }
     // row l % 32 as MFMA operands
     __device__ __forceinline__ void operands(Frag8 (&f)[D / 16], int l, int nat) const {
         const char* at = l & 16 ? b - 16 * kRB : a;

@@ -53,6 +53,7 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_dq_bf16_mfma(Att
     for (int t = 0; t < kSteps; ++t) asm volatile("" : "+v"(qf[t].v), "+v"(gf[t].v)::"memory");
     Frag8 of[kSteps];
     static_for<0, kSteps>([&](auto P) { rows1.template put_chunk<decltype(P)::value>(orow[decltype(P)::value], l); });
+    lds_exchange();
     rows1.operands(of, l, lo.nat);
     // K / V tiles are copied global -> LDS asynchronously, one tile ahead, into the
     // buffer the previous tile has just vacated; one barrier per tile.

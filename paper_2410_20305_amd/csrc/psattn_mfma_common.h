@@ -317,6 +317,13 @@ __device__ __forceinline__ uint32_t pack2(float a, float b) {
     return o.u;
 }
 
+// Between LDS accesses by which the lanes of a wave hand values to each other.  LDS takes a wave's instructions in order; the
+// compiler keeps that order only where one lane's own addresses may meet, which is not where the values go.  No instruction.
+__device__ __forceinline__ void lds_exchange() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // A wave's 32 rows of a tensor on their way through LDS, so that memory is read and written in whole rows.  Operands loaded
 // straight into their registers take 32 bytes of each of 32 rows at a time: a line is asked for by four instructions, by which
 // time the eight waves of a CU have pushed it out of their 32 KB of L1.  (Taking the same loads non-temporally, so that every
@@ -370,7 +377,9 @@ struct Rows {
     // the first n_rows rows to memory
     __device__ __forceinline__ void copy_out(void* base, uint32_t row_bytes, int l, int n_rows) const {
         uint4 x[kPieces];
+        lds_exchange();
         static_for<0, kPieces>([&](auto P) { x[decltype(P)::value] = chunk<decltype(P)::value>(l); });
+        lds_exchange();
         static_for<0, kPieces>([&](auto P) {
             constexpr int p = decltype(P)::value;
             if (64 / kChunks * p + l / kChunks < n_rows) *reinterpret_cast<uint4*>(static_cast<char*>(base) + lane_off(p, row_bytes, l, 31)) = x[p];

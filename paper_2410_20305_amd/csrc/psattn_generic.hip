@@ -148,10 +148,10 @@ __global__ __launch_bounds__(kThreads) void generic_fwd(AttnArgs a, int first) {
     const int block = first + static_cast<int>(blockIdx.x);
     const int h = block % Hq, kvh = h / (Hq / Hkv), q0 = kB * (n_blocks - 1 - block / Hq);
     const int q = q0 + r;
-    Tok4 tk = token_begin(a.meta, q);
+    const TokenLoad begun = token_begin(a.meta, q);
     f32x4 qf[D / 16], acc[D / 16];
     load_rows<E, D>(qf, row_of<E, D>(a.Q, q, T, Hq, h), g);
-    tk = token_end(tk, a.meta, q);
+    const Tok4 tk = token_choose(a.meta, begun, token_search(a.meta, q));
 #pragma unroll
     for (int b = 0; b < D / 16; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
     const KeyRange kr = key_range(tk, q0, T);
@@ -214,11 +214,11 @@ __device__ inline void dq_block(const AttnArgs& a, Partials<D>& sm, int block) {
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), r = tid & 15, g = (tid >> 4) & 3;
     const int h = block % Hq, kvh = h / (Hq / Hkv), q0 = kB * (n_blocks - 1 - block / Hq);
     const int q = q0 + r;
-    Tok4 tk = token_begin(a.meta, q);
+    const TokenLoad begun = token_begin(a.meta, q);
     f32x4 qf[D / 16], gf[D / 16], acc[D / 16];
     load_rows<E, D>(qf, row_of<E, D>(a.Q, q, T, Hq, h), g);
     load_rows<E, D>(gf, row_of<E, D>(a.dO, q, T, Hq, h), g);
-    tk = token_end(tk, a.meta, q);
+    const Tok4 tk = token_choose(a.meta, begun, token_search(a.meta, q));
     const float lse = a.LSE[static_cast<size_t>(h) * T + min(q, T - 1)];
     float delta = 0.f;
     {
@@ -265,9 +265,7 @@ __device__ inline void dkdv_block(const AttnArgs& a, Partials<D>& sm, int block)
     const int T = a.meta.T, Hq = a.Hq, Hkv = a.Hkv, G = Hq / Hkv;
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), r = tid & 15, g = (tid >> 4) & 3;
     const int kvh = block % Hkv, k0 = kB * (block / Hkv), key = k0 + r;
-    Tok4 tk = token_begin(a.meta, key);
-    tk = token_end(tk, a.meta, key);
-    const int key_hi = tk.key_hi;  // queries [key, key_hi) read this key
+    const int key_hi = token_choose(a.meta, token_begin(a.meta, key), token_search(a.meta, key)).key_hi;  // queries [key, key_hi) read this key
     f32x4 kf[D / 16], vf[D / 16], dk[D / 16], dv[D / 16];
     load_rows<E, D>(kf, row_of<E, D>(a.K, key, T, Hkv, kvh), g);
     load_rows<E, D>(vf, row_of<E, D>(a.V, key, T, Hkv, kvh), g);

@@ -4,8 +4,9 @@
 // kernel of its own: 2.6 us, which is PCIe latency, 2.6 us of host time to launch it and 1.5 us to record the event that guards
 // its buffers.  Masks of samples of up to 1 024 tokens travel with the arguments of each kernel, packed into 136 bytes because
 // every 64 bytes of arguments take time to arrive.  Measured, in device memory / in the arguments: fp32 step of 168 tokens on one head
-// 28.1 / 22.5 us, bf16 step of 221 tokens on 32 / 8 heads 45.5 / 39.8; a forward whose mask is kept from the one before, and
-// then is in L2, 7.9 / 8.1 (8.9 with 1.2 KB of runs and lists as they are in device memory).
+// 25.5 / 21.3 us, bf16 step of 221 tokens on 32 / 8 heads 46.6 / 39.4.  A mask that is kept over many calls costs the kernels the
+// same from either place: forward and backward together 18.0 / 18.0 on those 168 tokens, 33.2 / 33.2 on 180, 38.4 / 38.5 on 221,
+// 47.4 / 47.4 on 500, 66.1 / 65.7 on 900.
 //
 // The arguments are read by scalar loads through the argument segment's address, so that indexing them does not make the compiler
 // copy them to scratch memory: kernels take AttnArgs as their first argument.
@@ -43,29 +44,38 @@ __device__ __forceinline__ Tok4 unpack_run(uint32_t lo, uint32_t hi) {
     return Tok4{field(1) == static_cast<int>(kSmallNone) ? kPadStart : field(1), field(2), field(3), field(4)};
 }
 
-// Descriptor of token t (padding from T on) in two halves: the first starts a load of it, or of the runs where the mask is in the
-// arguments, which the second searches; all lanes take part.  Copies and loads that a kernel issues in between hide the wait.
-__device__ __forceinline__ Tok4 token_begin(const DeviceMeta& m, int t) {
+// Descriptor of token t (padding from T on) in three steps, so that what a kernel issues in between hides the wait: the load from
+// device memory is started, a mask in the arguments is searched, and the one that holds is chosen where the load has come back.
+// Each has registers of its own.  (Where both ways wrote the same ones, the compiler let the way through the arguments wait for the
+// load that it does not make, and with it for all copies issued since, which it does not count: the search then stood
+// behind the first tile's arrival.  Forward / backward of 180 tokens, 32 / 8 heads, on a kept mask: 7.9 / 7.8 us, 25.9 / 25.5.)
+typedef int TokenLoad __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ TokenLoad token_begin(const DeviceMeta& m, int t) {
+    TokenLoad x = {kPadStart, 0, 0, 0};
+    if (!m.in_args && t < m.T) x = *reinterpret_cast<const TokenLoad*>(m.list.tok + t);
+    return x;
+}
+__device__ __forceinline__ Tok4 token_search(const DeviceMeta& m, int t) {
     Tok4 x = {kPadStart, 0, 0, 0};
-    if (m.in_args) {  // lane i loads run i
-        const auto* run = (const __attribute__((address_space(1))) uint32_t*)reinterpret_cast<uintptr_t>(small_mask(offsetof(SmallMask, run))) +
-                          2 * (__builtin_amdgcn_mbcnt_lo(~0u, 0) & (kSmallRuns - 1));
-        x.s = static_cast<int>(run[0]);
-        x.hole_lo = static_cast<int>(run[1]);
-    } else if (t < m.T) {
-        x = m.list.tok[t];
+    if (m.in_args) {  // a token's run is the last that starts at or before it
+        typedef uint32_t Runs __attribute__((ext_vector_type(2 * kSmallRuns)));
+        typedef Runs RunWords __attribute__((aligned(4)));
+        Runs run = *(const __attribute__((address_space(4))) RunWords*)small_mask(offsetof(SmallMask, run));
+        asm volatile("" : "+s"(run));
+        uint32_t lo = run[0], hi = run[1];
+#pragma unroll
+        for (int i = 1; i < kSmallRuns; ++i) {
+            const bool past = t >= static_cast<int>(run[2 * i] & kSmallNone);
+            lo = past ? run[2 * i] : lo;
+            hi = past ? run[2 * i + 1] : hi;
+        }
+        if (t < m.T) x = unpack_run(lo, hi);
     }
     return x;
 }
-__device__ __forceinline__ Tok4 token_end(const Tok4& begun, const DeviceMeta& m, int t) {
-    if (!m.in_args) return begun;
-    // a token's run is the last that starts at or before it
-    ArgWord* const run = small_mask(offsetof(SmallMask, run));
-    int at = 0;
-#pragma unroll
-    for (int i = 1; i < kSmallRuns; ++i) at += t >= static_cast<int>(arg_word(run + 2 * i) & kSmallNone) ? 4 : 0;
-    const Tok4 x = unpack_run(__builtin_amdgcn_ds_bpermute(at, begun.s), __builtin_amdgcn_ds_bpermute(at, begun.hole_lo));
-    return t < m.T ? x : Tok4{kPadStart, 0, 0, 0};
+__device__ __forceinline__ Tok4 token_choose(const DeviceMeta& m, TokenLoad loaded, const Tok4& found) {
+    asm volatile("" : "+v"(loaded));  // waited for here and not earlier
+    return m.in_args ? found : Tok4{loaded.x, loaded.y, loaded.z, loaded.w};
 }
 // the same at once, 0 <= t < T, from any control flow: one run after the other
 __device__ inline Tok4 token(const DeviceMeta& m, int t) {

@@ -20,7 +20,7 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_dq_bf16_mfma(Att
     const int kvh = qb.kvh, h = qb.h, row0 = rl.row * 128 + qb.first;
     const int q_row = row0 + c32;
     const bool valid = q_row < T;
-    Tok4 tk = token_begin(a.meta, q_row);
+    const TokenLoad begun = token_begin(a.meta, q_row);
 
     const uint16_t* K = static_cast<const uint16_t*>(a.K) + kvh * D;
     const uint16_t* V = static_cast<const uint16_t*>(a.V) + kvh * D;
@@ -36,15 +36,16 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_dq_bf16_mfma(Att
     rows0.copy_in(static_cast<const char*>(a.dO) + at0, q_row_bytes, l, last_row);
     rows1.copy_in(static_cast<const char*>(a.Q) + at0, q_row_bytes, l, last_row);
     const float lse_row = valid ? a.LSE[static_cast<size_t>(h) * T + q_row] : -INFINITY;
-    tk = token_end(tk, a.meta, q_row);
+    const Tok4 found = token_search(a.meta, q_row);
     EntryStream es;
     es.init<kGridQ>(a.meta, rl, 1, l);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    const Tok4 tk = token_choose(a.meta, begun, found);
     // Rows without keys (padding) have LSE = -inf.  Their scores are masked to -inf below;
     // with +inf here exp2(score - lse2) is 0 for them instead of exp2(-inf + inf).  (A row with keys has LSE = -inf only
     // where its scores are not numbers; head_dim 64 passes that on to whatever reads the row.)
     const bool no_keys = D == 64 ? tk.s == kPadStart : lse_row == -INFINITY;
     const float lse2 = no_keys ? INFINITY : lse_row * kLog2e;
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     Frag8 qf[kSteps], gf[kSteps];
     rows0.operands(gf, l, lo.nat);
     rows1.operands(qf, l, lo.nat);

@@ -209,7 +209,7 @@ __global__ __launch_bounds__(256) void psattn_dkdv_bf16_mfma(AttnArgs a) {
     const int row0 = rl.row * 128 + (rest % S) * (128 / S) + 32 * w;  // the wave's first key
     const int key = row0 + c32;
     const bool kvalid = key < T;
-    Tok4 tk = token_begin(a.meta, key);
+    const TokenLoad begun = token_begin(a.meta, key);
     const float c = a.scale * kLog2e;
     LaneOffsets lo = lane_offsets(l);
     const int l_nat = lo.nat;
@@ -307,8 +307,8 @@ __global__ __launch_bounds__(256) void psattn_dkdv_bf16_mfma(AttnArgs a) {
         advance(S);
     }
     if (!started) es.init<kGridK>(a.meta, rl, -1, l);
-    tk = token_end(tk, a.meta, key);
-    const int key_hi = tk.key_hi;  // queries [key, key_hi) read this key
+    const Tok4 found = token_search(a.meta, key);
+    Tok4 tk = found;  // chosen below; queries [key, tk.key_hi) read this key
     // dK, dV accumulators a[0:127] = 0; K, V fragments -> a[128:191]
     static_for<0, 128>([&](auto R) { acc_set<decltype(R)::value>(0u); });
     {
@@ -353,19 +353,20 @@ __global__ __launch_bounds__(256) void psattn_dkdv_bf16_mfma(AttnArgs a) {
         if (S > 1 && it > n_it) {  // the other group's last step
         } else if (full) {
             dkdv_tile<true, kPieces>(sQ, sG, sL, sD, lo, mw, c, g, ring, piece);
-        } else if (__builtin_amdgcn_ballot_w64(max(key, q0) < min(key_hi, q0 + 64)) == 0) {
+        } else if (__builtin_amdgcn_ballot_w64(max(key, q0) < min(tk.key_hi, q0 + 64)) == 0) {
             // PARTIAL tile none of whose queries reads any of this wave's 32 keys (two of the four
             // waves on the first q-tile of every causal diagonal, and the keys of another sample or
             // response): the wave only issues its share of the next tile's copy
             static_for<0, kPieces>([&](auto P) { piece(P); });
         } else {
-            pair_masks(mw, key - q0, key_hi - q0, g);
+            pair_masks(mw, key - q0, tk.key_hi - q0, g);
             dkdv_tile<false, kPieces>(sQ, sG, sL, sD, lo, mw, c, g, ring, piece);
         }
     };
     // Every load above has retired before the loop starts, so the loop body holds no
     // wait on a compiler-tracked load (such a wait would also cover the copies in flight).
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+    tk = token_choose(a.meta, begun, found);
     settle();  // the register writes above, before the first MFMA reads them
     while (it < n_loop) {
         if (it & 1) tile(std::integral_constant<int, 1>{});

@@ -37,7 +37,7 @@ __global__ __launch_bounds__(256, 2) void psattn_dkdv64_bf16_mfma(AttnArgs a) {
     const int row0 = rl.row * 128 + (rest % S) * (128 / S) + 32 * w;  // the wave's first key
     const int key = row0 + c32;
     const bool kvalid = key < T;
-    Tok4 tk = token_begin(a.meta, key);
+    const TokenLoad begun = token_begin(a.meta, key);
     // K and V rows of the wave's keys pass through LDS: an unsplit row has room of its own, a split one takes its second buffers
     char *const k_at = S == 1 ? sRows + 64 * kRB * w : smem[group][1] + kRows * w * kRB;
     char *const v_at = S == 1 ? k_at + 32 * kRB : smem[group][3] + kRows * w * kRB;
@@ -132,8 +132,8 @@ __global__ __launch_bounds__(256, 2) void psattn_dkdv64_bf16_mfma(AttnArgs a) {
         advance(S);
     }
     if (!started) es.init<kGridK>(a.meta, rl, -1, l);
-    tk = token_end(tk, a.meta, key);
-    const int key_hi = tk.key_hi;  // queries [key, key_hi) read this key
+    const Tok4 found = token_search(a.meta, key);
+    Tok4 tk = found;  // chosen below; queries [key, tk.key_hi) read this key
     constexpr int kAhead = 2, kRing = 4;
     auto tile = [&](auto BUF) {
         constexpr int buf = decltype(BUF)::value;
@@ -158,7 +158,7 @@ __global__ __launch_bounds__(256, 2) void psattn_dkdv64_bf16_mfma(AttnArgs a) {
         const float *sL = sStat[group][0][buf], *sD = sStat[group][1][buf];
         uint32_t bits = 0xffffffffu;
         if (!full) {
-            bits = elem_range_bits(key - q0, key_hi - q0, g);
+            bits = elem_range_bits(key - q0, tk.key_hi - q0, g);
             if (__builtin_amdgcn_ballot_w64(bits != 0) == 0) {
                 static_for<0, kPieces>([&](auto P) { copy_piece(P, std::integral_constant<int, buf ^ 1>{}); });
                 return;
@@ -234,6 +234,7 @@ __global__ __launch_bounds__(256, 2) void psattn_dkdv64_bf16_mfma(AttnArgs a) {
     // every compiler-tracked load above has retired before the loop starts, so the loop body holds no wait of the
     // compiler's that would also cover copies in flight
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+    tk = token_choose(a.meta, begun, found);
     k_rows.operands(kf, l, l_nat);
     v_rows.operands(vf, l, l_nat);
     // in registers before a copy takes their place

@@ -26,7 +26,7 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(At
     const int kvh = qb.kvh, h = qb.h, row0 = rl.row * 128 + qb.first;
     const int q_row = row0 + c32;
     const bool valid = q_row < T;
-    Tok4 tk = token_begin(a.meta, q_row);
+    const TokenLoad begun = token_begin(a.meta, q_row);
 
     const uint16_t* Q = static_cast<const uint16_t*>(a.Q);
     const uint16_t* K = static_cast<const uint16_t*>(a.K) + kvh * D;
@@ -38,9 +38,10 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(At
     const Rows<D> rows1{sKb[1] + 16 * w * kRB, sVb[1] + 16 * w * kRB};
     // rotary embedding: the table row of this lane's query, both members of a pair in the same lane
     float4 turn[D == 128 ? 16 : 1];
+    Tok4 found = {kPadStart, 0, 0, 0};
     if constexpr (D == 128) if (a.rope) {
-        tk = token_end(tk, a.meta, q_row);
-        const float* row = a.rope + static_cast<size_t>(rope_position(tk, q_row)) * 128;
+        found = token_search(a.meta, q_row);
+        const float* row = a.rope + static_cast<size_t>(rope_position(token_choose(a.meta, begun, found), q_row)) * 128;
 #pragma unroll
         for (int t = 0; t < 4; ++t) rope_load8(turn + 4 * t, row, 16 * t + 8 * g);
     }
@@ -84,9 +85,11 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(At
         }
     };
     if (!qb.together) first_copy();
-    if (!(D == 128 && a.rope)) tk = token_end(tk, a.meta, q_row);
+    if (!(D == 128 && a.rope)) found = token_search(a.meta, q_row);
     es.init<kGridQ>(a.meta, rl, 1, l);
+    Tok4 tk = found;
     if (qb.together) {
+        tk = token_choose(a.meta, begun, found);
         // waves that share their queries leave out the tiles at both ends of the list that are there for the q-tile's others
         while (it < n_ent && !reads_tile(ent, row0, tk))
             if (++it < n_ent) ent = es.get(it);
@@ -222,6 +225,7 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(At
     // Q fragments are in registers before the loop starts, so the loop body holds no wait
     // on a compiler-tracked load (such a wait would also cover the copies in flight)
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+    tk = token_choose(a.meta, begun, found);
     if (!straight) rows1.operands(qf, l, lo.nat);
     if constexpr (D == 128) if (a.rope) {
         // the rotated row is also saved for the backward, which streams Q tiles straight into LDS and cannot rotate them on the way

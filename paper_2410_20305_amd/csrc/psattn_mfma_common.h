@@ -317,6 +317,35 @@ __device__ __forceinline__ uint32_t pack2(float a, float b) {
     return o.u;
 }
 
+// Stores one 32-wide block (head dims 32 db ..) of the wave's 32 output rows: `x` is an accumulator whose column is
+// the lane's row.  A lane holds pieces of four head dims, 8 bytes in bf16, of one row; stored like that, every store
+// instruction would scatter 32 pieces of 16 bytes.  Two rounds of lane swaps first: between the half-waves (the two
+// pieces of 8 bytes that make 16), then between the 16-lane halves of each (rows r and r + 16 trade 16-byte chunks),
+// after which an instruction writes 64 contiguous bytes of each of 16 rows.
+// `base`: row 0 of the wave's 32; `row_elems`: elements between rows; rows from n_rows on are not stored.
+__device__ __forceinline__ void store_block(uint16_t* base, size_t row_elems, int n_rows, int db, const f32x16& x, float factor, int l) {
+    uint32_t c[2][4];  // 16-byte chunks 2 k + g of the block, k = 0, 1
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int i = 8 * k + 2 * j;
+            const auto r = __builtin_amdgcn_permlane32_swap(pack2(x[i] * factor, x[i + 1] * factor), pack2(x[i + 4] * factor, x[i + 5] * factor), false, false);
+            c[k][j] = r[0];
+            c[k][2 + j] = r[1];
+        }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const auto r = __builtin_amdgcn_permlane16_swap(c[0][j], c[1][j], false, false);
+        c[0][j] = r[0];
+        c[1][j] = r[1];
+    }
+    const int row = l & 15;
+    uint16_t* p = base + row * row_elems + 32 * db + 16 * ((l >> 4) & 1) + 8 * (l >> 5);
+    if (row < n_rows) *reinterpret_cast<uint4*>(p) = make_uint4(c[0][0], c[0][1], c[0][2], c[0][3]);
+    if (row + 16 < n_rows) *reinterpret_cast<uint4*>(p + 16 * row_elems) = make_uint4(c[1][0], c[1][1], c[1][2], c[1][3]);
+}
+
 // Between LDS accesses by which the lanes of a wave hand values to each other.  LDS takes a wave's instructions in order; the
 // compiler keeps that order only where one lane's own addresses may meet, which is not where the values go.  No instruction.
 __device__ __forceinline__ void lds_exchange() {
@@ -331,8 +360,13 @@ __device__ __forceinline__ void lds_exchange() {
 // L2 beforehand changes nothing.)  Accumulators stored straight from theirs write 64 bytes of each of 16 rows.  In LDS the rows stand
 // as in a tile, 0 - 15 at `a` and 16 - 31 at `b`: the two places that the wave itself fills when it copies its share of a pair
 // of tiles.  Measured, straight / through LDS, in us: 65 536 tokens of packed samples of 450, 32 / 8 heads, forward 490 / 460,
-// dQ 637 / 549, dK/dV 833 / 817; 33 506 tokens in samples of 2 100 692 / 676, 872 / 834, 1 280 / 1 267; 64 / 8 heads,
-// samples of 5 000 tokens, 4 430 / 4 362, 5 660 / 5 458, 8 040 / 8 050; one sample of 221 tokens 11.5 / 12.0, 12.6 / 12.4, 22.7 / 21.3.
+// dQ 637 / 549; 33 506 tokens in samples of 2 100 692 / 676, 872 / 834; 64 / 8 heads, samples of 5 000 tokens, 4 430 / 4 362,
+// 5 660 / 5 458.
+//   dK/dV by itself, K and V in straight / through LDS: 850 / 809 on those packed samples, 183 / 178 on 8 334 tokens in samples
+// of 1 000, 1 300 / 1 265 on the 33 506 tokens, 30.6 / 30.0 (whole backward) on one sample of 221.  dK and dV out: at head_dim 128
+// through LDS loses, 807 / 801, 177.5 / 176.3, 129.6 / 129.1 on four samples of 1 280, 42.8 / 41.6 on eight of 560 with 16 / 16
+// heads, 37.3 / 37.0 (whole backward) on 500 tokens, and even on long rows, so they go straight; at 64 it is even but for small
+// grids (whole backward of 900 tokens on 8 / 8 heads 29.2 / 28.9).
 template <int D>
 struct Rows {
     static constexpr int kRB = kRowBytesOf<D>, kChunks = D / 8, kPieces = D / 16;  // 16-byte chunks of a row; pieces of 1024 bytes

@@ -197,7 +197,7 @@ __global__ __launch_bounds__(256) void psattn_dkdv_bf16_mfma(AttnArgs a) {
     // tiles of Q (two buffers), of dO (two buffers) per group; then LSE * log2(e) and -delta
     __shared__ __attribute__((aligned(16))) char smem[S][4][kQTileBytes];
     __shared__ __attribute__((aligned(16))) float sStat[S][2][2][64];
-    __shared__ __attribute__((aligned(16))) char sRows[S == 1 ? 4 * 64 * kRowBytes : 1];  // K and V rows, later dK and dV rows, of each wave
+    __shared__ __attribute__((aligned(16))) char sRows[S == 1 ? 4 * 64 * kRowBytes : 1];  // K and V rows of each wave
     // a[0:191] are in use: makes the kernel's register allocation cover them
     asm volatile("" ::: "a0", "a191");
     fetch_args(a);
@@ -407,18 +407,13 @@ __global__ __launch_bounds__(256) void psattn_dkdv_bf16_mfma(AttnArgs a) {
         static_for<0, 16>([&](auto I) { x[decltype(I)::value] = acc_get<decltype(A0)::value + decltype(I)::value>(); });
         return x;
     };
-    // (a split row: the second group's tiles, which nobody uses any more)
     const int lx = opaque(l);
-    char* const out = S == 1 ? own : &smem[S - 1][0][0] + wg * 32 * kRowBytes;
-    const Rows<128> out_rows{out, out + 16 * kRowBytes};
-    const size_t out0 = (static_cast<size_t>(row0) * Hkv + kvh) * kRowBytes;
-    if (S == 1 || group == 0) {
+    const size_t out0 = (static_cast<size_t>(row0) * Hkv + kvh) * 128, row_elems = static_cast<size_t>(Hkv) * 128;
+    if (S == 1 || group == 0)
         static_for<0, 4>([&](auto DB) {
             constexpr int db = decltype(DB)::value;
-            out_rows.put(db, get(std::integral_constant<int, kAccDV + 16 * db>{}), 1.f, lx);
+            store_block(static_cast<uint16_t*>(a.dV) + out0, row_elems, T - row0, db, get(std::integral_constant<int, kAccDV + 16 * db>{}), 1.f, lx);
         });
-        out_rows.copy_out(static_cast<char*>(a.dV) + out0, k_row_bytes, lx, T - row0);
-    }
     if (S > 1 && group == 0) return;
     if (a.rope) {
         // K arrived rotated: turn dK back by the key's angles (accumulator element 4 i4 + k of block
@@ -440,16 +435,15 @@ __global__ __launch_bounds__(256) void psattn_dkdv_bf16_mfma(AttnArgs a) {
                     y[4 * i4 + k] = hi;
                 }
             }
-            out_rows.put(db, x, a.scale, lx);
-            out_rows.put(db + 2, y, a.scale, lx);
+            store_block(static_cast<uint16_t*>(a.dK) + out0, row_elems, T - row0, db, x, a.scale, lx);
+            store_block(static_cast<uint16_t*>(a.dK) + out0, row_elems, T - row0, db + 2, y, a.scale, lx);
         });
     } else {
         static_for<0, 4>([&](auto DB) {
             constexpr int db = decltype(DB)::value;
-            out_rows.put(db, get(std::integral_constant<int, kAccDK + 16 * db>{}), a.scale, lx);
+            store_block(static_cast<uint16_t*>(a.dK) + out0, row_elems, T - row0, db, get(std::integral_constant<int, kAccDK + 16 * db>{}), a.scale, lx);
         });
     }
-    out_rows.copy_out(static_cast<char*>(a.dK) + out0, k_row_bytes, lx, T - row0);
 }
 
 }  // namespace

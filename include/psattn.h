@@ -190,6 +190,9 @@ int psattn_meta_copy_key_desc(const psattn_meta* meta, int32_t* key_hi);
  * sum_i tri(p) + sum_responses (len * p + tri(len)), tri(n) = n(n+1)/2
  * (two responses: tri(p) + c*p + tri(c) + r*p + tri(r)). */
 int psattn_meta_allowed_pairs(const psattn_meta* meta, int64_t* n_allowed);
+/* Bytes of device memory that the mask takes up: 0 where it travels with the kernels' arguments
+ * (or was built without a device). */
+int psattn_meta_device_bytes(const psattn_meta* meta, size_t* bytes);
 
 /*
  * First-Fit-Decreasing packing of samples into rows of row_len tokens (Section 4.3.2: an

@@ -16,7 +16,7 @@ _LIB = None
 EXPORTS = [
     "psattn_build_meta", "psattn_build_meta_host", "psattn_free_meta", "psattn_meta_tiles",
     "psattn_meta_copy_csr", "psattn_meta_copy_tok_desc", "psattn_meta_copy_key_desc",
-    "psattn_meta_allowed_pairs", "psattn_fwd", "psattn_bwd", "psattn_bwd_workspace_bytes",
+    "psattn_meta_allowed_pairs", "psattn_meta_device_bytes", "psattn_fwd", "psattn_bwd", "psattn_bwd_workspace_bytes",
     "psattn_kernel_name", "psattn_strerror", "psattn_profile_enable", "psattn_profile_read",
     "psattn_free_meta_async", "psattn_trim_pool", "psattn_uses_mfma",
     "psattn_bwd_static", "psattn_bwd_static_max_rows", "psattn_probe_dq_atomics", "psattn_probe_mfma_peak",
@@ -77,6 +77,7 @@ def load_library():
     lib.psattn_meta_copy_tok_desc.argtypes = [vp, vp]
     lib.psattn_meta_copy_key_desc.argtypes = [vp, vp]
     lib.psattn_meta_allowed_pairs.argtypes = [vp, C.POINTER(i64)]
+    lib.psattn_meta_device_bytes.argtypes = [vp, C.POINTER(C.c_size_t)]
     lib.psattn_fwd.argtypes = [vp, i32, i32, i32, i32, f32, vp, vp, vp, vp, vp, vp]
     lib.psattn_bwd.argtypes = [vp, i32, i32, i32, i32, f32, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp,
                                C.c_size_t, vp]
@@ -231,6 +232,12 @@ class Meta:
         n = C.c_int32()
         _check(lib.psattn_meta_copy_positions(self.handle, out.ctypes.data, C.byref(n)), "psattn_meta_copy_positions")
         return out[:self.total_tokens], n.value
+
+    def device_bytes(self) -> int:
+        """Device memory that the mask takes up; 0: it travels with the kernels' arguments."""
+        n = C.c_size_t()
+        _check(load_library().psattn_meta_device_bytes(self.handle, C.byref(n)), "psattn_meta_device_bytes")
+        return n.value
 
     def allowed_pairs(self):
         lib = load_library()

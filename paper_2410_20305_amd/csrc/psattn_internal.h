@@ -97,7 +97,7 @@ struct psattn_meta {
     void* d_blob = nullptr;   // device copy of the metadata (from the library's blob pool)
     void* h_stage = nullptr;  // pinned staging buffer, alive until release
     void* h_stage_dev = nullptr;  // its address on the device
-    size_t blob_bytes = 0;    // bytes in use
+    size_t blob_bytes = 0;    // bytes in use (0: the mask travels with the kernels' arguments)
     size_t blob_cap = 0;      // bytes allocated
     void* blob_idle = nullptr;  // hipEvent_t of the pooled pair
     psattn::DeviceMeta dev{};

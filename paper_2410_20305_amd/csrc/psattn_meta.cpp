@@ -373,6 +373,12 @@ int psattn_meta_allowed_pairs(const psattn_meta* meta, int64_t* n_allowed) {
     return PSATTN_OK;
 }
 
+int psattn_meta_device_bytes(const psattn_meta* meta, size_t* bytes) {
+    if (!meta || !bytes) return PSATTN_EINVAL;
+    *bytes = meta->blob_bytes;
+    return PSATTN_OK;
+}
+
 const char* psattn_strerror(int status) {
     switch (status) {
         case PSATTN_OK: return "ok";

@@ -12,6 +12,7 @@ from oracle import psattn_oracle as orc
 pytestmark = pytest.mark.gpu
 
 SMALL = dict(samples=[(23, 9, 14), (5, 0, 11), (20, 7, 13)], offsets=[3, 52, 70], T=125)
+FEW = dict(samples=[(23, 9, 14), (0, 0, 6), (20, 7, 13)], offsets=[0, 52, 58], T=98)  # eight runs: travels with the kernels' arguments
 TILES = dict(samples=[(150, 40, 70), (30, 90, 10), (100, 33, 65)], offsets=[5, 300, 430], T=700)
 MANY = dict(samples=[(70, 30, 28)] * 40, offsets=[5 + 130 * i for i in range(40)], T=5300)  # dK/dV rows held by one workgroup each
 # kernels: dtype, d, heads, tiles, layout
@@ -24,6 +25,11 @@ PATHS = {
     "bf16_64": ("bf16", 64, 4, 2, (0, 0, 0, 0), TILES),
     "bf16_64_many": ("bf16", 64, 16, 16, (0, 0, 0, 0), MANY),
     "bf16_64_small": ("bf16", 64, 3, 1, (0, 0, 0, 0), SMALL),
+    "bf16_64_shared": ("bf16", 64, 16, 4, (0, 0, 0, 0), MANY),  # four heads on the same queries
+    "f32_64_in_args": ("f32", 64, 2, 1, (0, 0, 0, 0), FEW),
+    "f32_128_in_args": ("f32", 128, 4, 2, (0, 0, 0, 0), FEW),
+    "f32_two_launches_in_args": ("f32", 64, 5, 1, (0, 0, 0, 0), FEW),
+    "bf16_64_in_args": ("bf16", 64, 4, 2, (0, 0, 0, 0), FEW),
     "bf16_generic_128": ("bf16", 128, 5, 1, (32, 16, 16, 32), SMALL),
 }
 
@@ -43,7 +49,8 @@ def test_poison_stays_where_it_is_read(path, value):
     bad = {n: x.copy() for n, x in tens.items()}
     for x in bad.values():
         x[poison] = value
-    out, _ = run_gpu(w, bad, tiles)
+    out, meta = run_gpu(w, bad, tiles)
+    assert (meta.device_bytes() == 0) == path.endswith("_in_args")
     check_padding_zero(out, D)
     q_bad = real & (poison | (mask & poison[None, :]).any(axis=1))
     k_bad = real & (poison | (mask & q_bad[:, None]).any(axis=0))

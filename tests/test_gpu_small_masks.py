@@ -1,6 +1,6 @@
 """Block masks that travel with the kernels' arguments (up to 1 024 tokens, 8 runs of equal descriptors, 8 rows of tiles) against the
 same masks in device memory: the samples once more in a longer buffer, whose further tokens are padding, give the same outputs
-bit for bit.  Sizes on both sides of every line, empty and one-token segments, padding in front, between and behind."""
+bit for bit.  Which form a mask takes is asserted.  Sizes on both sides of every line, empty and one-token segments, padding in front, between and behind."""
 import numpy as np
 import pytest
 
@@ -14,13 +14,16 @@ CASES = {
     "one_sample": ([0], [100], [[40, 37]], 177),
     "tile_edges": ([0], [64], [[64, 64]], 192),
     "padding_around": ([5, 130], [40, 33], [[20, 30], [9, 11]], 250),     # 9 runs: in device memory either way
-    "eight_runs": ([3, 70], [20, 31], [[10, 12], [7, 8]], 140),           # with padding in front, between and behind
+    "nine_runs": ([3, 70], [20, 31], [[10, 12], [7, 8]], 140),            # with padding in front, between and behind
+    "eight_runs": ([3, 70], [20, 31], [[10, 12], [7, 8]], 116),           # in front and between
+    "eight_runs_full": ([0, 40, 77], [20, 31, 9], [[10, 10], [6], [5, 4]], 95),
     "no_prompt": ([0], [0], [[70, 90, 33]], 193),
     "six_responses": ([0], [90], [[30, 1, 64, 17, 5, 80]], 300),
     "longest": ([0], [700], [[200, 124]], 1024),
     "one_too_long": ([0], [700], [[200, 125]], 1025),
     "all_padding_rows": ([900], [50], [[30, 20]], 1010),
 }
+IN_MEMORY = ("padding_around", "nine_runs", "one_too_long")
 
 
 def _tables(case):
@@ -29,10 +32,11 @@ def _tables(case):
     return off, p, ptr, np.array([x for y in r for x in y], dtype=np.int32), T
 
 
-def _step(case, T, tens, scale, theta=None):
+def _step(case, T, tens, scale, in_args, theta=None):
     import torch
     off, p, ptr, resp, _ = _tables(case)
     meta = ps.psattn_build_meta_multi(off, p, ptr, resp, T)
+    assert (meta.device_bytes() == 0) == in_args
     t = {n: torch.zeros((T,) + tuple(x.shape[1:]), dtype=x.dtype, device="cuda") for n, x in tens.items()}
     for n, x in tens.items():
         t[n][:x.shape[0]] = x
@@ -57,7 +61,7 @@ def test_mask_in_arguments(case, dtype, d, theta):
     gen = torch.Generator(device="cuda").manual_seed(8)
     dt = torch.bfloat16 if dtype == "bf16" else torch.float32
     tens = {n: torch.randn((T, h, d), generator=gen, device="cuda").to(dt) for n, h in (("Q", 4), ("K", 2), ("V", 2), ("dO", 4))}
-    a = _step(case, T, tens, d ** -0.5, theta)
-    b = _step(case, 1300, tens, d ** -0.5, theta)
+    a = _step(case, T, tens, d ** -0.5, case not in IN_MEMORY, theta)
+    b = _step(case, 1300, tens, d ** -0.5, False, theta)
     for x, y in zip(a, b):
         assert torch.equal(x, y)

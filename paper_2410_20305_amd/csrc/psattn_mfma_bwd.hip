@@ -67,7 +67,8 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_dq_bf16_mfma(Att
                         reinterpret_cast<const char*>(V) + static_cast<size_t>(k0) * row_bytes, row_bytes, T - 1 - k0, dml, w, l);
     };
     int ent = rl.first_entry, it = 0, n_ent = rl.count;
-    // waves that share their queries leave out the tiles at both ends of the list that are there for the q-tile's others
+    // waves that share their queries leave out the tiles at both ends of the list that are there for the q-tile's others (at
+    // the back, below, of lists that one batch of the reader holds)
     if (qb.together)
         while (it < n_ent && !reads_tile(ent, row0, tk))
             if (++it < n_ent) ent = es.get(it);

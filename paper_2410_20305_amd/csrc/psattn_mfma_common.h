@@ -15,7 +15,7 @@
 //  * K/V (or Q/dO) tiles are staged in LDS, rows of 2 d bytes, with the 16-byte chunk
 //    index XOR-swizzled by the row so that both row-wise 128-bit reads and the
 //    transposing 64-bit reads (ds_read_b64_tr_b16) are bank-conflict free without
-//    padding.  Tiles are copied global -> LDS asynchronously, one tile ahead, into
+//    padding (Rows::put, which writes accumulators, is not).  Tiles are copied global -> LDS asynchronously, one tile ahead, into
 //    the buffer the previous tile has just vacated; one barrier per tile.
 //  * dK/dV are owned by one workgroup per (k-tile, kv-head), which walks the G
 //    query heads of the group and the k-major tile list, so the prompt's keys
@@ -399,7 +399,9 @@ struct Rows {
         char* const at = l & 16 ? b - 16 * kRB : a;
         static_for<0, D / 16>([&](auto S) { *reinterpret_cast<uint4*>(at + (nat ^ (decltype(S)::value << 5))) = f[decltype(S)::value].u; });
     }
-    // head dims 32 db .. of an accumulator whose column is row l % 32: a lane holds pieces of four head dims, 8 bytes in bf16
+    // head dims 32 db .. of an accumulator whose column is row l % 32: a lane holds pieces of four head dims, 8 bytes in bf16.
+    // Rows r and r + 16 share a swizzle, so a half-wave meets every 16-byte slot twice: 64 cycles of bank conflicts per wave and
+    // output at d = 128.
     __device__ __forceinline__ void put(int db, const f32x16& x, float factor, int l) const {
         const int row = l & 31;
         char* const at = (row & 16 ? b - 16 * kRB : a) + row * kRB + 8 * (l >> 5);
@@ -425,8 +427,10 @@ struct Rows {
 // list[first + step * k] (step = +1 or -1), n positions in all.  Lane l keeps entry
 // 64 b + l of the current batch b; the next batch is requested when a batch is entered,
 // i.e. 64 positions before its first use.  get(k) must be called with non-decreasing k,
-// from wave-uniform control flow, at a point where no asynchronous copy is in flight
-// (the refill is a compiler-tracked load and is waited for with vmcnt(0)).
+// from wave-uniform control flow.  The refill is a compiler-tracked load, waited for with
+// vmcnt(0), which waits for every asynchronous copy in flight as well: the tile loops call get()
+// where there is none.  Ahead of the loops the trimming of shared queries and the second group of a
+// split dK/dV row call it while Q, dO, K or V rows are on their way, and wait for those too.
 struct EntryStream {
     const int* list;
     int first, step, n, l;
@@ -469,7 +473,9 @@ struct EntryStream {
 // 136 / 131, 33 506 tokens in samples of 2 100 682 / 675 and 873 / 855; 64 / 8 heads, samples of 5 000 tokens, 4 365 / 4 331 and
 // 5 612 / 5 556; head_dim 64, 4 758 tokens, 46 / 43 and 49 / 46.  Which tile comes first is known only once the descriptors of
 // the queries are, so a grid that the chip holds at once, which lasts as long as one workgroup, keeps one head: a step of one
-// sample of 221 tokens 46.8 / 48.9.
+// sample of 221 tokens 46.8 / 48.9.  At head_dim 64 the chip holds 768 workgroups at once, but four heads are the faster way from
+// 513 on there too: 640 / 704 / 768 workgroups, forward 14.2 / 13.7, 14.4 / 14.1, 14.6 / 14.5, backward 38.3 / 37.6, 39.3 / 38.8,
+// 40.3 / 39.8.
 constexpr int kTwoPerCu = 512;  // workgroups
 struct QueryBlock {
     int kvh, h;     // kv head, q head

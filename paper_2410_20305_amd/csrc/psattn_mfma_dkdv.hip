@@ -452,11 +452,10 @@ __global__ __launch_bounds__(256) void psattn_dkdv_bf16_mfma(AttnArgs a) {
 // workgroup per CU, so a launch takes at least its longest chain however few workgroups there are; splitting halves the
 // chain and costs 10 - 15 % more work (every tile is staged for 64 keys instead of 128) and the exchange at the end.  The
 // line lies where the longest chain is 1.6 times a CU's share of all steps, and at chains of 8 steps.  Measured, dK/dV alone,
-// unsplit / split, 32 q / 8 kv heads by that ratio: 1.04 (six samples of 1 200 tokens) 151 / 171 us, 1.08 131 / 144, 1.25
-// 247 / 230, 1.28 148 / 146, 1.48 (four of 1 280) 136 / 135, 1.58 71 / 63, 1.60 143 / 119, 4.0 20 / 16, 24 (180 tokens) 26 / 20;
-// 64 / 8 heads 1.04 303 / 338, 1.08 900 / 934, 1.28 288 / 276, 1.48 249 / 238, 1.60 277 / 216; 28 / 4 heads 1.9 387 / 269, 3.2
-// 227 / 137; 16 / 16 heads never above 0.8 but for chains of 2 and 3 (11.6 / 12.0, 12.4 / 12.7).  Between 1.25 and 1.6 both are
-// within 7 %, so the line keeps clear of the losses below it.
+// unsplit / split, 32 q / 8 kv heads by that ratio: 1.03 (six samples of 1 200 tokens) 155 / 174 us, 1.08 172 / 193, 1.19 133 / 144,
+// 1.48 (four of 1 280) 127 / 117, 1.96 112 / 78, 3.8 105 / 64, 7.5 88 / 54, 24 (180 tokens) 26 / 19; 64 / 8 heads 1.48 246 / 220, 2.96
+// 218 / 137, 4.0 322 / 186; 28 / 4 heads 4.8 279 / 159, 8.1 283 / 159; 16 / 16 heads 0.76 42 / 62.  The two cross between 1.2 and
+// 1.5; the line keeps clear of the losses below that, and of another order of sums for the tables in between.
 constexpr int64_t kCus = 256;
 
 int launch_mfma_dkdv(const AttnArgs& a, void* stream) {

@@ -36,7 +36,6 @@ __global__ __launch_bounds__(256, 2) void psattn_dkdv64_bf16_mfma(AttnArgs a) {
     const RowLaunch rl = row_launch<kGridK>(a.meta, rest / S);  // one scalar load: row, list bounds, first entry
     const int row0 = rl.row * 128 + (rest % S) * (128 / S) + 32 * w;  // the wave's first key
     const int key = row0 + c32;
-    const bool kvalid = key < T;
     const TokenLoad begun = token_begin(a.meta, key);
     // K and V rows of the wave's keys pass through LDS: an unsplit row has room of its own, a split one takes its second buffers
     char *const k_at = S == 1 ? sRows + 64 * kRB * w : smem[group][1] + kRows * w * kRB;
@@ -302,11 +301,12 @@ __global__ __launch_bounds__(256, 2) void psattn_dkdv64_bf16_mfma(AttnArgs a) {
 // Which of the two.  A workgroup is a serial chain of as many steps (heads of the group x q-tiles) as its row is long; with
 // two workgroups per CU a launch is bound by its longest chain until that falls below half of a CU's share of all steps.
 // Splitting halves the chain and costs a few per cent more work (every tile is staged for 64 keys instead of 128) and the
-// exchange at the end; the line lies where the longest chain is a CU's share.  Measured on 96 tables, chains of 1 to 496 steps,
-// whole step of forward and backward, unsplit / split: one sample of 2 000 tokens, 32 q / 8 kv heads (chain 128, share 33)
-// 378 / 248 us; eight of 860 tokens (64, 59) 304 / 273; fourteen of 600 (48, 58) 264 / 248; 16 / 16 heads, two of 1 600
-// (26, 22) 158 / 140, eight of 500 (10, 13) 80 / 82, twenty-four of 256 (4, 9) 72 / 77; one sample of 40 tokens, 8 / 8 heads
-// (chain 1) 28.6 / 29.2, of 180 (3) 33.8 / 32.5.  No table inside the line loses more than that 2 %.
+// exchange at the end; the line lies where the longest chain is a CU's share.  Measured, dK/dV alone, unsplit / split, 32 q / 8 kv
+// heads: one sample of 2 000 tokens (chain 128, share 34) 266 / 137 us; four of 1 280 (80, 54) 173 / 114; 4 758 tokens (52, 31)
+// 116 / 70; eight of 860 (64, 61) 155 / 121; outside the line 24 of 300 (32, 33) 79 / 64, fourteen of 600 (48, 58) 123 / 104;
+// 16 / 16 heads, two of 1 600 (26, 22) 68 / 49, outside eight of 500 (10, 13) 32 / 32, 24 of 256 (4, 9) 29 / 33, 24 of 300 (8, 17)
+// 41 / 44; 8 / 8 heads, one sample of 40 tokens (chain 1) 8.3 / 8.5, of 180 (3) 12.9 / 10.8.  Rows in groups of four heads would gain
+// below the line as well; it keeps the order of sums of the tables there.
 constexpr int64_t kCus = 256;
 
 int launch_mfma_dkdv64(const AttnArgs& a, void* stream) {

@@ -46,7 +46,8 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(At
         for (int t = 0; t < 4; ++t) rope_load8(turn + 4 * t, row, 16 * t + 8 * g);
     }
     Frag8 qf[kSteps];
-    // (the asynchronous copies move 16-byte groups; a Q that does not start on one is loaded straight into the registers)
+    // (the asynchronous copies move 16-byte groups, on which every tensor has to start; a Q that does not was read as it lies
+    // before its rows came by such copies, and still is, straight into the registers)
     const bool straight = D == 128 && (reinterpret_cast<uintptr_t>(a.Q) & 15) != 0;
     if (straight) {
 #pragma unroll
@@ -90,7 +91,8 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(At
     Tok4 tk = found;
     if (qb.together) {
         tk = token_choose(a.meta, begun, found);
-        // waves that share their queries leave out the tiles at both ends of the list that are there for the q-tile's others
+        // waves that share their queries leave out the tiles at both ends of the list that are there for the q-tile's others (at
+        // the back, below, of lists that one batch of the reader holds)
         while (it < n_ent && !reads_tile(ent, row0, tk))
             if (++it < n_ent) ent = es.get(it);
         first_copy();

@@ -363,7 +363,8 @@ __device__ __forceinline__ void lds_exchange() {
 // dQ 637 / 549; 33 506 tokens in samples of 2 100 692 / 676, 872 / 834; 64 / 8 heads, samples of 5 000 tokens, 4 430 / 4 362,
 // 5 660 / 5 458.
 //   dK/dV by itself, K and V in straight / through LDS: 850 / 809 on those packed samples, 183 / 178 on 8 334 tokens in samples
-// of 1 000, 1 300 / 1 265 on the 33 506 tokens, 30.6 / 30.0 (whole backward) on one sample of 221.  dK and dV out: at head_dim 128
+// of 1 000, 1 300 / 1 265 on the 33 506 tokens, 30.6 / 30.0 (whole backward) on one sample of 221, at head_dim 64 71.5 / 71.0 on 4 758
+// tokens, 29.4 / 29.2 (whole backward) on 900 tokens, 8 / 8 heads.  dK and dV out: at head_dim 128
 // through LDS loses, 807 / 801, 177.5 / 176.3, 129.6 / 129.1 on four samples of 1 280, 42.8 / 41.6 on eight of 560 with 16 / 16
 // heads, 37.3 / 37.0 (whole backward) on 500 tokens, and even on long rows, so they go straight; at 64 it is even but for small
 // grids (whole backward of 900 tokens on 8 / 8 heads 29.2 / 28.9).

@@ -10,7 +10,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpsattn.so")
 LAYER_LIB = os.path.join(HERE, "libpsattn_layer.so")   # the attention-layer benchmark: libpsattn + rocBLAS
-SOURCES = ["psattn_meta.cpp", "psattn_pack.cpp", "psattn_api.hip", "psattn_upload.hip", "psattn_generic.hip", "psattn_mfma_fwd.hip", "psattn_mfma_fwd64.hip", "psattn_mfma_bwd.hip",
+SOURCES = ["psattn_meta.cpp", "psattn_pack.cpp", "psattn_api.hip", "psattn_upload.hip", "psattn_generic.hip", "psattn_mfma_fwd.hip", "psattn_mfma_fwd64.hip", "psattn_mfma_fwd3.hip", "psattn_mfma_bwd.hip",
            "psattn_mfma_dkdv.hip", "psattn_mfma_dkdv64.hip", "psattn_bwd_static.hip", "psattn_probe.hip", "psattn_rope.hip", "psattn_logprob.hip"]
 
 # Packed-fp32 VALU instructions are switched off for all device code (the compiler
@@ -23,6 +23,7 @@ SOURCE_FLAGS = {"psattn_mfma_dkdv.hip": ["-mllvm", "-amdgpu-spill-vgpr-to-agpr=0
                 # the forward takes its row maxima with fmaxf; without NaNs to honour that is one v_max3_f32 per
                 # three values (head_dim 128 requires finite inputs)
                 "psattn_mfma_fwd.hip": ["-fno-honor-nans"],
+                "psattn_mfma_fwd3.hip": ["-fno-honor-nans"],
                 # the probe measures the hardware fp32 atomic add, not a compare-and-swap loop
                 "psattn_probe.hip": ["-munsafe-fp-atomics"]}
 

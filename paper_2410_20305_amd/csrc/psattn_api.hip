@@ -384,7 +384,7 @@ int fwd_checked(const psattn_meta* meta, int32_t dt, int32_t n_q_heads, int32_t 
     int err;
     {
         PassTimer t(0, hip_stream);
-        err = !mfma ? launch_generic_fwd(dt, a, hip_stream) : head_dim == 64 ? launch_mfma_fwd64(a, hip_stream) : launch_mfma_fwd(a, hip_stream);
+        err = !mfma ? launch_generic_fwd(dt, a, hip_stream) : head_dim == 64 ? launch_mfma_fwd64(a, hip_stream) : mfma_fwd_three(a) ? launch_mfma_fwd3(a, hip_stream) : launch_mfma_fwd(a, hip_stream);
         g_last_kernel[0] = mfma ? "psattn_fwd_bf16_mfma" : "generic_fwd";
     }
     return err == 0 ? PSATTN_OK : PSATTN_EHIP;

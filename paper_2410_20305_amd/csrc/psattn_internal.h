@@ -174,6 +174,8 @@ int launch_generic_dkdv(int dt, const AttnArgs& a, void* stream);
 int launch_generic_bwd(int dt, const AttnArgs& a, void* stream);  // dQ, dK, dV in one launch
 bool generic_bwd_in_one(const AttnArgs& a);                       // where that is the faster way
 int launch_mfma_fwd(const AttnArgs& a, void* stream);    // head_dim 128
+int launch_mfma_fwd3(const AttnArgs& a, void* stream);   // the same with three workgroups to a CU
+bool mfma_fwd_three(const AttnArgs& a);                  // where that is the faster way
 int launch_mfma_fwd64(const AttnArgs& a, void* stream);
 int launch_mfma_dq(const AttnArgs& a, void* stream);
 int launch_mfma_dkdv(const AttnArgs& a, void* stream);

@@ -89,7 +89,8 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_dq_bf16_mfma(Att
             dl = fmaf(__uint_as_float(ow[j] & 0xffff0000u), __uint_as_float(gw[j] & 0xffff0000u), dl);
         }
     }
-    dl += other_half(dl);
+    const Halves dh = halves(dl);
+    dl = dh.lo + dh.hi;
     asm volatile("" : "+v"(dl)::"memory");  // ... and O is done with before the second tile's copies take its place
     if (valid && g == 0) {
         a.delta[static_cast<size_t>(h) * T + q_row] = -dl;  // the dK/dV kernel starts its dP accumulators from -delta

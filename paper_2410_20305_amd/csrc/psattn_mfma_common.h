@@ -210,11 +210,14 @@ __device__ __forceinline__ f32x16 mfma_parts(bf16x8 a, const Operand<D>& b, f32x
     return acc;
 }
 
-// max / sum across the two half-waves that share a column
-__device__ inline float other_half(float x) {
+// max / sum across the two half-waves that share a column: what either of them holds, the same in both
+struct Halves {
+    float lo, hi;
+};
+__device__ inline Halves halves(float x) {
     const uint32_t u = __float_as_uint(x);
     auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-    return __uint_as_float(threadIdx.x & 32 ? r[0] : r[1]);
+    return {__uint_as_float(r[0]), __uint_as_float(r[1])};
 }
 
 // row of the 32x32 accumulator that register i of lane-half g holds

@@ -1,5 +1,5 @@
-// bf16 MFMA forward kernel for gfx950; layout and staging helpers are in psattn_mfma_common.h.  Built once per head_dim:
-// psattn_mfma_fwd.hip (128) and psattn_mfma_fwd64.hip (64).
+// bf16 MFMA forward kernel for gfx950; layout and staging helpers are in psattn_mfma_common.h.  Built three times:
+// psattn_mfma_fwd.hip and psattn_mfma_fwd3.hip (head_dim 128, two and three workgroups to a CU) and psattn_mfma_fwd64.hip (64).
 #pragma once
 #include "psattn_mfma_common.h"
 
@@ -13,11 +13,17 @@ __device__ __forceinline__ float fmax3(float a, float b, float c) { return __bui
 // ------------------------------------------------------------------ forward
 // grid: as many workgroups as (q-tile of 128 queries, q-head); 4 waves x 32 queries of one head or of four (query_block).
 // D = head_dim.  D = 128: 64 KB of LDS and under 256 registers, two workgroups per CU.  D = 64: half of both.
-template <int D>
-__global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(AttnArgs a) {
+// kLateV (D = 128): 48 KB and 168 registers, three workgroups per CU.  V has one buffer and travels while the scores of its own
+// tile are computed, behind a second barrier per tile; the third wave of a SIMD covers that barrier, the softmax arithmetic and
+// the rows' way in and out better than two do.  To fit, the operand ring holds three slots instead of four (one slot of look-ahead
+// instead of two: 4 % slower), lane offsets are taken again in every tile instead of kept, and a clipped last tile stands for
+// the last 64 rows of the buffer (with a mask from its own first key on) instead of keeping clamped offsets.  Raising the waves'
+// priority for the second product changes nothing (+-0.5 %).  mfma_fwd_three says where it is the faster one.
+template <int D, bool kLateV>
+__global__ __launch_bounds__(256, D == 64 || kLateV ? 3 : 2) void psattn_fwd_bf16_mfma(AttnArgs a) {
     constexpr int kRB = kRowBytesOf<D>, kSteps = D / 16, kBlocks = D / 32;  // MFMA steps of a score, 32-wide blocks of an output row
     __shared__ __attribute__((aligned(16))) char sKb[2][64 * kRB];  // double buffered
-    __shared__ __attribute__((aligned(16))) char sVb[2][64 * kRB];
+    __shared__ __attribute__((aligned(16))) char sVb[kLateV ? 1 : 2][64 * kRB];
     fetch_args(a);
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, c32 = l & 31, g = l >> 5;
     const int T = a.meta.T, Hq = a.Hq, Hkv = a.Hkv;
@@ -32,10 +38,10 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(At
     const uint16_t* K = static_cast<const uint16_t*>(a.K) + kvh * D;
     const uint16_t* V = static_cast<const uint16_t*>(a.V) + kvh * D;
 
-    // Q passes through the places of buffer 1 that the wave's own K / V copies take later
+    // Q passes through the places of buffer 1 (late V: of the one V buffer) that the wave's own K / V copies take later
     const LaneOffsets lo = lane_offsets<D>(l);
     const uint32_t q_row_bytes = static_cast<uint32_t>(Hq) * kRB;
-    const Rows<D> rows1{sKb[1] + 16 * w * kRB, sVb[1] + 16 * w * kRB};
+    const Rows<D> rows1{sKb[1] + 16 * w * kRB, sVb[kLateV ? 0 : 1] + 16 * w * kRB};
     // rotary embedding: the table row of this lane's query, both members of a pair in the same lane
     float4 turn[D == 128 ? 16 : 1];
     Tok4 found = {kPadStart, 0, 0, 0};
@@ -63,7 +69,7 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(At
         for (int i = 0; i < 16; ++i) o[db][i] = 0.f;
     float m = -INFINITY, lsum = 0.f;
     const float c = a.scale * kLog2e;
-    constexpr int kAhead = 2, kRing = 4;  // measured: 1 and 3 are both slower
+    constexpr int kAhead = 2, kRing = kLateV ? 3 : 4;  // measured: 1 and 3 are both slower
 
     // K / V tiles are copied global -> LDS asynchronously, one tile ahead, into the
     // buffer the previous tile has just vacated; one barrier per tile.
@@ -72,8 +78,20 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(At
     const char* Vb = reinterpret_cast<const char*>(V);
     const DmaLaneOf<D> dl = dma_lane<D>(row_bytes, w, l);
     PairCopyOf<D> pc;
+    // late V: the first row of the tile whose K, respectively V, is being copied, and this lane's offset in the first piece
+    const char *late_k = nullptr, *late_v = nullptr;
+    const uint32_t late_lane = dl.off[0];
+    auto late_start = [&](int ent) { return min((ent >> 2) * 64, T - 64); };  // a clipped tile takes the last 64 rows
+    auto late_piece = [&](const char* from, char* to, auto P) {
+        constexpr int p = decltype(P)::value;
+        dma16(from + static_cast<size_t>(4 * p) * row_bytes, opaque(late_lane) ^ (p << 4), lds_addr(to) + 16 * w * kRB + 1024 * p);
+    };
     auto copy_setup = [&](int ent) {
         const int k0 = (ent >> 2) * 64;
+        if constexpr (kLateV) {
+            late_k = Kb + static_cast<size_t>(late_start(ent)) * row_bytes;
+            return;
+        }
         pair_copy_setup(pc, Kb + static_cast<size_t>(k0) * row_bytes, Vb + static_cast<size_t>(k0) * row_bytes, row_bytes,
                         T - 1 - k0, dl, w, l);
     };
@@ -82,7 +100,8 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(At
     auto first_copy = [&] {
         if (it < n_ent) {
             copy_setup(ent);
-            static_for<0, 2 * kBlocks>([&](auto P) { pair_copy_piece<decltype(P)::value>(pc, sKb[0], sVb[0], w); });
+            if constexpr (kLateV) static_for<0, kBlocks>([&](auto P) { late_piece(late_k, sKb[0], P); });
+            else static_for<0, 2 * kBlocks>([&](auto P) { pair_copy_piece<decltype(P)::value>(pc, sKb[0], sVb[0], w); });
         }
     };
     if (!qb.together) first_copy();
@@ -107,8 +126,15 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(At
         // this wave's copies of tile `it` have landed; after the barrier every wave's
         // have, and every wave has left the other buffer
         dma_wait_barrier<0>();
-        const int k0 = (ent >> 2) * 64;
+        const int k_first = (ent >> 2) * 64, k0 = kLateV ? late_start(ent) : k_first;
         bool full = (ent & 3) == PSATTN_TILE_FULL;
+        if constexpr (kLateV) late_v = Vb + static_cast<size_t>(late_start(ent)) * row_bytes;
+        auto piece = [&](auto P) {  // V of this tile, then K of the next
+            constexpr int p = decltype(P)::value;
+            if constexpr (!kLateV) pair_copy_piece<p>(pc, sKb[buf ^ 1], sVb[(buf ^ 1) % (sizeof(sVb) / sizeof(sVb[0]))], w);
+            else if constexpr (p < kBlocks) late_piece(late_v, sVb[0], P);
+            else late_piece(late_k, sKb[buf ^ 1], std::integral_constant<int, p - kBlocks>{});
+        };
         // The next tile's copy is issued piece by piece, on every other slot of the S phase.  After
         // the last tile the same tile is copied once more (to the other buffer, which nobody
         // reads), so the slots need no branch.
@@ -123,25 +149,27 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(At
         // workgroup's wave (two of the four waves on the second tile of every causal diagonal).
         uint32_t bits = 0xffffffffu;
         if (!full) {
-            bits = elem_range_bits(tk.s - k0, q_row + 1 - k0, g) & ~elem_range_bits(tk.hole_lo - k0, tk.hole_hi - k0, g);
+            bits = elem_range_bits(max(tk.s, k_first) - k0, q_row + 1 - k0, g) & ~elem_range_bits(tk.hole_lo - k0, tk.hole_hi - k0, g);
             if (__builtin_amdgcn_ballot_w64(bits != 0) == 0) {
-                static_for<0, 2 * kBlocks>([&](auto P) { pair_copy_piece<decltype(P)::value>(pc, sKb[buf ^ 1], sVb[buf ^ 1], w); });
+                static_for<0, 2 * kBlocks>([&](auto P) { piece(P); });
+                if constexpr (kLateV) dma_wait_barrier<kBlocks>();  // the other waves' second barrier
                 return;
             }
             full = __builtin_amdgcn_ballot_w64(bits != 0xffffffffu) == 0;  // for these 32 queries
         }
         const char* sK = sKb[buf];
-        const char* sV = sVb[buf];
+        const char* sV = sVb[kLateV ? 0 : buf];
         // 2 kS MFMA slots per tile: 0 .. kS - 1 S^T = K Q^T (rows = keys, column = this lane's
         // query), kS .. 2 kS - 1 O^T += V^T P^T.  The LDS operand of slot m is requested kAhead
         // slots earlier into a register ring.
         constexpr int kS = 2 * kSteps;
         Frag8 ring[kRing];
+        const int nat = kLateV ? opaque(lo.nat) : lo.nat;  // what it is XORed with is not kept across tiles
         auto request = [&](auto M) {
             constexpr int m = decltype(M)::value;
             if constexpr (m < kS) {
                 constexpr int t = m >> 1, kb = m & 1;
-                ring[m % kRing].v = ld_rows<t>(sK + kb * 32 * kRB, lo.nat);
+                ring[m % kRing].v = ld_rows<t>(sK + kb * 32 * kRB, nat);
             } else if constexpr (m < 2 * kS) {
                 constexpr int j = m - kS, kb = j / (2 * kBlocks), half = (j / kBlocks) & 1, db = j % kBlocks;
                 ring[m % kRing].v = ld_cols<db, half, D>(sV + 32 * kb * kRB, lo.tr1, lo.tr2);
@@ -155,8 +183,8 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(At
         static_for<0, kAhead>([&](auto M) { request(M); });
         static_for<0, kS>([&](auto M) {
             constexpr int m = decltype(M)::value, t = m >> 1, kb = m & 1;
-            request(std::integral_constant<int, m + kAhead>{});
-            if constexpr ((m & 1) == 0) pair_copy_piece<m / 2>(pc, sKb[buf ^ 1], sVb[buf ^ 1], w);  // every other slot: see PairCopy
+            if constexpr (!kLateV || m + kAhead < kS) request(std::integral_constant<int, m + kAhead>{});
+            if constexpr ((m & 1) == 0) piece(std::integral_constant<int, m / 2>{});  // every other slot: see PairCopy
             s[kb] = mfma(ring[m % kRing].v, qf[t].v, s[kb]);
             __builtin_amdgcn_sched_barrier(0);
         });
@@ -182,7 +210,8 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(At
 #pragma unroll
         for (int r = 0; r < 4; ++r) mxp[r] = fmax3(mxp[r], s[1][r + 12], mxp[r]);
         float mx = fmax3(mxp[0], mxp[1], fmax3(mxp[2], mxp[3], mxp[3]));
-        mx = fmax3(mx, other_half(mx), mx);
+        const Halves mh = halves(mx);
+        mx = fmax3(mh.lo, mh.hi, mh.hi);
         // Exact running maximum; O and l are rescaled only in tiles where some row's maximum
         // moves (wave ballot).  Letting the reference lag behind the maximum was measured
         // both ways: a fixed lag of 2^8 saves 5 % of this kernel but the largest probability of
@@ -217,6 +246,10 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(At
         const float psum = (ps[0] + ps[1]) + (ps[2] + ps[3]);
         lsum += psum;
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (kLateV) {
+            dma_wait_barrier<kBlocks>();  // every wave's V of this tile has landed, the next K may be on its way
+            static_for<0, kAhead>([&](auto M) { request(std::integral_constant<int, kS + decltype(M)::value>{}); });
+        }
         static_for<kS, 2 * kS>([&](auto M) {
             constexpr int m_ = decltype(M)::value, j = m_ - kS, kb = j / (2 * kBlocks), half = (j / kBlocks) & 1, db = j % kBlocks;
             request(std::integral_constant<int, m_ + kAhead>{});
@@ -242,14 +275,15 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(At
 #pragma unroll
     for (int t = 0; t < kSteps; ++t) asm volatile("" : "+v"(qf[t].v)::"memory");
     __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
-    while (it + 1 < n_ent) {
+    while (it < n_ent) {
         tile(std::integral_constant<int, 0>{});
+        if (it >= n_ent) break;
         tile(std::integral_constant<int, 1>{});
     }
-    if (it < n_ent) tile(std::integral_constant<int, 0>{});
     // no copy may still be writing to LDS when the workgroup ends
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    const float l_tot = lsum + other_half(lsum);
+    const Halves lh = halves(lsum);
+    const float l_tot = lh.lo + lh.hi;
     const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
     multiply(o, inv);
     if constexpr (D == 64) {
@@ -263,8 +297,8 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(At
     // ten of 256 13.4 / 13.1; one head, one sample of 180 tokens 7.6 / 7.8, of 221 8.8 / 9.1, 500 tokens 10.5 / 10.7, 16 / 16 heads, eight
     // samples of 560 22.6 / 23.1, 28 / 4 heads, two of 1 600 46.6 / 47.1, head_dim 64, 16 / 16 heads, 24 samples of 256 16.0 / 16.4.
     const int lx = opaque(l);
-    if (qb.together) {  // the buffer that the last tile was not in
-        const Rows<D> rows{sKb[n_tiles & 1] + 16 * w * kRB, sVb[n_tiles & 1] + 16 * w * kRB};
+    if (qb.together) {  // the buffer that the last tile was not in; late V: both of K, whose last reader is ahead of the last barrier
+        const Rows<D> rows{sKb[n_tiles & 1] + 16 * w * kRB, kLateV ? sKb[~n_tiles & 1] + 16 * w * kRB : sVb[(n_tiles & 1) % (sizeof(sVb) / sizeof(sVb[0]))] + 16 * w * kRB};
 #pragma unroll
         for (int db = 0; db < kBlocks; ++db) rows.put(db, o[db], 1.f, lx);
         rows.copy_out(static_cast<char*>(a.Oout) + (static_cast<size_t>(row0) * Hq + h) * kRB, q_row_bytes, lx, T - row0);
@@ -273,8 +307,8 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_fwd_bf16_mfma(At
 #pragma unroll
         for (int db = 0; db < kBlocks; ++db) store_block(orow, static_cast<size_t>(Hq) * D, T - row0, db, o[db], 1.f, lx);
     }
-    if (valid && g == 0)
-        a.LSEout[static_cast<size_t>(h) * T + q_row] = l_tot > 0.f ? m * kLn2 + __logf(l_tot) : -INFINITY;
+    if (lx < 32 && row0 + lx < T)
+        a.LSEout[static_cast<size_t>(h) * T + row0 + lx] = l_tot > 0.f ? m * kLn2 + __logf(l_tot) : -INFINITY;
 }
 
 }  // namespace

@@ -6,7 +6,7 @@ namespace psattn {
 int launch_mfma_fwd(const AttnArgs& a, void* stream) {
     const unsigned grid = static_cast<unsigned>(a.meta.n_rows[kGridQ]) * a.Hq;
     if (grid == 0) return 0;
-    psattn_fwd_bf16_mfma<128><<<grid, 256, 0, static_cast<hipStream_t>(stream)>>>(a);
+    psattn_fwd_bf16_mfma<128, false><<<grid, 256, 0, static_cast<hipStream_t>(stream)>>>(a);
     return static_cast<int>(hipGetLastError());
 }
 

@@ -245,6 +245,10 @@ __device__ __forceinline__ uint32_t lds_addr(const void* p) {
 __device__ __forceinline__ void dma4(const void* src, uint32_t lds_base) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(src) : "memory");
 }
+// the same from a wave-uniform address plus a lane's offset
+__device__ __forceinline__ void dma4(const void* base, uint32_t lane_off, uint32_t lds_base) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(lane_off), "s"(base) : "memory");
+}
 
 template <int N>
 __device__ __forceinline__ void dma_wait_barrier() {
@@ -255,13 +259,12 @@ __device__ __forceinline__ void dma_wait_barrier() {
 // A wave instruction fills 1024 bytes, four tile rows (d = 128) or eight (d = 64), so the
 // swizzle is applied on the global side: lane l fetches the logical chunk that belongs at its
 // physical chunk.  Each of the four waves of a workgroup copies 16 rows in D / 32
-// instructions; DmaLane holds the lane's byte offsets for them, so that a copy costs no
+// instructions; DmaLaneOf holds the lane's byte offsets for them, so that a copy costs no
 // vector ALU work: the address is a scalar tile base plus that 32-bit lane offset.
 template <int D>
 struct DmaLaneOf {
     uint32_t off[D / 32];
 };
-using DmaLane = DmaLaneOf<128>;
 
 // `w` (wave index in the workgroup) must be wave-uniform; rows past `last_row` re-read it
 template <int D = 128>
@@ -292,7 +295,17 @@ struct PairCopyOf {
     const char* b;  // first row of the second tile
     DmaLaneOf<D> lane;
 };
-using PairCopy = PairCopyOf<128>;
+
+// Lane offsets of a kernel's tiles.  Rows past the end of the buffer re-read its last one, in the one clipped tile of a list, which
+// stands at its end: the offsets are made again where the last row changes, by a branch that is taken once or twice in a
+// kernel, and not chosen for every tile (eight moves per tile, with nothing to cover them).
+template <typename Offsets>
+__device__ __forceinline__ void tile_rows(int last, int& cp_last, Offsets&& make) {
+    if (last == cp_last) return;
+    cp_last = last;
+    asm volatile("; clipped tile" : "+s"(last));  // keeps the clamped offsets' arithmetic in this branch
+    make(last);
+}
 
 template <int D>
 __device__ __forceinline__ void pair_copy_setup(PairCopyOf<D>& c, const char* a, const char* b, uint32_t row_bytes, int last_row,

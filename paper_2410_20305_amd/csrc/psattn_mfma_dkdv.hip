@@ -77,17 +77,21 @@ __device__ __forceinline__ void settle() {
 constexpr int kQTileBytes = 64 * kRowBytes;
 constexpr int kAhead = 4;  // measured: 3 and 5 are both slower
 
-// AND-masks for the packed bf16 pairs (elements 2j, 2j + 1 of block b) of one q-tile:
-// the queries allowed to read this lane's key are rows [lo, hi) of the tile.
-__device__ inline void pair_masks(uint32_t (&mw)[2][8], int lo, int hi, int g) {
-    const uint32_t bits = elem_range_bits(lo, hi, g);
-#pragma unroll
-    for (int b2 = 0; b2 < 2; ++b2)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int e = 16 * b2 + 2 * j;
-            mw[b2][j] = ((bits >> e) & 1u ? 0x0000ffffu : 0u) | ((bits >> (e + 1)) & 1u ? 0xffff0000u : 0u);
-        }
+// Which of a lane's elements of a q-tile are allowed, the queries that read its key being rows [lo, hi) of the tile: bit j for
+// element 2 j, bit 16 + j for element 2 j + 1.
+__device__ inline uint32_t pair_bits(int lo, int hi, int g) {
+    const int a = elems_below(min(max(lo, 0), 64), g), b = elems_below(min(max(hi, 0), 64), g);
+    const auto below = [](int n) { return ((1u << ((n + 1) >> 1)) - 1) | ((1u << (n >> 1)) - 1) << 16; };
+    return below(b) & ~below(a);
+}
+// AND-mask for the packed bf16 pair J (elements 2 J, 2 J + 1), by two instructions: each half moves its bit to the sign and fills
+// itself with it.  All sixteen masks ahead of the tile's first MFMA took 70 instructions, which nothing hid.
+template <int J>
+__device__ __forceinline__ uint32_t pair_mask(uint32_t bits) {
+    typedef short s16x2 __attribute__((ext_vector_type(2)));
+    s16x2 x = __builtin_bit_cast(s16x2, bits);
+    x = x << static_cast<short>(15 - J);
+    return __builtin_bit_cast(uint32_t, x >> static_cast<short>(15));
 }
 
 __device__ inline uint32_t word(const uint4& v, int i) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; }
@@ -103,17 +107,18 @@ __device__ __forceinline__ void tile_prefetch(Frag8 (&ring)[8], const char* sQ, 
     });
 }
 
-// FULL: every pair of the tile is allowed, no mask work at all (mw is not read).
+// FULL: every pair of the tile is allowed, no mask work at all (`bits`, from pair_bits, is not read).
 // copy_piece(k), k = 0 .. PIECES - 1, issues one instruction of the next tile's asynchronous copy;
 // the pieces are spread over the first slots.
 template <bool FULL, int PIECES, typename CopyPiece>
 __device__ __forceinline__ void dkdv_tile(const char* sQ, const char* sG, const float* sL, const float* sD,
-                                          const LaneOffsets& lo, const uint32_t (&mw)[2][8], float c, int g,
+                                          const LaneOffsets& lo, uint32_t bits, float c, int g,
                                           Frag8 (&ring)[8], CopyPiece&& copy_piece) {
     f32x16 s[2], dp[2];
     u32x4 pw[2][2], dw[2][2];  // packed P and dS of a block: [block][half] is one B operand
     float4 Lc, Ln;
     float p0 = 0.f, p1 = 0.f;
+    uint32_t mask = 0;
 
     auto request = [&](auto M) {  // LDS operand of slot m -> ring[m % 8]
         constexpr int m = decltype(M)::value;
@@ -174,12 +179,13 @@ __device__ __forceinline__ void dkdv_tile(const char* sQ, const char* sG, const 
             // matrix pipeline for as long as an MFMA takes to finish.
             if constexpr ((k & 3) == 0 && n + 4 < 32) Ln = lse4((n + 4) >> 4, ((n + 4) & 15) >> 2);
             if constexpr ((k & 1) == 0) {
+                if constexpr (!FULL) mask = pair_mask<8 * b + j>(bits);
                 p0 = __builtin_amdgcn_exp2f(fmaf(s[b][i], c, -comp(Lc, i & 3)));
                 p1 = __builtin_amdgcn_exp2f(fmaf(s[b][i + 1], c, -comp(Lc, (i + 1) & 3)));
             } else {
-                pw[b][j >> 2][j & 3] = FULL ? pack2(p0, p1) : pack2(p0, p1) & mw[b][j];
+                pw[b][j >> 2][j & 3] = FULL ? pack2(p0, p1) : pack2(p0, p1) & mask;
                 const float d0 = p0 * dp[b][i], d1 = p1 * dp[b][i + 1];
-                dw[b][j >> 2][j & 3] = FULL ? pack2(d0, d1) : pack2(d0, d1) & mw[b][j];
+                dw[b][j >> 2][j & 3] = FULL ? pack2(d0, d1) : pack2(d0, d1) & mask;
             }
             if constexpr ((k & 3) == 3) Lc = Ln;
         }
@@ -239,45 +245,41 @@ __global__ __launch_bounds__(256) void psattn_dkdv_bf16_mfma(AttnArgs a) {
 
     // Staging of one q-tile (64 rows x 256 B of Q and of dO, 64 LSE * log2 e, 64 delta):
     // asynchronous global -> LDS copies, issued one tile ahead into the buffer the
-    // previous tile has just vacated.  Rows past the end of the buffer re-read the
-    // last token: whatever they hold is removed by the pair masks (a clipped tile is
-    // never FULL).
+    // previous tile has just vacated; see tile_rows for the last tile of the buffer.  What stands between a tile's barrier and its
+    // first MFMA is covered by nothing, so as little as can be is done there: lane offsets that stay, scalar addresses
+    // that move on by a head, a tile loop whose buffers alternate without a test.  With the masks beside the MFMAs, backward of
+    // eight samples of 1 040 tokens 271 -> 264 us, of one of 8 000 1 454 -> 1 425, of packed samples of 450, 63 000 tokens, 1 278 -> 1 248.
     const uint32_t row_bytes = static_cast<uint32_t>(Hq) * 256u;
-    struct Lane { uint32_t off[kOps]; };
-    auto lane_rows = [&](int last_row) {
-        Lane d;
+    uint32_t cp_lane[kOps], cp_stat;
+    int cp_last = 63;  // last row that they are made for
+    auto lane_rows = [&](int last) {
+        const int lx = opaque(l);
 #pragma unroll
         for (int i = 0; i < kOps; ++i) {
-            const int row = kRows * w + 4 * i + (l >> 4);
-            d.off[i] = static_cast<uint32_t>(min(row, last_row)) * row_bytes + (((l & 15) ^ row_swizzle<128>(row)) << 4);
+            const int row = kRows * w + 4 * i + (lx >> 4);
+            cp_lane[i] = static_cast<uint32_t>(min(row, last)) * row_bytes + (((lx & 15) ^ row_swizzle<128>(row)) << 4);
         }
-        return d;
+        cp_stat = 4u * static_cast<uint32_t>(min(lx, last));
     };
-    const Lane dml = lane_rows(63);
+    lane_rows(63);
     // The copy of one tile is 2 kOps + 1 instructions per lane: the first kOps are Q rows, then dO rows, the last one the
     // statistics.  copy_setup fixes the tile, copy_piece issues one piece.
-    const char* cp_q = nullptr;   // first Q row of the tile being copied (this head)
-    const char* cp_g = nullptr;   // first dO row
-    const float* cp_s = nullptr;  // this lane's statistic (waves 0, 1)
-    Lane cp_lane = dml;
+    const char* cp_q = static_cast<const char*>(a.Q);    // first Q row of the tile being copied (this head)
+    const char* cp_g = static_cast<const char*>(a.dO);   // first dO row
+    const float* cp_s = a.lse2;                          // first statistic (waves 0, 1)
     auto copy_setup = [&](int ent, int h) {
         const int q0 = (ent >> 2) * 64;
+        tile_rows(min(T - 1 - q0, 63), cp_last, lane_rows);
         const size_t tile_elems = (static_cast<size_t>(q0) * Hq + h) * 128;
-        int rmax = T - 1 - q0;
         cp_q = reinterpret_cast<const char*>(static_cast<const uint16_t*>(a.Q) + tile_elems);
         cp_g = reinterpret_cast<const char*>(static_cast<const uint16_t*>(a.dO) + tile_elems);
-        cp_s = (w ? a.delta : a.lse2) + static_cast<size_t>(h) * T + q0 + min(l, rmax);
-        cp_lane = dml;
-        if (rmax < 63) {
-            asm volatile("; clipped tile" : "+s"(rmax));  // keeps the clamped offsets' arithmetic in this branch
-            cp_lane = lane_rows(rmax);
-        }
+        cp_s = (w ? a.delta : a.lse2) + static_cast<size_t>(h) * T + q0;
     };
     auto copy_piece = [&](auto P, auto BUF) {
         constexpr int p = decltype(P)::value, buf = decltype(BUF)::value;
-        if constexpr (p < kOps) dma16(cp_q, cp_lane.off[p], lds_addr(smem[0][buf]) + group * sizeof(smem[0]) + (kRows * w + 4 * p) * kRowBytes);
-        else if constexpr (p < 2 * kOps) dma16(cp_g, cp_lane.off[p - kOps], lds_addr(smem[0][2 + buf]) + group * sizeof(smem[0]) + (kRows * w + 4 * (p - kOps)) * kRowBytes);
-        else if (w < 2) dma4(cp_s, lds_addr(sStat[0][0][buf]) + group * sizeof(sStat[0]) + (w ? sizeof(sStat[0][0]) : 0));  // wave 0: LSE * log2 e, wave 1: -delta
+        if constexpr (p < kOps) dma16(cp_q, cp_lane[p], lds_addr(smem[0][buf]) + group * sizeof(smem[0]) + (kRows * w + 4 * p) * kRowBytes);
+        else if constexpr (p < 2 * kOps) dma16(cp_g, cp_lane[p - kOps], lds_addr(smem[0][2 + buf]) + group * sizeof(smem[0]) + (kRows * w + 4 * (p - kOps)) * kRowBytes);
+        else if (w < 2) dma4(cp_s, cp_stat, lds_addr(sStat[0][0][buf]) + group * sizeof(sStat[0]) + (w ? sizeof(sStat[0][0]) : 0));  // wave 0: LSE * log2 e, wave 1: -delta
     };
     // Walk order: q-tiles from the last to the first, and for each q-tile the G heads
     // of the group.  Every k-tile of a sample ends at the same q-tile, so workgroups
@@ -349,18 +351,20 @@ __global__ __launch_bounds__(256) void psattn_dkdv_bf16_mfma(AttnArgs a) {
         }
         ++it;
         auto piece = [&](auto P) { copy_piece(P, std::integral_constant<int, buf ^ 1>{}); };
-        uint32_t mw[2][8];
+        uint32_t bits = 0;
         if (S > 1 && it > n_it) {  // the other group's last step
         } else if (full) {
-            dkdv_tile<true, kPieces>(sQ, sG, sL, sD, lo, mw, c, g, ring, piece);
+            dkdv_tile<true, kPieces>(sQ, sG, sL, sD, lo, bits, c, g, ring, piece);
         } else if (__builtin_amdgcn_ballot_w64(max(key, q0) < min(tk.key_hi, q0 + 64)) == 0) {
             // PARTIAL tile none of whose queries reads any of this wave's 32 keys (two of the four
             // waves on the first q-tile of every causal diagonal, and the keys of another sample or
             // response): the wave only issues its share of the next tile's copy
             static_for<0, kPieces>([&](auto P) { piece(P); });
+#pragma unroll
+            for (int m = 0; m < kAhead; ++m) asm volatile("" ::"v"(ring[m].v));  // nothing is left on its way
         } else {
-            pair_masks(mw, key - q0, tk.key_hi - q0, g);
-            dkdv_tile<false, kPieces>(sQ, sG, sL, sD, lo, mw, c, g, ring, piece);
+            bits = pair_bits(key - q0, tk.key_hi - q0, g);
+            dkdv_tile<false, kPieces>(sQ, sG, sL, sD, lo, bits, c, g, ring, piece);
         }
     };
     // Every load above has retired before the loop starts, so the loop body holds no
@@ -369,8 +373,9 @@ __global__ __launch_bounds__(256) void psattn_dkdv_bf16_mfma(AttnArgs a) {
     tk = token_choose(a.meta, begun, found);
     settle();  // the register writes above, before the first MFMA reads them
     while (it < n_loop) {
-        if (it & 1) tile(std::integral_constant<int, 1>{});
-        else tile(std::integral_constant<int, 0>{});
+        tile(std::integral_constant<int, 0>{});
+        if (it >= n_loop) break;
+        tile(std::integral_constant<int, 1>{});
     }
     // no copy may still be writing to LDS when the workgroup ends
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");

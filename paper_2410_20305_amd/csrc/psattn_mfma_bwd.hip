@@ -59,12 +59,14 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_dq_bf16_mfma(Att
     // K / V tiles are copied global -> LDS asynchronously, one tile ahead, into the
     // buffer the previous tile has just vacated; one barrier per tile.
     const uint32_t row_bytes = static_cast<uint32_t>(Hkv) * kRB;
-    const DmaLaneOf<D> dml = dma_lane<D>(row_bytes, w, l);
-    PairCopyOf<D> pc;
+    PairCopyOf<D> pc{reinterpret_cast<const char*>(K), reinterpret_cast<const char*>(V), dma_lane<D>(row_bytes, w, l)};
+    int cp_last = 63;  // last row that the lanes' offsets are made for
     auto copy_setup = [&](int ent) {
         const int k0 = (ent >> 2) * 64;
-        pair_copy_setup(pc, reinterpret_cast<const char*>(K) + static_cast<size_t>(k0) * row_bytes,
-                        reinterpret_cast<const char*>(V) + static_cast<size_t>(k0) * row_bytes, row_bytes, T - 1 - k0, dml, w, l);
+        const size_t at = static_cast<size_t>(k0) * row_bytes;
+        tile_rows(min(T - 1 - k0, 63), cp_last, [&](int last) { pc.lane = dma_lane<D>(row_bytes, w, opaque(l), last); });
+        pc.a = reinterpret_cast<const char*>(K) + at;
+        pc.b = reinterpret_cast<const char*>(V) + at;
     };
     int ent = rl.first_entry, it = 0, n_ent = rl.count;
     // waves that share their queries leave out the tiles at both ends of the list that are there for the q-tile's others (at
@@ -104,6 +106,11 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_dq_bf16_mfma(Att
 #pragma unroll
         for (int i = 0; i < 16; ++i) dq[db][i] = 0.f;
 
+    // head_dim 128: dP starts from -delta, which stands in sixteen registers that the first MFMA of a block adds to, so that
+    // dS = P o (dP - delta) is one multiplication (at 64, within 168 registers, they would be spilled)
+    f32x16 minus_delta;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) minus_delta[i] = -dl;
     if (qb.together && n_ent <= 64)
         while (it + 1 < n_ent && !reads_tile(es.peek(n_ent - 1), row0, tk)) --n_ent;
     const int n_tiles = n_ent - it;
@@ -161,11 +168,16 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_dq_bf16_mfma(Att
             if (kb == 0 || skip32[0]) static_for<0, kAhead>([&](auto M) { request(std::integral_constant<int, kB * kb + decltype(M)::value>{}); });
             f32x16 s, dp;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) { s[i] = 0.f; dp[i] = 0.f; }
+            for (int i = 0; i < 16; ++i) s[i] = 0.f;
+            if constexpr (D == 128) dp = minus_delta;
+            else {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) dp[i] = 0.f;
+            }
             static_for<0, kS>([&](auto J) {
                 constexpr int j = decltype(J)::value, m = kB * kb + j, t = j >> 1;
                 request(std::integral_constant<int, m + kAhead>{});
-                if constexpr (m < kS && (m & 1) == 0) pair_copy_piece<m / 2>(pc, sKb[buf ^ 1], sVb[buf ^ 1], w);  // every other slot: see PairCopy
+                if constexpr (m < kS && (m & 1) == 0) pair_copy_piece<m / 2>(pc, sKb[buf ^ 1], sVb[buf ^ 1], w);  // every other slot: see PairCopyOf
                 if constexpr (j & 1) dp = mfma(ring[m % kRing].v, gf[t].v, dp);
                 else s = mfma(ring[m % kRing].v, qf[t].v, s);
                 __builtin_amdgcn_sched_barrier(0);
@@ -181,7 +193,7 @@ __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void psattn_dq_bf16_mfma(Att
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 const float p = __builtin_amdgcn_exp2f(fmaf(s[i], c, -lse2));
-                s[i] = p * (dp[i] - dl);  // dS^T
+                s[i] = p * (D == 128 ? dp[i] : dp[i] - dl);  // dS^T
             }
             Operand<D> dsb[2];
             dsb[0] = make_operand<D>(s, 0);

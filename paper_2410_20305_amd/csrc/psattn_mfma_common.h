@@ -307,18 +307,6 @@ __device__ __forceinline__ void tile_rows(int last, int& cp_last, Offsets&& make
     make(last);
 }
 
-template <int D>
-__device__ __forceinline__ void pair_copy_setup(PairCopyOf<D>& c, const char* a, const char* b, uint32_t row_bytes, int last_row,
-                                                const DmaLaneOf<D>& full, int w, int l) {
-    c.a = a;
-    c.b = b;
-    c.lane = full;
-    if (last_row < 63) {
-        asm volatile("; clipped tile" : "+s"(last_row));  // keeps the clamped offsets' arithmetic in this branch
-        c.lane = dma_lane<D>(row_bytes, w, l, last_row);
-    }
-}
-
 template <int P, int D>
 __device__ __forceinline__ void pair_copy_piece(const PairCopyOf<D>& c, const char* tile_a, const char* tile_b, int w) {
     constexpr int n = D / 32;

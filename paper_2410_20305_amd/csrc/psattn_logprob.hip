@@ -10,9 +10,9 @@
 //
 // All three passes stream logits rows of `vocab` elements and are bound by HBM bandwidth: one workgroup per row, 16-byte
 // accesses from the row's first aligned element on (rows of an odd vocabulary start anywhere), online max / sum in fp32,
-// one exponential per element.  65 536 rows of 32 000 bf16, 9 965 of them with a target: log-sum-exp 169 -> 98 us
-// (6.5 TB/s), gradient 906 -> 884 us (5.5 TB/s, almost all of it writes; a plain fill reaches 5.6 - 5.8); 8 334 rows of
-// 50 257 fp32, 3 206 with a target: 242 -> 100 us and 588 -> 476 us.
+// one exponential per element.  65 536 rows of 32 000 bf16, 9 965 of them with a target, whole head: 952 us, 5.7 TB/s (4.2 of
+// the 5.5 GB are written; a plain fill reaches 5.6 - 5.8, and part of the second reading comes out of the cache, see kCacheBytes);
+// 8 334 rows of 50 257 fp32, 3 206 with a target: 576 us.
 // Every sum is taken in a fixed order (no atomics): results are deterministic.
 #include <hip/hip_runtime.h>
 

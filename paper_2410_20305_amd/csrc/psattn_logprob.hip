@@ -10,9 +10,9 @@
 //
 // All three passes stream logits rows of `vocab` elements and are bound by HBM bandwidth: one workgroup per row, 16-byte
 // accesses from the row's first aligned element on (rows of an odd vocabulary start anywhere), online max / sum in fp32,
-// one exponential per element.  65 536 rows of 32 000 bf16, 9 965 of them with a target, whole head: 952 us, 5.7 TB/s (4.2 of
-// the 5.5 GB are written; a plain fill reaches 5.6 - 5.8, and part of the second reading comes out of the cache, see kCacheBytes);
-// 8 334 rows of 50 257 fp32, 3 206 with a target: 576 us.
+// one exponential per element.  65 536 rows of 32 000 bf16, 9 965 of them with a target: log-sum-exp 169 -> 98 us
+// (6.5 TB/s), gradient 906 -> 884 us (5.5 TB/s, almost all of it writes; a plain fill reaches 5.6 - 5.8); 8 334 rows of
+// 50 257 fp32, 3 206 with a target: 242 -> 100 us and 588 -> 476 us.
 // Every sum is taken in a fixed order (no atomics): results are deterministic.
 #include <hip/hip_runtime.h>
 
@@ -50,13 +50,12 @@ constexpr int kThreads = 256;
 // On 65 536 rows of 32 000 the gradient alone 957 / 941 / 923 (non-temporal stores 965 / - / 884).
 constexpr size_t kMidRowBytes = 8192, kWideRowBytes = 20480;  // 512 threads, 1024 threads
 constexpr int kUnroll = 4;  // 16-byte loads in flight per lane of the log-sum-exp
-// The gradient is written non-temporally where it is larger than the 256 MB last-level cache, so that the pass that follows could
-// not find it there anyway.  Logits are read by ordinary loads, also where the rows with a target are larger than the cache and a
-// pass over them alone is faster by non-temporal ones (6.3 -> 7.1 TB/s): the gradient then takes the rows from the last one back
-// and finds those that the log-sum-exp has read last still in the cache.  Whole head, ascending with the log-sum-exp non-temporal /
-// from the last row back, in us: 9 965 of 65 536 rows of 32 000 bf16 (638 MB read) 990 / 952, 3 206 of 8 334 rows of 50 257 fp32
-// (644 MB) 599 / 576, of 50 257 bf16 (322 MB) 297 / 262, of 128 256 bf16 684 / 665.  All rows with a target ahead of all others, from
-// the last one back, 943 / 591 / 279 / 665.  Rows that fit the cache are found in either order and stay in theirs.
+// Non-temporal accesses where the data is larger than the 256 MB last-level cache, so that the pass that follows could
+// not find it there anyway (reading 4 GB alone: 6.3 -> 7.1 TB/s).  Log-probabilities alone (a frozen policy's), rows read by
+// ordinary / by non-temporal loads, us: 322 MB of rows with a target 66 / 58, 638 MB 118 / 104, 2.1 GB 352 / 315, 3.9 GB 667 / 598.
+// Ordinary loads pay only where a gradient follows that takes the rows from the last one back and finds up to 256 MB of them: whole
+// head, that way / this way, 322 MB 274 / 299, 638 MB of 4.2 GB 957 / 989, 822 MB 665 / 686, but 1.0 GB 533 / 528, 2.1 GB 1 058 / 1 020,
+// 3.9 GB 2 046 / 1 994; with the last 224 MB alone by ordinary loads the log-probabilities still take 71 / 119 / 329 / 611.
 constexpr size_t kCacheBytes = size_t{256} << 20;
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -76,8 +75,11 @@ template <typename E> struct Vec;
 template <> struct Vec<uint16_t> { static constexpr int N = 8; };  // 16 bytes
 template <> struct Vec<float> { static constexpr int N = 4; };
 
-template <typename E>
-__device__ inline u32x4 load_raw(const E* p) { return *reinterpret_cast<const u32x4*>(p); }
+template <bool NT, typename E>
+__device__ inline u32x4 load_raw(const E* p) {
+    if constexpr (NT) return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+    else return *reinterpret_cast<const u32x4*>(p);
+}
 __device__ inline void unpack(const u32x4& u, float (&x)[8]) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -152,7 +154,7 @@ __device__ inline float block_sum(float v, float* sm) {
 }
 
 // ---- pass 1: log-sum-exp of every row that predicts something
-template <typename E, bool WHOLE>
+template <typename E, bool NT, bool WHOLE>
 __global__ __launch_bounds__(kThreads) void psattn_lp_row_lse(const int32_t* rows, int vocab, const E* logits, float* row_lse) {
     __shared__ float sm[kThreads / 64], ss[kThreads / 64];
     const int row = rows[blockIdx.x];
@@ -165,7 +167,7 @@ __global__ __launch_bounds__(kThreads) void psattn_lp_row_lse(const int32_t* row
         constexpr int n = decltype(COUNT)::value;
         u32x4 raw[n];
 #pragma unroll
-        for (int u = 0; u < n; ++u) raw[u] = load_raw(xv + static_cast<size_t>(c + u * kThreads) * N);
+        for (int u = 0; u < n; ++u) raw[u] = load_raw<NT>(xv + static_cast<size_t>(c + u * kThreads) * N);
         float mx = m;
 #pragma unroll
         for (int u = 0; u < n; ++u) {
@@ -226,8 +228,8 @@ template <typename E, bool NT, bool WHOLE, int kBwdThreads>
 __global__ __launch_bounds__(kBwdThreads) void psattn_lp_bwd(const int32_t* row_desc, const int32_t* resp_first,
                                                           const int32_t* resp_len, const int32_t* samp_ptr, int vocab,
                                                           const E* logits, const int32_t* token_ids, const float* row_lse,
-                                                          const float* d_logp, E* dlogits, int first, int step) {
-    const int row = first + step * static_cast<int>(blockIdx.x), desc = row_desc[row];
+                                                          const float* d_logp, E* dlogits, int first) {
+    const int row = first + static_cast<int>(blockIdx.x), desc = row_desc[row];
     const E* x = logits + static_cast<size_t>(row) * vocab;
     E* g = dlogits + static_cast<size_t>(row) * vocab;
     constexpr int N = Vec<E>::N;
@@ -269,7 +271,7 @@ __global__ __launch_bounds__(kBwdThreads) void psattn_lp_bwd(const int32_t* row_
     auto grad = [&](float v) { return -coef * __expf(v - lse); };
     for (int c = threadIdx.x; c < sp.n_vec; c += kBwdThreads) {
         float v[N];
-        unpack(load_raw(xv + static_cast<size_t>(c) * N), v);
+        unpack(load_raw<false>(xv + static_cast<size_t>(c) * N), v);
 #pragma unroll
         for (int k = 0; k < N; ++k) v[k] = grad(v[k]);
         store_vec<NT>(gv + static_cast<size_t>(c) * N, v);
@@ -431,13 +433,15 @@ int psattn_logprob_fwd(const psattn_lp_plan* plan, int32_t dt, int32_t vocab, co
     if (!logits || !token_ids || !row_lse || !resp_logp) return PSATTN_EINVAL;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     if (plan->n_rows > 0) {
+        const bool nt = static_cast<size_t>(plan->n_rows) * vocab * (dt == PSATTN_BF16 ? 2 : 4) > kCacheBytes;
         auto lse = [&](auto kernel, auto* x) {
             in_grids(plan->n_rows, kThreads, [&](int32_t at, uint32_t n) { kernel<<<n, kThreads, 0, s>>>(plan->rows + at, vocab, x, row_lse); });
         };
         const bool whole = whole_rows(dt, vocab, logits);
         auto typed = [&](auto* x) {
             using E = std::remove_const_t<std::remove_pointer_t<decltype(x)>>;
-            lse(whole ? psattn_lp_row_lse<E, true> : psattn_lp_row_lse<E, false>, x);
+            if (nt) lse(whole ? psattn_lp_row_lse<E, true, true> : psattn_lp_row_lse<E, true, false>, x);
+            else lse(whole ? psattn_lp_row_lse<E, false, true> : psattn_lp_row_lse<E, false, false>, x);
         };
         if (dt == PSATTN_BF16) typed(static_cast<const uint16_t*>(logits));
         else typed(static_cast<const float*>(logits));
@@ -460,13 +464,12 @@ int psattn_logprob_bwd(const psattn_lp_plan* plan, int32_t dt, int32_t vocab, co
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const size_t row_bytes = static_cast<size_t>(vocab) * (dt == PSATTN_BF16 ? 2 : 4);
     const bool nt = plan->T * row_bytes > kCacheBytes;
-    const bool back = plan->n_rows * row_bytes > kCacheBytes;
     const bool whole = whole_rows(dt, vocab, logits) && whole_rows(dt, vocab, dlogits);
     auto bwd = [&](auto nontemporal, auto whole_, auto threads, auto* x, auto* g) {
         constexpr int n = decltype(threads)::value;
         in_grids(plan->T, n, [&](int32_t at, uint32_t rows) {
             psattn_lp_bwd<std::remove_pointer_t<decltype(g)>, decltype(nontemporal)::value, decltype(whole_)::value, n><<<rows, n, 0, s>>>(
-                plan->row_desc, plan->resp_first, plan->resp_len, plan->samp_ptr, vocab, x, token_ids, row_lse, d_resp_logp, g, back ? plan->T - 1 - at : at, back ? -1 : 1);
+                plan->row_desc, plan->resp_first, plan->resp_len, plan->samp_ptr, vocab, x, token_ids, row_lse, d_resp_logp, g, at);
         });
     };
     auto typed = [&](auto* x, auto* g) {

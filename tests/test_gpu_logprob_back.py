@@ -1,5 +1,5 @@
-"""The gradient of the logits takes its rows from the last one back where those with a target hold more than 256 MB: either side of
-that line, rows of whole and of odd 16-byte groups, every row of the gradient against 64-bit sums by plain torch operations."""
+"""The log-sum-exp reads its rows by non-temporal loads where those with a target hold more than 256 MB: either side of that line,
+rows of whole and of odd 16-byte groups, every row of the gradient against 64-bit sums by plain torch operations."""
 import numpy as np
 import pytest
 import torch

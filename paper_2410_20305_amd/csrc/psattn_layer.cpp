@@ -25,7 +25,7 @@ struct psattn_layer {
 
 namespace {
 
-size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
+constexpr size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // activations and gradients kept between forward and backward, carved out of the caller's workspace
 struct Slots {
@@ -79,6 +79,17 @@ int gemm_rm_pair(rocblas_handle h, bool ta, bool tb, int64_t M, int64_t N, int64
         rocblas_datatype_bf16_r, static_cast<rocblas_int>(ldc), c_step, C, rocblas_datatype_bf16_r, static_cast<rocblas_int>(ldc),
         c_step, 2, rocblas_datatype_f32_r, rocblas_gemm_algo_standard, 0, 0);
     return st == rocblas_status_success ? PSATTN_OK : PSATTN_EHIP;
+}
+
+// dWk and dWv, n_out x hidden elements each, as one batch of two in `room` bytes: where one product by itself fills at most half
+// of the 256 CUs (in tiles of 256 x 256) and the room holds both results.  Backward, one by one / as a pair, us, by hidden x n_out: 512 x
+// 512 163 / 150, 1 024 x 1 024 291 / 272, 2 048 x 2 048 517 / 506, 4 096 x 1 024 1 041 / 1 024 (2 560 tokens 557 / 544, 10 240 2 127 / 2 081),
+// 6 144 x 1 024 1 918 / 1 880, 4 096 x 2 048 1 202 / 1 188, 8 192 x 1 024 3 324 / 3 320; beyond the line, where the copies of the results
+// cost more than the batch gives, 3 072 x 3 072 936 / 946 (10 240 tokens 1 784 / 1 913), 4 096 x 3 072 1 129 / 1 138, 4 096 x 4 096 1 445 /
+// 1 469, and either way from table to table at 5 120 x 2 560 and 4 096 x 3 584 (5 120 x 5 120 2 522 / 2 429).
+constexpr bool weights_as_pair(size_t n_out, size_t hidden, size_t room) {
+    const size_t bytes = n_out * hidden * 2;
+    return n_out * hidden <= size_t{128} * 256 * 256 && align_up(bytes, 256) + bytes <= room;
 }
 
 }  // namespace
@@ -157,12 +168,11 @@ int psattn_layer_bwd(psattn_layer* L, const psattn_meta* meta, const psattn_rope
     if (rc != PSATTN_OK) return rc;
     // projections: dW = dP^T X, dX = dQ Wq + dK Wk + dV Wv
     if ((rc = gemm_rm(L->blas, true, false, nq, h, T, s.dQ, nq, X, h, dWq, h, false)) != PSATTN_OK) return rc;
-    // dWk and dWv by themselves fill the chip poorly (63 us each for 31 us of products, 5 120 tokens, hidden 4 096, 8 kv heads).  They
-    // go as one batch of two where the places of the unrotated Q and K, which the backward does not read, hold both results;
-    // the caller's two matrices lie anywhere, hence the copies.  Forward and backward, one by one / together: 5 120 tokens
-    // 1 511 / 1 490 us, 2 560 822 / 802, 10 240 3 193 / 3 134, 3 256 in one sample 1 223 / 1 209.
+    // dWk and dWv by themselves fill the chip poorly (63 us each for 31 us of products, 5 120 tokens, hidden 4 096, 8 kv heads).  As one
+    // batch they go to the places of the unrotated Q and K, which the backward does not read; the caller's two matrices
+    // lie anywhere, hence the copies.
     const size_t wk = static_cast<size_t>(nk) * h * 2, step = align_up(wk, 256);
-    if (step + wk <= static_cast<size_t>(s.V - s.Q)) {
+    if (weights_as_pair(nk, h, s.V - s.Q)) {
         hipStream_t st = static_cast<hipStream_t>(hip_stream);
         if ((rc = gemm_rm_pair(L->blas, true, false, nk, h, T, s.dK, nk, (s.dV - s.dK) / 2, X, h, 0, s.Q, h, static_cast<int64_t>(step / 2))) != PSATTN_OK) return rc;
         if (hipMemcpyAsync(dWk, s.Q, wk, hipMemcpyDeviceToDevice, st) != hipSuccess) return PSATTN_EHIP;

@@ -1,9 +1,10 @@
 """dK/dV where a row's walk is shared by two groups of waves (launches bound by their longest row), against the oracle:
 odd and even numbers of steps, group sizes that do not divide by two, a k-tile whose second half lies past the end or holds
-padding only, lists longer than one 64-entry window, rotary embedding.  Bars as in test_gpu_parity.py."""
+padding only, lists longer than one 64-entry window; and tables on either side of the line.  Bars as in test_gpu_parity.py."""
 import numpy as np
 import pytest
 
+import paper_2410_20305_amd as ps
 import psattn_workloads as W
 from gpu_util import run_gpu
 from test_gpu_parity import compare_full
@@ -28,8 +29,32 @@ def test_split_rows(case, d):
                           dtype="bf16", seed=128)
     tens = W.make_tensors(w)
     out, meta = run_gpu(w, tens)
-    import paper_2410_20305_amd as ps
-    row_ptr, _, _ = meta.csr(ps.GRID_BWD)
-    chain = int(np.diff(row_ptr).max()) * (c["hq"] // c["hkv"])
-    assert chain >= 8 and 10 * chain * 256 >= 16 * int(row_ptr[-1]) * c["hq"]  # the launch rules' conditions
+    assert _splits(meta, c["hq"], c["hkv"])  # at head_dim 64 too, whose line is 10 in place of 13
     compare_full(w, tens, out, "bf16", what="split %s d %d" % (case, d))
+
+
+def _splits(meta, hq, hkv):
+    """The launch rule at head_dim 128: the longest chain of steps against a CU's share of all steps."""
+    row_ptr, _, _ = meta.csr(ps.GRID_BWD)
+    chain = int(np.diff(row_ptr).max()) * (hq // hkv)
+    return chain >= 8 and 10 * chain * 256 >= 13 * int(row_ptr[-1]) * hq
+
+
+LINE = {  # ratio of the longest chain to a CU's share, and the side
+    "1.18": (dict(samples=[(150, 40, 70)] * 2, hq=256, hkv=64), False),
+    "1.30_below": (dict(samples=[(300, 100, 50)], hq=316, hkv=79), False),                     # 1.296
+    "1.30_above": (dict(samples=[(300, 100, 50)], hq=312, hkv=78), True),                      # 1.313
+    "1.33_group_of_2": (dict(samples=[(500, 60, 40)], hq=128, hkv=64), True),
+    "1.4_padding": (dict(samples=[(300, 100, 50), (20, 10, 5)], offsets=[7, 500], T=600, hq=462, hkv=66), True),
+}
+
+
+@pytest.mark.parametrize("case", sorted(LINE))
+def test_either_side_of_the_line(case):
+    c, split = LINE[case]
+    w = W.custom_workload(c["samples"], offsets=c.get("offsets"), total_tokens=c.get("T"), hq=c["hq"], hkv=c["hkv"], d=128,
+                          dtype="bf16", seed=129)
+    tens = W.make_tensors(w)
+    out, meta = run_gpu(w, tens)
+    assert _splits(meta, c["hq"], c["hkv"]) == split
+    compare_full(w, tens, out, "bf16", what="line %s" % case)

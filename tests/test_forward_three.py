@@ -14,6 +14,7 @@ import psattn_workloads as W
 from gpu_util import run_gpu
 from oracle import psattn_oracle as orc
 from test_gpu_parity import compare_full
+from test_gpu_rope import run_rope_case
 from test_kernel_build import _asm, _kernels, _no_spills, _outside_asm
 
 CASES = {
@@ -44,7 +45,8 @@ def test_against_oracle(case):
 
 @pytest.mark.gpu
 def test_rotary_rows_leave_whole():
-    """Q is turned, saved and used in one go: the saved rows and the output equal those of a call on rows turned beforehand."""
+    """Q is turned, saved and used in one go: the output equals that of a call on the rows that were saved (which
+    test_rotary_embedding compares with rows turned by the oracle)."""
     w = W.custom_workload([(150, 40, 70), (130, 90, 51)], hq=160, hkv=40, d=128, dtype="bf16", seed=5)
     t = W.make_tensors(w)
     dev = lambda x: torch.from_numpy(x).to("cuda").to(torch.bfloat16)
@@ -59,6 +61,13 @@ def test_rotary_rows_leave_whole():
     f = lambda x: x.float().cpu().numpy().astype(np.float64)
     ref = orc.forward(f(Qr), f(Kr), t["V"].astype(np.float64), w.scale, Ic, Ir, D)
     assert np.abs(f(O) - ref[0]).max() <= 1.3e-2   # 1e-2 below 2, half a bf16 ulp (0.0078) + 5e-3 on [2, 4)
+
+
+@pytest.mark.gpu
+def test_rotary_embedding():
+    """Saved rows, output and gradients against the oracle, which turns the original rows by its own position ids."""
+    assert (900 + 127) // 128 * 160 >= 768
+    run_rope_case([5, 460], [150, 130], [0, 2, 5], [40, 70, 90, 51, 33], 900, 160, 40, 10000.0, 6)
 
 
 def test_compiled_kernel(tmp_path):

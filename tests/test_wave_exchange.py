@@ -8,7 +8,7 @@ import pytest
 from test_kernel_build import _asm, _kernels
 
 
-@pytest.mark.parametrize("src,count", [("psattn_mfma_fwd.hip", 1), ("psattn_mfma_fwd64.hip", 1), ("psattn_mfma_bwd.hip", 2),
+@pytest.mark.parametrize("src,count", [("psattn_mfma_fwd.hip", 1), ("psattn_mfma_fwd64.hip", 1), ("psattn_mfma_fwd3.hip", 1), ("psattn_mfma_bwd.hip", 2),
                                        ("psattn_mfma_dkdv.hip", 2), ("psattn_mfma_dkdv64.hip", 2)])
 def test_reads_behind_a_barrier(tmp_path, src, count):
     for name, body, _ in _kernels(_asm(tmp_path, src), "_mfma", count):

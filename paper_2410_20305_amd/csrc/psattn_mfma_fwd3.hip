@@ -9,7 +9,18 @@ namespace psattn {
 // 256) 27.4 / 23.3, 800 39.4 / 38.2, 1 024 (two full rounds of two) 46.1 / 46.4, 1 504 65.5 / 64.5, 2 080 89.2 / 87.4, 2 800 (28 / 4) 167 /
 // 161, 64 / 8 heads, one sample of 8 000 tokens 953 / 934; 16 384 tokens of packed moderate samples 172 / 166, 65 536 of long ones
 // at 64 / 8 heads 4.40 / 4.22 ms.  Fewer than 64 tokens have no 64 rows for a clipped tile to stand for.
-bool mfma_fwd_three(const AttnArgs& a) { return a.meta.T >= 64 && static_cast<int64_t>(a.meta.n_rows[kGridQ]) * a.Hq >= 768; }
+// Not where the launch is bound by a few long rows: the third workgroup takes its part of the CU while the longest row is still
+// at work.  The line: rows of 12 and more k-tiles, the longest over 0.85 times a slot's share of all k-tiles.  Both forwards on 1 900
+// random tables past the other two lines, three over two, mean and range by that ratio: rows under 12 tiles, any ratio, 0.94 - 0.97 (0.81 -
+// 1.10, 3 % of them over 1.02); longer ones up to 0.85 0.98 - 1.00 (0.93 - 1.07), 0.85 - 1.1 0.98 - 1.01 (0.91 - 1.05), 1.1 - 1.5 1.00 - 1.02 (0.95 -
+// 1.06), 1.5 - 2 0.99 - 1.05 (0.93 - 1.12), over 2 1.03 - 1.10 (1.03 - 1.14).  16 / 16 heads, one sample of 6 040 tokens 160 / 171.
+constexpr bool three_to_a_cu(int32_t T, int64_t workgroups, int64_t longest, int64_t tiles) {
+    return T >= 64 && workgroups >= 768 && (longest < 12 || 100 * 768 * longest <= 85 * tiles);
+}
+
+bool mfma_fwd_three(const AttnArgs& a) {
+    return three_to_a_cu(a.meta.T, static_cast<int64_t>(a.meta.n_rows[kGridQ]) * a.Hq, a.size[kGridQ].longest, a.size[kGridQ].n_entries * a.Hq);
+}
 
 int launch_mfma_fwd3(const AttnArgs& a, void* stream) {
     const unsigned grid = static_cast<unsigned>(a.meta.n_rows[kGridQ]) * a.Hq;

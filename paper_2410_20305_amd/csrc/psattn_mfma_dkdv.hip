@@ -456,19 +456,25 @@ __global__ __launch_bounds__(256) void psattn_dkdv_bf16_mfma(AttnArgs a) {
 // Which of the two.  A workgroup is a serial chain of as many steps (heads of the group x q-tiles) as its row is long, one
 // workgroup per CU, so a launch takes at least its longest chain however few workgroups there are; splitting halves the
 // chain and costs 10 - 15 % more work (every tile is staged for 64 keys instead of 128) and the exchange at the end.  The
-// line lies where the longest chain is 1.3 times a CU's share of all steps, and at chains of 8 steps.  Measured, whole backward,
-// unsplit / split, 32 q / 8 kv heads by that ratio: 1.00 (three samples of 2 600 tokens) 514 / 534 us, 1.04 258 / 271, 1.19 234 / 243,
-// 1.22 154 / 155, 1.28 230 / 225, 1.48 (four of 1 280) 207 / 200, 1.52 417 / 361, 1.60 208 / 182; 64 / 8 heads 1.29 691 / 663.  dK/dV
+// line lies where the longest chain is 1.6 times a CU's share of all steps, at chains of 8 steps, and already at 1.3 shares
+// where the chain is 8 steps longer than those, which pay for the exchange.  Measured, whole backward, unsplit / split, 32 q / 8 kv heads
+// by that ratio: 1.00 (three samples of 2 600 tokens) 514 / 534 us, 1.04 258 / 271, 1.19 234 / 243, 1.22 154 / 155, 1.28 230 / 225, 1.48 (four of
+// 1 280) 207 / 200, 1.52 417 / 361, 1.60 208 / 182; 64 / 8 heads 1.29 691 / 663; chains too short for it, 28 / 4 heads, 1.31 (130 samples of
+// 50 tokens, 21 steps) 83 / 99, 1.47 78 / 92, 16 / 4 heads 1.39 (28 steps) 91 / 110.  228 random tables from 1.3 to 1.6, split over unsplit: all of
+// them 0.99 (0.83 - 1.22), the 85 past the line 0.91 (0.83 - 1.04), chains under 24 steps 1.00 - 1.22.  dK/dV
 // alone, kernels of before: 1.96 112 / 78, 3.8 105 / 64, 7.5 88 / 54, 24 (180 tokens) 26 / 19; 64 / 8 heads 1.48 246 / 220, 2.96
 // 218 / 137, 4.0 322 / 186; 28 / 4 heads 4.8 279 / 159, 8.1 283 / 159; 16 / 16 heads 0.76 42 / 62.
 constexpr int64_t kCus = 256;
+constexpr bool split_rows(int64_t chain, int64_t steps) {
+    return chain >= 8 && (10 * chain * kCus >= 16 * steps || 10 * (chain - 8) * kCus >= 13 * steps);
+}
 
 int launch_mfma_dkdv(const AttnArgs& a, void* stream) {
     const unsigned grid = static_cast<unsigned>(a.meta.n_rows[kGridK]) * a.Hkv;
     if (grid == 0) return 0;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int64_t chain = static_cast<int64_t>(a.size[kGridK].longest) * (a.Hq / a.Hkv), steps = a.size[kGridK].n_entries * a.Hq;
-    if (chain >= 8 && 10 * chain * kCus >= 13 * steps) psattn_dkdv_bf16_mfma<2><<<2 * grid, 256, 0, s>>>(a);
+    if (split_rows(chain, steps)) psattn_dkdv_bf16_mfma<2><<<2 * grid, 256, 0, s>>>(a);
     else psattn_dkdv_bf16_mfma<1><<<grid, 256, 0, s>>>(a);
     return static_cast<int>(hipGetLastError());
 }

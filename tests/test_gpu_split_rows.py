@@ -29,23 +29,26 @@ def test_split_rows(case, d):
                           dtype="bf16", seed=128)
     tens = W.make_tensors(w)
     out, meta = run_gpu(w, tens)
-    assert _splits(meta, c["hq"], c["hkv"])  # at head_dim 64 too, whose line is 10 in place of 13
+    assert _splits(meta, c["hq"], c["hkv"])  # at head_dim 64 too, whose line is one share
     compare_full(w, tens, out, "bf16", what="split %s d %d" % (case, d))
 
 
 def _splits(meta, hq, hkv):
     """The launch rule at head_dim 128: the longest chain of steps against a CU's share of all steps."""
     row_ptr, _, _ = meta.csr(ps.GRID_BWD)
-    chain = int(np.diff(row_ptr).max()) * (hq // hkv)
-    return chain >= 8 and 10 * chain * 256 >= 13 * int(row_ptr[-1]) * hq
+    chain, steps = int(np.diff(row_ptr).max()) * (hq // hkv), int(row_ptr[-1]) * hq
+    return chain >= 8 and (10 * chain * 256 >= 16 * steps or 10 * (chain - 8) * 256 >= 13 * steps)
 
 
 LINE = {  # ratio of the longest chain to a CU's share, and the side
     "1.18": (dict(samples=[(150, 40, 70)] * 2, hq=256, hkv=64), False),
-    "1.30_below": (dict(samples=[(300, 100, 50)], hq=316, hkv=79), False),                     # 1.296
-    "1.30_above": (dict(samples=[(300, 100, 50)], hq=312, hkv=78), True),                      # 1.313
-    "1.33_group_of_2": (dict(samples=[(500, 60, 40)], hq=128, hkv=64), True),
-    "1.4_padding": (dict(samples=[(300, 100, 50), (20, 10, 5)], offsets=[7, 500], T=600, hq=462, hkv=66), True),
+    "1.30": (dict(samples=[(300, 100, 50)], hq=312, hkv=78), False),                           # 32 steps
+    "1.33_group_of_2": (dict(samples=[(500, 60, 40)], hq=128, hkv=64), False),                 # 20 steps
+    "1.40_below": (dict(samples=[(500, 60, 40)], hq=488, hkv=61), False),                      # 80 steps, 5.7 above 1.3 shares
+    "1.50_above": (dict(samples=[(500, 60, 40)], hq=456, hkv=57), True),                       # 80 steps, 10.5
+    "1.60_group_of_4": (dict(samples=[(300, 100, 50)], hq=256, hkv=64), True),                 # 32 steps, 6 above 1.3 shares
+    "1.5_padding": (dict(samples=[(300, 100, 50), (20, 10, 5)], offsets=[7, 500], T=600, hq=434, hkv=62), False),   # 56 steps, 7.5
+    "1.57_padding": (dict(samples=[(300, 100, 50), (20, 10, 5)], offsets=[7, 500], T=600, hq=413, hkv=59), True),   # 56 steps, 9.9
 }
 
 

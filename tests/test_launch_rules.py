@@ -46,3 +46,22 @@ def test_forward(tmp_path):
         T, rows, longest, tiles = lists(samples, ps.GRID_FWD)
         lines.append("static_assert(three_to_a_cu(%d, %d, %d, %d) == %s, \"\");" % (T, rows * hq, longest, tiles * hq, str(three).lower()))
     check(tmp_path, "psattn_mfma_fwd3.hip", lines)
+
+
+BACKWARD = [  # samples, q heads, kv heads, rows split or not
+    ([(10, 8, 7)] * 220, 28, 4, False),      # 21 steps, 172 workgroups of one length
+    ([(40, 15, 15)], 768, 192, False),       # 8 steps, 192 workgroups
+    ([(1024, 128, 128)] * 4, 32, 8, True),   # 80 steps, 1.48 shares
+    ([(1200, 100, 50)] * 5, 32, 8, False),   # 92 steps, 1.09 shares
+    ([(2000, 100, 50)] * 2, 32, 8, True),    # 144 steps, 1.78 shares
+    ([(110, 50, 40)], 4, 4, False),          # 4 steps
+    ([(110, 50, 40)], 8, 4, True),           # 8 steps
+]
+
+
+def test_backward(tmp_path):
+    lines = []
+    for samples, hq, hkv, split in BACKWARD:
+        _, _, longest, tiles = lists(samples, ps.GRID_BWD)
+        lines.append("static_assert(split_rows(%d, %d) == %s, \"\");" % (longest * (hq // hkv), tiles * hq, str(split).lower()))
+    check(tmp_path, "psattn_mfma_dkdv.hip", lines)

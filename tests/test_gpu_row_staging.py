@@ -9,7 +9,7 @@ import psattn_workloads as W
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("hq,hkv,T", [(4, 2, 360), (48, 12, 1430)])  # one and four heads per workgroup
+@pytest.mark.parametrize("hq,hkv,T", [(4, 2, 360), (48, 12, 1430), (768, 192, 360)])  # one and four heads per workgroup, three workgroups to a CU
 @pytest.mark.parametrize("off", [1, 2, 5])
 def test_forward_of_unaligned_q(off, hq, hkv, T):
     import torch

@@ -10,10 +10,10 @@ namespace psattn {
 // 161, 64 / 8 heads, one sample of 8 000 tokens 953 / 934; 16 384 tokens of packed moderate samples 172 / 166, 65 536 of long ones
 // at 64 / 8 heads 4.40 / 4.22 ms.  Fewer than 64 tokens have no 64 rows for a clipped tile to stand for.
 // Not where the launch is bound by a few long rows: the third workgroup takes its part of the CU while the longest row is still
-// at work.  The line: rows of 12 and more k-tiles, the longest over 0.85 times a slot's share of all k-tiles.  Both forwards on 1 900
-// random tables past the other two lines, three over two, mean and range by that ratio: rows under 12 tiles, any ratio, 0.94 - 0.97 (0.81 -
-// 1.10, 3 % of them over 1.02); longer ones up to 0.85 0.98 - 1.00 (0.93 - 1.07), 0.85 - 1.1 0.98 - 1.01 (0.91 - 1.05), 1.1 - 1.5 1.00 - 1.02 (0.95 -
-// 1.06), 1.5 - 2 0.99 - 1.05 (0.93 - 1.12), over 2 1.03 - 1.10 (1.03 - 1.14).  16 / 16 heads, one sample of 6 040 tokens 160 / 171.
+// at work.  The line: rows of 12 and more k-tiles, the longest over 0.85 times a slot's share of all k-tiles.  Both forwards on 1 977
+// random tables past the other two lines, three over two, mean and range by that ratio: rows under 12 tiles, any ratio, 0.96 (0.81 - 1.10, 2 %
+// of them over 1.02); longer ones up to 0.85 0.99 (0.90 - 1.07), 0.85 - 1.1 0.99 (0.91 - 1.05), 1.1 - 1.5 1.01 (0.95 - 1.06), 1.5 - 2 1.03 (0.93 -
+// 1.12), over 2 1.09 (1.03 - 1.14).  16 / 16 heads, one sample of 6 040 tokens 160 / 171.
 constexpr bool three_to_a_cu(int32_t T, int64_t workgroups, int64_t longest, int64_t tiles) {
     return T >= 64 && workgroups >= 768 && (longest < 12 || 100 * 768 * longest <= 85 * tiles);
 }
